@@ -8,6 +8,7 @@
 // marking a NIL child. Nodes carry no global offsets, only their Morton key.
 #include "qt_internal.h"
 #include "qt_morton.h"
+#include "qt_sort.h"
 
 #include <algorithm>
 #include <atomic>
@@ -75,20 +76,72 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-__global__ void k_build_keys(const int32_t* __restrict__ I, const int32_t* __restrict__ J, int64_t n,
-                             int64_t nbr, int64_t nbc, uint64_t* __restrict__ keys,
-                             int32_t* __restrict__ perm, int32_t* __restrict__ err) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    int32_t i = I[t], j = J[t];
-    if (i < 0 || j < 0 || i >= nbr || j >= nbc) {
-        atomicOr(err, 1);
-        keys[t] = (uint64_t)t;
-    } else {
-        keys[t] = morton_key((uint32_t)i, (uint32_t)j);
+// Sort sources and sinks (see qt_sort.h). A block list's entry t sorts by the
+// Morton key of (I[t], J[t]); one out of range sets the error flag.
+struct ListKeys {
+    const int32_t* I;
+    const int32_t* J;
+    int64_t nbr, nbc;
+    int32_t* err;
+    __device__ uint64_t operator()(int32_t t) const {
+        const int32_t i = I[t], j = J[t];
+        if (i < 0 || j < 0 || i >= nbr || j >= nbc) {
+            atomicOr(err, 1);
+            return (uint64_t)t;
+        }
+        return morton_key((uint32_t)i, (uint32_t)j);
     }
-    perm[t] = (int32_t)t;
-}
+};
+
+struct KeyPermSink {
+    uint64_t* keys;
+    int32_t* perm;
+    __device__ void operator()(int32_t at, int32_t t, uint64_t k) const {
+        keys[at] = k;
+        perm[at] = t;
+    }
+};
+
+// Blocks in Morton order come out row-major when sorted by row alone: the
+// sort is stable, and Morton order lists the blocks of one row by column.
+struct RowKeys {
+    const uint64_t* bkey;
+    __device__ uint64_t operator()(int32_t t) const { return morton_row(bkey[t]); }
+};
+
+// Row-major copy-out: coordinates and source block of every output position.
+struct RowMajorSink {
+    const uint64_t* bkey;
+    int32_t* perm;
+    int32_t* I;
+    int32_t* J;
+    __device__ void operator()(int32_t at, int32_t t, uint64_t row) const {
+        perm[at] = t;
+        I[at] = (int32_t)row;
+        J[at] = (int32_t)morton_col(bkey[t]);
+    }
+};
+
+struct GatherF64Sink {
+    const double* src;
+    double* dst;
+    __device__ void operator()(int32_t at, int32_t t, uint64_t) const { dst[at] = src[t]; }
+};
+
+// Squared norms by their bit pattern (non-negative doubles order like it).
+struct NormKeys {
+    const double* norm2;
+    __device__ uint64_t operator()(int32_t t) const { return (uint64_t)__double_as_longlong(norm2[t]); }
+};
+
+struct NormSink {
+    double* sorted;
+    int32_t* idx;
+    __device__ void operator()(int32_t at, int32_t t, uint64_t k) const {
+        sorted[at] = __longlong_as_double((long long)k);
+        idx[at] = t;
+    }
+};
 
 __global__ void k_build_dups(const uint64_t* __restrict__ keys, int64_t n, int32_t* __restrict__ err) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -235,23 +288,6 @@ __global__ void k_bf16_split(const T* __restrict__ src, int64_t nblk, int b, uin
     lo[i] = l;
     hi_t[t * bb + (int64_t)c * b + r] = h;
     lo_t[t * bb + (int64_t)c * b + r] = l;
-}
-
-__global__ void k_rowmajor_keys(const uint64_t* __restrict__ bkey, int64_t n, int64_t nbc,
-                                uint64_t* __restrict__ rk, int32_t* __restrict__ perm) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    rk[t] = (uint64_t)morton_row(bkey[t]) * (uint64_t)nbc + morton_col(bkey[t]);
-    perm[t] = (int32_t)t;
-}
-
-__global__ void k_coords(const uint64_t* __restrict__ bkey, const int32_t* __restrict__ perm, int64_t n,
-                         int32_t* __restrict__ I, int32_t* __restrict__ J) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    uint64_t k = bkey[perm[t]];
-    I[t] = (int32_t)morton_row(k);
-    J[t] = (int32_t)morton_col(k);
 }
 
 template <class S, class D>
@@ -498,21 +534,19 @@ void build_tree_levels(qt_matrix* M, hipStream_t s);
 // of the block at sorted position t. Rejects out-of-range and repeated (I, J).
 static void build_structure(qt_matrix* M, const int32_t* pI, const int32_t* pJ, int64_t nblocks, int64_t nbr,
                             int64_t nbc, DBuf<int32_t>& perm, hipStream_t s) {
-    int64_t npow2 = 1;
-    while (npow2 < nblocks) npow2 <<= 1;
-    DBuf<uint64_t> keys(npow2, s);
-    perm.alloc(npow2, s);
-    DBuf<int32_t> derr(1, s);
+    const int key_bits = 2 * ilog2(std::max(nbr, nbc));
+    DBuf<uint64_t> keys(nblocks, s);
+    perm.alloc(nblocks, s);
+    DBuf<int32_t> derr(1, s), tmp(sort_tmp_words(nblocks, key_bits), s);
     QT_HIP(hipMemsetAsync(derr.p, 0, sizeof(int32_t), s));
-    k_build_keys<<<grid_for(nblocks), 256, 0, s>>>(pI, pJ, nblocks, nbr, nbc, keys.p, perm.p, derr.p);
-    QT_LAUNCH("k_build_keys");
-    bitonic_sort(keys.p, perm.p, nblocks, s);
+    stable_sort(ListKeys{pI, pJ, nbr, nbc, derr.p}, KeyPermSink{keys.p, perm.p}, nblocks, key_bits, tmp.p, perm.p,
+                s);
     k_build_dups<<<grid_for(nblocks), 256, 0, s>>>(keys.p, nblocks, derr.p);
     QT_LAUNCH("k_build_dups");
     const int32_t err = read_scalar(derr.p, s);
     if (err & 1) fail(QT_ERR_ARG, "block index out of range");
     if (err & 2) fail(QT_ERR_DUPLICATE, "the same (I, J) block is listed twice");
-    M->bkey = std::move(keys);   // first nblocks entries are the sorted keys
+    M->bkey = std::move(keys);
     build_tree_levels(M, s);
 }
 
@@ -664,19 +698,20 @@ void build_tree_levels(qt_matrix* M, hipStream_t s) {
 
 // ------------------------------------------------------------ copy out
 
-// Copy-out into device arrays I, J, values (values may be NULL): row-major
-// sort keys and the permutation go to rk / perm, which hold npow2 entries
-// each (npow2 = the next power of two >= M->nblocks, as the sort needs).
-static void rowmajor_copy(const qt_matrix* M, uint64_t* rk, int32_t* perm, int32_t* I, int32_t* J, void* values,
-                          qt_prec out_type, hipStream_t s) {
+// Words of scratch of a row-major copy-out: the permutation and the sort's.
+static size_t rowmajor_words(const qt_matrix* M) {
+    return (size_t)M->nblocks + sort_tmp_words(M->nblocks, ilog2(M->n_rows / M->b));
+}
+
+// Copy-out into device arrays I, J, values (values may be NULL); tmp holds
+// rowmajor_words(M).
+static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t* J, void* values, qt_prec out_type,
+                          hipStream_t s) {
     const int64_t n = M->nblocks;
     const int bb = M->b * M->b;
-    const int64_t nbc = M->n_cols / M->b;
-    k_rowmajor_keys<<<grid_for(n), 256, 0, s>>>(M->bkey.p, n, nbc, rk, perm);
-    QT_LAUNCH("k_rowmajor_keys");
-    bitonic_sort(rk, perm, n, s);
-    k_coords<<<grid_for(n), 256, 0, s>>>(M->bkey.p, perm, n, I, J);
-    QT_LAUNCH("k_coords");
+    int32_t* perm = tmp;
+    stable_sort(RowKeys{M->bkey.p}, RowMajorSink{M->bkey.p, perm, I, J}, n, ilog2(M->n_rows / M->b), tmp + n,
+                perm, s);
     if (!values) return;   // pattern only
     const unsigned g = block_grid(n);
     if (M->vtype == QT_F64 && out_type == QT_F64)
@@ -690,12 +725,6 @@ static void rowmajor_copy(const qt_matrix* M, uint64_t* rk, int32_t* perm, int32
     QT_LAUNCH("k_gather_convert");
 }
 
-static int64_t pow2_at_least(int64_t n) {
-    int64_t p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
-
 void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec out_type, qt_mem where,
                hipStream_t s) {
     if (out_type != QT_F64 && out_type != QT_F32) fail(QT_ERR_UNSUPPORTED, "output type must be F64 or F32");
@@ -704,9 +733,7 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
     if (n == 0) return;
     if (!I || !J) fail(QT_ERR_ARG, "NULL output array");
     const int bb = M->b * M->b;
-    const int64_t npow2 = pow2_at_least(n);
-    DBuf<uint64_t> rk(npow2, s);
-    DBuf<int32_t> perm(npow2, s);
+    DBuf<int32_t> tmp(rowmajor_words(M), s);
     const size_t vbytes = values ? (size_t)n * bb * (out_type == QT_F64 ? sizeof(double) : sizeof(float)) : 0;
     DBuf<int32_t> tI, tJ;
     DBuf<char> tV;
@@ -721,7 +748,7 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
         oJ = tJ.p;
         oV = values ? (void*)tV.p : nullptr;
     }
-    rowmajor_copy(M, rk.p, perm.p, oI, oJ, oV, out_type, s);
+    rowmajor_copy(M, tmp.p, oI, oJ, oV, out_type, s);
     if (where == QT_MEM_HOST) {
         QT_HIP(hipMemcpyAsync(I, oI, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         QT_HIP(hipMemcpyAsync(J, oJ, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -732,14 +759,14 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
 
 // -------------------------------------------- copy-out without allocation
 
-// Scratch of the allocation-free copy-out: the row-major sort keys (8 bytes
-// per entry) followed by the permutation (4 bytes per entry) of up to
-// QT_NOALLOC_MAX_BLOCKS blocks, 12 MiB, one copy per device for the life of
-// the process. Host code never passes `scratch` itself (on the host it names
+// Scratch of the allocation-free copy-out of up to QT_NOALLOC_MAX_BLOCKS
+// blocks: the permutation, and the sort's counts and permutations, 12 MiB in
+// all, one copy per device for the life of the process. Host code never passes `scratch` itself (on the host it names
 // a stand-in, not device memory): it takes the array's device address once
 // per device with hipGetSymbolAddress and uses that address only.
 constexpr int64_t kNoAllocEntries = QT_NOALLOC_MAX_BLOCKS;
-static __device__ __align__(256) uint64_t scratch[kNoAllocEntries + kNoAllocEntries / 2];
+constexpr int64_t kNoAllocWords = 3 * kNoAllocEntries;
+static __device__ __align__(256) int32_t scratch[kNoAllocWords];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -771,14 +798,13 @@ void to_blocks_noalloc(const qt_matrix* M, int32_t* I, int32_t* J, void* values,
     int dev = 0;
     QT_HIP(hipGetDevice(&dev));
     if (dev != M->device) fail(QT_ERR_ARG, "the matrix lives on another device than the current one");
-    uint64_t* rk = static_cast<uint64_t*>(scratch_address(dev));
+    int32_t* tmp = static_cast<int32_t*>(scratch_address(dev));
     if (n == 0) return;
     if (!I || !J) fail(QT_ERR_ARG, "NULL output array");
-    int32_t* perm = reinterpret_cast<int32_t*>(rk + kNoAllocEntries);
-    // rk and perm are written in full (entries < n by the key kernel, the
-    // rest up to the power of two by the sort's padding) before any read, so
-    // nothing left by an earlier call is seen and nothing needs clearing.
-    rowmajor_copy(M, rk, perm, I, J, values, out_type, s);
+    // every word is written before it is read, so nothing left by an earlier
+    // call is seen and nothing needs clearing
+    if (rowmajor_words(M) > (size_t)kNoAllocWords) fail(QT_ERR_DEVICE, "copy-out scratch exceeded");
+    rowmajor_copy(M, tmp, I, J, values, out_type, s);
 }
 
 // ------------------------------------------------------------ norms
@@ -877,28 +903,20 @@ void build_norms(qt_matrix* M, hipStream_t s) {
     form_ready(M->ev_norms, s);
 }
 
-__global__ void k_gather_f64(const double* __restrict__ src, const int32_t* __restrict__ idx, int64_t n,
-                             double* __restrict__ dst);   // dst[i] = src[idx[i]] (below)
-
 // The squared norms of M's blocks in (I, J) row-major order, and of M.
 void norms_out(qt_matrix* M, double* block_norm2, double* total_norm2, qt_mem where, hipStream_t s) {
     build_norms(M, s);
     const int64_t n = M->nblocks;
     if (block_norm2 && n > 0) {
-        const int64_t npow2 = pow2_at_least(n);
-        DBuf<uint64_t> rk(npow2, s);
-        DBuf<int32_t> perm(npow2, s);
-        k_rowmajor_keys<<<grid_for(n), 256, 0, s>>>(M->bkey.p, n, M->n_cols / M->b, rk.p, perm.p);
-        QT_LAUNCH("k_rowmajor_keys");
-        bitonic_sort(rk.p, perm.p, n, s);
+        const int row_bits = ilog2(M->n_rows / M->b);
+        DBuf<int32_t> stmp(sort_tmp_words(n, row_bits), s), perm(n, s);
         DBuf<double> tmp;
         double* out = block_norm2;
         if (where == QT_MEM_HOST) {
             tmp.alloc(n, s);
             out = tmp.p;
         }
-        k_gather_f64<<<grid_for(n), 256, 0, s>>>(M->bn2, perm.p, n, out);
-        QT_LAUNCH("k_gather_f64");
+        stable_sort(RowKeys{M->bkey.p}, GatherF64Sink{M->bn2, out}, n, row_bits, stmp.p, perm.p, s);
         if (where == QT_MEM_HOST) QT_HIP(hipMemcpyAsync(block_norm2, tmp.p, n * sizeof(double), hipMemcpyDeviceToHost, s));
     }
     if (total_norm2) {
@@ -1117,10 +1135,8 @@ qt_matrix* add(qt_matrix* A, qt_matrix* B, hipStream_t s) {
 
 // --------------------------------------------------- value truncation
 
-// Squared Frobenius norm of every block, and its bit pattern as a sort key
-// (non-negative doubles order like their bit patterns).
-__global__ void k_block_norm2(const double* __restrict__ v, int64_t n, int bb, double* __restrict__ norm2,
-                              uint64_t* __restrict__ key, int32_t* __restrict__ idx) {
+// Squared Frobenius norm of every block.
+__global__ void k_block_norm2(const double* __restrict__ v, int64_t n, int bb, double* __restrict__ norm2) {
     __shared__ double part[256];
     for (int64_t t = blockIdx.x; t < n; t += gridDim.x) {
         double s = 0.0;
@@ -1134,19 +1150,9 @@ __global__ void k_block_norm2(const double* __restrict__ v, int64_t n, int bb, d
             if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
             __syncthreads();
         }
-        if (threadIdx.x == 0) {
-            norm2[t] = part[0];
-            key[t] = (uint64_t)__double_as_longlong(part[0]);
-            idx[t] = (int32_t)t;
-        }
+        if (threadIdx.x == 0) norm2[t] = part[0];
         __syncthreads();
     }
-}
-
-__global__ void k_gather_f64(const double* __restrict__ src, const int32_t* __restrict__ idx, int64_t n,
-                             double* __restrict__ dst) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[idx[i]];
 }
 
 // Sorted position p is removed while the running sum of squared norms up to
@@ -1179,16 +1185,11 @@ qt_matrix* truncate(qt_matrix* M, double eps, hipStream_t s, int64_t* removed, d
     if (removed) *removed = 0;
     if (removed_norm2) *removed_norm2 = 0.0;
     if (n == 0) return build(M->n_rows, M->n_cols, M->b, M->leaf, 0, nullptr, nullptr, nullptr, QT_MEM_DEVICE, s);
-    int64_t npow2 = 1;
-    while (npow2 < n) npow2 <<= 1;
     DBuf<double> norm2(n, s), sorted(n, s), excl(n + 1, s), dtmp(scan_tmp_elems(n) + 1, s);
-    DBuf<uint64_t> key(npow2, s);
-    DBuf<int32_t> idx(npow2, s), keep(n, s), pos(n + 1, s), itmp(scan_tmp_elems(n) + 1, s);
-    k_block_norm2<<<block_grid(n), 256, 0, s>>>(v, n, bb, norm2.p, key.p, idx.p);
+    DBuf<int32_t> idx(n, s), keep(n, s), pos(n + 1, s), itmp(scan_tmp_elems(n) + 1, s), stmp(sort_tmp_words(n, 64), s);
+    k_block_norm2<<<block_grid(n), 256, 0, s>>>(v, n, bb, norm2.p);
     QT_LAUNCH("k_block_norm2");
-    bitonic_sort(key.p, idx.p, n, s);
-    k_gather_f64<<<grid_for(n), 256, 0, s>>>(norm2.p, idx.p, n, sorted.p);
-    QT_LAUNCH("k_gather_f64");
+    stable_sort(NormKeys{norm2.p}, NormSink{sorted.p, idx.p}, n, 64, stmp.p, idx.p, s);
     exclusive_scan(sorted.p, excl.p, n, dtmp.p, s);
     k_trunc_flags<<<grid_for(n), 256, 0, s>>>(excl.p, sorted.p, n, eps * eps, idx.p, keep.p);
     QT_LAUNCH("k_trunc_flags");

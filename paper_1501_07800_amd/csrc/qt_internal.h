@@ -223,11 +223,6 @@ struct ArenaPlan {
     }
 };
 
-// sort.hip -----------------------------------------------------------------
-// Sort n (key, value) pairs by key, ascending (keys assumed distinct for a
-// unique order; equal keys are kept adjacent). Buffers of length npow2 >= n.
-void bitonic_sort(uint64_t* keys, int32_t* vals, int64_t n, hipStream_t s);
-
 // build.hip ----------------------------------------------------------------
 void build_histograms(qt_matrix* M, hipStream_t s);   // fills M->hist (synchronizes)
 const double* operand_f64(qt_matrix* M, hipStream_t s);

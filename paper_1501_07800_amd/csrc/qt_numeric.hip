@@ -27,9 +27,9 @@
 //    k_numeric_f32_b64, k_numeric_bf16x3_b64).
 // The dispatcher hands workgroup w to XCD w % 8, and each XCD has its own L2.
 // Consecutive C blocks in Morton order share most of their A and B blocks,
-// so the launch gives each XCD runs of consecutive tiles (1024 single-wave
-// tiles, or 256 four-wave C blocks; XCD x takes runs x, x+8, x+16, ...)
-// instead of every eighth tile: neighbours then meet in the same L2, while
+// so the launch gives each XCD runs of consecutive tiles (up to 1024
+// single-wave tiles, or 256 four-wave C blocks; XCD x takes runs x, x+8,
+// x+16, ...) instead of every eighth tile: neighbours then meet in the same L2, while
 // the interleaved runs keep the eight XCDs equally loaded. C is written with
 // non-temporal stores, since no later step of the multiply reads it.
 //
@@ -83,23 +83,33 @@ template <int BS> struct Geo {
     static constexpr int NCH = BS / KC;
 };
 
-constexpr int XCD_CHUNK_LOG = 10;
+// Longest runs of consecutive tiles given to one XCD (see the top of the
+// file): single-wave tiles, and four-wave C blocks.
+constexpr int XCD_RUN_LOG = 10, XCD_RUN_LOG_B64 = 8;
 
-// Logical tile of physical workgroup w; a bijection on [0, grid) when the
-// grid is a multiple of 8 << XCD_CHUNK_LOG (xcd_grid pads it so).
-template <int LOG = XCD_CHUNK_LOG>
-__device__ __forceinline__ int64_t xcd_logical(int64_t w) {
+// Logical tile of physical workgroup w, in runs of 2^log tiles; a bijection
+// on [0, grid) when the grid is a multiple of 8 << log (XcdGrid pads it so).
+__device__ __forceinline__ int64_t xcd_logical(int64_t w, int log) {
     const int64_t x = w & 7, i = w >> 3;
-    return ((((i >> LOG) << 3) + x) << LOG) | (i & ((1 << LOG) - 1));
+    return ((((i >> log) << 3) + x) << log) | (i & ((int64_t(1) << log) - 1));
 }
 
-template <int LOG = XCD_CHUNK_LOG>
-static unsigned xcd_grid(int64_t tiles) {
-    const int64_t q = int64_t(8) << LOG;
-    const int64_t g = (tiles + q - 1) / q * q;
-    if (g > 0x7fffffffLL) fail(QT_ERR_UNSUPPORTED, "numeric launch too large");
-    return (unsigned)g;
-}
+// The grid over `tiles` tiles and its run length: the longest that still gives
+// every XCD 16 runs. Runs of 1024 tiles whatever the size left a C of 374
+// blocks on one XCD (its numeric kernel 22.7 instead of 11.3 us) and one of
+// 70 k blocks with nine runs on some XCDs and eight on others (sysq of a
+// 24576 decay matrix 818 instead of 746 us with the copy-out).
+struct XcdGrid {
+    unsigned grid;
+    int log;
+    XcdGrid(int64_t tiles, int max_log) : log(max_log) {
+        while (log > 0 && tiles < (int64_t(128) << log)) --log;
+        const int64_t q = int64_t(8) << log;
+        const int64_t g = (tiles + q - 1) / q * q;
+        if (g > 0x7fffffffLL) fail(QT_ERR_UNSUPPORTED, "numeric launch too large");
+        grid = (unsigned)g;
+    }
+};
 
 // One wave: tile `sub` of a C block, over the products t0 .. t1-1. BUF: the
 // C tile is written with buffer stores instead of global stores (the same
@@ -457,9 +467,9 @@ __global__ __launch_bounds__(64, (MinWaves<T, BS>::value)) void k_numeric(const 
                                                 const int32_t* __restrict__ prodA,
                                                 const int32_t* __restrict__ prodB,
                                                 const int32_t* __restrict__ seg, int32_t nseg,
-                                                const int32_t* __restrict__ order, T* __restrict__ C) {
+                                                const int32_t* __restrict__ order, T* __restrict__ C, int xlog) {
     typedef Geo<BS> G;
-    const int64_t tile = xcd_logical<>(blockIdx.x);
+    const int64_t tile = xcd_logical(blockIdx.x, xlog);
     const int64_t q = tile / G::WPB;
     if (q >= nseg) return;
     const int64_t s = order ? order[q] : q;
@@ -491,10 +501,9 @@ __global__ __launch_bounds__(64, (MinWaves<T, BS>::value)) void k_numeric_byk(co
                                                                              const int32_t* __restrict__ prodB,
                                                                              const int32_t* __restrict__ seg,
                                                                              int32_t nseg,
-                                                                             const int32_t* __restrict__ order,
-                                                                             T* __restrict__ C) {
+                                                                             const int32_t* __restrict__ order, T* __restrict__ C, int xlog) {
     typedef Geo<BS> G;
-    const int64_t tile = xcd_logical<>(blockIdx.x);
+    const int64_t tile = xcd_logical(blockIdx.x, xlog);
     const int64_t q = tile / G::WPB;
     if (q >= nseg) return;
     const int64_t s = order[q];
@@ -511,9 +520,9 @@ __global__ __launch_bounds__(64) void k_numeric_bf16x3(const uint16_t* __restric
                                                        const int32_t* __restrict__ prodA,
                                                        const int32_t* __restrict__ prodB,
                                                        const int32_t* __restrict__ seg, int32_t nseg,
-                                                       const int32_t* __restrict__ order, double* __restrict__ C) {
+                                                       const int32_t* __restrict__ order, double* __restrict__ C, int xlog) {
     constexpr int WPB = (BS / 32) * (BS / 32);
-    const int64_t tile = xcd_logical<>(blockIdx.x);
+    const int64_t tile = xcd_logical(blockIdx.x, xlog);
     const int64_t q = tile / WPB;
     if (q >= nseg) return;
     const int64_t s = order ? order[q] : q;
@@ -531,10 +540,9 @@ __global__ __launch_bounds__(64, (MinWaves<T, BS>::value)) void k_numeric_op(con
                                                                            const int32_t* __restrict__ prodB,
                                                                            const int32_t* __restrict__ seg,
                                                                            int32_t nseg,
-                                                                           const int32_t* __restrict__ order,
-                                                                           T* __restrict__ C) {
+                                                                           const int32_t* __restrict__ order, T* __restrict__ C, int xlog) {
     typedef Geo<BS> G;
-    const int64_t tile = xcd_logical<>(blockIdx.x);
+    const int64_t tile = xcd_logical(blockIdx.x, xlog);
     const int64_t q = tile / G::WPB;
     if (q >= nseg) return;
     const int64_t s = order ? order[q] : q;
@@ -545,9 +553,9 @@ template <int BS>
 __global__ __launch_bounds__(64) void k_numeric_bf16x3_op(SplitOps ops, const int32_t* __restrict__ prodA,
                                                           const int32_t* __restrict__ prodB,
                                                           const int32_t* __restrict__ seg, int32_t nseg,
-                                                          const int32_t* __restrict__ order, double* __restrict__ C) {
+                                                          const int32_t* __restrict__ order, double* __restrict__ C, int xlog) {
     constexpr int WPB = (BS / 32) * (BS / 32);
-    const int64_t tile = xcd_logical<>(blockIdx.x);
+    const int64_t tile = xcd_logical(blockIdx.x, xlog);
     const int64_t q = tile / WPB;
     if (q >= nseg) return;
     const int64_t s = order ? order[q] : q;
@@ -656,8 +664,8 @@ __global__ __launch_bounds__(256, 4) void k_numeric_f64_b64(const double* __rest
                                                          const int32_t* __restrict__ prodA,
                                                          const int32_t* __restrict__ prodB,
                                                          const int32_t* __restrict__ seg, int32_t nseg,
-                                                         const int32_t* __restrict__ order, double* __restrict__ C) {
-    const int64_t q = xcd_logical<8>(blockIdx.x);
+                                                         const int32_t* __restrict__ order, double* __restrict__ C, int xlog) {
+    const int64_t q = xcd_logical(blockIdx.x, xlog);
     if (q >= nseg) return;   // uniform over the workgroup
     const int64_t s = order ? order[q] : q;
     lds_block_f64(A, B, prodA, prodB, seg[s], seg[s + 1], C + (size_t)s * (64 * 64));
@@ -766,8 +774,8 @@ __global__ __launch_bounds__(256) void k_numeric_f32_b64(const float* __restrict
                                                          const int32_t* __restrict__ prodA,
                                                          const int32_t* __restrict__ prodB,
                                                          const int32_t* __restrict__ seg, int32_t nseg,
-                                                         const int32_t* __restrict__ order, float* __restrict__ C) {
-    const int64_t q = xcd_logical<8>(blockIdx.x);
+                                                         const int32_t* __restrict__ order, float* __restrict__ C, int xlog) {
+    const int64_t q = xcd_logical(blockIdx.x, xlog);
     if (q >= nseg) return;   // uniform over the workgroup
     const int64_t s = order ? order[q] : q;
     lds_block_f32(A, B, prodA, prodB, seg[s], seg[s + 1], C + (size_t)s * (64 * 64));
@@ -776,28 +784,30 @@ __global__ __launch_bounds__(256) void k_numeric_f32_b64(const float* __restrict
 template <class T, int BS>
 static void launch_t(const NumericArgs& a, hipStream_t s) {
     if (sizeof(T) == 8 && BS == 64) {
-        k_numeric_f64_b64<<<xcd_grid<8>(a.nseg), 256, 0, s>>>((const double*)a.A, (const double*)a.B, a.prodA,
-                                                             a.prodB, a.seg, a.nseg, a.order, (double*)a.C);
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        k_numeric_f64_b64<<<x.grid, 256, 0, s>>>((const double*)a.A, (const double*)a.B, a.prodA, a.prodB, a.seg,
+                                                 a.nseg, a.order, (double*)a.C, x.log);
         QT_LAUNCH("k_numeric_f64_b64");
         return;
     }
     if (sizeof(T) == 4 && BS == 64) {
-        k_numeric_f32_b64<<<xcd_grid<8>(a.nseg), 256, 0, s>>>((const float*)a.A, (const float*)a.B, a.prodA,
-                                                             a.prodB, a.seg, a.nseg, a.order, (float*)a.C);
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        k_numeric_f32_b64<<<x.grid, 256, 0, s>>>((const float*)a.A, (const float*)a.B, a.prodA, a.prodB, a.seg,
+                                                 a.nseg, a.order, (float*)a.C, x.log);
         QT_LAUNCH("k_numeric_f32_b64");
         return;
     }
     typedef Geo<BS> G;
-    const unsigned grid = xcd_grid<>((int64_t)a.nseg * G::WPB);
+    const XcdGrid x((int64_t)a.nseg * G::WPB, XCD_RUN_LOG);
     if (a.by_k && a.order) {
         const size_t cap = occupancy_cap_lds(ByKCap<T, BS>::waves);
-        k_numeric_byk<T, BS><<<grid, 64, cap, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg,
-                                                   a.order, (T*)a.C);
+        k_numeric_byk<T, BS><<<x.grid, 64, cap, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg,
+                                                   a.order, (T*)a.C, x.log);
         QT_LAUNCH("k_numeric_byk");
         return;
     }
-    k_numeric<T, BS><<<grid, 64, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg, a.order,
-                                         (T*)a.C);
+    k_numeric<T, BS><<<x.grid, 64, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg, a.order,
+                                         (T*)a.C, x.log);
     QT_LAUNCH("k_numeric");
 }
 
@@ -916,9 +926,8 @@ __global__ __launch_bounds__(256, 2) void k_numeric_bf16x3_b64(const uint16_t* _
                                                                 const int32_t* __restrict__ prodA,
                                                                 const int32_t* __restrict__ prodB,
                                                                 const int32_t* __restrict__ seg, int32_t nseg,
-                                                                const int32_t* __restrict__ order,
-                                                                double* __restrict__ C) {
-    const int64_t q = xcd_logical<8>(blockIdx.x);
+                                                                const int32_t* __restrict__ order, double* __restrict__ C, int xlog) {
+    const int64_t q = xcd_logical(blockIdx.x, xlog);
     if (q >= nseg) return;   // uniform over the workgroup
     const int64_t s = order ? order[q] : q;
     lds_block_bf16x3(Ahi, Alo, Bhi_t, Blo_t, prodA, prodB, seg[s], seg[s + 1], C + (size_t)s * (64 * 64));
@@ -927,25 +936,25 @@ __global__ __launch_bounds__(256, 2) void k_numeric_bf16x3_b64(const uint16_t* _
 template <int BS>
 static void launch_bf(const NumericArgs& a, hipStream_t s) {
     if (BS == 64) {
-        const unsigned grid = xcd_grid<8>(a.nseg);
-        k_numeric_bf16x3_b64<<<grid, 256, 0, s>>>(a.Ahi, a.Alo, a.Bhi_t, a.Blo_t, a.prodA, a.prodB, a.seg,
-                                                  a.nseg, a.order, (double*)a.C);
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        k_numeric_bf16x3_b64<<<x.grid, 256, 0, s>>>(a.Ahi, a.Alo, a.Bhi_t, a.Blo_t, a.prodA, a.prodB, a.seg,
+                                                  a.nseg, a.order, (double*)a.C, x.log);
         QT_LAUNCH("k_numeric_bf16x3_b64");
         return;
     }
     constexpr int WPB = (BS / 32) * (BS / 32);
-    const unsigned grid = xcd_grid<>((int64_t)a.nseg * WPB);
-    k_numeric_bf16x3<BS><<<grid, 64, 0, s>>>(a.Ahi, a.Alo, a.Bhi_t, a.Blo_t, a.prodA, a.prodB, a.seg, a.nseg,
-                                             a.order, (double*)a.C);
+    const XcdGrid x((int64_t)a.nseg * WPB, XCD_RUN_LOG);
+    k_numeric_bf16x3<BS><<<x.grid, 64, 0, s>>>(a.Ahi, a.Alo, a.Bhi_t, a.Blo_t, a.prodA, a.prodB, a.seg, a.nseg,
+                                             a.order, (double*)a.C, x.log);
     QT_LAUNCH("k_numeric_bf16x3");
 }
 
 template <class T, int BS>
 static void launch_op(const NumericArgs& a, hipStream_t s) {
     typedef Geo<BS> G;
-    const unsigned grid = xcd_grid<>((int64_t)a.nseg * G::WPB);
-    k_numeric_op<T, BS><<<grid, 64, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg, a.order,
-                                            (T*)a.C);
+    const XcdGrid x((int64_t)a.nseg * G::WPB, XCD_RUN_LOG);
+    k_numeric_op<T, BS><<<x.grid, 64, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg, a.order,
+                                            (T*)a.C, x.log);
     QT_LAUNCH("k_numeric_op");
 }
 
@@ -953,8 +962,8 @@ template <int BS>
 static void launch_bf_op(const NumericArgs& a, hipStream_t s) {
     constexpr int WPB = (BS / 32) * (BS / 32);
     const SplitOps ops{a.Ahi, a.Alo, a.Ahi_t, a.Alo_t, a.Bhi, a.Blo, a.Bhi_t, a.Blo_t};
-    const unsigned grid = xcd_grid<>((int64_t)a.nseg * WPB);
-    k_numeric_bf16x3_op<BS><<<grid, 64, 0, s>>>(ops, a.prodA, a.prodB, a.seg, a.nseg, a.order, (double*)a.C);
+    const XcdGrid x((int64_t)a.nseg * WPB, XCD_RUN_LOG);
+    k_numeric_bf16x3_op<BS><<<x.grid, 64, 0, s>>>(ops, a.prodA, a.prodB, a.seg, a.nseg, a.order, (double*)a.C, x.log);
     QT_LAUNCH("k_numeric_bf16x3_op");
 }
 
@@ -1135,8 +1144,8 @@ template <int KIND, int BS, bool LDS>
 __global__ __launch_bounds__(LDS ? 256 : 64) void k_batch_flat(const BatchProblem* __restrict__ probs,
                                                                  const char* __restrict__ base,
                                                                  const int64_t* __restrict__ item_base,
-                                                                 int32_t nprob) {
-    const int64_t it = LDS ? xcd_logical<8>(blockIdx.x) : xcd_logical<>(blockIdx.x);
+                                                                 int32_t nprob, int xlog) {
+    const int64_t it = xcd_logical(blockIdx.x, xlog);
     if (it >= item_base[nprob]) return;
     Item<KIND, BS, LDS>::template run<true>(probs, base, item_base, nprob, it);
 }
@@ -1207,7 +1216,7 @@ template <int KIND, int BS, bool LDS>
 __global__ __launch_bounds__(LDS ? 256 : 64) void k_batch_xcd(
     const BatchProblem* __restrict__ probs, const char* __restrict__ base, const int64_t* __restrict__ item_base,
     int32_t nprob, unsigned long long* __restrict__ counters) {
-    constexpr int LOG = LDS ? 8 : XCD_CHUNK_LOG;
+    constexpr int LOG = LDS ? XCD_RUN_LOG_B64 : XCD_RUN_LOG;
     __shared__ unsigned long long grab[2];
     const int64_t total = item_base[nprob];
     const int64_t x = blockIdx.x & 7;
@@ -1276,8 +1285,8 @@ static void launch_batch_k(const BatchLaunch& L, hipStream_t s) {
     constexpr int T = Item<KIND, BS, LDS>::THREADS;
     const int64_t items = L.total_items;
     if (L.schedule == 0) {
-        const unsigned grid = LDS ? xcd_grid<8>(items) : xcd_grid<>(items);
-        k_batch_flat<KIND, BS, LDS><<<grid, T, 0, s>>>(L.probs, L.base, L.item_base, L.nprob);
+        const XcdGrid x(items, LDS ? XCD_RUN_LOG_B64 : XCD_RUN_LOG);
+        k_batch_flat<KIND, BS, LDS><<<x.grid, T, 0, s>>>(L.probs, L.base, L.item_base, L.nprob, x.log);
         QT_LAUNCH("k_batch_flat");
         return;
     }

@@ -531,8 +531,8 @@ __global__ __launch_bounds__(64) void k_numeric_bf16x3(const uint16_t* __restric
 }
 
 // One multiply whose products may read blocks transposed (transposed
-// operands, symmetric operands stored as a triangle): one wave per tile, as
-// k_numeric at b = 16 and 32, at every block size.
+// operands, symmetric operands stored as a triangle) at b = 16 and 32: one
+// wave per tile, as k_numeric.
 template <class T, int BS>
 __global__ __launch_bounds__(64, (MinWaves<T, BS>::value)) void k_numeric_op(const T* __restrict__ A,
                                                                            const T* __restrict__ B,
@@ -781,6 +781,140 @@ __global__ __launch_bounds__(256) void k_numeric_f32_b64(const float* __restrict
     lds_block_f32(A, B, prodA, prodB, seg[s], seg[s + 1], C + (size_t)s * (64 * 64));
 }
 
+// b = 64, fp64 or fp32, for product lists whose blocks may be read transposed
+// (PROD_TRANS): the LDS sharing of the two kernels above. A staged half holds
+// 64 rows (or columns) of op(X) by 32 inner indices in one of two layouts,
+// whichever the stored block gives with whole 16-byte pieces: row-major in
+// the inner index (MK: A as stored, B transposed) or inner index first (KM: B
+// as stored, A transposed). Both operands use the same two loaders; the
+// choice is uniform over the workgroup, one scalar branch per half. Rows and
+// columns of a wave's tile are not interleaved here, since a KM panel then
+// gives both 16-wide tiles of a lane in one two-address LDS read. The inner
+// index order is the per-wave kernel's, so every result is bitwise what that
+// gives. A^T A of 20 k blocks (0.51 TFLOP), a wave per 32 x 32 tile, which
+// reads every operand from L2 twice, against this: FP32 8.22 and 5.26 ms,
+// FP64 10.9 and 10.7 ms, the split path (k_numeric_bf16x3_op_b64) 7.77 and
+// 2.68 ms.
+template <class T> struct LdsOp {
+    static constexpr int VEC = 16 / sizeof(T), KH = 32;
+    static constexpr int MKROW = sizeof(T) == 8 ? 34 : 36;   // 16 rows of a lane group: distinct banks
+    static constexpr int KMROW = sizeof(T) == 8 ? 72 : 68;   // the groups' rows: distinct banks
+    static constexpr int WORDS = 64 * MKROW > KH * KMROW ? 64 * MKROW : KH * KMROW;
+    static constexpr int PIECES = 64 * KH / VEC / 256;       // 16-byte pieces per thread and half
+    typedef T vec_t __attribute__((ext_vector_type(VEC)));
+
+    static __device__ __forceinline__ void fetch(const T* __restrict__ x, bool km, int half, vec_t (&p)[PIECES]) {
+        const int tid = threadIdx.x;
+        constexpr int PR = KH / VEC;   // pieces per MK row
+        const int base = km ? tid * VEC + half * KH * 64 : (tid / PR) * 64 + (tid % PR) * VEC + half * KH;
+        const int step = km ? 256 * VEC : (256 / PR) * 64;
+#pragma unroll
+        for (int r = 0; r < PIECES; ++r) p[r] = *reinterpret_cast<const vec_t*>(x + base + r * step);
+    }
+    static __device__ __forceinline__ void stage(T* lds, bool km, const vec_t (&p)[PIECES]) {
+        const int tid = threadIdx.x;
+        constexpr int PR = KH / VEC, PK = 64 / VEC;
+        const int base = km ? (tid / PK) * KMROW + (tid % PK) * VEC : (tid / PR) * MKROW + (tid % PR) * VEC;
+        const int step = km ? (256 / PK) * KMROW : (256 / PR) * MKROW;
+#pragma unroll
+        for (int r = 0; r < PIECES; ++r) *reinterpret_cast<vec_t*>(lds + base + r * step) = p[r];
+    }
+    // half a panel, steps ks = 4 q .. 4 q + 3: x[mt][ks - 4 q] is row (or column)
+    // w + 16 mt + r16, inner index 4 VEC (ks / VEC) + VEC g + ks % VEC
+    static __device__ __forceinline__ void panel(const T* lds, bool km, int q, int w, int r16, int g, T (&x)[2][4]) {
+        if (km) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int ks = 4 * q + e;
+                const T* at = lds + (4 * VEC * (ks / VEC) + VEC * g + ks % VEC) * KMROW + w + r16;
+                x[0][e] = at[0];
+                x[1][e] = at[16];
+            }
+        } else {
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4 / VEC; ++v) {
+                    const vec_t y = *reinterpret_cast<const vec_t*>(lds + (w + mt * 16 + r16) * MKROW +
+                                                                    4 * VEC * (4 / VEC * q + v) + VEC * g);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) x[mt][VEC * v + e] = y[e];
+                }
+        }
+    }
+};
+
+template <class T>
+__global__ __launch_bounds__(256, 4) void k_numeric_op_b64(const T* __restrict__ A, const T* __restrict__ B,
+                                                           const int32_t* __restrict__ prodA,
+                                                           const int32_t* __restrict__ prodB,
+                                                           const int32_t* __restrict__ seg, int32_t nseg,
+                                                           const int32_t* __restrict__ order, T* __restrict__ C,
+                                                           int xlog) {
+    typedef LdsOp<T> O;
+    constexpr int BS = 64;
+    const int64_t q = xcd_logical(blockIdx.x, xlog);
+    if (q >= nseg) return;   // uniform over the workgroup
+    const int64_t s = order ? order[q] : q;
+    const int32_t t0 = seg[s], t1 = seg[s + 1];
+    T* c = C + (size_t)s * (BS * BS);
+    __shared__ __attribute__((aligned(16))) T la[O::WORDS];
+    __shared__ __attribute__((aligned(16))) T lb[O::WORDS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    typedef typename Mfma<T>::acc acc_t;
+    acc_t acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+    typename O::vec_t pa[O::PIECES], pb[O::PIECES];
+    int32_t ia = prodA[t0], ib = prodB[t0];   // a segment holds at least one product
+    O::fetch(A + (size_t)(ia & PROD_INDEX) * (BS * BS), ia < 0, 0, pa);
+    O::fetch(B + (size_t)(ib & PROD_INDEX) * (BS * BS), ib >= 0, 0, pb);
+    for (int32_t t = t0; t < t1; ++t) {
+        const bool ka = ia < 0, kb = ib >= 0;   // op(A) transposed, op(B) as stored: inner index first
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            __syncthreads();   // every wave is done reading the previous half
+            O::stage(la, ka, pa);
+            O::stage(lb, kb, pb);
+            __syncthreads();
+            // the next half's loads are in flight during this half's MFMAs
+            if (h == 1 && t + 1 < t1) {
+                ia = prodA[t + 1];
+                ib = prodB[t + 1];
+            }
+            if (h == 0 || t + 1 < t1) {
+                O::fetch(A + (size_t)(ia & PROD_INDEX) * (BS * BS), ia < 0, 1 - h, pa);
+                O::fetch(B + (size_t)(ib & PROD_INDEX) * (BS * BS), ib >= 0, 1 - h, pb);
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                T ar[2][4], br[2][4];
+                O::panel(la, ka, p, wm, r16, g, ar);
+                O::panel(lb, kb, p, wn, r16, g, br);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                        for (int nt = 0; nt < 2; ++nt)
+                            acc[mt][nt] = Mfma<T>::step(ar[mt][ks], br[nt][ks], acc[mt][nt]);
+            }
+        }
+    }
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                __builtin_nontemporal_store(acc[mt][nt][i],
+                                            c + (wm + mt * 16 + Mfma<T>::row(g, i)) * BS + wn + nt * 16 + r16);
+}
+
 template <class T, int BS>
 static void launch_t(const NumericArgs& a, hipStream_t s) {
     if (sizeof(T) == 8 && BS == 64) {
@@ -826,9 +960,10 @@ constexpr int BFL_ARR = 64 * BFL_ROW;      // elements per staged block
 
 // One C block of the LDS-sharing kernel below, products t0 .. t1-1, into c
 // (all four waves of the workgroup take part).
+template <bool DYN = false>
 __device__ __forceinline__ void lds_block_bf16x3(const uint16_t* __restrict__ Ahi, const uint16_t* __restrict__ Alo, const uint16_t* __restrict__ Bhi_t, const uint16_t* __restrict__ Blo_t,
         const int32_t* __restrict__ prodA, const int32_t* __restrict__ prodB, int32_t t0, int32_t t1,
-        double* __restrict__ c) {
+        double* __restrict__ c, const SplitOps* ops = nullptr) {
     constexpr int BS = 64, MT = 2;
     __shared__ __attribute__((aligned(16))) uint16_t lds[4 * BFL_ARR];   // Ahi, Alo, Bhi^T, Blo^T
     const int tid = threadIdx.x;
@@ -838,11 +973,19 @@ __device__ __forceinline__ void lds_block_bf16x3(const uint16_t* __restrict__ Ah
 
     // thread tid moves 16-byte pieces tid and tid + 256 of each 64 x 64 block:
     // piece q is row q / 8, elements 8 * (q % 8) .. + 7
-    const uint16_t* const base4[4] = {Ahi, Alo, Bhi_t, Blo_t};
+    const uint16_t* base4[4] = {Ahi, Alo, Bhi_t, Blo_t};
     u32x4 st0, st1, st2, st3, st4, st5, st6, st7;   // [block m][half h] = st(2m + h)
 #define QT_BFL_FETCH(t)                                                                             \
     do {                                                                                            \
-        const size_t oa_ = (size_t)prodA[t] * (BS * BS), ob_ = (size_t)prodB[t] * (BS * BS);        \
+        const int32_t ia_ = prodA[t], ib_ = prodB[t];                                               \
+        if constexpr (DYN) { /* a transposed block's row-major op form is its other layout */       \
+            base4[0] = ia_ < 0 ? ops->Ahi_t : ops->Ahi;                                             \
+            base4[1] = ia_ < 0 ? ops->Alo_t : ops->Alo;                                             \
+            base4[2] = ib_ < 0 ? ops->Bhi : ops->Bhi_t;                                             \
+            base4[3] = ib_ < 0 ? ops->Blo : ops->Blo_t;                                             \
+        }                                                                                           \
+        const size_t oa_ = (size_t)(DYN ? ia_ & PROD_INDEX : ia_) * (BS * BS);                      \
+        const size_t ob_ = (size_t)(DYN ? ib_ & PROD_INDEX : ib_) * (BS * BS);                      \
         st0 = *reinterpret_cast<const u32x4*>(base4[0] + oa_ + (size_t)tid * 8);                    \
         st1 = *reinterpret_cast<const u32x4*>(base4[0] + oa_ + (size_t)(tid + 256) * 8);            \
         st2 = *reinterpret_cast<const u32x4*>(base4[1] + oa_ + (size_t)tid * 8);                    \
@@ -933,6 +1076,18 @@ __global__ __launch_bounds__(256, 2) void k_numeric_bf16x3_b64(const uint16_t* _
     lds_block_bf16x3(Ahi, Alo, Bhi_t, Blo_t, prodA, prodB, seg[s], seg[s + 1], C + (size_t)s * (64 * 64));
 }
 
+__global__ __launch_bounds__(256, 2) void k_numeric_bf16x3_op_b64(SplitOps ops, const int32_t* __restrict__ prodA,
+                                                                   const int32_t* __restrict__ prodB,
+                                                                   const int32_t* __restrict__ seg, int32_t nseg,
+                                                                   const int32_t* __restrict__ order,
+                                                                   double* __restrict__ C, int xlog) {
+    const int64_t q = xcd_logical(blockIdx.x, xlog);
+    if (q >= nseg) return;   // uniform over the workgroup
+    const int64_t s = order ? order[q] : q;
+    lds_block_bf16x3<true>(nullptr, nullptr, nullptr, nullptr, prodA, prodB, seg[s], seg[s + 1],
+                           C + (size_t)s * (64 * 64), &ops);
+}
+
 template <int BS>
 static void launch_bf(const NumericArgs& a, hipStream_t s) {
     if (BS == 64) {
@@ -951,20 +1106,33 @@ static void launch_bf(const NumericArgs& a, hipStream_t s) {
 
 template <class T, int BS>
 static void launch_op(const NumericArgs& a, hipStream_t s) {
-    typedef Geo<BS> G;
-    const XcdGrid x((int64_t)a.nseg * G::WPB, XCD_RUN_LOG);
-    k_numeric_op<T, BS><<<x.grid, 64, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg, a.order,
-                                            (T*)a.C, x.log);
-    QT_LAUNCH("k_numeric_op");
+    if constexpr (BS == 64) {
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        k_numeric_op_b64<T><<<x.grid, 256, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg,
+                                                   a.order, (T*)a.C, x.log);
+        QT_LAUNCH("k_numeric_op_b64");
+    } else {
+        const XcdGrid x(a.nseg, XCD_RUN_LOG);
+        k_numeric_op<T, BS><<<x.grid, 64, 0, s>>>((const T*)a.A, (const T*)a.B, a.prodA, a.prodB, a.seg, a.nseg,
+                                                  a.order, (T*)a.C, x.log);
+        QT_LAUNCH("k_numeric_op");
+    }
 }
 
 template <int BS>
 static void launch_bf_op(const NumericArgs& a, hipStream_t s) {
-    constexpr int WPB = (BS / 32) * (BS / 32);
     const SplitOps ops{a.Ahi, a.Alo, a.Ahi_t, a.Alo_t, a.Bhi, a.Blo, a.Bhi_t, a.Blo_t};
-    const XcdGrid x((int64_t)a.nseg * WPB, XCD_RUN_LOG);
-    k_numeric_bf16x3_op<BS><<<x.grid, 64, 0, s>>>(ops, a.prodA, a.prodB, a.seg, a.nseg, a.order, (double*)a.C, x.log);
-    QT_LAUNCH("k_numeric_bf16x3_op");
+    if constexpr (BS == 64) {
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        k_numeric_bf16x3_op_b64<<<x.grid, 256, 0, s>>>(ops, a.prodA, a.prodB, a.seg, a.nseg, a.order, (double*)a.C,
+                                                       x.log);
+        QT_LAUNCH("k_numeric_bf16x3_op_b64");
+    } else {
+        const XcdGrid x(a.nseg, XCD_RUN_LOG);
+        k_numeric_bf16x3_op<BS><<<x.grid, 64, 0, s>>>(ops, a.prodA, a.prodB, a.seg, a.nseg, a.order, (double*)a.C,
+                                                      x.log);
+        QT_LAUNCH("k_numeric_bf16x3_op");
+    }
 }
 
 void launch_numeric(const NumericArgs& a, hipStream_t s) {

@@ -64,26 +64,51 @@ __device__ __forceinline__ int32_t hi32(int64_t v) { return (int32_t)((uint64_t)
 
 __device__ __forceinline__ uint64_t lanes_below(int lane) { return lane ? (~0ull >> (64 - lane)) : 0ull; }
 
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+// Inclusive prefix sum over the wave with data-parallel row moves: one add
+// each, where a general shuffle goes through the LDS crossbar (the leaf
+// kernels are bound by instructions and these chains).
+__device__ __forceinline__ int wave_incl_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // from 1 lane below, within a row of 16
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // 2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // 4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // a row's last lane into the next: rows 1, 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // lane 31 into rows 2 and 3
     return x;
 }
 
-__device__ __forceinline__ uint64_t wave_or(uint64_t x) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) x |= __shfl_xor(x, d, 64);
-    return x;
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_incl_scan(x), 63); }
+
+__device__ __forceinline__ int wave_excl_scan(int x) { return wave_incl_scan(x) - x; }
+
+// Swaps index bits a > b of a 64-bit mask (bit i of the result is the bit of
+// the mask whose index has these two bits of i exchanged). pos: the mask of
+// all indices with bit b set and bit a clear.
+__device__ __forceinline__ uint64_t swap_index_bits(uint64_t m, int a, int b, uint64_t pos) {
+    const int sh = (1 << a) - (1 << b);
+    const uint64_t d = ((m >> sh) ^ m) & pos;
+    return m ^ d ^ (d << sh);
 }
 
-__device__ __forceinline__ int wave_excl_scan(int x, int lane) {
-    int v = x;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int y = __shfl_up(v, d, 64);
-        if (lane >= d) v += y;
+// A leaf's occupancy in Morton order (index bits r2 c2 r1 c1 r0 c0) as
+// row-major (r2 r1 r0 c2 c1 c0), and that transposed as column-major; leaves
+// of 4 x 4 and 2 x 2 blocks have the lower four and two index bits only.
+__device__ __forceinline__ uint64_t morton_to_rowmajor(uint64_t m, int lb_log) {
+    if (lb_log == 3) {
+        m = swap_index_bits(m, 4, 3, 0x0000FF000000FF00ull);   // r2 r1 c2 c1 r0 c0
+        m = swap_index_bits(m, 2, 1, 0x0C0C0C0C0C0C0C0Cull);   // r2 r1 c2 r0 c1 c0
+        return swap_index_bits(m, 3, 2, 0x00F000F000F000F0ull);
     }
-    return v - x;
+    return lb_log == 2 ? swap_index_bits(m, 2, 1, 0x0C0Cull) : m;
+}
+__device__ __forceinline__ uint64_t rowmajor_to_colmajor(uint64_t m, int lb_log) {
+    if (lb_log == 3) {
+        m = swap_index_bits(m, 5, 2, 0x00000000F0F0F0F0ull);
+        m = swap_index_bits(m, 4, 1, 0x0000CCCC0000CCCCull);
+        return swap_index_bits(m, 3, 0, 0x00AA00AA00AA00AAull);
+    }
+    if (lb_log == 2) return swap_index_bits(swap_index_bits(m, 3, 1, 0x00CCull), 2, 0, 0x0A0Aull);
+    return lb_log == 1 ? swap_index_bits(m, 1, 0, 0x2ull) : m;
 }
 
 __device__ __forceinline__ int4 load_children(const int32_t* tab, int32_t node) {
@@ -153,9 +178,16 @@ struct TreeStep {
 };
 
 // Child a of op(A) and child b of op(B) form a pair: both present and, with
-// a norm threshold, the product of their norms not below it.
-__device__ __forceinline__ bool pair_kept(const TreeStep& st, int32_t a, int32_t b) {
-    return a >= 0 && b >= 0 && (!st.An2 || st.An2[a] * st.Bn2[b] >= st.tau2);
+// a norm threshold (PRUNE), the product of their norms not below it. PRUNE is
+// a template argument of every traversal kernel: tested at run time, the
+// norm loads sat behind 80 branches of k_tree_fill, 36 KB of code of which a
+// level of a few nodes runs each line once, from a cold instruction cache.
+template <bool PRUNE>
+__device__ __forceinline__ bool pair_kept(const double* An2, const double* Bn2, double tau2, int32_t a, int32_t b) {
+    if constexpr (PRUNE)
+        return a >= 0 && b >= 0 && An2[a] * Bn2[b] >= tau2;
+    else
+        return (a | b) >= 0;
 }
 
 // Children of an operand node in the orientation of op(X): for a transposed
@@ -192,7 +224,8 @@ __device__ __forceinline__ bool quadrant_dropped(int upper, uint64_t key, int mn
     return upper && mn == 2 && morton_row(key) == morton_col(key);
 }
 
-__device__ int64_t tree_count_node(const TreeStep& st, int32_t c, int lane) {
+template <bool PRUNE>
+__device__ __forceinline__ int64_t tree_count_node(const TreeStep& st, int32_t c, int lane) {
     if (c >= *st.ncount) {
         if (lane == 0) st.cnt[c] = 0;
         return 0;
@@ -204,10 +237,11 @@ __device__ int64_t tree_count_node(const TreeStep& st, int32_t c, int lane) {
             const int32_t p = s0 + base + lane;
             int4 a, b;   // A child (m, k) at 2m + k, B child (k, n) at 2k + n
             op_children2(st.Ach, st.fa[p], st.ta, st.Bch, st.fb[p], st.tb, a, b);
-            t0 += pair_kept(st, a.x, b.x) + pair_kept(st, a.y, b.z);
-            t1 += pair_kept(st, a.x, b.y) + pair_kept(st, a.y, b.w);
-            t2 += pair_kept(st, a.z, b.x) + pair_kept(st, a.w, b.z);
-            t3 += pair_kept(st, a.z, b.y) + pair_kept(st, a.w, b.w);
+            auto kept = [&](int32_t x, int32_t y) { return pair_kept<PRUNE>(st.An2, st.Bn2, st.tau2, x, y); };
+            t0 += kept(a.x, b.x) + kept(a.y, b.z);
+            t1 += kept(a.x, b.y) + kept(a.y, b.w);
+            t2 += kept(a.z, b.x) + kept(a.w, b.z);
+            t3 += kept(a.z, b.y) + kept(a.w, b.w);
         }
     }
     if (quadrant_dropped(st.upper, st.ckey[c], 2)) t2 = 0;
@@ -234,55 +268,92 @@ __device__ void tree_level_totals(const TreeStep& st, int64_t T) {
 // Workgroup aggregates of a level are summed in groups of 64 (aggregate path, below).
 constexpr int AGG_GROUP_LOG = 6;
 
-// Child pairs of the next level's pairs, per quadrant q, summed over the
-// wave (the rule of tree_count_node one level down), into u: each lane
-// holds at most two pairs (a0, b0) and (a1, b1) (valid: has0, has1), whose
-// child tables x0, y0, x1, y1 were loaded by next_level_tables; the totals
-// are wave-uniform, kept in scalar registers (popcounts of ballots).
-__device__ __forceinline__ void next_level_tables(const TreeStep& st, bool has0, int32_t a0, int32_t b0, bool has1,
-                                                  int32_t a1, int32_t b1, int4& x0, int4& y0, int4& x1,
-                                                  int4& y1) {
-    // a lane without a pair reads node 0 (every level of a non-empty operand
-    // has one) and drops the value, so the loads need no branch
-    const int4 rx0 = *reinterpret_cast<const int4*>(st.nAch + 4 * (int64_t)(has0 ? a0 : 0));
-    const int4 ry0 = *reinterpret_cast<const int4*>(st.nBch + 4 * (int64_t)(has0 ? b0 : 0));
-    const int4 rx1 = *reinterpret_cast<const int4*>(st.nAch + 4 * (int64_t)(has1 ? a1 : 0));
-    const int4 ry1 = *reinterpret_cast<const int4*>(st.nBch + 4 * (int64_t)(has1 ? b1 : 0));
-    const int4 none = make_int4(-1, -1, -1, -1);
-    x0 = has0 ? rx0 : none;
-    y0 = has0 ? ry0 : none;
-    x1 = has1 ? rx1 : none;
-    y1 = has1 ? ry1 : none;
+// Counting the next level's child pairs (the rule of tree_count_node one
+// level down). A pair of child tables x, y gives quadrant q = 2m + n the pairs
+// k' = 0 and 1 for which x(m, k') and y(k', n) are both present: with the
+// presence bits spread over the bytes of a word per k', byte q, two ANDs and
+// an add count all four quadrants at once. A lane adds up its own pairs that
+// way; the lanes are summed once per node. (Counted with a ballot per
+// quadrant and k', 64 of them per 64 pairs into 16 scalar counters, the
+// compiler ran out of scalar registers: 800 of k_tree_fill's 3400 instructions
+// moved spilled ones, 36 KB of code. With this and the template arguments
+// above, 12 KB, the traversal of decay32768 went from 0.162 to 0.130 ms alone,
+// of a random 48000 product from 0.386 to 0.334.)
+struct QuadBytes {
+    uint32_t k0, k1;
+};
+
+__device__ __forceinline__ uint32_t present(int32_t node) { return (uint32_t)~node >> 31; }
+
+__device__ __forceinline__ QuadBytes a_bytes(int4 x, uint32_t has) {
+    return {(present(x.x) * 0x00000101u + present(x.z) * 0x01010000u) * has,
+            (present(x.y) * 0x00000101u + present(x.w) * 0x01010000u) * has};
+}
+__device__ __forceinline__ QuadBytes b_bytes(int4 y, uint32_t has) {
+    return {(present(y.x) * 0x00010001u + present(y.y) * 0x01000100u) * has,
+            (present(y.z) * 0x00010001u + present(y.w) * 0x01000100u) * has};
 }
 
-__device__ __forceinline__ void next_level_count(const TreeStep& st, int4 x, int4 y, uint32_t (&u)[4]) {
-    x = op_swap(x, st.ta);
-    y = op_swap(y, st.tb);
-    auto kept = [&](int32_t p, int32_t q) {
-        return p >= 0 && q >= 0 && (!st.nAn2 || st.nAn2[p] * st.nBn2[q] >= st.tau2);
-    };
-    u[0] += __popcll(__ballot(kept(x.x, y.x))) + __popcll(__ballot(kept(x.y, y.z)));
-    u[1] += __popcll(__ballot(kept(x.x, y.y))) + __popcll(__ballot(kept(x.y, y.w)));
-    u[2] += __popcll(__ballot(kept(x.z, y.x))) + __popcll(__ballot(kept(x.w, y.z)));
-    u[3] += __popcll(__ballot(kept(x.z, y.y))) + __popcll(__ballot(kept(x.w, y.w)));
+// Byte q: the child pairs of quadrant q that a norm threshold keeps.
+__device__ __forceinline__ uint32_t pruned_bytes(const double* An2, const double* Bn2, double tau2, int4 x, int4 y) {
+    const int xa[4] = {x.x, x.y, x.z, x.w}, yb[4] = {y.x, y.y, y.z, y.w};
+    uint32_t u = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            u += (uint32_t)pair_kept<true>(An2, Bn2, tau2, xa[(q & 2) + k], yb[2 * k + (q & 1)]) << (8 * q);
+    return u;
+}
+
+// The child table of one child of a pair: a NIL child reads node 0 (every
+// level of a non-empty operand has one) and its value is dropped, so the loads
+// need no branch.
+__device__ __forceinline__ int4 next_table(const int32_t* tab, int32_t node) {
+    return *reinterpret_cast<const int4*>(tab + 4 * (int64_t)(node >= 0 ? node : 0));
+}
+
+constexpr int QUAD_FLUSH = 60;   // chunks of 64 pairs after which a byte (at most 4 per chunk) is added up
+
+// Lanes with bit 8 h set keep the upper h of 2 h words, the others the lower.
+template <int H>
+__device__ __forceinline__ void halve(uint32_t (&w)[8], int lane) {
+    const bool up = lane & (8 * H);
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const uint32_t keep = up ? w[i + H] : w[i], give = up ? w[i] : w[i + H];
+        w[i] = keep + __shfl_xor(give, 8 * H, 64);
+    }
+}
+
+// Sums u[mn] over the wave; lane mn adds its quadrants' totals to mine[0..3].
+__device__ __forceinline__ void quad_flush(uint32_t (&u)[4], int lane, int (&mine)[4]) {
+    uint32_t w[8];   // 16-bit sums: quadrants 0 and 2, 1 and 3 of child mn
+#pragma unroll
+    for (int mn = 0; mn < 4; ++mn) {
+        w[2 * mn] = u[mn] & 0x00ff00ffu;
+        w[2 * mn + 1] = (u[mn] >> 8) & 0x00ff00ffu;
+        u[mn] = 0;
+    }
+    // halving exchanges: lanes 8 i .. 8 i + 7 end up with word i
+    halve<4>(w, lane);
+    halve<2>(w, lane);
+    halve<1>(w, lane);
+#pragma unroll
+    for (int d = 4; d >= 1; d >>= 1) w[0] += __shfl_xor(w[0], d, 64);
+    const uint32_t even = __shfl(w[0], (16 * lane) & 63, 64), odd = __shfl(w[0], (16 * lane + 8) & 63, 64);
+    mine[0] += even & 0xffffu;
+    mine[1] += odd & 0xffffu;
+    mine[2] += even >> 16;
+    mine[3] += odd >> 16;
 }
 
 // The counts of c's children, as the next level's count kernel would write
 // them for single-wave workgroups (node c2 is workgroup c2, its offset inside
-// the workgroup 0); lane mn writes those of child quadrant mn.
-__device__ void next_level_write(const TreeStep& st, int32_t c, int lane, const int (&cid)[4],
-                                 const uint32_t (&u)[4][4]) {
-    if (lane >= 4) return;
-    int c2 = -1;
-    int mine[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int mn = 0; mn < 4; ++mn)
-        if (mn == lane) {
-            c2 = cid[mn];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) mine[q] = (int)u[mn][q];
-        }
-    if (c2 < 0 || c2 >= st.nc_next) return;
+// the workgroup 0); lane mn writes those of child quadrant mn: node c2 (-1:
+// none) with child pairs mine[0..3].
+__device__ __forceinline__ void next_level_write(const TreeStep& st, int32_t c, int lane, int c2, int (&mine)[4]) {
+    if (lane >= 4 || c2 < 0 || c2 >= st.nc_next) return;
     if (quadrant_dropped(st.upper, st.ckey[c] * 4 + (uint64_t)lane, 2)) mine[2] = 0;
     const int64_t v = pack2(mine[0] + mine[1] + mine[2] + mine[3],
                             (mine[0] > 0) + (mine[1] > 0) + (mine[2] > 0) + (mine[3] > 0));
@@ -294,38 +365,38 @@ __device__ void next_level_write(const TreeStep& st, int32_t c, int lane, const 
 }
 
 // o: (first child pair, first child C node) of node c in the next level.
-__device__ void tree_fill_node(const TreeStep& st, int32_t c, int lane, int64_t o) {
+template <bool PRUNE, bool COUNTS>
+__device__ __forceinline__ void tree_fill_node(const TreeStep& st, int32_t c, int lane, int64_t o) {
     if (c >= *st.ncount) return;
     const int4 t4 = st.tot4[c];
     const int t[4] = {t4.x, t4.y, t4.z, t4.w};
-    int run[4], cid[4];
-    int pr = lo32(o), ci = hi32(o);
+    int run[4], my_c = -1;
+    {
+        int pr = lo32(o), ci = hi32(o), my_run = 0;
 #pragma unroll
-    for (int mn = 0; mn < 4; ++mn) {
-        run[mn] = pr;
-        pr += t[mn];
-        cid[mn] = t[mn] > 0 ? ci++ : -1;
-    }
-    if (lane < 4) {
-        int my_c = -1, my_run = 0;
-#pragma unroll
-        for (int mn = 0; mn < 4; ++mn)
-            if (mn == lane) {
-                my_c = cid[mn];
-                my_run = run[mn];
+        for (int mn = 0; mn < 4; ++mn) {
+            run[mn] = pr;
+            if (lane == mn && t[mn] > 0) {
+                my_c = ci;
+                my_run = pr;
             }
-        st.cchild[4 * (int64_t)c + lane] = my_c;
-        if (my_c >= 0 && my_c < st.nc_next) {
-            st.nckey[my_c] = st.ckey[c] * 4 + (uint64_t)lane;
-            st.ncseg[my_c] = my_run;
-            st.nparent[my_c] = c;
+            pr += t[mn];
+            ci += t[mn] > 0 ? 1 : 0;
+        }
+        if (lane < 4) {
+            st.cchild[4 * (int64_t)c + lane] = my_c;
+            if (my_c >= 0 && my_c < st.nc_next) {
+                st.nckey[my_c] = st.ckey[c] * 4 + (uint64_t)lane;
+                st.ncseg[my_c] = my_run;
+                st.nparent[my_c] = c;
+            }
         }
     }
     const int32_t s0 = st.cseg[c], len = st.cseg[c + 1] - s0;
     const uint64_t below = lanes_below(lane);
     const bool drop_lower = quadrant_dropped(st.upper, st.ckey[c], 2);
-    const bool counts = st.ncnt != nullptr;
-    uint32_t u[4][4] = {};   // per child quadrant mn of c: that child's child pairs, per quadrant
+    uint32_t u[4] = {0, 0, 0, 0};      // per child quadrant mn of c: bytes of its child pairs, this lane's
+    int mine[4] = {0, 0, 0, 0}, chunks = 0;
     for (int32_t base = 0; base < len; base += 64) {
         const bool act = base + lane < len;
         int4 a = make_int4(-1, -1, -1, -1), b = make_int4(-1, -1, -1, -1);
@@ -335,50 +406,75 @@ __device__ void tree_fill_node(const TreeStep& st, int32_t c, int lane, int64_t 
         }
         const int av[4] = {a.x, a.y, a.z, a.w};
         const int bv[4] = {b.x, b.y, b.z, b.w};
-        // per child quadrant mn: this lane's pairs (k' = 0 and 1) and where they go
-        bool e[4][2];
-        int out[4];
-#pragma unroll
-        for (int mn = 0; mn < 4; ++mn) {
-            const int m = mn >> 1, n = mn & 1;
-            const bool keep = !(mn == 2 && drop_lower);
-            e[mn][0] = keep && pair_kept(st, av[2 * m], bv[n]);           // k' = 0
-            e[mn][1] = keep && pair_kept(st, av[2 * m + 1], bv[2 + n]);   // k' = 1
-            const uint64_t m0 = __ballot(e[mn][0]), m1 = __ballot(e[mn][1]);
-            out[mn] = run[mn] + __popcll(m0 & below) + __popcll(m1 & below);
-            run[mn] += __popcll(m0) + __popcll(m1);
-        }
+        // this lane's pair k' of child quadrant mn
+        auto kept = [&](int mn, int k) {
+            const int x = av[(mn & 2) + k], y = bv[2 * k + (mn & 1)];
+            return !(mn == 2 && drop_lower) && pair_kept<PRUNE>(st.An2, st.Bn2, st.tau2, x, y);
+        };
         // the next level's counts first, the chunk's pair stores after them: a
         // wait for loads issued after stores would wait for the stores too
-        if (counts) {
+        if constexpr (COUNTS) {
+            int4 x[4], y[4];   // the eight children's tables: each serves two quadrants
 #pragma unroll
-            for (int mn = 0; mn < 4; ++mn) {
-                const int m = mn >> 1, n = mn & 1;
-                int4 x0, y0, x1, y1;
-                next_level_tables(st, e[mn][0], av[2 * m], bv[n], e[mn][1], av[2 * m + 1], bv[2 + n], x0, y0, x1,
-                                  y1);
-                next_level_count(st, x0, y0, u[mn]);
-                next_level_count(st, x1, y1, u[mn]);
+            for (int q = 0; q < 4; ++q) {
+                x[q] = next_table(st.nAch, av[q]);
+                y[q] = next_table(st.nBch, bv[q]);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // all eight loads before the first use
+            if constexpr (PRUNE) {
+#pragma unroll
+                for (int mn = 0; mn < 4; ++mn)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (kept(mn, k))
+                            u[mn] += pruned_bytes(st.nAn2, st.nBn2, st.tau2, x[(mn & 2) + k], y[2 * k + (mn & 1)]);
+            } else {
+                QuadBytes xa[4], yb[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    xa[q] = a_bytes(op_swap(x[q], st.ta), present(av[q]));
+                    yb[q] = b_bytes(op_swap(y[q], st.tb), present(bv[q]));
+                }
+#pragma unroll
+                for (int mn = 0; mn < 4; ++mn) {
+                    uint32_t v = 0;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const QuadBytes &xk = xa[(mn & 2) + k], &yk = yb[2 * k + (mn & 1)];
+                        v += (xk.k0 & yk.k0) + (xk.k1 & yk.k1);
+                    }
+                    u[mn] += (mn == 2 && drop_lower) ? 0u : v;
+                }
+            }
+            if (++chunks == QUAD_FLUSH) {
+                quad_flush(u, lane, mine);
+                chunks = 0;
             }
         }
 #pragma unroll
         for (int mn = 0; mn < 4; ++mn) {
             const int m = mn >> 1, n = mn & 1;
-            int w = out[mn];
-            if (e[mn][0]) {
+            const bool e0 = kept(mn, 0), e1 = kept(mn, 1);
+            const uint64_t m0 = __ballot(e0), m1 = __ballot(e1);
+            int w = run[mn] + __popcll(m0 & below) + __popcll(m1 & below);
+            run[mn] += __popcll(m0) + __popcll(m1);
+            if (e0) {
                 if (w < st.np_next) {
                     st.nfa[w] = av[2 * m];
                     st.nfb[w] = bv[n];
                 }
                 ++w;
             }
-            if (e[mn][1] && w < st.np_next) {
+            if (e1 && w < st.np_next) {
                 st.nfa[w] = av[2 * m + 1];
                 st.nfb[w] = bv[2 + n];
             }
         }
     }
-    if (counts) next_level_write(st, c, lane, cid, u);
+    if constexpr (COUNTS) {
+        quad_flush(u, lane, mine);
+        next_level_write(st, c, lane, my_c, mine);
+    }
 }
 
 // The per-level kernels run W waves (one C node each) per workgroup: W = 1
@@ -392,11 +488,8 @@ static inline int level_waves(int64_t n) { return n <= WIDE_LEVEL ? 1 : 4; }
 
 constexpr int32_t AGG_MAX = 65536;   // workgroups per level on the aggregate path
 
-__device__ __forceinline__ int64_t wave_sum64(int64_t x) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
-    return x;
-}
+// Sum over the wave of packed pairs of counts (neither half overflows).
+__device__ __forceinline__ int64_t wave_sum_pack2(int64_t x) { return pack2(wave_sum(lo32(x)), wave_sum(hi32(x))); }
 
 // Aggregate path, count side: node offsets inside the workgroup and the
 // workgroup's aggregate, from each wave's packed count v.
@@ -428,7 +521,7 @@ __device__ __forceinline__ int64_t level_base(const int64_t* wagg, const int64_t
     int64_t part = 0;
     for (int32_t i = threadIdx.x; i < g; i += 64 * W) part += gsum[i];
     for (int32_t i = first + threadIdx.x; i < b; i += 64 * W) part += wagg[i];
-    part = wave_sum64(part);
+    part = wave_sum_pack2(part);
     if (lane == 0) lds[wave] = part;
     __syncthreads();
     int64_t base = 0;
@@ -445,7 +538,7 @@ __device__ __forceinline__ bool level_wg_empty(const int32_t* ncount) {
     return (int64_t)blockIdx.x * W >= *ncount;
 }
 
-template <int W>
+template <int W, bool PRUNE>
 __global__ __launch_bounds__(64 * W) void k_tree_count(TreeStep st) {
     __shared__ int64_t lds[W];
     if (st.use_agg && level_wg_empty<W>(st.ncount)) {
@@ -454,11 +547,12 @@ __global__ __launch_bounds__(64 * W) void k_tree_count(TreeStep st) {
     }
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
     int64_t v = 0;
-    if (c < st.ncap) v = tree_count_node(st, c, threadIdx.x & 63);
+    if (c < st.ncap) v = tree_count_node<PRUNE>(st, c, threadIdx.x & 63);
     if (st.use_agg) level_local_offsets<W>(v, c, st.ncap, st.off, st.wagg, st.gsum, lds);
 }
 
-template <int W>
+// COUNTS: the fill also makes the next level's counts (st.ncnt is set).
+template <int W, bool PRUNE, bool COUNTS>
 __global__ __launch_bounds__(64 * W) void k_tree_fill(TreeStep st) {
     __shared__ int64_t lds[W];
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
@@ -467,10 +561,10 @@ __global__ __launch_bounds__(64 * W) void k_tree_fill(TreeStep st) {
         if (level_wg_empty<W>(st.ncount) && blockIdx.x != gridDim.x - 1) return;
         const int64_t base = level_base<W>(st.wagg, st.gsum, lds);
         if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) tree_level_totals(st, base + st.wagg[blockIdx.x]);
-        if (c < st.ncap) tree_fill_node(st, c, lane, base + st.off[c]);
+        if (c < st.ncap) tree_fill_node<PRUNE, COUNTS>(st, c, lane, base + st.off[c]);
     } else {
         if (c == 0 && lane == 0) tree_level_totals(st, st.off[st.ncap]);
-        if (c < st.ncap) tree_fill_node(st, c, lane, st.off[c]);
+        if (c < st.ncap) tree_fill_node<PRUNE, COUNTS>(st, c, lane, st.off[c]);
     }
 }
 
@@ -481,7 +575,7 @@ struct RootInit {
     int32_t* cseg;
     uint64_t* ckey;
     int32_t* ncount;
-    int32_t* clear;           // NIL flags and tile counts, group sums, workgroup aggregates (as words)
+    int32_t* clear;           // NIL flags, group sums, workgroup aggregates (as words)
     int64_t nclear;
 };
 
@@ -505,35 +599,43 @@ __global__ __launch_bounds__(64) void k_root_init(RootInit r) { root_init(r); }
 
 // ------------------------------------------------------ the leaf step
 
-// NIL normalisation of C (see below): the leaf step flags every C leaf that
-// receives a block, and its ancestors, as it fills the leaf.
+// NIL normalisation of C (see below): the leaf step's count flags every C leaf
+// that receives a block, and its ancestors; its fill counts the flags per tile.
 constexpr int NIL_MAX_LEVELS = 32;
+constexpr int NIL_TILE = 256;   // four flags per lane
 
 struct NilMark {
     int L;
     int64_t foff[NIL_MAX_LEVELS + 2];              // flags of level l at foff[l] .. foff[l+1]-1
     const int32_t* uparent[NIL_MAX_LEVELS + 1];    // parent of every C node, levels 1 .. L
-    int32_t* flags;                                // foff[L+1] entries, cleared before the traversal
-    int32_t* tcnt;                                 // flags set per tile of 64, cleared with them
+    int32_t* flags;                                // foff[L+1] entries (whole tiles), cleared before the traversal
+    int32_t* tcnt;                                 // flags set per tile
+    int64_t tiles;                                 // foff[L+1] / NIL_TILE + 1
 };
 
-// Flags C node p of level l; true when this call set it. Each flag is set
-// once (an atomic exchange), and each first setting is counted in its tile.
-__device__ __forceinline__ bool nil_flag(const NilMark& m, int l, int32_t p) {
-    const int64_t f = m.foff[l] + p;
-    if (atomicExch(m.flags + f, 1) != 0) return false;
-    atomicAdd(m.tcnt + (f >> 6), 1);
-    return true;
-}
-
 // C leaf c holds a block: it and its ancestors are kept. A walk stops at the
-// first node flagged already: whoever flagged it walks on from there.
-__device__ void nil_mark_up(const NilMark& m, int32_t c) {
-    if (!nil_flag(m, m.L, c)) return;
+// first ancestor flagged already: whoever flagged it walks on from there. Two
+// waves may both find an ancestor unflagged and walk on; they store the same
+// value, so no atomics are needed.
+__device__ __forceinline__ void nil_mark_up(const NilMark& m, int32_t c) {
     int32_t p = c;
+    m.flags[m.foff[m.L] + p] = 1;
     for (int l = m.L; l > 0; --l) {
         p = m.uparent[l][p];
-        if (!nil_flag(m, l - 1, p)) return;
+        int32_t* f = m.flags + m.foff[l - 1] + p;
+        if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) return;
+        __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+// The flags set in every tile of NIL_TILE, by the waves of the leaf fill (the
+// marks are the leaf count's): wave w of nw.
+__device__ __forceinline__ void nil_tile_counts(const NilMark& m, int64_t w, int64_t nw) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t t = w; t < m.tiles; t += nw) {
+        const int4 f = reinterpret_cast<const int4*>(m.flags)[t * 64 + lane];
+        const int c = wave_sum(f.x + f.y + f.z + f.w);
+        if (lane == 0) m.tcnt[t] = c;
     }
 }
 
@@ -576,7 +678,7 @@ struct LeafStep {
     const double* Abn2;       // squared block norms (nullptr: no norm threshold): a block product
     const double* Bbn2;       // is dropped when Abn2 Bbn2 < tau2
     double tau2;
-    NilMark nil;              // the fill flags the kept C leaves and their ancestors
+    NilMark nil;              // the kept C leaves and their ancestors
 };
 
 // Lane t's value in every lane, for a t that is the same in every lane: a
@@ -600,12 +702,8 @@ __device__ __forceinline__ bool leaf_block_kept(const LeafStep& st, uint64_t lea
 // can add a block product at all are walked: some inner index k with column
 // k of the op(A) leaf and row k of the op(B) leaf both occupied. In an
 // unstructured product most leaf pairs have none (random65536: four in five).
-__device__ int leaf_lane_count_norms(const LeafStep& st, int32_t s0, int32_t len, int lane, int i, int j, int lb,
-                                     bool on);
-
-__device__ int leaf_lane_count(const LeafStep& st, int32_t s0, int32_t len, int lane, int i, int j, int lb,
-                               bool on) {
-    if (st.Abn2) return leaf_lane_count_norms(st, s0, len, lane, i, j, lb, on);
+__device__ __forceinline__ int leaf_lane_count(const LeafStep& st, int32_t s0, int32_t len, int lane, int i, int j,
+                                               int lb, bool on) {
     int cnt = 0;
     for (int32_t base = 0; base < len; base += 64) {
         const int32_t nb = min(64, len - base);
@@ -633,8 +731,8 @@ __device__ __forceinline__ void leaf_positions(const LeafStep& st, int i, int k,
 // leaf_lane_count with a norm threshold: every candidate product A(i,k)
 // B(k,j) is looked at on its own, kept when its blocks' squared norms
 // multiply to at least tau2.
-__device__ int leaf_lane_count_norms(const LeafStep& st, int32_t s0, int32_t len, int lane, int i, int j, int lb,
-                                     bool on) {
+__device__ __forceinline__ int leaf_lane_count_norms(const LeafStep& st, int32_t s0, int32_t len, int lane, int i,
+                                                     int j, int lb, bool on) {
     int cnt = 0;
     for (int32_t base = 0; base < len; base += 64) {
         const int32_t nb = min(64, len - base);
@@ -669,7 +767,8 @@ __device__ int leaf_lane_count_norms(const LeafStep& st, int32_t s0, int32_t len
     return cnt;
 }
 
-__device__ int64_t leaf_count_node(const LeafStep& st, int32_t c, int lane) {
+template <bool PRUNE>
+__device__ __forceinline__ int64_t leaf_count_node(const LeafStep& st, int32_t c, int lane) {
     if (c >= *st.ncount) {
         if (lane == 0) st.cnt[c] = 0;
         return 0;
@@ -678,12 +777,16 @@ __device__ int64_t leaf_count_node(const LeafStep& st, int32_t c, int lane) {
     const int i = (int)morton_row((uint64_t)lane), j = (int)morton_col((uint64_t)lane);
     const bool on = lane < lb * lb && leaf_block_kept(st, st.ckey[c], i, j);
     const int32_t s0 = st.cseg[c], len = st.cseg[c + 1] - s0;
-    const int cnt = leaf_lane_count(st, s0, len, lane, i, j, lb, on);
+    const int cnt = PRUNE ? leaf_lane_count_norms(st, s0, len, lane, i, j, lb, on)
+                          : leaf_lane_count(st, s0, len, lane, i, j, lb, on);
     st.lane_cnt[(int64_t)c * 64 + lane] = cnt;   // the fill reads it instead of walking the pairs twice
     const uint64_t em = __ballot(cnt > 0);
     const int tot = wave_sum(cnt);
     const int64_t v = pack2(tot, __popcll(em));
-    if (lane == 0) st.cnt[c] = v;
+    if (lane == 0) {
+        st.cnt[c] = v;
+        if (em) nil_mark_up(st.nil, c);
+    }
     return v;
 }
 
@@ -695,23 +798,12 @@ __device__ void leaf_level_totals(const LeafStep& st, int64_t T) {
     *st.check = lo32(T);
 }
 
-// o: (first product, first C block) of leaf c.
-__device__ void leaf_fill_node(const LeafStep& st, int32_t c, int lane, int64_t o) {
-    if (c >= *st.ncount) return;
-    const int lb = 1 << st.lb_log;
-    const int i = (int)morton_row((uint64_t)lane), j = (int)morton_col((uint64_t)lane);
-    const bool on = lane < lb * lb && leaf_block_kept(st, st.ckey[c], i, j);
-    const int32_t s0 = st.cseg[c], len = st.cseg[c + 1] - s0;
-    const int cnt = st.lane_cnt[(int64_t)c * 64 + lane];   // from the count kernel
-    const bool exists = cnt > 0;
-    const uint64_t em = __ballot(exists);
-    const int32_t bidx = hi32(o) + __popcll(em & lanes_below(lane));
-    int32_t out = lo32(o) + wave_excl_scan(cnt, lane);
-    if (exists && bidx < st.cap) {
-        st.cbkey[bidx] = (st.ckey[c] << (2 * st.lb_log)) | (uint64_t)lane;
-        st.cbseg[bidx] = out;
-    }
-    const bool plain = !st.amap && !st.bmap && !st.Abn2;
+// Lists the products of every block of a C leaf (lane: one block), pair by
+// pair of the leaf pairs s0 .. s0 + len - 1, k ascending, from place `out` on.
+// PLAIN: stored operands (no block maps) and no norm threshold.
+template <bool PLAIN>
+__device__ __forceinline__ void leaf_fill_products(const LeafStep& st, int32_t s0, int32_t len, int lane, int i, int j,
+                                                   int lb, bool on, int32_t out) {
     for (int32_t base = 0; base < len; base += 64) {
         const int32_t nb = min(64, len - base);
         uint64_t ra = 0, cb = 0, amo = 0, bmo = 0;
@@ -737,7 +829,7 @@ __device__ void leaf_fill_node(const LeafStep& st, int32_t c, int lane, int64_t 
             const uint64_t bmot = lane_value(bmo, t);
             const int32_t abt = (int32_t)lane_value((uint32_t)ab, t);
             const int32_t bbt = (int32_t)lane_value((uint32_t)bb, t);
-            if (plain) {
+            if constexpr (PLAIN) {
                 // stored operands, no norm threshold: no loads in this loop, so
                 // no wait on memory (a wait here would also wait for the stores
                 // of the products before)
@@ -755,9 +847,7 @@ __device__ void leaf_fill_node(const LeafStep& st, int32_t c, int lane, int64_t 
                     }
                     ++out;
                 }
-                continue;
-            }
-            while (m) {
+            } else while (m) {
                 const int k = __ffs(m) - 1;
                 m &= m - 1;
                 uint32_t qa, qb;   // local Morton positions of A(i,k) / B(k,j) in the stored leaves
@@ -774,18 +864,36 @@ __device__ void leaf_fill_node(const LeafStep& st, int32_t c, int lane, int64_t 
             }
         }
     }
-    const uint64_t rm = wave_or(exists ? (1ull << (i * lb + j)) : 0ull);
-    const uint64_t cm = wave_or(exists ? (1ull << (j * lb + i)) : 0ull);
+}
+
+// o: (first product, first C block) of leaf c.
+template <bool PLAIN>
+__device__ __forceinline__ void leaf_fill_node(const LeafStep& st, int32_t c, int lane, int64_t o) {
+    if (c >= *st.ncount) return;
+    const int lb = 1 << st.lb_log;
+    const int i = (int)morton_row((uint64_t)lane), j = (int)morton_col((uint64_t)lane);
+    const bool on = lane < lb * lb && leaf_block_kept(st, st.ckey[c], i, j);
+    const int32_t s0 = st.cseg[c], len = st.cseg[c + 1] - s0;
+    const int cnt = st.lane_cnt[(int64_t)c * 64 + lane];   // from the count kernel
+    const bool exists = cnt > 0;
+    const uint64_t em = __ballot(exists);
+    const int32_t bidx = hi32(o) + __popcll(em & lanes_below(lane));
+    int32_t out = lo32(o) + wave_excl_scan(cnt);
+    if (exists && bidx < st.cap) {
+        st.cbkey[bidx] = (st.ckey[c] << (2 * st.lb_log)) | (uint64_t)lane;
+        st.cbseg[bidx] = out;
+    }
+    leaf_fill_products<PLAIN>(st, s0, len, lane, i, j, lb, on, out);
     if (lane == 0) {
+        const uint64_t rm = morton_to_rowmajor(em, st.lb_log);
         st.lbase[c] = hi32(o);
         st.lmo[c] = em;
         st.lrm[c] = rm;
-        st.lcm[c] = cm;
-        if (em) nil_mark_up(st.nil, c);
+        st.lcm[c] = rowmajor_to_colmajor(rm, st.lb_log);
     }
 }
 
-template <int W>
+template <int W, bool PRUNE>
 __global__ __launch_bounds__(64 * W) void k_leaf_count(LeafStep st) {
     __shared__ int64_t lds[W];
     if (st.use_agg && level_wg_empty<W>(st.ncount)) {
@@ -794,23 +902,24 @@ __global__ __launch_bounds__(64 * W) void k_leaf_count(LeafStep st) {
     }
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
     int64_t v = 0;
-    if (c < st.ncap) v = leaf_count_node(st, c, threadIdx.x & 63);
+    if (c < st.ncap) v = leaf_count_node<PRUNE>(st, c, threadIdx.x & 63);
     if (st.use_agg) level_local_offsets<W>(v, c, st.ncap, st.off, st.wagg, st.gsum, lds);
 }
 
-template <int W>
+template <int W, bool PLAIN>
 __global__ __launch_bounds__(64 * W) void k_leaf_fill(LeafStep st) {
     __shared__ int64_t lds[W];
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
+    nil_tile_counts(st.nil, c, (int64_t)gridDim.x * W);
     if (st.use_agg) {
         if (level_wg_empty<W>(st.ncount) && blockIdx.x != gridDim.x - 1) return;
         const int64_t base = level_base<W>(st.wagg, st.gsum, lds);
         if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) leaf_level_totals(st, base + st.wagg[blockIdx.x]);
-        if (c < st.ncap) leaf_fill_node(st, c, lane, base + st.off[c]);
+        if (c < st.ncap) leaf_fill_node<PLAIN>(st, c, lane, base + st.off[c]);
     } else {
         if (c == 0 && lane == 0) leaf_level_totals(st, st.off[st.ncap]);
-        if (c < st.ncap) leaf_fill_node(st, c, lane, st.off[c]);
+        if (c < st.ncap) leaf_fill_node<PLAIN>(st, c, lane, st.off[c]);
     }
 }
 
@@ -822,22 +931,26 @@ __global__ __launch_bounds__(64 * W) void k_leaf_fill(LeafStep st) {
 // B(k,j) both present) holds no block, and so does a node above only such
 // leaves. Zero submatrices are NIL at every level of the quadtree (Sec. 3.1),
 // so C's tree keeps exactly the nodes with a stored block below them:
-//   mark:    the leaf fill flags every leaf that receives a block, and its
-//            ancestors (parents were recorded by the traversal), counting
-//            the flags set per tile of 64 (nil_mark_up);
+//   mark:    the leaf count flags every leaf that receives a block, and its
+//            ancestors (parents were recorded by the traversal); the leaf
+//            fill's waves count the flags per tile (nil_mark_up,
+//            nil_tile_counts);
 //   offsets: one wave per tile adds up the counts of the tiles before it and
-//            ranks its own flags with a ballot: the exclusive scan of the
-//            flags of all levels, concatenated, which gives every kept node
-//            its index among the kept nodes of its level (one launch, where
-//            a general scan takes three);
+//            ranks its own flags: the exclusive scan of the flags of all
+//            levels, concatenated, which gives every kept node its index among
+//            the kept nodes of its level (one launch, where a general scan
+//            takes three);
 //   compact: kept nodes are copied into C's tree, child tables remapped
 //            (a child that is not kept becomes NIL), and the kept counts of
 //            every level are written for the read-back.
 // C's blocks, their order and the product lists do not change: an empty leaf
 // owns none of them. The traversal runs beside the previous multiply's
 // numeric kernel, where each launch waits tens of microseconds for wave
-// slots; folding the marks into the leaf fill and the scan into one launch
-// leaves two launches of the five a separate pass would take.
+// slots; folding the marks and the tile counts into the leaf step and the scan
+// into one launch leaves two launches of the five a separate pass would take.
+// (Marked with an atomic exchange per flag and an atomic count per tile, in
+// the leaf fill, that kernel took 460 instead of 373 us on an R-MAT product
+// of 0.6 M leaves, 110 instead of 75 us on a random 48000 one.)
 
 struct NilTree {
     int L;
@@ -859,21 +972,25 @@ struct NilTree {
     int32_t* kept;                           // kept nodes per level, levels 0 .. L
 };
 
-// ex[i] = number of flags set before i, for i <= n: one wave per tile of 64
-// indices, n / 64 + 1 tiles (the lane of index n writes the total); tcnt
-// holds the flags set in each tile.
+// ex[i] = number of flags set before i, for every i of the tiles (n among
+// them: the total); one wave per tile, which adds up the counts of the tiles
+// before its own. (With tiles of 64 and 4-byte loads the waves of an R-MAT
+// product with 1.4 M nodes read 1 GB of counts, 90 us; 6 us now.)
 __global__ __launch_bounds__(64) void k_nil_offsets(const int32_t* __restrict__ flags,
-                                                    const int32_t* __restrict__ tcnt, int64_t n,
-                                                    int32_t* __restrict__ ex) {
+                                                    const int32_t* __restrict__ tcnt, int32_t* __restrict__ ex) {
     const int lane = threadIdx.x;
     const int64_t t = blockIdx.x;
+    const int4 f = reinterpret_cast<const int4*>(flags)[t * 64 + lane];
     int before = 0;
-    for (int64_t u = lane; u < t; u += 64) before += tcnt[u];
-    before = wave_sum(before);
-    const int64_t i = t * 64 + lane;
-    const uint64_t set = __ballot(i < n && flags[i] != 0);
-    if (i < n) ex[i] = before + __popcll(set & lanes_below(lane));
-    if (i == n) ex[n] = before + __popcll(set);
+#pragma unroll 4
+    for (int64_t u = lane; u < t / 4; u += 64) {
+        const int4 c = reinterpret_cast<const int4*>(tcnt)[u];
+        before += c.x + c.y + c.z + c.w;
+    }
+    if (lane < (t & 3)) before += tcnt[(t & ~int64_t(3)) + lane];
+    before = wave_sum(before) + wave_excl_scan(f.x + f.y + f.z + f.w);
+    reinterpret_cast<int4*>(ex)[t * 64 + lane] =
+        make_int4(before, before + f.x, before + f.x + f.y, before + f.x + f.y + f.z);
 }
 
 __device__ __forceinline__ int32_t nil_rank(const NilTree& t, int l, int64_t c) {
@@ -1164,13 +1281,14 @@ static inline int64_t level_wgs(int64_t n) {
     return std::max<int64_t>((n + w - 1) / w, 1);
 }
 
-// Launch kernel template K (count or fill) with the level's workgroup width.
-#define QT_LEVEL_LAUNCH(K, n, wgs, stream, arg)                                  \
+// Launch kernel template K (count or fill) with the level's workgroup width
+// and the template arguments that follow it.
+#define QT_LEVEL_LAUNCH(K, n, wgs, stream, arg, ...)                             \
     do {                                                                          \
         if (level_waves(n) == 1)                                                  \
-            K<1><<<(unsigned)(wgs), 64, 0, (stream)>>>(arg);                      \
+            K<1, __VA_ARGS__><<<(unsigned)(wgs), 64, 0, (stream)>>>(arg);         \
         else                                                                      \
-            K<4><<<(unsigned)(wgs), 256, 0, (stream)>>>(arg);                     \
+            K<4, __VA_ARGS__><<<(unsigned)(wgs), 256, 0, (stream)>>>(arg);        \
         QT_LAUNCH(#K);                                                            \
     } while (0)
 
@@ -1405,13 +1523,13 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     for (int l = 0; l <= L; ++l) foff[l + 1] = foff[l] + ncap[l];
     if (foff[L + 1] > kMaxI32) fail(QT_ERR_UNSUPPORTED, "too many C nodes");
     // Cleared by the traversal's first kernel, in one run: the NIL flags of all
-    // levels and their counts per tile of 64, the group sums of every level's
+    // levels, the group sums of every level's
     // workgroup aggregates, and the aggregates themselves (the levels whose
     // counts the previous level's fill makes have no count kernel to write
     // the aggregates of workgroups without a node).
-    const int64_t nil_tiles = foff[L + 1] / 64 + 1;
-    const int64_t nil_flags = foff[L + 1] + nil_tiles;
-    const size_t o_nflags = tmp.take(nil_flags * sizeof(int32_t));
+    const int64_t nil_tiles = foff[L + 1] / NIL_TILE + 1;
+    const size_t o_ntcnt = tmp.take(nil_tiles * sizeof(int32_t));
+    const size_t o_nflags = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     std::vector<int64_t> gsum_at(L + 1);
     int64_t gsum_total = 0;
     for (int l = 0; l <= L; ++l) {
@@ -1423,7 +1541,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         o_wagg(L + 1);
     for (int l = 0; l <= L; ++l) o_wagg[l] = tmp.take(level_wgs(ncap[l]) * sizeof(int64_t));
     const int64_t nclear = (int64_t)(tmp.bytes - o_nflags) / (int64_t)sizeof(int32_t);
-    const size_t o_nex = tmp.take((foff[L + 1] + 1) * sizeof(int32_t));
+    const size_t o_nex = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     size_t scan_elems = 0;
     for (int l = 0; l <= L; ++l) {
         o_fa[l] = tmp.take(pairs[l] * sizeof(int32_t));
@@ -1533,7 +1651,10 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         const int64_t wgs = level_wgs(ncap[l]);
         sl.use_agg = wgs <= AGG_MAX;
         if (!counted) {
-            QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl);
+            if (prune)
+                QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, true);
+            else
+                QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, false);
             if (!sl.use_agg) exclusive_scan(sl.cnt, sl.off, ncap[l], scan_tmp, ss);
         }
         // a single-wave next tree level gets its counts from this fill
@@ -1550,7 +1671,14 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
             sl.nwagg = nx.wagg;
             sl.ngsum = nx.gsum;
         }
-        QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl);
+        if (prune && counted)
+            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, true);
+        else if (prune)
+            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, false);
+        else if (counted)
+            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, true);
+        else
+            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, false);
     }
 
     // leaf step
@@ -1602,10 +1730,17 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     for (int l = 0; l <= L + 1; ++l) ls.nil.foff[l] = foff[l];
     for (int l = 1; l <= L; ++l) ls.nil.uparent[l] = (const int32_t*)at(W, u_parent[l]);
     ls.nil.flags = nflags;
-    ls.nil.tcnt = nflags + foff[L + 1];
-    QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls);
+    ls.nil.tcnt = (int32_t*)at(W, o_ntcnt);
+    ls.nil.tiles = nil_tiles;
+    if (prune)
+        QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, true);
+    else
+        QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, false);
     if (!ls.use_agg) exclusive_scan(ls.cnt, ls.off, ncap[L], scan_tmp, ss);
-    QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls);
+    if (prune || ls.amap || ls.bmap)
+        QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, false);
+    else
+        QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, true);
     int32_t* order = (make_order || may_korder) ? (int32_t*)at(W, o_order) : nullptr;
     if (make_order) {
         int32_t* otab = (int32_t*)at(W, o_otab);
@@ -1647,8 +1782,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         nt.rm = (uint64_t*)at(K, o_lrm);
         nt.cm = (uint64_t*)at(K, o_lcm);
         nt.kept = dcount + 2 * L + 3;
-        k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nflags, ls.nil.tcnt, foff[L + 1],
-                                                            (int32_t*)at(W, o_nex));
+        k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nflags, ls.nil.tcnt, (int32_t*)at(W, o_nex));
         QT_LAUNCH("k_nil_offsets");
         k_nil_compact<<<(unsigned)((foff[L + 1] + 63) / 64), 64, 0, ss>>>(nt);
         QT_LAUNCH("k_nil_compact");

@@ -8,6 +8,7 @@
 // marking a NIL child. Nodes carry no global offsets, only their Morton key.
 #include "qt_internal.h"
 #include "qt_morton.h"
+#include "qt_readback.h"
 #include "qt_sort.h"
 
 #include <algorithm>
@@ -87,7 +88,7 @@ struct ListKeys {
         const int32_t i = I[t], j = J[t];
         if (i < 0 || j < 0 || i >= nbr || j >= nbc) {
             atomicOr(err, 1);
-            return (uint64_t)t;
+            return 0;   // some position of the grid: the tree is formed before the flag is read
         }
         return morton_key((uint32_t)i, (uint32_t)j);
     }
@@ -142,11 +143,6 @@ struct NormSink {
         idx[at] = t;
     }
 };
-
-__global__ void k_build_dups(const uint64_t* __restrict__ keys, int64_t n, int32_t* __restrict__ err) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 1 && t < n && keys[t] == keys[t - 1]) atomicOr(err, 2);
-}
 
 // Blocks copied in permuted order: dst block t = src block perm[t], converted
 // (fp64 to fp32 rounds to nearest even). A wave moves COPY_PIECES pieces of
@@ -204,87 +200,153 @@ static void copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D*
         launch_copy_blocks<S, D, 1>(src, perm, n, bb, dst, s);
 }
 
-// Node counts of every level at once from the sorted block keys: node
-// boundaries at level l are where the key prefix above shift(l) changes.
-// cnt[l] for l = 0 .. L (L: the leaves); one ballot per wave and level.
-__global__ void k_level_counts(const uint64_t* __restrict__ keys, int64_t n, int L, int leaf_shift,
-                               int32_t* __restrict__ cnt) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool in = t < n;
-    const uint64_t k = in ? keys[t] : 0, kp = (in && t > 0) ? keys[t - 1] : 0;
-    for (int l = 0; l <= L; ++l) {
-        const int sh = leaf_shift + 2 * (L - l);
-        const bool first = in && (t == 0 || (sh < 64 ? (k >> sh) != (kp >> sh) : false));
-        const uint64_t m = __ballot(first);
-        if ((threadIdx.x & 63) == 0 && m) atomicAdd(cnt + l, (int32_t)__popcll(m));
-    }
-}
+// The quadtree over n blocks from their ascending Morton keys. A block starts
+// a node of level l when its key's prefix above that level differs from the
+// block's before it, so it starts nodes of every level from some first one
+// down (L: the leaves); node numbers are ranks of those starts.
+//   init:  clears the read-back words and the histograms, and marks every
+//          child NIL;
+//   tiles: the starts of every level per tile of blocks (and equal
+//          neighbours: the same block twice);
+//   scan:  k_radix_scan over the tiles, a lane per level, whose totals are the
+//          levels' node counts;
+//   fill:  ranks within the tile from ballots, then every level's keys and
+//          child links, the leaves' masks, and the node and block counts per
+//          row and column.
+// The tables are placed by bounds on the levels' node counts, so the host
+// waits once, for the counts and histograms together. Bound by that chain of
+// dependent launches: with the counts read back first, a flag per block and
+// level, a scan of them all and a histogram launch per level, three waits and
+// 25 launches, build and copy-out of 29300 blocks took 437 us, now 278.
+constexpr int MAX_TREE_LEVELS = 32;
+constexpr int TREE_THREADS = 256, TREE_WAVES = TREE_THREADS / 64;
+constexpr int64_t TREE_TILES_MAX = 2048;
 
-// Every level's tables in one pass. flags[l*n + t] = 1 when block t starts a
-// node of level l (l = 0 .. L, L the leaves); with ex the exclusive scan of
-// the concatenated flags, block t lies in node rank(l, t) = ex[l*n + t + 1] -
-// ex[l*n] - 1 of level l. The flags and their scan are int32 while (L+1) n
-// fits, int64 beyond.
-constexpr int MAX_FUSED_LEVELS = 32;
-struct LevelTables {
-    int32_t* child[MAX_FUSED_LEVELS];     // levels 0 .. L-1: 4 per node, -1 for NIL (cleared first)
-    uint64_t* key[MAX_FUSED_LEVELS];
+struct TreeBuild {
+    const uint64_t* keys;
+    const int32_t* n;                      // number of blocks (device)
+    int L, lb_log;
+    int64_t tile;                          // blocks per workgroup
+    int32_t* starts;                       // per tile and level
+    int32_t* err;
+    int32_t* child[MAX_TREE_LEVELS];       // levels 0 .. L-1: 4 per node
+    uint64_t* key[MAX_TREE_LEVELS];
     int32_t* base;                         // leaves
     uint64_t* lkey;
     uint64_t* mo;
     uint64_t* rm;
     uint64_t* cm;
+    int32_t* hist;                         // levels 0 .. L, then blocks: counts per row, per column
 };
 
-__device__ __forceinline__ int level_shift(int l, int L, int leaf_shift) { return leaf_shift + 2 * (L - l); }
-
-template <class I>
-__global__ void k_level_flags(const uint64_t* __restrict__ keys, int64_t n, int L, int leaf_shift,
-                              I* __restrict__ flags) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const uint64_t k = keys[t], kp = t > 0 ? keys[t - 1] : 0;
-    for (int l = 0; l <= L; ++l) {
-        const int sh = level_shift(l, L, leaf_shift);
-        flags[(int64_t)l * n + t] = (t == 0 || (sh < 64 && (k >> sh) != (kp >> sh))) ? 1 : 0;
-    }
+// words[at] = n, the others 0; nil[..] = -1
+__global__ void k_tree_init(int32_t* words, int64_t nwords, int64_t at, int32_t n, int32_t* nil, int64_t nnil) {
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = i0; i < nwords; i += step) words[i] = i == at ? n : 0;
+    for (int64_t i = i0; i < nnil; i += step) nil[i] = -1;
 }
 
-template <class I>
-__global__ void k_level_fill(const uint64_t* __restrict__ keys, int64_t n, int L, int lb_log,
-                             const I* __restrict__ flags, const I* __restrict__ ex, LevelTables tb) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int leaf_shift = 2 * lb_log;
-    const uint64_t k = keys[t];
-    auto rank = [&](int l) { return (int32_t)(ex[(int64_t)l * n + t + 1] - ex[(int64_t)l * n] - 1); };
-    for (int l = 0; l < L; ++l) {
-        const int sh = level_shift(l, L, leaf_shift);
-        if (flags[(int64_t)l * n + t]) tb.key[l][rank(l)] = sh < 64 ? (k >> sh) : 0;
-        if (flags[(int64_t)(l + 1) * n + t]) {   // t starts a child node: link it to its parent
-            const int shc = sh - 2;                 // the child level's shift
-            const int q = shc < 64 ? (int)((k >> shc) & 3) : 0;
-            tb.child[l][4 * (int64_t)rank(l) + q] = rank(l + 1);
+// First level of which block t (key k, kp the key before it) starts a node;
+// L + 1: none.
+__device__ __forceinline__ int first_level(int64_t t, uint64_t k, uint64_t kp, int L, int lb_log) {
+    if (t == 0) return 0;
+    const uint64_t d = k ^ kp;
+    if ((d >> (2 * lb_log)) == 0) return L + 1;
+    const int depth = (63 - __clzll((long long)d) - 2 * lb_log) >> 1;   // levels above the leaves
+    return depth >= L ? 0 : L - depth;
+}
+
+__global__ __launch_bounds__(TREE_THREADS) void k_tree_tiles(TreeBuild b) {
+    __shared__ int32_t cnt[MAX_TREE_LEVELS + 1];
+    const int64_t n = *b.n, t0 = (int64_t)blockIdx.x * b.tile;
+    if ((int)threadIdx.x <= b.L) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    bool dup = false;
+    for (int64_t base = t0; base < t0 + b.tile; base += TREE_THREADS) {
+        const int64_t t = base + threadIdx.x;
+        int f = b.L + 1;
+        if (t < n) {
+            const uint64_t k = b.keys[t], kp = t > 0 ? b.keys[t - 1] : 0;
+            dup = dup || (t > 0 && k == kp);
+            f = first_level(t, k, kp, b.L, b.lb_log);
+        }
+        for (int l = 0; l <= b.L; ++l) {
+            const uint64_t m = __ballot(f <= l);
+            if ((threadIdx.x & 63) == 0 && m) atomicAdd(&cnt[l], (int32_t)__popcll(m));
         }
     }
-    if (!flags[(int64_t)L * n + t]) return;
-    // t starts a leaf: its base, key and masks
-    const int lb = 1 << lb_log;
-    const uint64_t lk = k >> leaf_shift;
-    const int32_t li = rank(L);
-    uint64_t m0 = 0, m1 = 0, m2 = 0;
-    for (int64_t u = t; u < n && (keys[u] >> leaf_shift) == lk; ++u) {
-        const uint32_t q = (uint32_t)(keys[u] & ((1ull << leaf_shift) - 1));
-        const uint32_t r = morton_row(q), c = morton_col(q);
-        m0 |= 1ull << q;
-        m1 |= 1ull << (r * lb + c);
-        m2 |= 1ull << (c * lb + r);
+    if (dup) atomicOr(b.err, 2);
+    __syncthreads();
+    if ((int)threadIdx.x <= b.L) b.starts[(int64_t)blockIdx.x * (b.L + 1) + threadIdx.x] = cnt[threadIdx.x];
+}
+
+__global__ __launch_bounds__(TREE_THREADS) void k_tree_tables(TreeBuild b) {
+    __shared__ int32_t before[MAX_TREE_LEVELS + 1];                 // starts before this round of blocks
+    __shared__ int32_t wcnt[TREE_WAVES][MAX_TREE_LEVELS + 1];
+    const int64_t n = *b.n, t0 = (int64_t)blockIdx.x * b.tile;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int L = b.L, leaf_shift = 2 * b.lb_log;
+    if ((int)threadIdx.x <= L) before[threadIdx.x] = b.starts[(int64_t)blockIdx.x * (L + 1) + threadIdx.x];
+    const uint64_t upto = ~0ull >> (63 - lane);
+    for (int64_t base = t0; base < t0 + b.tile && base < n; base += TREE_THREADS) {
+        const int64_t t = base + threadIdx.x;
+        uint64_t k = 0;
+        int f = L + 1;
+        if (t < n) {
+            k = b.keys[t];
+            f = first_level(t, k, t > 0 ? b.keys[t - 1] : 0, L, b.lb_log);
+        }
+        for (int l = 0; l <= L; ++l) {
+            const uint64_t m = __ballot(f <= l);
+            if (lane == 0) wcnt[wave][l] = (int32_t)__popcll(m);
+        }
+        __syncthreads();
+        int32_t up = 0;              // this block's node one level up
+        int32_t* hist = b.hist;
+        for (int l = 0; l <= L; ++l) {
+            int32_t r = before[l] + (int32_t)__popcll(__ballot(f <= l) & upto) - 1;
+            for (int w = 0; w < wave; ++w) r += wcnt[w][l];
+            const int64_t side = int64_t(1) << l;
+            if (f <= l) {
+                const uint64_t nk = k >> (leaf_shift + 2 * (L - l));
+                (l < L ? b.key[l] : b.lkey)[r] = nk;
+                if (l > 0) b.child[l - 1][4 * (int64_t)up + (int)(nk & 3)] = r;
+                atomicAdd(hist + morton_row(nk), 1);
+                atomicAdd(hist + side + morton_col(nk), 1);
+                if (l == L) {
+                    // the leaf's blocks: eight keys at a time, so that their loads overlap
+                    uint64_t mo = 0;
+                    bool more = true;
+                    for (int64_t u = t; more; u += 8) {
+                        uint64_t x[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) x[e] = u + e < n ? b.keys[u + e] : ~nk << leaf_shift;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            more = more && (x[e] >> leaf_shift) == nk;
+                            if (more) mo |= 1ull << (x[e] & ((1ull << leaf_shift) - 1));
+                        }
+                    }
+                    const uint64_t rm = morton_to_rowmajor(mo, b.lb_log);
+                    b.base[r] = (int32_t)t;
+                    b.mo[r] = mo;
+                    b.rm[r] = rm;
+                    b.cm[r] = rowmajor_to_colmajor(rm, b.lb_log);
+                }
+            }
+            up = r;
+            hist += 2 * side;
+        }
+        if (t < n) {
+            atomicAdd(hist + morton_row(k), 1);
+            atomicAdd(hist + ((int64_t)(1 << b.lb_log) << L) + morton_col(k), 1);
+        }
+        __syncthreads();
+        if ((int)threadIdx.x <= L)
+            for (int w = 0; w < TREE_WAVES; ++w) before[threadIdx.x] += wcnt[w][threadIdx.x];
+        __syncthreads();
     }
-    tb.base[li] = (int32_t)t;
-    tb.lkey[li] = lk;
-    tb.mo[li] = m0;
-    tb.rm[li] = m1;
-    tb.cm[li] = m2;
 }
 
 __global__ void k_hist(const uint64_t* __restrict__ keys, int64_t n, int32_t* __restrict__ rowcnt,
@@ -437,24 +499,45 @@ static int ilog2(int64_t x) {
 
 // ------------------------------------------------------------ histograms
 
-void build_histograms(qt_matrix* M, hipStream_t s) {
-    std::lock_guard<std::mutex> lk(M->mu);
-    if (M->hist.ready) return;
+// The counts of M as the device makes them: per level 0 .. L the nodes per row
+// and per column, then the blocks per row and per column of the padded grid.
+static int64_t histogram_words(const qt_matrix* M) {
+    int64_t total = 2 * ((int64_t)M->lb << M->L);
+    for (int l = 0; l <= M->L; ++l) total += 2 * (int64_t(1) << l);
+    return total;
+}
+
+static void adopt_histograms(qt_matrix* M, const int32_t* w) {
     Histograms h;
     h.rowcnt.resize(M->L + 1);
     h.colcnt.resize(M->L + 1);
+    auto take = [&](std::vector<int32_t>& v, int64_t side) {
+        v.assign(w, w + side);
+        w += side;
+    };
+    for (int l = 0; l <= M->L; ++l) {
+        take(h.rowcnt[l], int64_t(1) << l);
+        take(h.colcnt[l], int64_t(1) << l);
+    }
+    take(h.blk_row, (int64_t)M->lb << M->L);
+    take(h.blk_col, (int64_t)M->lb << M->L);
+    h.ready = true;
+    M->hist = std::move(h);
+}
+
+void build_histograms(qt_matrix* M, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(M->mu);
+    if (M->hist.ready) return;
     const int64_t nb_pad = (int64_t)M->lb << M->L;
-    int64_t total = 2 * nb_pad;
-    for (int l = 0; l <= M->L; ++l) total += 2 * (int64_t(1) << l);
+    const int64_t total = histogram_words(M);
     DBuf<int32_t> d(total, s);
-    QT_HIP(hipMemsetAsync(d.p, 0, total * sizeof(int32_t), s));
+    k_fill_i32<<<grid_for(total), 256, 0, s>>>(d.p, total, 0);
+    QT_LAUNCH("k_fill_i32");
     int64_t off = 0;
-    std::vector<int64_t> offs;
     for (int l = 0; l <= M->L; ++l) {
         const int64_t side = int64_t(1) << l;
         const uint64_t* keys = (l < M->L) ? M->levels[l].key.p : M->leaves.key.p;
         const int64_t n = (l < M->L) ? M->levels[l].n : M->leaves.n;
-        offs.push_back(off);
         if (n > 0) {
             k_hist<<<grid_for(n), 256, 0, s>>>(keys, n, d.p + off, d.p + off + side);
             QT_LAUNCH("k_hist");
@@ -465,18 +548,9 @@ void build_histograms(qt_matrix* M, hipStream_t s) {
         k_hist<<<grid_for(M->nblocks), 256, 0, s>>>(M->bkey.p, M->nblocks, d.p + off, d.p + off + nb_pad);
         QT_LAUNCH("k_hist");
     }
-    std::vector<int32_t> host(total);
-    QT_HIP(hipMemcpyAsync(host.data(), d.p, total * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    QT_HIP(hipStreamSynchronize(s));
-    for (int l = 0; l <= M->L; ++l) {
-        const int64_t side = int64_t(1) << l;
-        h.rowcnt[l].assign(host.begin() + offs[l], host.begin() + offs[l] + side);
-        h.colcnt[l].assign(host.begin() + offs[l] + side, host.begin() + offs[l] + 2 * side);
-    }
-    h.blk_row.assign(host.begin() + off, host.begin() + off + nb_pad);
-    h.blk_col.assign(host.begin() + off + nb_pad, host.begin() + off + 2 * nb_pad);
-    h.ready = true;
-    M->hist = std::move(h);
+    ReadBack words(total);
+    words.publish(d.p, s);
+    adopt_histograms(M, words.wait(s));
 }
 
 // ----------------------------------------------------- operand forms
@@ -552,27 +626,131 @@ void operand_bf16(qt_matrix* M, hipStream_t s) {
 
 // ----------------------------------------------------------------- build
 
-void build_tree_levels(qt_matrix* M, hipStream_t s);
+// A tree under construction: its arrays, placed by bounds, and the words the
+// host reads when they are done: kErr, kCount, two for a caller's double
+// (kSum), the node counts of levels 0 .. L, the histograms.
+struct TreeJob {
+    enum { kErr = 0, kCount = 1, kSum = 2, kLevels = 4 };
+    qt_matrix* M;
+    int64_t bound;                 // at most this many blocks
+    DBuf<int32_t> words, starts;
+    std::vector<size_t> child_at, key_at;
+    size_t base_at = 0, lkey_at = 0, mo_at = 0, rm_at = 0, cm_at = 0;
+    int64_t nwords = 0;
+    TreeBuild b{};
+    int32_t* err() { return words.p + kErr; }
+    int32_t* count() { return words.p + kCount; }
+};
 
-// Block keys in Morton order and the quadtree levels of M (shape fields set,
-// nblocks > 0) from a device block list; perm[t] receives the list position
-// of the block at sorted position t. Rejects out-of-range and repeated (I, J).
-static void build_structure(qt_matrix* M, const int32_t* pI, const int32_t* pJ, int64_t nblocks, int64_t nbr,
-                            int64_t nbc, DBuf<int32_t>& perm, hipStream_t s) {
+// Allocates and clears everything (n: the number of blocks, where the device
+// does not write it to count() before tree_fill).
+static void tree_begin(TreeJob& j, qt_matrix* M, int64_t bound, int64_t n, hipStream_t s) {
+    const int L = M->L;
+    if (L >= MAX_TREE_LEVELS) fail(QT_ERR_UNSUPPORTED, "quadtree too deep");
+    j.M = M;
+    j.bound = bound;
+    ArenaPlan plan;
+    std::vector<int64_t> cap(L + 1);
+    for (int l = 0; l <= L; ++l) {   // node positions of M's shape at level l
+        const int64_t side = (int64_t)M->leaf << (L - l);
+        cap[l] = std::min(bound, ((M->n_rows + side - 1) / side) * ((M->n_cols + side - 1) / side));
+        j.child_at.push_back(0);
+        j.key_at.push_back(0);
+    }
+    for (int l = 0; l < L; ++l) j.child_at[l] = plan.take(4 * (size_t)cap[l] * sizeof(int32_t));
+    const size_t child_end = plan.bytes;   // the child tables come first: one clear covers them
+    for (int l = 0; l < L; ++l) j.key_at[l] = plan.take((size_t)cap[l] * sizeof(uint64_t));
+    j.base_at = plan.take((size_t)cap[L] * sizeof(int32_t));
+    j.lkey_at = plan.take((size_t)cap[L] * sizeof(uint64_t));
+    j.mo_at = plan.take((size_t)cap[L] * sizeof(uint64_t));
+    j.rm_at = plan.take((size_t)cap[L] * sizeof(uint64_t));
+    j.cm_at = plan.take((size_t)cap[L] * sizeof(uint64_t));
+    M->arena.alloc(plan.bytes, s);
+    j.nwords = TreeJob::kLevels + (L + 1) + histogram_words(M);
+    j.words.alloc(j.nwords, s);
+    TreeBuild& b = j.b;
+    b.tile = TREE_THREADS;
+    while (bound > TREE_TILES_MAX * b.tile) b.tile *= 2;
+    const int64_t tiles = (bound + b.tile - 1) / b.tile;
+    j.starts.alloc(tiles * (L + 1), s);
+    char* at = M->arena.p;
+    for (int l = 0; l < L; ++l) {
+        b.child[l] = (int32_t*)(at + j.child_at[l]);
+        b.key[l] = (uint64_t*)(at + j.key_at[l]);
+    }
+    b.base = (int32_t*)(at + j.base_at);
+    b.lkey = (uint64_t*)(at + j.lkey_at);
+    b.mo = (uint64_t*)(at + j.mo_at);
+    b.rm = (uint64_t*)(at + j.rm_at);
+    b.cm = (uint64_t*)(at + j.cm_at);
+    b.n = j.count();
+    b.L = L;
+    b.lb_log = M->lb_log;
+    b.starts = j.starts.p;
+    b.err = j.err();
+    b.hist = j.words.p + TreeJob::kLevels + (L + 1);
+    const int64_t nnil = (int64_t)(child_end / sizeof(int32_t));
+    const unsigned g = (unsigned)std::min<int64_t>(grid_for(std::max(nnil, j.nwords)), 4096);
+    k_tree_init<<<g, 256, 0, s>>>(j.words.p, j.nwords, TreeJob::kCount, (int32_t)n, (int32_t*)at, nnil);
+    QT_LAUNCH("k_tree_init");
+}
+
+// Forms the tree over the ascending keys (j.bound of them at most).
+static void tree_fill(TreeJob& j, const uint64_t* keys, hipStream_t s) {
+    TreeBuild& b = j.b;
+    b.keys = keys;
+    const unsigned tiles = (unsigned)((j.bound + b.tile - 1) / b.tile);
+    k_tree_tiles<<<tiles, TREE_THREADS, 0, s>>>(b);
+    QT_LAUNCH("k_tree_tiles");
+    k_radix_scan<<<1, 1024, 0, s>>>(b.starts, j.words.p + TreeJob::kLevels, b.L + 1, (int)tiles);
+    QT_LAUNCH("k_radix_scan");
+    k_tree_tables<<<tiles, TREE_THREADS, 0, s>>>(b);
+    QT_LAUNCH("k_tree_tables");
+}
+
+// Reads the words back and sets M's tree, block count and histograms; throws
+// what the error flags say. out (may be nullptr): the caller's double.
+static void tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
+    ReadBack back(j.nwords);
+    back.publish(j.words.p, s);
+    const int32_t* w = back.wait(s);
+    if (w[TreeJob::kErr] & 1) fail(QT_ERR_ARG, "block index out of range");
+    if (w[TreeJob::kErr] & 2) fail(QT_ERR_DUPLICATE, "the same (I, J) block is listed twice");
+    qt_matrix* M = j.M;
+    const int L = M->L;
+    const int32_t* cnt = w + TreeJob::kLevels;
+    M->nblocks = w[TreeJob::kCount];
+    char* at = M->arena.p;
+    for (int l = 0; l < L; ++l) {
+        M->levels[l].n = cnt[l];
+        M->levels[l].child.view(at + j.child_at[l], 4 * (size_t)cnt[l]);
+        M->levels[l].key.view(at + j.key_at[l], cnt[l]);
+    }
+    LeafLevel& lv = M->leaves;
+    lv.n = cnt[L];
+    lv.base.view(at + j.base_at, cnt[L]);
+    lv.key.view(at + j.lkey_at, cnt[L]);
+    lv.mask_mo.view(at + j.mo_at, cnt[L]);
+    lv.mask_rm.view(at + j.rm_at, cnt[L]);
+    lv.mask_cm.view(at + j.cm_at, cnt[L]);
+    if (out) std::memcpy(out, w + TreeJob::kSum, sizeof(double));
+    adopt_histograms(M, cnt + (L + 1));
+}
+
+// Block keys in Morton order and the quadtree of M (shape fields set) from a
+// device block list; perm[t] receives the list position of the block at sorted
+// position t. Queued on s; tree_finish completes it and rejects out-of-range
+// and repeated (I, J).
+static void begin_structure(TreeJob& j, qt_matrix* M, const int32_t* pI, const int32_t* pJ, int64_t nblocks,
+                            int64_t nbr, int64_t nbc, DBuf<int32_t>& perm, hipStream_t s) {
     const int key_bits = 2 * ilog2(std::max(nbr, nbc));
-    DBuf<uint64_t> keys(nblocks, s);
+    M->bkey.alloc(nblocks, s);
     perm.alloc(nblocks, s);
-    DBuf<int32_t> derr(1, s), tmp(sort_tmp_words(nblocks, key_bits), s);
-    QT_HIP(hipMemsetAsync(derr.p, 0, sizeof(int32_t), s));
-    stable_sort(ListKeys{pI, pJ, nbr, nbc, derr.p}, KeyPermSink{keys.p, perm.p}, nblocks, key_bits, tmp.p, perm.p,
+    DBuf<int32_t> tmp(sort_tmp_words(nblocks, key_bits), s);
+    tree_begin(j, M, nblocks, nblocks, s);
+    stable_sort(ListKeys{pI, pJ, nbr, nbc, j.err()}, KeyPermSink{M->bkey.p, perm.p}, nblocks, key_bits, tmp.p, perm.p,
                 s);
-    k_build_dups<<<grid_for(nblocks), 256, 0, s>>>(keys.p, nblocks, derr.p);
-    QT_LAUNCH("k_build_dups");
-    const int32_t err = read_scalar(derr.p, s);
-    if (err & 1) fail(QT_ERR_ARG, "block index out of range");
-    if (err & 2) fail(QT_ERR_DUPLICATE, "the same (I, J) block is listed twice");
-    M->bkey = std::move(keys);
-    build_tree_levels(M, s);
+    tree_fill(j, M->bkey.p, s);
 }
 
 qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_t nblocks, const int32_t* I,
@@ -635,89 +813,12 @@ qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_
     }
 
     DBuf<int32_t> perm;
-    build_structure(M.get(), pI, pJ, nblocks, nbr, nbc, perm, s);
+    TreeJob job;
     M->v64.alloc((size_t)nblocks * bb, s);
+    begin_structure(job, M.get(), pI, pJ, nblocks, nbr, nbc, perm, s);
     copy_blocks(pV, perm.p, nblocks, bb, M->v64.p, s);
-    build_histograms(M.get(), s);
-    QT_HIP(hipStreamSynchronize(s));
+    tree_finish(job, s);   // the last thing queued: the caller's arrays have been read
     return M.release();
-}
-
-// Leaves and levels above, from the sorted block keys of M.
-// The node-start flags of every level, their scan, and the tables from them.
-template <class I>
-static void fill_levels(qt_matrix* M, int64_t nflags, int shift, const LevelTables& tb, hipStream_t s) {
-    const int64_t n = M->nblocks;
-    DBuf<I> flags(nflags, s), ex(nflags + 1, s), tmp(scan_tmp_elems(nflags) + 1, s);
-    k_level_flags<I><<<grid_for(n), 256, 0, s>>>(M->bkey.p, n, M->L, shift, flags.p);
-    QT_LAUNCH("k_level_flags");
-    exclusive_scan(flags.p, ex.p, nflags, tmp.p, s);
-    k_level_fill<I><<<grid_for(n), 256, 0, s>>>(M->bkey.p, n, M->L, M->lb_log, flags.p, ex.p, tb);
-    QT_LAUNCH("k_level_fill");
-}
-
-void build_tree_levels(qt_matrix* M, hipStream_t s) {
-    const int64_t n = M->nblocks;
-    const int shift = 2 * M->lb_log;
-    // all node counts in one pass and one read-back, so the levels below
-    // are built without further synchronization
-    std::vector<int32_t> counts(M->L + 1);
-    {
-        DBuf<int32_t> dcnt(M->L + 1, s);
-        k_fill_i32<<<1, 64, 0, s>>>(dcnt.p, M->L + 1, 0);
-        QT_LAUNCH("k_fill_i32");
-        k_level_counts<<<grid_for(n), 256, 0, s>>>(M->bkey.p, n, M->L, shift, dcnt.p);
-        QT_LAUNCH("k_level_counts");
-        QT_HIP(hipMemcpyAsync(counts.data(), dcnt.p, counts.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        QT_HIP(hipStreamSynchronize(s));
-    }
-    const int32_t nleaves = counts[M->L];
-    const int64_t nflags = (int64_t)(M->L + 1) * n;
-    if (M->L >= MAX_FUSED_LEVELS) fail(QT_ERR_UNSUPPORTED, "quadtree too deep");
-    ArenaPlan plan;
-    std::vector<size_t> o_child(M->L), o_key(M->L);
-    for (int l = 0; l < M->L; ++l) {
-        o_child[l] = plan.take(4 * (size_t)counts[l] * sizeof(int32_t));
-        o_key[l] = plan.take((size_t)counts[l] * sizeof(uint64_t));
-    }
-    const size_t child_end = plan.bytes;   // the child tables come first: one clear covers them
-    const size_t o_base = plan.take((size_t)nleaves * sizeof(int32_t));
-    const size_t o_lkey = plan.take((size_t)nleaves * sizeof(uint64_t));
-    const size_t o_mo = plan.take((size_t)nleaves * sizeof(uint64_t));
-    const size_t o_rm = plan.take((size_t)nleaves * sizeof(uint64_t));
-    const size_t o_cm = plan.take((size_t)nleaves * sizeof(uint64_t));
-    M->arena.alloc(plan.bytes, s);
-    char* base = M->arena.p;
-    LevelTables tb{};
-    for (int l = 0; l < M->L; ++l) {
-        TreeLevel& tl = M->levels[l];
-        tl.n = counts[l];
-        tl.child.view(base + o_child[l], 4 * (size_t)counts[l]);
-        tl.key.view(base + o_key[l], counts[l]);
-        tb.child[l] = tl.child.p;
-        tb.key[l] = tl.key.p;
-    }
-    LeafLevel& lv = M->leaves;
-    lv.n = nleaves;
-    lv.base.view(base + o_base, nleaves);
-    lv.key.view(base + o_lkey, nleaves);
-    lv.mask_mo.view(base + o_mo, nleaves);
-    lv.mask_rm.view(base + o_rm, nleaves);
-    lv.mask_cm.view(base + o_cm, nleaves);
-    tb.base = lv.base.p;
-    tb.lkey = lv.key.p;
-    tb.mo = lv.mask_mo.p;
-    tb.rm = lv.mask_rm.p;
-    tb.cm = lv.mask_cm.p;
-    if (child_end > 0) {
-        const int64_t words = (int64_t)(child_end / sizeof(int32_t));
-        k_fill_i32<<<grid_for(words), 256, 0, s>>>((int32_t*)base, words, -1);
-        QT_LAUNCH("k_fill_i32");
-    }
-    if (nflags < (int64_t(1) << 31) - 2)
-        fill_levels<int32_t>(M, nflags, shift, tb, s);
-    else
-        fill_levels<int64_t>(M, nflags, shift, tb, s);
 }
 
 // ------------------------------------------------------------ copy out
@@ -1014,7 +1115,8 @@ qt_matrix* symmetric_full(qt_matrix* A, hipStream_t s) {
     S->vsrc = A;
     if (n > 0) {
         DBuf<int32_t> up(n, s), rank(n + 1, s), tmp(scan_tmp_elems(n) + 1, s), err(1, s);
-        QT_HIP(hipMemsetAsync(err.p, 0, sizeof(int32_t), s));
+        k_fill_i32<<<1, 64, 0, s>>>(err.p, 1, 0);
+        QT_LAUNCH("k_fill_i32");
         k_mirror_flags<<<grid_for(n), 256, 0, s>>>(A->bkey.p, n, up.p, err.p);
         QT_LAUNCH("k_mirror_flags");
         exclusive_scan(up.p, rank.p, n, tmp.p, s);
@@ -1030,13 +1132,15 @@ qt_matrix* symmetric_full(qt_matrix* A, hipStream_t s) {
         QT_LAUNCH("k_mirror_list");
         S->nblocks = total;
         DBuf<int32_t> perm;
-        build_structure(S.get(), I.p, J.p, total, A->n_rows / A->b, A->n_cols / A->b, perm, s);
+        TreeJob job;
         S->bmap.alloc(total, s);
+        begin_structure(job, S.get(), I.p, J.p, total, A->n_rows / A->b, A->n_cols / A->b, perm, s);
         k_gather_i32<<<grid_for(total), 256, 0, s>>>(src.p, perm.p, total, S->bmap.p);
         QT_LAUNCH("k_gather_i32");
+        tree_finish(job, s);
+    } else {
+        build_histograms(S.get(), s);
     }
-    build_histograms(S.get(), s);
-    QT_HIP(hipStreamSynchronize(s));
     A->sym_full = std::move(S);
     return A->sym_full.get();
 }
@@ -1062,9 +1166,15 @@ static qt_matrix* assemble_sorted(const qt_matrix* like, int L, int64_t nb, DBuf
     C->levels.resize(L);
     C->bkey = std::move(keys);
     C->v64 = std::move(values);
-    if (nb > 0) build_tree_levels(C.get(), s);
-    build_histograms(C.get(), s);
-    QT_HIP(hipStreamSynchronize(s));
+    if (nb > 0) {
+        TreeJob job;
+        tree_begin(job, C.get(), nb, nb, s);
+        tree_fill(job, C->bkey.p, s);
+        tree_finish(job, s);
+    } else {
+        build_histograms(C.get(), s);
+        QT_HIP(hipStreamSynchronize(s));
+    }
     return C.release();
 }
 

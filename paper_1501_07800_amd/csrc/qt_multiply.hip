@@ -43,16 +43,13 @@
 // side_stream below).
 #include "qt_internal.h"
 #include "qt_morton.h"
+#include "qt_readback.h"
 
 #include <algorithm>
-#include <chrono>
-#include <cstring>
 #include <map>
 #include <string>
 
 namespace qt {
-
-constexpr int kPublishMax = 128;  // counts read back per multiply: 3 * (depth + 1) + 1
 
 // ------------------------------------------------------------- helpers
 
@@ -80,36 +77,6 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 __device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_incl_scan(x), 63); }
 
 __device__ __forceinline__ int wave_excl_scan(int x) { return wave_incl_scan(x) - x; }
-
-// Swaps index bits a > b of a 64-bit mask (bit i of the result is the bit of
-// the mask whose index has these two bits of i exchanged). pos: the mask of
-// all indices with bit b set and bit a clear.
-__device__ __forceinline__ uint64_t swap_index_bits(uint64_t m, int a, int b, uint64_t pos) {
-    const int sh = (1 << a) - (1 << b);
-    const uint64_t d = ((m >> sh) ^ m) & pos;
-    return m ^ d ^ (d << sh);
-}
-
-// A leaf's occupancy in Morton order (index bits r2 c2 r1 c1 r0 c0) as
-// row-major (r2 r1 r0 c2 c1 c0), and that transposed as column-major; leaves
-// of 4 x 4 and 2 x 2 blocks have the lower four and two index bits only.
-__device__ __forceinline__ uint64_t morton_to_rowmajor(uint64_t m, int lb_log) {
-    if (lb_log == 3) {
-        m = swap_index_bits(m, 4, 3, 0x0000FF000000FF00ull);   // r2 r1 c2 c1 r0 c0
-        m = swap_index_bits(m, 2, 1, 0x0C0C0C0C0C0C0C0Cull);   // r2 r1 c2 r0 c1 c0
-        return swap_index_bits(m, 3, 2, 0x00F000F000F000F0ull);
-    }
-    return lb_log == 2 ? swap_index_bits(m, 2, 1, 0x0C0Cull) : m;
-}
-__device__ __forceinline__ uint64_t rowmajor_to_colmajor(uint64_t m, int lb_log) {
-    if (lb_log == 3) {
-        m = swap_index_bits(m, 5, 2, 0x00000000F0F0F0F0ull);
-        m = swap_index_bits(m, 4, 1, 0x0000CCCC0000CCCCull);
-        return swap_index_bits(m, 3, 0, 0x00AA00AA00AA00AAull);
-    }
-    if (lb_log == 2) return swap_index_bits(swap_index_bits(m, 3, 1, 0x00CCull), 2, 0, 0x0A0Aull);
-    return lb_log == 1 ? swap_index_bits(m, 1, 0, 0x2ull) : m;
-}
 
 __device__ __forceinline__ int4 load_children(const int32_t* tab, int32_t node) {
     return *reinterpret_cast<const int4*>(tab + 4 * (int64_t)node);
@@ -1163,24 +1130,6 @@ __global__ __launch_bounds__(KORDER_THREADS) void k_korder_place(const uint64_t*
 
 // ----------------------------------------------------------- host side
 
-// Reading C's counts back. Instead of a device-to-host copy followed by a
-// stream synchronization (whose wake-up latency is tens of microseconds), a
-// one-wave kernel writes the counts into pinned, host-coherent memory and
-// then releases a sequence number there at system scope; the host spins on
-// that word. The spin checks the stream every so often, so a failed launch
-// ends it with the stream's error instead of a hang.
-struct alignas(64) HostSlot {
-    int32_t counts[kPublishMax];
-    uint32_t flag;
-};
-
-__global__ void k_publish(const int32_t* __restrict__ counts, int n, HostSlot* slot, uint32_t seq) {
-    for (int t = threadIdx.x; t < n; t += blockDim.x) slot->counts[t] = counts[t];
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(&slot->flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Events that order one stream after another (record on one, wait on the
 // other), kept for reuse per device: a wait already queued keeps the
 // recording it was queued after, so an event can be recorded again as soon as
@@ -1188,9 +1137,10 @@ __global__ void k_publish(const int32_t* __restrict__ counts, int n, HostSlot* s
 static std::mutex g_order_ev_mu;
 static std::map<int, std::vector<hipEvent_t>> g_order_ev;
 
-static void stream_after(hipStream_t waiter, hipStream_t first) {
+static hipError_t stream_after(hipStream_t waiter, hipStream_t first) {
     int dev = 0;
-    QT_HIP(hipGetDevice(&dev));
+    hipError_t r = hipGetDevice(&dev);
+    if (r != hipSuccess) return r;
     hipEvent_t e = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_order_ev_mu);
@@ -1200,79 +1150,17 @@ static void stream_after(hipStream_t waiter, hipStream_t first) {
             pool.pop_back();
         }
     }
-    if (!e) QT_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    const hipError_t r1 = hipEventRecord(e, first);
-    const hipError_t r2 = r1 == hipSuccess ? hipStreamWaitEvent(waiter, e, 0) : r1;
+    if (!e) {
+        r = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+        if (r != hipSuccess) return r;
+    }
+    r = hipEventRecord(e, first);
+    if (r == hipSuccess) r = hipStreamWaitEvent(waiter, e, 0);
     {
         std::lock_guard<std::mutex> lk(g_order_ev_mu);
         g_order_ev[dev].push_back(e);
     }
-    QT_HIP(r1);
-    QT_HIP(r2);
-}
-
-static std::mutex g_slot_mu;
-static std::vector<std::pair<HostSlot*, HostSlot*>> g_slot_free;   // (host address, device address)
-static uint32_t g_slot_seq = 0;
-
-// A pinned slot for one read-back, returned to the free list on scope exit.
-struct SlotLease {
-    HostSlot* slot = nullptr;
-    HostSlot* dslot = nullptr;
-    uint32_t seq = 0;
-    SlotLease() {
-        std::lock_guard<std::mutex> lk(g_slot_mu);
-        if (g_slot_free.empty()) {
-            constexpr int kChunk = 16;
-            HostSlot* chunk = nullptr;
-            QT_HIP(hipHostMalloc((void**)&chunk, kChunk * sizeof(HostSlot),
-                                 hipHostMallocCoherent | hipHostMallocPortable | hipHostMallocMapped));
-            HostSlot* dchunk = nullptr;
-            QT_HIP(hipHostGetDevicePointer((void**)&dchunk, chunk, 0));
-            for (int i = 0; i < kChunk; ++i) {
-                chunk[i].flag = 0;
-                g_slot_free.emplace_back(chunk + i, dchunk + i);
-            }
-        }
-        slot = g_slot_free.back().first;
-        dslot = g_slot_free.back().second;
-        g_slot_free.pop_back();
-        if (++g_slot_seq == 0) ++g_slot_seq;   // 0 never marks a publication
-        seq = g_slot_seq;
-    }
-    ~SlotLease() {
-        std::lock_guard<std::mutex> lk(g_slot_mu);
-        g_slot_free.emplace_back(slot, dslot);
-    }
-    SlotLease(const SlotLease&) = delete;
-    SlotLease& operator=(const SlotLease&) = delete;
-};
-
-// Reads n counts from the device after the work queued on s; when `waiter`
-// is given, work queued on it afterwards follows that work too (ordered while
-// the counts are still on their way).
-static void read_back_counts(const int32_t* dcount, int n, hipStream_t s, int32_t* out, hipStream_t waiter) {
-    if (n > kPublishMax) fail(QT_ERR_UNSUPPORTED, "tree too deep for the count read-back");
-    SlotLease lease;
-    __atomic_store_n(&lease.slot->flag, 0u, __ATOMIC_RELAXED);
-    k_publish<<<1, 64, 0, s>>>(dcount, n, lease.dslot, lease.seq);
-    QT_LAUNCH("k_publish");
-    if (waiter) stream_after(waiter, s);
-    const auto t0 = std::chrono::steady_clock::now();
-    for (uint64_t it = 1;; ++it) {
-        if (__atomic_load_n(&lease.slot->flag, __ATOMIC_ACQUIRE) == lease.seq) break;
-        if ((it & 4095) == 0) {
-            const hipError_t e = hipStreamQuery(s);
-            if (e == hipSuccess) {
-                if (__atomic_load_n(&lease.slot->flag, __ATOMIC_ACQUIRE) == lease.seq) break;
-                fail(QT_ERR_DEVICE, "symbolic phase: counts were not published");
-            }
-            if (e != hipErrorNotReady) fail(QT_ERR_DEVICE, std::string("symbolic phase: ") + hipGetErrorString(e));
-            if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(600))
-                fail(QT_ERR_DEVICE, "symbolic phase: no progress for 600 s");
-        }
-    }
-    std::memcpy(out, (const void*)lease.slot->counts, n * sizeof(int32_t));
+    return r;
 }
 
 // Workgroups of the per-level kernels for n C nodes (one wave each).
@@ -1418,7 +1306,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         // stream: made there, and the traversal waits for them
         build_norms(A, s);
         build_norms(B, s);
-        stream_after(ss, s);
+        QT_HIP(stream_after(ss, s));
     }
 
     // pair counts per level and block products: exact, or upper bounds when
@@ -1790,10 +1678,16 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     if (prof) QT_HIP(hipEventRecord(ev.e1, ss));
 
     // the one synchronization: node and block counts of C
-    std::vector<int32_t> hc(3 * L + 4);
+    const int nhc = 3 * L + 4;
+    if (nhc > kSlotWords) fail(QT_ERR_UNSUPPORTED, "tree too deep for the count read-back");
+    ReadBack counts(nhc);
+    counts.publish(dcount, ss);
     // the caller's stream follows the traversal from here on (the numeric
-    // kernel first); a launch order built below adds a second wait
-    read_back_counts(dcount, (int)hc.size(), ss, hc.data(), s);
+    // kernel first), ordered while the counts are on their way; a launch order
+    // built below adds a second wait
+    const hipError_t ordered = stream_after(s, ss);
+    const int32_t* hc = counts.wait(ss);
+    QT_HIP(ordered);
     for (int l = 0; l <= L; ++l) {
         if (hc[l] < 0 || hc[l] > ncap[l]) fail(QT_ERR_DEVICE, "symbolic phase: C node count out of range");
         if (hc[2 * L + 3 + l] < 0 || hc[2 * L + 3 + l] > hc[l])
@@ -1823,11 +1717,11 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
                                                                     (int32_t)kdim, (int32_t)nwg, knext, order);
         QT_LAUNCH("k_korder_place");
         if (prof) QT_HIP(hipEventRecord(ev.e1, ss));   // the symbolic phase ends here then
-        stream_after(s, ss);
+        QT_HIP(stream_after(s, ss));
     }
 
     // C's tree (NIL-normalised): views into its arena
-    const int32_t* kept = hc.data() + 2 * L + 3;
+    const int32_t* kept = hc + 2 * L + 3;
     for (int l = 0; l < L; ++l) {
         C->levels[l].n = kept[l];
         C->levels[l].child.view(at(K, o_child[l]), 4 * (size_t)kept[l]);

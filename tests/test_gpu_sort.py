@@ -39,7 +39,7 @@ def _list(n, nbr, nbc, seed):
 @pytest.mark.parametrize("n,nbr,nbc", [(1, 1, 1), (2, 1, 70000), (63, 63, 1), (64, 8, 8), (65, 40, 40), (255, 3, 1000),
                                        (4095, 64, 64), (4096, 64, 64), (4097, 70, 60), (8192, 2048, 50),
                                        (8193, 2049, 50), (20000, 5000, 5), (7001, (1 << 22) + 1, 3),
-                                       (448 * 1024, 1024, 1024), (448 * 1024 + 1, 700, 4096)])
+                                       (448 * 1024, 1024, 1024), (448 * 1024 + 1, 700, 4096), ((1 << 19) + 1, 1024, 1024)])
 def test_build_and_copy_out_order(qt, n, nbr, nbc):
     import torch
     print("sort", n, nbr, nbc, flush=True)

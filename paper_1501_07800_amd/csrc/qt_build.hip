@@ -481,14 +481,6 @@ static inline unsigned block_grid(int64_t n) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, 1 << 20));
 }
 
-template <class T>
-static T read_scalar(const T* dptr, hipStream_t s) {
-    T v{};
-    QT_HIP(hipMemcpyAsync(&v, dptr, sizeof(T), hipMemcpyDeviceToHost, s));
-    QT_HIP(hipStreamSynchronize(s));
-    return v;
-}
-
 uint64_t morton2(uint32_t r, uint32_t c) { return morton_key(r, c); }
 
 static int ilog2(int64_t x) {
@@ -640,6 +632,7 @@ struct TreeJob {
     TreeBuild b{};
     int32_t* err() { return words.p + kErr; }
     int32_t* count() { return words.p + kCount; }
+    double* sum() { return reinterpret_cast<double*>(words.p + kSum); }
 };
 
 // Allocates and clears everything (n: the number of blocks, where the device
@@ -941,43 +934,101 @@ void to_blocks_noalloc(const qt_matrix* M, int32_t* I, int32_t* J, void* values,
 // non-negative and rounding is monotone), which is what lets a product be
 // dropped by its norm at any level.
 
+// One wave per block, 16 bytes per lane and load, the loads ahead of the sums.
+// Bound by HBM.
 template <class T>
-__global__ __launch_bounds__(64) void k_block_norm2(const T* __restrict__ v, int64_t n, int bb,
-                                                   double* __restrict__ out) {
-    const int64_t t = blockIdx.x;
+__global__ __launch_bounds__(256) void k_block_norm2(const T* __restrict__ v, int64_t n, int bb,
+                                                    double* __restrict__ out) {
+    constexpr int VE = 16 / sizeof(T), U = 4;
+    typedef T vec __attribute__((ext_vector_type(VE)));
+    const int lane = threadIdx.x & 63;
+    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= n) return;
-    const T* x = v + (size_t)t * bb;
+    const vec* x = reinterpret_cast<const vec*>(v + (size_t)t * bb);
+    const int m = bb / VE;   // 64 (fp32, b = 16) to 2048 vectors
     double s = 0.0;
-    for (int e = threadIdx.x; e < bb; e += 64) {
-        const double d = (double)x[e];
-        s += d * d;
+    for (int e = lane; e < m; e += 64 * U) {
+        vec y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (e + 64 * u < m) y[u] = x[e + 64 * u];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (e + 64 * u < m) {
+#pragma unroll
+                for (int c = 0; c < VE; ++c) {
+                    const double d = (double)y[u][c];
+                    s += d * d;
+                }
+            }
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
-    if (threadIdx.x == 0) out[t] = s;
+    if (lane == 0) out[t] = s;
 }
 
+static void launch_block_norm2(const qt_matrix* M, double* out, hipStream_t s) {
+    const unsigned g = (unsigned)((M->nblocks + 3) / 4);
+    const int bb = M->b * M->b;
+    if (M->vtype == QT_F64)
+        k_block_norm2<double><<<g, 256, 0, s>>>(M->v64.p, M->nblocks, bb, out);
+    else
+        k_block_norm2<float><<<g, 256, 0, s>>>(M->v32.p, M->nblocks, bb, out);
+    QT_LAUNCH("k_block_norm2");
+}
+
+// The leaf's norms are added in block order, eight loads at a time.
 __global__ void k_leaf_norm2(const int32_t* __restrict__ base, const uint64_t* __restrict__ mo, int64_t n,
                              const double* __restrict__ bn2, double* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t b0 = base[i], cnt = __popcll(mo[i]);
     double s = 0.0;
-    for (int32_t k = 0; k < cnt; ++k) s += bn2[b0 + k];
+    for (int32_t k = 0; k < cnt; k += 8) {
+        double x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = k + e < cnt ? bn2[b0 + k + e] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += x[e];
+    }
     out[i] = s;
 }
 
-__global__ void k_node_norm2(const int32_t* __restrict__ child, int64_t n, const double* __restrict__ below,
-                             double* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+__device__ __forceinline__ double node_norm2(const int32_t* __restrict__ child, int64_t i, const double* below) {
     double s = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int32_t c = child[4 * i + q];
         if (c >= 0) s += below[c];
     }
-    out[i] = s;
+    return s;
+}
+
+__global__ void k_node_norm2(const int32_t* __restrict__ child, int64_t n, const double* __restrict__ below,
+                             double* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = node_norm2(child, i, below);
+}
+
+// The small levels at the top in one launch: a workgroup goes up the tree,
+// level by level.
+constexpr int64_t TOP_NODES = 4096;
+struct TopNorms {
+    int levels;
+    const int32_t* child[MAX_TREE_LEVELS];   // from the lowest up
+    int32_t n[MAX_TREE_LEVELS];
+    double* out[MAX_TREE_LEVELS];
+    const double* below;
+};
+
+__global__ __launch_bounds__(1024) void k_top_norm2(TopNorms a) {
+    const double* below = a.below;
+    for (int l = 0; l < a.levels; ++l) {
+        for (int i = threadIdx.x; i < a.n[l]; i += 1024) a.out[l][i] = node_norm2(a.child[l], i, below);
+        below = a.out[l];
+        __threadfence_block();
+        __syncthreads();
+    }
 }
 
 void build_norms(qt_matrix* M, hipStream_t s) {
@@ -991,14 +1042,7 @@ void build_norms(qt_matrix* M, hipStream_t s) {
         double* p = M->norms.p;
         double* bn2 = p;
         p += std::max<int64_t>(M->nblocks, 1);
-        const int bb = M->b * M->b;
-        if (M->nblocks > 0) {
-            if (M->vtype == QT_F64)
-                k_block_norm2<double><<<(unsigned)M->nblocks, 64, 0, s>>>(M->v64.p, M->nblocks, bb, bn2);
-            else
-                k_block_norm2<float><<<(unsigned)M->nblocks, 64, 0, s>>>(M->v32.p, M->nblocks, bb, bn2);
-            QT_LAUNCH("k_block_norm2");
-        }
+        if (M->nblocks > 0) launch_block_norm2(M, bn2, s);
         std::vector<const double*> nn2(L + 1, nullptr);
         double* below = p;
         p += M->leaves.n;
@@ -1008,16 +1052,26 @@ void build_norms(qt_matrix* M, hipStream_t s) {
             QT_LAUNCH("k_leaf_norm2");
         }
         nn2[L] = below;
+        TopNorms top{};
         for (int l = L - 1; l >= 0; --l) {
             double* here = p;
-            p += M->levels[l].n;
-            if (M->levels[l].n > 0) {
-                k_node_norm2<<<grid_for(M->levels[l].n), 256, 0, s>>>(M->levels[l].child.p, M->levels[l].n, below,
-                                                                     here);
+            const int64_t nl = M->levels[l].n;
+            p += nl;
+            if (nl > TOP_NODES) {
+                k_node_norm2<<<grid_for(nl), 256, 0, s>>>(M->levels[l].child.p, nl, below, here);
                 QT_LAUNCH("k_node_norm2");
+            } else {   // and no level above has more nodes
+                if (top.levels == 0) top.below = below;
+                top.child[top.levels] = M->levels[l].child.p;
+                top.n[top.levels] = (int32_t)nl;
+                top.out[top.levels++] = here;
             }
             nn2[l] = here;
             below = here;
+        }
+        if (top.levels > 0 && top.n[0] > 0) {
+            k_top_norm2<<<1, 1024, 0, s>>>(top);
+            QT_LAUNCH("k_top_norm2");
         }
         M->nn2 = nn2;
         M->bn2 = bn2;
@@ -1050,9 +1104,13 @@ void norms_out(qt_matrix* M, double* block_norm2, double* total_norm2, qt_mem wh
                 *total_norm2 = 0.0;
             else
                 QT_HIP(hipMemsetAsync(total_norm2, 0, sizeof(double), s));
+        } else if (where == QT_MEM_HOST) {
+            ReadBack back(2);
+            back.publish(reinterpret_cast<const int32_t*>(M->nn2[0]), s);
+            std::memcpy(total_norm2, back.wait(s), sizeof(double));
+            if (!block_norm2) return;   // everything queued here is done
         } else {
-            QT_HIP(hipMemcpyAsync(total_norm2, M->nn2[0], sizeof(double),
-                                  where == QT_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, s));
+            QT_HIP(hipMemcpyAsync(total_norm2, M->nn2[0], sizeof(double), hipMemcpyDeviceToDevice, s));
         }
     }
     if (where == QT_MEM_HOST) QT_HIP(hipStreamSynchronize(s));
@@ -1147,10 +1205,8 @@ qt_matrix* symmetric_full(qt_matrix* A, hipStream_t s) {
 
 // ------------------------------------------------------------- C = A + B
 
-// A matrix shaped like `like` from nb blocks whose keys are already in
-// ascending Morton order (adopts keys and values).
-static qt_matrix* assemble_sorted(const qt_matrix* like, int L, int64_t nb, DBuf<uint64_t>&& keys,
-                                  DBuf<double>&& values, hipStream_t s) {
+// An empty matrix shaped like `like` (L levels above the leaves).
+static qt_matrix* shaped_like(const qt_matrix* like, int L, hipStream_t s) {
     std::unique_ptr<qt_matrix> C(new qt_matrix);
     C->n_rows = like->n_rows;
     C->n_cols = like->n_cols;
@@ -1160,28 +1216,20 @@ static qt_matrix* assemble_sorted(const qt_matrix* like, int L, int64_t nb, DBuf
     C->lb_log = like->lb_log;
     C->L = L;
     C->vtype = QT_F64;
-    C->nblocks = nb;
     C->stream = s;
     QT_HIP(hipGetDevice(&C->device));
     C->levels.resize(L);
-    C->bkey = std::move(keys);
-    C->v64 = std::move(values);
-    if (nb > 0) {
-        TreeJob job;
-        tree_begin(job, C.get(), nb, nb, s);
-        tree_fill(job, C->bkey.p, s);
-        tree_finish(job, s);
-    } else {
-        build_histograms(C.get(), s);
-        QT_HIP(hipStreamSynchronize(s));
-    }
     return C.release();
 }
 
-// Merge of two ascending key lists without a sort: A's key i lands at
-// i + #{B keys < it}, B's key j at j + #{A keys <= it}, so a key present in
-// both comes out as A's entry followed by B's. src: s < na for A block s,
-// na + j for B block j.
+// Merge of two ascending key lists without a sort: A's key i comes after i
+// keys of A and #{B keys < it} of B, less the keys in both lists before it;
+// B's key j, where A does not hold it too, likewise. The common keys are
+// counted per tile of 256 of A's (and kept as a bit per key), so the result's
+// keys and its tree are formed without the host knowing their number: one
+// wait for the tree, one for the values, where a merge, a scan and a tree took
+// five (square, truncate, add and norms of a 16384 matrix: 1617 us with those,
+// 1467 with this and the truncation below, which waits as often).
 __device__ __forceinline__ int64_t count_below(const uint64_t* __restrict__ k, int64_t n, uint64_t x, bool le) {
     int64_t lo = 0, hi = n;   // first position whose key is >= x (le: > x)
     while (lo < hi) {
@@ -1195,46 +1243,94 @@ __device__ __forceinline__ int64_t count_below(const uint64_t* __restrict__ k, i
     return lo;
 }
 
-__global__ void k_merge_keys(const uint64_t* __restrict__ ka, int64_t na, const uint64_t* __restrict__ kb,
-                             int64_t nb, uint64_t* __restrict__ keys, int32_t* __restrict__ src) {
+constexpr int MERGE_TILE = 256;
+
+__global__ __launch_bounds__(MERGE_TILE) void k_merge_common(const uint64_t* __restrict__ ka, int64_t na,
+                                                             const uint64_t* __restrict__ kb, int64_t nb,
+                                                             int32_t* __restrict__ below_b,
+                                                             uint64_t* __restrict__ common,
+                                                             int32_t* __restrict__ tiles) {
+    __shared__ int32_t cnt;
+    if (threadIdx.x == 0) cnt = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * MERGE_TILE + threadIdx.x;
+    bool both = false;
+    if (i < na) {
+        const int64_t p = count_below(kb, nb, ka[i], false);
+        below_b[i] = (int32_t)p;
+        both = p < nb && kb[p] == ka[i];
+    }
+    const uint64_t m = __ballot(both);
+    if ((threadIdx.x & 63) == 0) {
+        common[i >> 6] = m;
+        if (m) atomicAdd(&cnt, (int32_t)__popcll(m));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) tiles[blockIdx.x] = cnt;
+}
+
+// common keys among A's first i (i <= na; tiles: scanned)
+__device__ __forceinline__ int64_t common_before(const uint64_t* __restrict__ common,
+                                                 const int32_t* __restrict__ tiles, int64_t i) {
+    int64_t c = tiles[i / MERGE_TILE];
+    for (int64_t w = i / MERGE_TILE * (MERGE_TILE / 64); w < (i >> 6); ++w) c += __popcll(common[w]);
+    if (i & 63) c += __popcll(common[i >> 6] & (~0ull >> (64 - (i & 63))));
+    return c;
+}
+
+// Output block o: A's block sa[o] (-1: none) plus B's block sb[o] (-1: none).
+__global__ void k_merge_write(const uint64_t* __restrict__ ka, int64_t na, const uint64_t* __restrict__ kb, int64_t nb,
+                              const int32_t* __restrict__ below_b, const uint64_t* __restrict__ common,
+                              const int32_t* __restrict__ tiles, const int32_t* __restrict__ total,
+                              uint64_t* __restrict__ key, int32_t* __restrict__ sa, int32_t* __restrict__ sb,
+                              int32_t* __restrict__ count) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0) *count = (int32_t)(na + nb - *total);
+    if (t >= na + nb) return;
+    int64_t o;
     if (t < na) {
-        const int64_t pos = t + count_below(kb, nb, ka[t], false);
-        keys[pos] = ka[t];
-        src[pos] = (int32_t)t;
-    } else if (t < na + nb) {
-        const int64_t j = t - na;
-        const int64_t pos = j + count_below(ka, na, kb[j], true);
-        keys[pos] = kb[j];
-        src[pos] = (int32_t)t;
+        o = t + below_b[t] - common_before(common, tiles, t);
+        key[o] = ka[t];
+        sa[o] = (int32_t)t;
+        sb[o] = (common[t >> 6] >> (t & 63)) & 1 ? below_b[t] : -1;
+    } else {
+        const int64_t j = t - na, p = count_below(ka, na, kb[j], false);
+        if (p < na && ka[p] == kb[j]) return;   // written with A's block
+        o = j + p - common_before(common, tiles, p);
+        key[o] = kb[j];
+        sa[o] = -1;
+        sb[o] = (int32_t)j;
     }
 }
 
-__global__ void k_key_flags(const uint64_t* __restrict__ keys, int64_t n, int32_t* __restrict__ flags) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) flags[t] = (t == 0 || keys[t] != keys[t - 1]) ? 1 : 0;
-}
-
-// Sorted keys of A's and B's blocks (source s < na: A block s, else B block
-// s - na): the first entry of every key writes the output block, adding the
-// second entry when both matrices hold the block.
-__global__ void k_add_blocks(const uint64_t* __restrict__ keys, const int32_t* __restrict__ src, int64_t n,
-                             const int32_t* __restrict__ flags, const int32_t* __restrict__ ex, int64_t na,
-                             const double* __restrict__ va, const double* __restrict__ vb, int bb,
-                             uint64_t* __restrict__ ckey, double* __restrict__ vc) {
-    for (int64_t t = blockIdx.x; t < n; t += gridDim.x) {
-        if (!flags[t]) continue;
-        const int64_t o = ex[t];
-        const int32_t s0 = src[t];
-        const double* x = (s0 < na) ? va + (size_t)s0 * bb : vb + (size_t)(s0 - na) * bb;
-        const bool two = (t + 1 < n) && keys[t + 1] == keys[t];
-        const double* y = nullptr;
-        if (two) {
-            const int32_t s1 = src[t + 1];
-            y = (s1 < na) ? va + (size_t)s1 * bb : vb + (size_t)(s1 - na) * bb;
-        }
-        if (threadIdx.x == 0) ckey[o] = keys[t];
-        for (int e = threadIdx.x; e < bb; e += blockDim.x) vc[(size_t)o * bb + e] = two ? x[e] + y[e] : x[e];
+// Values of the sum, in pieces of 64 two-entry vectors (see k_copy_blocks).
+__global__ __launch_bounds__(64 * COPY_WAVES) void k_add_blocks(const int32_t* __restrict__ sa,
+                                                                const int32_t* __restrict__ sb, int64_t pieces,
+                                                                int ppb_log, const double* __restrict__ va,
+                                                                const double* __restrict__ vb,
+                                                                double* __restrict__ vc) {
+    typedef double vec __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x & 63;
+    const int64_t p0 = ((int64_t)blockIdx.x * COPY_WAVES + (threadIdx.x >> 6)) * COPY_PIECES;
+    const int64_t in_block = (int64_t(1) << ppb_log) - 1;
+    vec x[COPY_PIECES], y[COPY_PIECES];
+    int32_t a[COPY_PIECES], b[COPY_PIECES];
+#pragma unroll
+    for (int r = 0; r < COPY_PIECES; ++r) {
+        const int64_t p = p0 + r;
+        if (p >= pieces) break;
+        a[r] = sa[p >> ppb_log];
+        b[r] = sb[p >> ppb_log];
+        const int64_t e = (p & in_block) * 64 + lane;
+        if (a[r] >= 0) x[r] = __builtin_nontemporal_load(reinterpret_cast<const vec*>(va) + ((int64_t)a[r] << ppb_log) * 64 + e);
+        if (b[r] >= 0) y[r] = __builtin_nontemporal_load(reinterpret_cast<const vec*>(vb) + ((int64_t)b[r] << ppb_log) * 64 + e);
+    }
+#pragma unroll
+    for (int r = 0; r < COPY_PIECES; ++r) {
+        const int64_t p = p0 + r;
+        if (p >= pieces) break;
+        const vec v = a[r] < 0 ? y[r] : b[r] < 0 ? x[r] : x[r] + y[r];
+        __builtin_nontemporal_store(v, reinterpret_cast<vec*>(vc) + p * 64 + lane);
     }
 }
 
@@ -1247,45 +1343,35 @@ qt_matrix* add(qt_matrix* A, qt_matrix* B, hipStream_t s) {
     if (n > (int64_t(1) << 31) - 2) fail(QT_ERR_UNSUPPORTED, "too many blocks");
     if (n == 0) return build(A->n_rows, A->n_cols, A->b, A->leaf, 0, nullptr, nullptr, nullptr, QT_MEM_DEVICE, s);
     const int bb = A->b * A->b;
-    // both key lists are ascending (Morton order): merge them
-    DBuf<uint64_t> keys(n, s);
-    DBuf<int32_t> src(n, s);
-    k_merge_keys<<<grid_for(n), 256, 0, s>>>(A->bkey.p, na, B->bkey.p, nb, keys.p, src.p);
-    QT_LAUNCH("k_merge_keys");
-    DBuf<int32_t> flags(n, s), ex(n + 1, s), tmp(scan_tmp_elems(n) + 1, s);
-    k_key_flags<<<grid_for(n), 256, 0, s>>>(keys.p, n, flags.p);
-    QT_LAUNCH("k_key_flags");
-    exclusive_scan(flags.p, ex.p, n, tmp.p, s);
-    const int32_t nc = read_scalar(ex.p + n, s);
-
-    DBuf<uint64_t> ck(nc, s);
-    DBuf<double> cv((size_t)nc * bb, s);
-    k_add_blocks<<<block_grid(n), 256, 0, s>>>(keys.p, src.p, n, flags.p, ex.p, na, va, vb, bb, ck.p, cv.p);
+    std::unique_ptr<qt_matrix> C(shaped_like(A, std::max(A->L, B->L), s));
+    const int64_t tiles = na / MERGE_TILE + 1;   // the last one may be empty: common_before(na) reads it
+    DBuf<int32_t> below(std::max<int64_t>(na, 1), s), tcnt(tiles + 1, s), sa(n, s), sb(n, s);
+    DBuf<uint64_t> common(tiles * (MERGE_TILE / 64), s);
+    C->bkey.alloc(n, s);
+    TreeJob job;
+    tree_begin(job, C.get(), n, 0, s);
+    k_merge_common<<<(unsigned)tiles, MERGE_TILE, 0, s>>>(A->bkey.p, na, B->bkey.p, nb, below.p, common.p, tcnt.p);
+    QT_LAUNCH("k_merge_common");
+    k_radix_scan<<<1, 1024, 0, s>>>(tcnt.p, tcnt.p + tiles, 1, (int)tiles);
+    QT_LAUNCH("k_radix_scan");
+    k_merge_write<<<grid_for(n), 256, 0, s>>>(A->bkey.p, na, B->bkey.p, nb, below.p, common.p, tcnt.p, tcnt.p + tiles,
+                                              C->bkey.p, sa.p, sb.p, job.count());
+    QT_LAUNCH("k_merge_write");
+    tree_fill(job, C->bkey.p, s);
+    tree_finish(job, s);
+    const int64_t nc = C->nblocks;
+    C->v64.alloc((size_t)nc * bb, s);
+    int ppb_log = 0;
+    while ((128 << ppb_log) < bb) ++ppb_log;
+    const int64_t pieces = nc << ppb_log, per = COPY_WAVES * COPY_PIECES;
+    k_add_blocks<<<(unsigned)((pieces + per - 1) / per), 64 * COPY_WAVES, 0, s>>>(sa.p, sb.p, pieces, ppb_log, va, vb,
+                                                                                 C->v64.p);
     QT_LAUNCH("k_add_blocks");
-    return assemble_sorted(A, std::max(A->L, B->L), nc, std::move(ck), std::move(cv), s);
+    QT_HIP(hipStreamSynchronize(s));
+    return C.release();
 }
 
 // --------------------------------------------------- value truncation
-
-// Squared Frobenius norm of every block.
-__global__ void k_block_norm2(const double* __restrict__ v, int64_t n, int bb, double* __restrict__ norm2) {
-    __shared__ double part[256];
-    for (int64_t t = blockIdx.x; t < n; t += gridDim.x) {
-        double s = 0.0;
-        for (int e = threadIdx.x; e < bb; e += blockDim.x) {
-            const double x = v[(size_t)t * bb + e];
-            s += x * x;
-        }
-        part[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) norm2[t] = part[0];
-        __syncthreads();
-    }
-}
 
 // Sorted position p is removed while the running sum of squared norms up to
 // and including p stays below eps^2; the survivors are flagged by block.
@@ -1295,19 +1381,50 @@ __global__ void k_trunc_flags(const double* __restrict__ excl, const double* __r
     if (p < n) keep[idx[p]] = (excl[p] + sorted[p] < eps2) ? 0 : 1;
 }
 
-// Kept blocks, in their (Morton) order: keys and values of the result.
-__global__ void k_compact_blocks(const uint64_t* __restrict__ bkey, const double* __restrict__ v, int64_t n, int bb,
-                                 const int32_t* __restrict__ keep, const int32_t* __restrict__ pos,
-                                 uint64_t* __restrict__ okey, double* __restrict__ out) {
-    for (int64_t t = blockIdx.x; t < n; t += gridDim.x) {
-        if (!keep[t]) continue;
-        const int64_t o = pos[t];
-        if (threadIdx.x == 0) okey[o] = bkey[t];
-        for (int e = threadIdx.x; e < bb; e += blockDim.x) out[(size_t)o * bb + e] = v[(size_t)t * bb + e];
-    }
+constexpr int KEEP_TILE = 256;
+
+__global__ __launch_bounds__(KEEP_TILE) void k_keep_tiles(const int32_t* __restrict__ keep, int64_t n,
+                                                         int32_t* __restrict__ tiles) {
+    __shared__ int32_t cnt;
+    if (threadIdx.x == 0) cnt = 0;
+    __syncthreads();
+    const int64_t t = (int64_t)blockIdx.x * KEEP_TILE + threadIdx.x;
+    const uint64_t m = __ballot(t < n && keep[t] != 0);
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(&cnt, (int32_t)__popcll(m));
+    __syncthreads();
+    if (threadIdx.x == 0) tiles[blockIdx.x] = cnt;
 }
 
-
+// Kept blocks, in their (Morton) order: keys and source blocks of the result,
+// their number, and the squared norm of the k = n - kept smallest (excl:
+// exclusive scan of the sorted norms).
+__global__ __launch_bounds__(KEEP_TILE) void k_keep_write(const int32_t* __restrict__ keep, int64_t n,
+                                                         const int32_t* __restrict__ tiles,
+                                                         const int32_t* __restrict__ total,
+                                                         const uint64_t* __restrict__ bkey,
+                                                         const double* __restrict__ excl,
+                                                         const double* __restrict__ sorted,
+                                                         uint64_t* __restrict__ okey, int32_t* __restrict__ src,
+                                                         int32_t* __restrict__ count, double* __restrict__ removed2) {
+    __shared__ int32_t wcnt[KEEP_TILE / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t t = (int64_t)blockIdx.x * KEEP_TILE + threadIdx.x;
+    const bool k = t < n && keep[t] != 0;
+    const uint64_t m = __ballot(k);
+    if (lane == 0) wcnt[wave] = (int32_t)__popcll(m);
+    __syncthreads();
+    if (k) {
+        int64_t o = tiles[blockIdx.x] + __popcll(m & (lane ? ~0ull >> (64 - lane) : 0ull));
+        for (int w = 0; w < wave; ++w) o += wcnt[w];
+        okey[o] = bkey[t];
+        src[o] = (int32_t)t;
+    }
+    if (t == 0) {
+        const int64_t gone = n - *total;
+        *count = *total;
+        *removed2 = gone > 0 ? excl[gone - 1] + sorted[gone - 1] : 0.0;
+    }
+}
 
 qt_matrix* truncate(qt_matrix* M, double eps, hipStream_t s, int64_t* removed, double* removed_norm2) {
     if (!(eps >= 0.0)) fail(QT_ERR_ARG, "eps must be a non-negative number");
@@ -1317,34 +1434,35 @@ qt_matrix* truncate(qt_matrix* M, double eps, hipStream_t s, int64_t* removed, d
     if (removed) *removed = 0;
     if (removed_norm2) *removed_norm2 = 0.0;
     if (n == 0) return build(M->n_rows, M->n_cols, M->b, M->leaf, 0, nullptr, nullptr, nullptr, QT_MEM_DEVICE, s);
+    std::unique_ptr<qt_matrix> T(shaped_like(M, M->L, s));
+    const int64_t tiles = (n + KEEP_TILE - 1) / KEEP_TILE;
     DBuf<double> norm2(n, s), sorted(n, s), excl(n + 1, s), dtmp(scan_tmp_elems(n) + 1, s);
-    DBuf<int32_t> idx(n, s), keep(n, s), pos(n + 1, s), itmp(scan_tmp_elems(n) + 1, s), stmp(sort_tmp_words(n, 64), s);
-    k_block_norm2<<<block_grid(n), 256, 0, s>>>(v, n, bb, norm2.p);
-    QT_LAUNCH("k_block_norm2");
+    DBuf<int32_t> idx(n, s), keep(n, s), tcnt(tiles + 1, s), stmp(sort_tmp_words(n, 64), s), src(n, s);
+    T->bkey.alloc(n, s);
+    TreeJob job;
+    tree_begin(job, T.get(), n, 0, s);
+    launch_block_norm2(M, norm2.p, s);
     stable_sort(NormKeys{norm2.p}, NormSink{sorted.p, idx.p}, n, 64, stmp.p, idx.p, s);
     exclusive_scan(sorted.p, excl.p, n, dtmp.p, s);
     k_trunc_flags<<<grid_for(n), 256, 0, s>>>(excl.p, sorted.p, n, eps * eps, idx.p, keep.p);
     QT_LAUNCH("k_trunc_flags");
-    exclusive_scan(keep.p, pos.p, n, itmp.p, s);
-    const int32_t nk = read_scalar(pos.p + n, s);
-    DBuf<uint64_t> K(nk, s);
-    DBuf<double> V((size_t)nk * bb, s);
-    if (nk > 0) {
-        k_compact_blocks<<<block_grid(n), 256, 0, s>>>(M->bkey.p, v, n, bb, keep.p, pos.p, K.p, V.p);
-        QT_LAUNCH("k_compact_blocks");
-    }
-    if (removed || removed_norm2) {
-        const int64_t k = n - nk;   // the k smallest blocks were removed
-        if (removed) *removed = k;
-        if (removed_norm2 && k > 0) {
-            double e = 0.0, last = 0.0;
-            QT_HIP(hipMemcpyAsync(&e, excl.p + (k - 1), sizeof(double), hipMemcpyDeviceToHost, s));
-            QT_HIP(hipMemcpyAsync(&last, sorted.p + (k - 1), sizeof(double), hipMemcpyDeviceToHost, s));
-            QT_HIP(hipStreamSynchronize(s));
-            *removed_norm2 = e + last;
-        }
-    }
-    return assemble_sorted(M, M->L, nk, std::move(K), std::move(V), s);
+    k_keep_tiles<<<(unsigned)tiles, KEEP_TILE, 0, s>>>(keep.p, n, tcnt.p);
+    QT_LAUNCH("k_keep_tiles");
+    k_radix_scan<<<1, 1024, 0, s>>>(tcnt.p, tcnt.p + tiles, 1, (int)tiles);
+    QT_LAUNCH("k_radix_scan");
+    k_keep_write<<<(unsigned)tiles, KEEP_TILE, 0, s>>>(keep.p, n, tcnt.p, tcnt.p + tiles, M->bkey.p, excl.p, sorted.p,
+                                                       T->bkey.p, src.p, job.count(), job.sum());
+    QT_LAUNCH("k_keep_write");
+    tree_fill(job, T->bkey.p, s);
+    double gone2 = 0.0;
+    tree_finish(job, s, &gone2);
+    const int64_t nk = T->nblocks;
+    if (removed) *removed = n - nk;
+    if (removed_norm2) *removed_norm2 = gone2;
+    T->v64.alloc((size_t)nk * bb, s);
+    if (nk > 0) copy_blocks(v, src.p, nk, bb, T->v64.p, s);
+    QT_HIP(hipStreamSynchronize(s));
+    return T.release();
 }
 
 void get_blocks(const qt_matrix* M, int64_t count, const int32_t* I, const int32_t* J, void* values,

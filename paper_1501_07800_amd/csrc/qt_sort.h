@@ -133,13 +133,19 @@ __global__ __launch_bounds__(RADIX_THREADS) void k_radix_scatter(Src src, Sink s
                                                                  int64_t tile, int shift, int digit,
                                                                  const int32_t* __restrict__ counts,
                                                                  const int32_t* __restrict__ totals) {
-    extern __shared__ int32_t radix_lds[];   // RADIX_WAVES x bins: each wave's next place per digit
-    __shared__ int32_t wsum[RADIX_WAVES];
+    extern __shared__ int32_t radix_lds[];   // RADIX_WAVES x bins: each wave's next place per digit; two rows of
+    __shared__ int32_t wsum[RADIX_WAVES];    // bins: the digits' totals and their entries in the tiles before
     const int bins = 1 << digit;
+    int32_t* tot = radix_lds + RADIX_WAVES * bins;
+    int32_t* prior = tot + bins;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t t0 = (int64_t)blockIdx.x * tile, quarter = tile / RADIX_WAVES;
     const int64_t w0 = min(n, t0 + wave * quarter), w1 = min(n, w0 + quarter);
     for (int d = threadIdx.x; d < RADIX_WAVES * bins; d += RADIX_THREADS) radix_lds[d] = 0;
+    for (int d = threadIdx.x; d < bins; d += RADIX_THREADS) {
+        tot[d] = totals[d];
+        prior[d] = counts[(int64_t)blockIdx.x * bins + d];
+    }
     __syncthreads();
     int32_t* mine = radix_lds + wave * bins;
     for (int64_t t = w0 + lane; t < w1; t += 64) {
@@ -152,7 +158,7 @@ __global__ __launch_bounds__(RADIX_THREADS) void k_radix_scatter(Src src, Sink s
     const int per = (bins + RADIX_THREADS - 1) / RADIX_THREADS;
     const int d0 = min(bins, (int)threadIdx.x * per), d1 = min(bins, d0 + per);
     int32_t sum = 0;
-    for (int d = d0; d < d1; ++d) sum += totals[d];
+    for (int d = d0; d < d1; ++d) sum += tot[d];
     int32_t x = sum;
 #pragma unroll
     for (int k = 1; k < 64; k <<= 1) {
@@ -164,14 +170,14 @@ __global__ __launch_bounds__(RADIX_THREADS) void k_radix_scatter(Src src, Sink s
     int32_t run = x - sum;
     for (int w = 0; w < wave; ++w) run += wsum[w];
     for (int d = d0; d < d1; ++d) {
-        int32_t at = run + counts[(int64_t)blockIdx.x * bins + d];
+        int32_t at = run + prior[d];
 #pragma unroll
         for (int w = 0; w < RADIX_WAVES; ++w) {
             const int32_t c = radix_lds[w * bins + d];
             radix_lds[w * bins + d] = at;
             at += c;
         }
-        run += totals[d];
+        run += tot[d];
     }
     __syncthreads();
     for (int64_t base = w0; base < w1; base += 64) {
@@ -227,7 +233,7 @@ void stable_sort(const Src& src, const Sink& sink, int64_t n, int key_bits, int3
         QT_LAUNCH("k_radix_count");
         k_radix_scan<<<(unsigned)((bins + 63) / 64), 1024, 0, s>>>(counts, totals, bins, (int)p.tiles);
         QT_LAUNCH("k_radix_scan");
-        k_radix_scatter<Src, Sink><<<(unsigned)p.tiles, RADIX_THREADS, RADIX_WAVES * bins * sizeof(int32_t), s>>>(
+        k_radix_scatter<Src, Sink><<<(unsigned)p.tiles, RADIX_THREADS, (RADIX_WAVES + 2) * bins * sizeof(int32_t), s>>>(
             src, sink, in, out, n, p.tile, shift, p.digit, counts, totals);
         QT_LAUNCH("k_radix_scatter");
         in = out;

@@ -36,14 +36,15 @@
 // C blocks there are before C's values are allocated. A level's per-node
 // arrays and its grids are sized by a bound on its C nodes: the smaller of its
 // pair count and the number of node positions C's shape has at that level.
-// A launch order of C's blocks may also be built: leaf-row strips with the
-// traversal, or, once the C block count is known, a grouping by inner index
-// (see "launch order" below).
+// Once the C block count is known, a launch order of C's blocks may also be
+// built: strips of block rows, or a grouping by inner index (see "launch
+// order" below).
 // The whole phase runs on a stream of the library, beside the caller's (see
 // side_stream below).
 #include "qt_internal.h"
 #include "qt_morton.h"
 #include "qt_readback.h"
+#include "qt_sort.h"
 
 #include <algorithm>
 #include <map>
@@ -993,58 +994,38 @@ __global__ void k_nil_compact(NilTree t) {
 
 // ------------------------------------------------ launch order of C's blocks
 //
-// The numeric kernels give each XCD runs of consecutive launch slots. With
-// the blocks taken leaf row by leaf row (leaves left to right, the blocks of
-// a leaf in Morton order), a run of about a thousand blocks is a strip a leaf
-// high across many leaf columns: the strip's A block rows stay in the XCD's
-// L2 while B streams past, instead of the square patch of C that a run in
-// Morton order covers. Measured on gfx950 this helps only the split kernel at
-// b = 64 when a C block has several block products (decay131072: 2.4%
-// faster); where C blocks average about one product a kernel is bound by
-// writing C, which Morton order keeps contiguous (random65536 fp64: 10%
-// slower in strips), and the other kernels gain nothing or lose (the b = 32
-// fp64 kernel gained 2.3% before its loads were issued ahead of the MFMAs,
-// and is 1% slower in strips since). So the order is built for the split
-// kernel at b = 64 and used when the products are at least twice the C
-// blocks. It comes from a table of leaf positions,
-// row-major: position p holds the C leaf there (or -1), and a scan over the
-// positions' block counts gives each leaf its first slot.
-__global__ void k_order_clear(int32_t* __restrict__ table, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) table[i] = -1;
-}
+// The numeric kernels give each XCD runs of consecutive launch slots. In
+// Morton order such a run is a square patch of C, whose operands, a patch of
+// A's rows and one of B's columns, are far more than an XCD's 4 MB of L2 holds
+// (a 64-block row of A at b = 64 in FP64 is 2 MB): 72% of the operand reads of
+// a 32768 decay product at b = 64 missed it, and those misses, 98 GB at about
+// 5 TB/s, bounded the kernel. Taken in strips instead, 2^s block rows high and
+// column by column, a run stays within rows whose blocks of A fit (STRIP_BYTES)
+// while B streams past, shared by the strip's rows. Measured at b = 64 with 58
+// blocks a row, Morton -> strips of 1, 2, 4, 8 rows: FP64 18.8 -> 17.2, 19.1,
+// 18.8, 20.2 ms, FP32 9.55 -> 8.77, 9.41, 9.48, 10.6, BF16X3 6.10 -> 5.09,
+// 5.20, 5.18, 6.12; A^T A of 20 k blocks in FP32 5.22 -> 4.90 ms. So a strip
+// holds about STRIP_BYTES of A, at most a leaf's height. At b = 32 the operands
+// of a run nearly fit as they are: FP64 2.5% faster, FP32 1.5%, but the order
+// costs 25 us of the next traversal, which shorter products (sysq of a 24576
+// matrix 0.594 -> 0.628 ms, a tau product 0.494 -> 0.524) do not win back; so
+// the rule is b = 64 and several products per C block.
+// Morton order lists the blocks of an aligned strip by column, so a stable
+// sort by row >> s of C's Morton-ordered keys gives the order, three launches
+// up to 2048 strips.
+constexpr int64_t STRIP_BYTES = 1 << 20;
+constexpr int STRIP_MAX_LOG = 3;
+constexpr int64_t STRIP_MIN_BLOCKS = 8192;   // fewer: under a millisecond of work
 
-__global__ void k_order_place(const uint64_t* __restrict__ lkey, const int32_t* __restrict__ ncount, int32_t ncap,
-                              int64_t rows, int64_t cols, int32_t* __restrict__ table) {
-    const int32_t c = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (c >= ncap || c >= *ncount) return;
-    const uint64_t k = lkey[c];
-    const int64_t r = morton_row(k), q = morton_col(k);
-    if (r < rows && q < cols) table[r * cols + q] = c;   // always true for a leaf of C
-}
-
-__global__ void k_order_counts(const int32_t* __restrict__ table, int64_t n, const uint64_t* __restrict__ lmo,
-                               int32_t* __restrict__ cnt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t c = table[i];
-    cnt[i] = c >= 0 ? __popcll(lmo[c]) : 0;
-}
-
-__global__ void k_order_fill(const int32_t* __restrict__ table, int64_t n, const int32_t* __restrict__ lbase,
-                             const int32_t* __restrict__ cnt, const int32_t* __restrict__ off, int32_t cap,
-                             int32_t* __restrict__ order) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t c = table[i];
-    if (c < 0) return;
-    const int32_t o = off[i], b0 = lbase[c], m = cnt[i];
-    for (int32_t j = 0; j < m; ++j)
-        if (o + j < cap) order[o + j] = b0 + j;
-}
-
-// leaf positions up to which the launch order is built (a 16 MiB table)
-constexpr int64_t ORDER_MAX_POSITIONS = int64_t(1) << 22;
+struct StripKeys {
+    const uint64_t* bkey;
+    int log;
+    __device__ uint64_t operator()(int32_t t) const { return morton_row(bkey[t]) >> log; }
+};
+struct OrderSink {
+    int32_t* order;
+    __device__ void operator()(int32_t at, int32_t t, uint64_t) const { order[at] = t; }
+};
 
 // Where C blocks average fewer than two block products (an unstructured
 // pattern such as random65536), neighbouring C blocks in Morton order share
@@ -1377,11 +1358,14 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
 
     // ---- plan the two allocations
     const int64_t cap = std::min<int64_t>(P, lb2 * ncap[L]);   // bound on C blocks
-    // leaf grid of C (row-major positions) for the launch order in leaf-row strips
-    const int64_t c_rows_all = op.ta ? A->n_cols : A->n_rows, c_cols_all = op.tb ? B->n_rows : B->n_cols;
-    const int64_t lrows = (c_rows_all + A->leaf - 1) / A->leaf, lcols = (c_cols_all + A->leaf - 1) / A->leaf;
-    const int64_t lpos = lrows * lcols;
-    const bool make_order = launch_order && prec == QT_BF16X3 && A->b == 64 && lpos <= ORDER_MAX_POSITIONS;
+    // the launch order in strips, of the block rows of C (see above)
+    const int64_t c_rows_blk = (op.ta ? A->n_cols : A->n_rows) / A->b;
+    const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);
+    int strip_log = 0;
+    while (strip_log < STRIP_MAX_LOG && (row_bytes << (strip_log + 1)) <= STRIP_BYTES) ++strip_log;
+    int strip_bits = 1;
+    while ((int64_t(1) << (strip_bits + strip_log)) < c_rows_blk) ++strip_bits;
+    const bool may_strip = launch_order && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
     // the order by inner index is built once C's block count is known, if
     // the products are then fewer than twice the C blocks (cap bounds those)
     const int64_t kdim = ((op.ta ? A->n_rows : A->n_cols) + A->b - 1) / A->b;
@@ -1445,20 +1429,14 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     const size_t o_prodA = tmp.take(P * sizeof(int32_t));
     const size_t o_prodB = tmp.take(P * sizeof(int32_t));
     const size_t o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
-    size_t o_otab = 0, o_ocnt = 0, o_ooff = 0, o_oscan = 0, o_order = 0;
-    if (make_order) {
-        o_otab = tmp.take(lpos * sizeof(int32_t));
-        o_ocnt = tmp.take(lpos * sizeof(int32_t));
-        o_ooff = tmp.take((lpos + 1) * sizeof(int32_t));
-        o_oscan = tmp.take((scan_tmp_elems(lpos) + 1) * sizeof(int32_t));
-    }
-    size_t o_kcnt = 0, o_knext = 0, o_kscan = 0;
+    size_t o_kcnt = 0, o_knext = 0, o_kscan = 0, o_strip = 0, o_order = 0;
     if (may_korder) {
         o_kcnt = tmp.take(kdim * kwg_cap * sizeof(int32_t));
         o_knext = tmp.take((kdim * kwg_cap + 1) * sizeof(int32_t));
         o_kscan = tmp.take((scan_tmp_elems(kdim * kwg_cap) + 1) * sizeof(int32_t));
     }
-    if (make_order || may_korder) o_order = tmp.take(cap * sizeof(int32_t));   // one order is used at most
+    if (may_strip) o_strip = tmp.take(sort_tmp_bound(cap, strip_bits) * sizeof(int32_t));
+    if (may_strip || may_korder) o_order = tmp.take(cap * sizeof(int32_t));   // one order is used at most
     const size_t o_count = tmp.take((3 * L + 4) * sizeof(int32_t));
 
     out.C.reset(new_result(A, B, L, prec, s, op));
@@ -1629,23 +1607,6 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, false);
     else
         QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, true);
-    int32_t* order = (make_order || may_korder) ? (int32_t*)at(W, o_order) : nullptr;
-    if (make_order) {
-        int32_t* otab = (int32_t*)at(W, o_otab);
-        int32_t* ocnt = (int32_t*)at(W, o_ocnt);
-        int32_t* ooff = (int32_t*)at(W, o_ooff);
-        const unsigned gp = (unsigned)((lpos + 63) / 64);
-        k_order_clear<<<gp, 64, 0, ss>>>(otab, lpos);
-        QT_LAUNCH("k_order_clear");
-        k_order_place<<<(unsigned)((ncap[L] + 63) / 64), 64, 0, ss>>>(ls.ckey, ls.ncount, ls.ncap, lrows, lcols,
-                                                                          otab);
-        QT_LAUNCH("k_order_place");
-        k_order_counts<<<gp, 64, 0, ss>>>(otab, lpos, ls.lmo, ocnt);
-        QT_LAUNCH("k_order_counts");
-        exclusive_scan(ocnt, ooff, lpos, (int32_t*)at(W, o_oscan), ss);
-        k_order_fill<<<gp, 64, 0, ss>>>(otab, lpos, ls.lbase, ocnt, ooff, ls.cap, order);
-        QT_LAUNCH("k_order_fill");
-    }
     {
         // NIL normalisation: C keeps only the nodes with a block below them
         NilTree nt{};
@@ -1701,7 +1662,8 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     const int32_t nnzC = hc[L + 1];
     if (nnzC < 0 || nnzC > cap || (nnzC == 0 && !bounds)) fail(QT_ERR_DEVICE, "symbolic phase: C block count out of range");
 
-    const bool leafrow = make_order && C->products >= 2 * (int64_t)nnzC;
+    int32_t* order = (may_strip || may_korder) ? (int32_t*)at(W, o_order) : nullptr;
+    const bool strips = may_strip && nnzC >= STRIP_MIN_BLOCKS && C->products >= 2 * (int64_t)nnzC;
     const bool korder = may_korder && nnzC > 0 && C->products < 2 * (int64_t)nnzC;
     if (korder) {
         int32_t* kcnt = (int32_t*)at(W, o_kcnt);
@@ -1717,6 +1679,13 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
                                                                     (int32_t)kdim, (int32_t)nwg, knext, order);
         QT_LAUNCH("k_korder_place");
         if (prof) QT_HIP(hipEventRecord(ev.e1, ss));   // the symbolic phase ends here then
+        QT_HIP(stream_after(s, ss));
+    }
+
+    if (strips) {
+        stable_sort(StripKeys{ls.cbkey, strip_log}, OrderSink{order}, nnzC, strip_bits, (int32_t*)at(W, o_strip),
+                    order, ss);
+        if (prof) QT_HIP(hipEventRecord(ev.e1, ss));
         QT_HIP(stream_after(s, ss));
     }
 
@@ -1746,7 +1715,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     na.prodA = ls.prodA;
     na.prodB = ls.prodB;
     na.seg = ls.cbseg;
-    na.order = (leafrow || korder) ? order : nullptr;
+    na.order = (strips || korder) ? order : nullptr;
     na.by_k = korder ? 1 : 0;
     na.nseg = nnzC;
     na.C = (prec == QT_F32) ? (void*)C->v32.p : (void*)C->v64.p;

@@ -54,6 +54,12 @@ inline size_t sort_tmp_words(int64_t n, int key_bits) {
     return (size_t)p.bins() * (p.tiles + 1) + (p.passes > 1 ? (size_t)n : 0);
 }
 
+// The same for any number of entries up to n (fewer can mean more tiles).
+inline size_t sort_tmp_bound(int64_t n, int key_bits) {
+    const RadixPlan p = radix_plan(n, key_bits);
+    return (size_t)p.bins() * (RADIX_TILES_MAX + 1) + (p.passes > 1 ? (size_t)n : 0);
+}
+
 template <class Src, class Sink>
 __global__ __launch_bounds__(256) void k_rank_sort(Src src, Sink sink, int n) {
     extern __shared__ uint64_t sort_keys[];

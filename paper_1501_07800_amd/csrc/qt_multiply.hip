@@ -1035,79 +1035,30 @@ struct OrderSink {
 // consecutive launch slots: the run an XCD receives reads block column k of
 // A and block row k of B, both small enough to stay in its L2, and the
 // blocks of each are fetched about once (random65536 fp64: 2.3 GB fetched
-// instead of 11.8 GB). A counting sort over k without global atomics: each
-// workgroup counts its KORDER_WG C blocks per k in LDS, an exclusive scan of
-// the counts taken k-major over (k, workgroup) gives each workgroup its first
-// slot for every k, and a second pass places the blocks. Inside one
-// workgroup and one k the slots are claimed by LDS atomics, so that order
-// varies from call to call; each C block is still computed by one wave with
-// its products in ascending k, so no result depends on it.
-constexpr int KORDER_THREADS = 64, KORDER_ITEMS = 32;   // single waves (see the scan)
-constexpr int64_t KORDER_WG = KORDER_THREADS * KORDER_ITEMS;   // C blocks per workgroup
-constexpr int64_t KORDER_MAX_K = 16384;                        // LDS table of 64 KiB
-constexpr int64_t KORDER_MAX_CELLS = int64_t(1) << 24;         // (k, workgroup) counts
+// instead of 11.8 GB). The order is a stable sort by k, three launches up to
+// 2048 inner blocks, six beyond. (A counting sort of its own, five launches
+// with tables of every k per workgroup, took a lone traversal of 437 k C blocks
+// 40 us more, one of 890 k with 8192 inner blocks 92 us.)
+// Small operands stay cached in any order, and then the sort only costs its
+// 35 us: lone calls, Morton and by k, with the operand bytes the products read:
+// FP32 b = 32, 0.42 GB 225 and 248 us, 0.82 GB 311 and 312, 4.0 GB 944 and 818;
+// FP64 b = 32, 0.35 GB 203 and 209, 0.84 GB 302 and 272, 8.0 GB 1663 and 1070;
+// FP64 b = 16, 0.41 GB 240 and 247, 2.0 GB 565 and 492.
+constexpr int64_t KORDER_MIN_BYTES = int64_t(700) << 20;
+constexpr int KORDER_MAX_BITS = 22;   // inner blocks: two sort passes
 
-__device__ __forceinline__ int32_t first_k(const uint64_t* __restrict__ akey, const int32_t* __restrict__ prodA,
-                                           const int32_t* __restrict__ seg, int64_t s, bool ta, int32_t kdim) {
-    // a product whose A block is read transposed (top bit set) has its inner
-    // index in the stored block's row
-    const int32_t pa = prodA[seg[s]];
-    const uint64_t key = akey[pa & PROD_INDEX];
-    const int64_t k = (pa < 0) ? (int64_t)morton_row(key) : (int64_t)morton_col(key);   // column of op(A)
-    (void)ta;
-    return (int32_t)(k < 0 ? 0 : (k >= kdim ? kdim - 1 : k));
-}
-
-// k of the workgroup's C blocks (-1 past the end), loaded before any use
-__device__ __forceinline__ void korder_keys(const uint64_t* __restrict__ akey, const int32_t* __restrict__ prodA,
-                                            const int32_t* __restrict__ seg, int32_t nseg, bool ta, int32_t kdim,
-                                            int32_t (&kk)[KORDER_ITEMS]) {
-    const int64_t base = (int64_t)blockIdx.x * KORDER_WG + threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < KORDER_ITEMS; ++j) {
-        const int64_t s = base + j * KORDER_THREADS;
-        kk[j] = s < nseg ? first_k(akey, prodA, seg, s, ta, kdim) : -1;
+struct FirstKeys {
+    const uint64_t* akey;      // keys of the blocks the products name
+    const int32_t* prodA;
+    const int32_t* seg;
+    __device__ uint64_t operator()(int32_t t) const {
+        // a product whose A block is read transposed (top bit set) has its
+        // inner index in the stored block's row
+        const int32_t pa = prodA[seg[t]];
+        const uint64_t key = akey[pa & PROD_INDEX];
+        return pa < 0 ? morton_row(key) : morton_col(key);   // column of op(A)
     }
-}
-
-// cnt[k * nwg + w]: C blocks of workgroup w whose first product has inner index k
-__global__ __launch_bounds__(KORDER_THREADS) void k_korder_counts(const uint64_t* __restrict__ akey,
-                                                                  const int32_t* __restrict__ prodA,
-                                                                  const int32_t* __restrict__ seg, int32_t nseg,
-                                                                  bool ta, int32_t kdim, int32_t nwg,
-                                                                  int32_t* __restrict__ cnt) {
-    extern __shared__ int32_t ktab[];
-    int32_t kk[KORDER_ITEMS];
-    korder_keys(akey, prodA, seg, nseg, ta, kdim, kk);
-    for (int32_t k = threadIdx.x; k < kdim; k += KORDER_THREADS) ktab[k] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < KORDER_ITEMS; ++j)
-        if (kk[j] >= 0) atomicAdd(&ktab[kk[j]], 1);
-    __syncthreads();
-    for (int32_t k = threadIdx.x; k < kdim; k += KORDER_THREADS) cnt[(int64_t)k * nwg + blockIdx.x] = ktab[k];
-}
-
-// off: the exclusive scan of cnt; order[slot] = C block
-__global__ __launch_bounds__(KORDER_THREADS) void k_korder_place(const uint64_t* __restrict__ akey,
-                                                                 const int32_t* __restrict__ prodA,
-                                                                 const int32_t* __restrict__ seg, int32_t nseg,
-                                                                 bool ta, int32_t kdim, int32_t nwg,
-                                                                 const int32_t* __restrict__ off,
-                                                                 int32_t* __restrict__ order) {
-    extern __shared__ int32_t ktab[];
-    int32_t kk[KORDER_ITEMS];
-    korder_keys(akey, prodA, seg, nseg, ta, kdim, kk);
-    for (int32_t k = threadIdx.x; k < kdim; k += KORDER_THREADS) ktab[k] = off[(int64_t)k * nwg + blockIdx.x];
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * KORDER_WG + threadIdx.x;
-#pragma unroll
-    for (int j = 0; j < KORDER_ITEMS; ++j)
-        if (kk[j] >= 0) {
-            const int32_t o = atomicAdd(&ktab[kk[j]], 1);
-            if (o >= 0 && o < nseg) order[o] = (int32_t)(base + j * KORDER_THREADS);
-        }
-}
+};
 
 // ----------------------------------------------------------- host side
 
@@ -1368,10 +1319,12 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     const bool may_strip = launch_order && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
     // the order by inner index is built once C's block count is known, if
     // the products are then fewer than twice the C blocks (cap bounds those)
-    const int64_t kdim = ((op.ta ? A->n_rows : A->n_cols) + A->b - 1) / A->b;
-    const int64_t kwg_cap = (cap + KORDER_WG - 1) / KORDER_WG;   // workgroups of the counting sort
+    const int64_t kdim = (op.ta ? A->n_rows : A->n_cols) / A->b;
+    int kbits = 1;
+    while ((int64_t(1) << kbits) < kdim) ++kbits;
+    const int64_t read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
     const bool may_korder =
-        launch_order && P < 2 * cap && kdim >= 1 && kdim <= KORDER_MAX_K && kdim * kwg_cap <= KORDER_MAX_CELLS;
+        launch_order && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
     ArenaPlan keep, tmp;   // keep: C's tree; tmp: scratch freed after the call
     std::vector<size_t> o_child(L), o_key(L + 1);
     for (int l = 0; l < L; ++l) o_child[l] = keep.take(4 * ncap[l] * sizeof(int32_t));
@@ -1429,14 +1382,11 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     const size_t o_prodA = tmp.take(P * sizeof(int32_t));
     const size_t o_prodB = tmp.take(P * sizeof(int32_t));
     const size_t o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
-    size_t o_kcnt = 0, o_knext = 0, o_kscan = 0, o_strip = 0, o_order = 0;
-    if (may_korder) {
-        o_kcnt = tmp.take(kdim * kwg_cap * sizeof(int32_t));
-        o_knext = tmp.take((kdim * kwg_cap + 1) * sizeof(int32_t));
-        o_kscan = tmp.take((scan_tmp_elems(kdim * kwg_cap) + 1) * sizeof(int32_t));
-    }
-    if (may_strip) o_strip = tmp.take(sort_tmp_bound(cap, strip_bits) * sizeof(int32_t));
-    if (may_strip || may_korder) o_order = tmp.take(cap * sizeof(int32_t));   // one order is used at most
+    size_t o_sort = 0, o_order = 0;
+    if (may_strip || may_korder)   // one order is built at most
+        o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
+                                   may_korder ? sort_tmp_bound(cap, kbits) : 0) * sizeof(int32_t));
+    if (may_strip || may_korder) o_order = tmp.take(cap * sizeof(int32_t));
     const size_t o_count = tmp.take((3 * L + 4) * sizeof(int32_t));
 
     out.C.reset(new_result(A, B, L, prec, s, op));
@@ -1665,27 +1615,13 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     int32_t* order = (may_strip || may_korder) ? (int32_t*)at(W, o_order) : nullptr;
     const bool strips = may_strip && nnzC >= STRIP_MIN_BLOCKS && C->products >= 2 * (int64_t)nnzC;
     const bool korder = may_korder && nnzC > 0 && C->products < 2 * (int64_t)nnzC;
-    if (korder) {
-        int32_t* kcnt = (int32_t*)at(W, o_kcnt);
-        int32_t* knext = (int32_t*)at(W, o_knext);
-        const uint64_t* akey = Av->bkey.p;   // keys of the blocks the products name
-        const int64_t nwg = (nnzC + KORDER_WG - 1) / KORDER_WG;   // <= kwg_cap, as nnzC <= cap
-        const size_t lds = (size_t)kdim * sizeof(int32_t);
-        k_korder_counts<<<(unsigned)nwg, KORDER_THREADS, lds, ss>>>(akey, ls.prodA, ls.cbseg, nnzC, op.ta,
-                                                                     (int32_t)kdim, (int32_t)nwg, kcnt);
-        QT_LAUNCH("k_korder_counts");
-        exclusive_scan(kcnt, knext, kdim * nwg, (int32_t*)at(W, o_kscan), ss);
-        k_korder_place<<<(unsigned)nwg, KORDER_THREADS, lds, ss>>>(akey, ls.prodA, ls.cbseg, nnzC, op.ta,
-                                                                    (int32_t)kdim, (int32_t)nwg, knext, order);
-        QT_LAUNCH("k_korder_place");
+    if (strips || korder) {
+        int32_t* sort_tmp = (int32_t*)at(W, o_sort);
+        if (strips)
+            stable_sort(StripKeys{ls.cbkey, strip_log}, OrderSink{order}, nnzC, strip_bits, sort_tmp, order, ss);
+        else
+            stable_sort(FirstKeys{Av->bkey.p, ls.prodA, ls.cbseg}, OrderSink{order}, nnzC, kbits, sort_tmp, order, ss);
         if (prof) QT_HIP(hipEventRecord(ev.e1, ss));   // the symbolic phase ends here then
-        QT_HIP(stream_after(s, ss));
-    }
-
-    if (strips) {
-        stable_sort(StripKeys{ls.cbkey, strip_log}, OrderSink{order}, nnzC, strip_bits, (int32_t*)at(W, o_strip),
-                    order, ss);
-        if (prof) QT_HIP(hipEventRecord(ev.e1, ss));
         QT_HIP(stream_after(s, ss));
     }
 

@@ -1060,6 +1060,265 @@ struct FirstKeys {
     }
 };
 
+// ------------------------------------------------- small products: one launch
+//
+// A product with few node pairs spends its symbolic phase on launches and on
+// chains of dependent loads, not on work: banded1024 (1 + 8 + 26 pairs) took
+// eleven launches and 37 us. Where every level fits, one workgroup runs the
+// whole phase in one launch: the frontier, C's tree before NIL normalisation
+// and every count stay in LDS, a barrier takes the place of a launch, and the
+// counts go to the host's slot from the same kernel. It lists the same
+// products in the same order and forms the same tree. What bounds it is its
+// own chain, a few us per level, on one compute unit, so the line lies where
+// the level by level launches with all of the GPU come out ahead. The phase
+// alone, levels and small, in us (b = 32; pairs of the widest level, products):
+// banded1024 (26, 1428) 54 and 25, decay 512 (8, 2228) 50 and 22, decay 1536
+// (216, 19048) 56 and 50, decay 2048 (396, 28610) 55 and 73, random 2048 (480,
+// 622) 54 and 44, random 3072 (1680, 2200) 56 and 99. Loops of banded1024 with
+// the numeric kernel 77 and 51 us a product.
+constexpr int SMALL_LEVELS = 8;
+constexpr int SMALL_PAIRS = 512;            // node pairs of one level
+constexpr int SMALL_NODES = 256;            // C nodes of all levels together
+constexpr int64_t SMALL_PRODUCTS = 20000;
+constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
+
+struct SmallStep {
+    int L;
+    const int32_t* Ach[SMALL_LEVELS];          // child tables, levels 0 .. L-1
+    const int32_t* Bch[SMALL_LEVELS];
+    const double* An2[SMALL_LEVELS + 1];       // squared norms of the nodes (norm threshold)
+    const double* Bn2[SMALL_LEVELS + 1];
+    LeafStep leaf;                             // operands' leaves, product lists, C blocks
+    int32_t* child[SMALL_LEVELS];              // C's tree
+    uint64_t* key[SMALL_LEVELS + 1];
+    int32_t* base;
+    uint64_t* mo;
+    uint64_t* rm;
+    uint64_t* cm;
+    HostSlot* slot;
+    uint32_t seq;
+};
+
+template <bool PRUNE, bool PLAIN>
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_symbolic(SmallStep a) {
+    __shared__ int32_t fa[2][SMALL_PAIRS], fb[2][SMALL_PAIRS];   // the frontier, this level's and the next
+    __shared__ int32_t cseg[2][SMALL_NODES + 1];
+    __shared__ uint64_t ukey[SMALL_NODES];                       // all levels' nodes, concatenated
+    __shared__ int32_t uchild[4 * SMALL_NODES];                  // index within the next level, or -1
+    __shared__ int4 tot[SMALL_NODES];                            // this level: child pairs per quadrant
+    __shared__ int32_t cnt_lo[SMALL_NODES], cnt_hi[SMALL_NODES]; // this level: (pairs, nodes) or (products,
+                                                                 // blocks) per node, then their scan
+    __shared__ uint64_t lmo[SMALL_NODES];
+    __shared__ int32_t lbase[SMALL_NODES], kept[SMALL_NODES], rank[SMALL_NODES];
+    __shared__ int32_t total_lo, total_hi;
+    __shared__ int32_t counts[3 * SMALL_LEVELS + 4], first[SMALL_LEVELS + 2];
+    const LeafStep& lf = a.leaf;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, L = a.L;
+    const uint64_t below = lanes_below(lane);
+    if (tid == 0) {
+        fa[0][0] = 0;
+        fb[0][0] = 0;
+        cseg[0][0] = 0;
+        cseg[0][1] = 1;
+        ukey[0] = 0;
+        counts[0] = 1;
+        first[0] = 0;
+        first[1] = 1;
+    }
+    __syncthreads();
+    // exclusive scans of cnt_lo and cnt_hi [0 .. n), by two waves
+    auto scan = [&](int n) {
+        __syncthreads();
+        if (wave < 2) {
+            int32_t* cnt = wave ? cnt_hi : cnt_lo;
+            int run = 0;
+            for (int b = 0; b < n; b += 64) {
+                const int v = b + lane < n ? cnt[b + lane] : 0;
+                const int x = wave_incl_scan(v);
+                if (b + lane < n) cnt[b + lane] = run + x - v;
+                run += __builtin_amdgcn_readlane(x, 63);
+            }
+            if (lane == 0) (wave ? total_hi : total_lo) = run;
+        }
+        __syncthreads();
+    };
+    int nodes = 1;
+    for (int l = 0; l < L; ++l) {
+        const int cur = l & 1, at = first[l];
+        const double* an2 = a.An2[l + 1];
+        const double* bn2 = a.Bn2[l + 1];
+        int4 hx = make_int4(-1, -1, -1, -1), hy = hx;   // a wave's child tables, kept from pass 0 where it
+                                                        // has one node of at most 64 pairs
+        // pass 0 counts the child pairs of every node, pass 1 writes them
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+            for (int c = wave; c < nodes; c += SMALL_WAVES) {
+                const int s0 = cseg[cur][c], len = cseg[cur][c + 1] - s0;
+                const uint64_t key = ukey[at + c];
+                const bool drop_lower = quadrant_dropped(lf.upper, key, 2);
+                int run[4] = {0, 0, 0, 0};
+                if (pass == 1) {
+                    const int4 t4 = tot[c];
+                    const int t[4] = {t4.x, t4.y, t4.z, t4.w};
+                    int pr = cnt_lo[c], ci = cnt_hi[c], mine = -1, my_run = 0;
+#pragma unroll
+                    for (int mn = 0; mn < 4; ++mn) {
+                        run[mn] = pr;
+                        if (lane == mn && t[mn] > 0) {
+                            mine = ci;
+                            my_run = pr;
+                        }
+                        pr += t[mn];
+                        ci += t[mn] > 0;
+                    }
+                    if (lane < 4) {
+                        uchild[4 * (at + c) + lane] = mine;
+                        if (mine >= 0 && at + nodes + mine < SMALL_NODES) {
+                            ukey[at + nodes + mine] = key * 4 + (uint64_t)lane;
+                            cseg[1 - cur][mine] = my_run;
+                        }
+                    }
+                }
+#pragma unroll 1
+                for (int b = 0; b < len; b += 64) {
+                    if (pass == 0 || nodes > SMALL_WAVES || len > 64) {
+                        hx = hy = make_int4(-1, -1, -1, -1);
+                        if (b + lane < len)
+                            op_children2(a.Ach[l], fa[cur][s0 + b + lane], lf.ta, a.Bch[l], fb[cur][s0 + b + lane],
+                                         lf.tb, hx, hy);
+                    }
+                    const int av[4] = {hx.x, hx.y, hx.z, hx.w}, bv[4] = {hy.x, hy.y, hy.z, hy.w};
+#pragma unroll
+                    for (int mn = 0; mn < 4; ++mn) {
+                        const int m = mn >> 1, n = mn & 1;
+                        const bool keep = !(mn == 2 && drop_lower);
+                        const bool e0 = keep && pair_kept<PRUNE>(an2, bn2, lf.tau2, av[2 * m], bv[n]);
+                        const bool e1 = keep && pair_kept<PRUNE>(an2, bn2, lf.tau2, av[2 * m + 1], bv[2 + n]);
+                        const uint64_t m0 = __ballot(e0), m1 = __ballot(e1);
+                        int w = run[mn] + __popcll(m0 & below) + __popcll(m1 & below);
+                        run[mn] += __popcll(m0) + __popcll(m1);
+                        if (pass == 0) continue;
+                        if (e0 && w < SMALL_PAIRS) {
+                            fa[1 - cur][w] = av[2 * m];
+                            fb[1 - cur][w] = bv[n];
+                        }
+                        w += e0;
+                        if (e1 && w < SMALL_PAIRS) {
+                            fa[1 - cur][w] = av[2 * m + 1];
+                            fb[1 - cur][w] = bv[2 + n];
+                        }
+                    }
+                }
+                if (pass == 0 && lane == 0) {
+                    tot[c] = make_int4(run[0], run[1], run[2], run[3]);
+                    cnt_lo[c] = run[0] + run[1] + run[2] + run[3];
+                    cnt_hi[c] = (run[0] > 0) + (run[1] > 0) + (run[2] > 0) + (run[3] > 0);
+                }
+            }
+            if (pass == 0) scan(nodes);
+        }
+        // (the host's bounds make everything fit; the limits keep every access inside)
+        const int fits = min(total_hi, SMALL_NODES - (at + nodes));
+        if (tid == 0) {
+            counts[l + 1] = total_hi;
+            counts[L + 2 + l] = total_lo;
+            first[l + 2] = at + nodes + fits;
+            cseg[1 - cur][fits] = min(total_lo, SMALL_PAIRS);
+        }
+        nodes = fits;
+        __syncthreads();
+    }
+    // leaf step over the frontier's leaf pairs
+    LeafStep st = lf;
+    st.fa = fa[L & 1];
+    st.fb = fb[L & 1];
+    const int at = first[L], lb = 1 << lf.lb_log;
+    const int i = (int)morton_row((uint64_t)lane), j = (int)morton_col((uint64_t)lane);
+    int n = 0;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+        for (int c = wave; c < nodes; c += SMALL_WAVES) {
+            const int s0 = cseg[L & 1][c], len = cseg[L & 1][c + 1] - s0;
+            const uint64_t key = ukey[at + c];
+            const bool on = lane < lb * lb && leaf_block_kept(st, key, i, j);
+            if (pass == 0 || nodes > SMALL_WAVES)
+                n = PRUNE ? leaf_lane_count_norms(st, s0, len, lane, i, j, lb, on)
+                          : leaf_lane_count(st, s0, len, lane, i, j, lb, on);
+            const uint64_t em = __ballot(n > 0);
+            const int incl = wave_incl_scan(n);
+            if (pass == 0) {
+                if (lane == 63) cnt_lo[c] = incl;
+                if (lane == 0) cnt_hi[c] = __popcll(em);
+                continue;
+            }
+            const int32_t bidx = cnt_hi[c] + __popcll(em & below), out = cnt_lo[c] + incl - n;
+            if (n > 0 && bidx < lf.cap) {
+                lf.cbkey[bidx] = (key << (2 * lf.lb_log)) | (uint64_t)lane;
+                lf.cbseg[bidx] = out;
+            }
+            leaf_fill_products<PLAIN>(st, s0, len, lane, i, j, lb, on, out);
+            if (lane == 0) {
+                lbase[c] = cnt_hi[c];
+                lmo[c] = em;
+                kept[at + c] = em != 0;
+            }
+        }
+        if (pass == 0) scan(nodes);
+    }
+    if (tid == 0) {
+        counts[L + 1] = total_hi;
+        counts[2 * L + 2] = total_lo;
+        if (total_hi <= lf.cap) lf.cbseg[total_hi] = total_lo;
+    }
+    // NIL normalisation: a node is kept when one of its children is
+    for (int l = L - 1; l >= 0; --l) {
+        __syncthreads();
+        for (int c = first[l] + tid; c < first[l + 1]; c += SMALL_THREADS) {
+            int k = 0;
+            for (int q = 0; q < 4; ++q) k |= uchild[4 * c + q] >= 0 && kept[first[l + 1] + uchild[4 * c + q]];
+            kept[c] = k;
+        }
+    }
+    __syncthreads();
+    for (int l = wave; l <= L; l += SMALL_WAVES) {   // ranks among a level's kept nodes
+        int run = 0;
+        for (int b = first[l]; b < first[l + 1]; b += 64) {
+            const bool k = b + lane < first[l + 1] && kept[b + lane];
+            const uint64_t m = __ballot(k);
+            if (k) rank[b + lane] = run + __popcll(m & below);
+            run += __popcll(m);
+        }
+        if (lane == 0) counts[2 * L + 3 + l] = run;
+    }
+    __syncthreads();
+    int l = 0;
+    for (int c = tid; c < first[L + 1]; c += SMALL_THREADS) {
+        while (c >= first[l + 1]) ++l;
+        if (!kept[c]) continue;
+        const int to = rank[c];
+        a.key[l][to] = ukey[c];
+        if (l < L) {
+            int out[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int u = uchild[4 * c + q];
+                out[q] = u >= 0 && kept[first[l + 1] + u] ? rank[first[l + 1] + u] : -1;
+            }
+            *reinterpret_cast<int4*>(a.child[l] + 4 * (int64_t)to) = make_int4(out[0], out[1], out[2], out[3]);
+        } else {
+            const int f = c - first[L];
+            const uint64_t rm = morton_to_rowmajor(lmo[f], lf.lb_log);
+            a.base[to] = lbase[f];
+            a.mo[to] = lmo[f];
+            a.rm[to] = rm;
+            a.cm[to] = rowmajor_to_colmajor(rm, lf.lb_log);
+        }
+    }
+    publish_words(counts, 3 * L + 4, a.slot, a.seq);
+}
+
 // ----------------------------------------------------------- host side
 
 // Events that order one stream after another (record on one, wait on the
@@ -1309,6 +1568,14 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
 
     // ---- plan the two allocations
     const int64_t cap = std::min<int64_t>(P, lb2 * ncap[L]);   // bound on C blocks
+    // one launch for the whole phase when every level fits one workgroup
+    bool small = L <= SMALL_LEVELS && P <= SMALL_PRODUCTS;
+    int64_t all_nodes = 0;
+    for (int l = 0; l <= L; ++l) {
+        small = small && pairs[l] <= SMALL_PAIRS;
+        all_nodes += ncap[l];
+    }
+    small = small && all_nodes <= SMALL_NODES;
     // the launch order in strips, of the block rows of C (see above)
     const int64_t c_rows_blk = (op.ta ? A->n_cols : A->n_rows) / A->b;
     const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);
@@ -1316,7 +1583,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     while (strip_log < STRIP_MAX_LOG && (row_bytes << (strip_log + 1)) <= STRIP_BYTES) ++strip_log;
     int strip_bits = 1;
     while ((int64_t(1) << (strip_bits + strip_log)) < c_rows_blk) ++strip_bits;
-    const bool may_strip = launch_order && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
+    const bool may_strip = launch_order && !small && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
     // the order by inner index is built once C's block count is known, if
     // the products are then fewer than twice the C blocks (cap bounds those)
     const int64_t kdim = (op.ta ? A->n_rows : A->n_cols) / A->b;
@@ -1324,7 +1591,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     while ((int64_t(1) << kbits) < kdim) ++kbits;
     const int64_t read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
     const bool may_korder =
-        launch_order && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
+        launch_order && !small && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
     ArenaPlan keep, tmp;   // keep: C's tree; tmp: scratch freed after the call
     std::vector<size_t> o_child(L), o_key(L + 1);
     for (int l = 0; l < L; ++l) o_child[l] = keep.take(4 * ncap[l] * sizeof(int32_t));
@@ -1334,7 +1601,13 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     const size_t o_lrm = keep.take(ncap[L] * sizeof(uint64_t));
     const size_t o_lcm = keep.take(ncap[L] * sizeof(uint64_t));
     const size_t o_bkey = keep.take(cap * sizeof(uint64_t));
-    // the tree as the traversal forms it, before NIL normalisation (scratch)
+    if (L + 1 > NIL_MAX_LEVELS) fail(QT_ERR_UNSUPPORTED, "quadtree too deep");
+    const size_t o_prodA = tmp.take(P * sizeof(int32_t));
+    const size_t o_prodB = tmp.take(P * sizeof(int32_t));
+    const size_t o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
+    // The scratch of the level by level traversal from here on (a small
+    // product's stays in LDS): first the tree before NIL normalisation.
+    const size_t small_bytes = tmp.bytes;
     std::vector<size_t> u_child(L), u_key(L + 1), u_parent(L + 1);
     for (int l = 0; l < L; ++l) u_child[l] = tmp.take(4 * ncap[l] * sizeof(int32_t));
     for (int l = 0; l <= L; ++l) u_key[l] = tmp.take(ncap[l] * sizeof(uint64_t));
@@ -1343,7 +1616,6 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     const size_t u_lmo = tmp.take(ncap[L] * sizeof(uint64_t));
     const size_t u_lrm = tmp.take(ncap[L] * sizeof(uint64_t));
     const size_t u_lcm = tmp.take(ncap[L] * sizeof(uint64_t));
-    if (L + 1 > NIL_MAX_LEVELS) fail(QT_ERR_UNSUPPORTED, "quadtree too deep");
     std::vector<int64_t> foff(L + 2, 0);
     for (int l = 0; l <= L; ++l) foff[l + 1] = foff[l] + ncap[l];
     if (foff[L + 1] > kMaxI32) fail(QT_ERR_UNSUPPORTED, "too many C nodes");
@@ -1379,9 +1651,6 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     }
     const size_t o_scan = tmp.take((scan_elems + 1) * sizeof(int64_t));
     const size_t o_lcnt = tmp.take(ncap[L] * 64 * sizeof(int32_t));   // leaf step: products per block position
-    const size_t o_prodA = tmp.take(P * sizeof(int32_t));
-    const size_t o_prodB = tmp.take(P * sizeof(int32_t));
-    const size_t o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
     size_t o_sort = 0, o_order = 0;
     if (may_strip || may_korder)   // one order is built at most
         o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
@@ -1397,7 +1666,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // after the numeric kernel that reads them
     C->arena.alloc(keep.bytes, ss);
     C->arena.s = s;
-    out.scratch.alloc(tmp.bytes, ss);
+    out.scratch.alloc(small ? small_bytes : tmp.bytes, ss);
     out.scratch.s = s;
     char* K = C->arena.p;
     char* W = out.scratch.p;
@@ -1455,56 +1724,8 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         }
         return st;
     };
-    RootInit root{(int32_t*)at(W, o_fa[0]), (int32_t*)at(W, o_fb[0]), (int32_t*)at(W, o_cseg[0]),
-                  (uint64_t*)at(W, u_key[0]), dcount, nflags, nclear};
-
-    k_root_init<<<(unsigned)((nclear + 63) / 64), 64, 0, ss>>>(root);
-    QT_LAUNCH("k_root_init");
-    int64_t* scan_tmp = (int64_t*)at(W, o_scan);
-    bool counted = false;   // this level's counts were made by the previous level's fill
-    for (int l = 0; l < L; ++l) {
-        TreeStep sl = tree_step(l);
-        const int64_t wgs = level_wgs(ncap[l]);
-        sl.use_agg = wgs <= AGG_MAX;
-        if (!counted) {
-            if (prune)
-                QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, true);
-            else
-                QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, false);
-            if (!sl.use_agg) exclusive_scan(sl.cnt, sl.off, ncap[l], scan_tmp, ss);
-        }
-        // a single-wave next tree level gets its counts from this fill
-        counted = l + 1 < L && level_waves(ncap[l + 1]) == 1;
-        if (counted) {
-            const TreeStep nx = tree_step(l + 1);
-            sl.nAch = nx.Ach;
-            sl.nBch = nx.Bch;
-            sl.nAn2 = nx.An2;
-            sl.nBn2 = nx.Bn2;
-            sl.ncnt = nx.cnt;
-            sl.ntot4 = nx.tot4;
-            sl.noff = nx.off;
-            sl.nwagg = nx.wagg;
-            sl.ngsum = nx.gsum;
-        }
-        if (prune && counted)
-            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, true);
-        else if (prune)
-            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, false);
-        else if (counted)
-            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, true);
-        else
-            QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, false);
-    }
-
-    // leaf step
+    // the leaf step's operands and outputs
     LeafStep ls{};
-    ls.fa = (const int32_t*)at(W, o_fa[L]);
-    ls.fb = (const int32_t*)at(W, o_fb[L]);
-    ls.cseg = (const int32_t*)at(W, o_cseg[L]);
-    ls.ckey = (const uint64_t*)at(W, u_key[L]);
-    ls.ncount = dcount + L;
-    ls.ncap = (int32_t)ncap[L];
     ls.lb_log = lb_log;
     // rows of op(A) are columns of A when transposed; columns of op(B) rows of B
     ls.Arm = op.ta ? A->leaves.mask_cm.p : A->leaves.mask_rm.p;
@@ -1523,82 +1744,163 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     ls.Bmo = B->leaves.mask_mo.p;
     ls.Abase = A->leaves.base.p;
     ls.Bbase = B->leaves.base.p;
-    ls.cnt = (int64_t*)at(W, o_cnt[L]);
-    ls.lane_cnt = (int32_t*)at(W, o_lcnt);
-    ls.off = (int64_t*)at(W, o_off[L]);
-    ls.wagg = (int64_t*)at(W, o_wagg[L]);
-    ls.gsum = (int64_t*)at(W, o_gsum) + gsum_at[L];
-    const int64_t leaf_wgs = level_wgs(ncap[L]);
-    ls.use_agg = leaf_wgs <= AGG_MAX;
     ls.prodA = (int32_t*)at(W, o_prodA);
     ls.prodB = (int32_t*)at(W, o_prodB);
     ls.P = (int32_t)P;
     ls.cbkey = (uint64_t*)at(K, o_bkey);
     ls.cbseg = (int32_t*)at(W, o_cbseg);
     ls.cap = (int32_t)cap;
-    ls.lbase = (int32_t*)at(W, u_lbase);
-    ls.lmo = (uint64_t*)at(W, u_lmo);
-    ls.lrm = (uint64_t*)at(W, u_lrm);
-    ls.lcm = (uint64_t*)at(W, u_lcm);
-    ls.nblocks_out = dcount + L + 1;
-    ls.check = dcount + 2 * L + 2;
-    ls.nil.L = L;
-    for (int l = 0; l <= L + 1; ++l) ls.nil.foff[l] = foff[l];
-    for (int l = 1; l <= L; ++l) ls.nil.uparent[l] = (const int32_t*)at(W, u_parent[l]);
-    ls.nil.flags = nflags;
-    ls.nil.tcnt = (int32_t*)at(W, o_ntcnt);
-    ls.nil.tiles = nil_tiles;
-    if (prune)
-        QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, true);
-    else
-        QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, false);
-    if (!ls.use_agg) exclusive_scan(ls.cnt, ls.off, ncap[L], scan_tmp, ss);
-    if (prune || ls.amap || ls.bmap)
-        QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, false);
-    else
-        QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, true);
-    {
-        // NIL normalisation: C keeps only the nodes with a block below them
-        NilTree nt{};
-        nt.L = L;
-        for (int l = 0; l <= L + 1; ++l) nt.foff[l] = foff[l];
-        for (int l = 0; l < L; ++l) {
-            nt.uchild[l] = (const int32_t*)at(W, u_child[l]);
-            nt.child[l] = (int32_t*)at(K, o_child[l]);
-        }
-        for (int l = 0; l <= L; ++l) {
-            nt.ukey[l] = (const uint64_t*)at(W, u_key[l]);
-            nt.key[l] = (uint64_t*)at(K, o_key[l]);
-        }
-        nt.ubase = ls.lbase;
-        nt.umo = ls.lmo;
-        nt.urm = ls.lrm;
-        nt.ucm = ls.lcm;
-        nt.flags = nflags;
-        nt.ex = (const int32_t*)at(W, o_nex);
-        nt.base = (int32_t*)at(K, o_lbase);
-        nt.mo = (uint64_t*)at(K, o_lmo);
-        nt.rm = (uint64_t*)at(K, o_lrm);
-        nt.cm = (uint64_t*)at(K, o_lcm);
-        nt.kept = dcount + 2 * L + 3;
-        k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nflags, ls.nil.tcnt, (int32_t*)at(W, o_nex));
-        QT_LAUNCH("k_nil_offsets");
-        k_nil_compact<<<(unsigned)((foff[L + 1] + 63) / 64), 64, 0, ss>>>(nt);
-        QT_LAUNCH("k_nil_compact");
-    }
-    if (prof) QT_HIP(hipEventRecord(ev.e1, ss));
-
-    // the one synchronization: node and block counts of C
     const int nhc = 3 * L + 4;
     if (nhc > kSlotWords) fail(QT_ERR_UNSUPPORTED, "tree too deep for the count read-back");
     ReadBack counts(nhc);
-    counts.publish(dcount, ss);
+    if (small) {
+        SmallStep sm{};
+        sm.L = L;
+        for (int l = 0; l < L; ++l) {
+            sm.Ach[l] = (l < liftA) ? lift : A->levels[l - liftA].child.p;
+            sm.Bch[l] = (l < liftB) ? lift : B->levels[l - liftB].child.p;
+            sm.child[l] = (int32_t*)at(K, o_child[l]);
+        }
+        for (int l = 0; l <= L; ++l) {
+            if (prune) {
+                sm.An2[l] = A->nn2[std::max(l - liftA, 0)];
+                sm.Bn2[l] = B->nn2[std::max(l - liftB, 0)];
+            }
+            sm.key[l] = (uint64_t*)at(K, o_key[l]);
+        }
+        sm.leaf = ls;
+        sm.base = (int32_t*)at(K, o_lbase);
+        sm.mo = (uint64_t*)at(K, o_lmo);
+        sm.rm = (uint64_t*)at(K, o_lrm);
+        sm.cm = (uint64_t*)at(K, o_lcm);
+        sm.slot = counts.device_slot();
+        sm.seq = counts.seq();
+        if (prune)
+            k_small_symbolic<true, false><<<1, SMALL_THREADS, 0, ss>>>(sm);
+        else if (ls.amap || ls.bmap)
+            k_small_symbolic<false, false><<<1, SMALL_THREADS, 0, ss>>>(sm);
+        else
+            k_small_symbolic<false, true><<<1, SMALL_THREADS, 0, ss>>>(sm);
+        QT_LAUNCH("k_small_symbolic");
+    } else {
+        RootInit root{(int32_t*)at(W, o_fa[0]), (int32_t*)at(W, o_fb[0]), (int32_t*)at(W, o_cseg[0]),
+                      (uint64_t*)at(W, u_key[0]), dcount, nflags, nclear};
+
+        k_root_init<<<(unsigned)((nclear + 63) / 64), 64, 0, ss>>>(root);
+        QT_LAUNCH("k_root_init");
+        int64_t* scan_tmp = (int64_t*)at(W, o_scan);
+        bool counted = false;   // this level's counts were made by the previous level's fill
+        for (int l = 0; l < L; ++l) {
+            TreeStep sl = tree_step(l);
+            const int64_t wgs = level_wgs(ncap[l]);
+            sl.use_agg = wgs <= AGG_MAX;
+            if (!counted) {
+                if (prune)
+                    QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, true);
+                else
+                    QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, false);
+                if (!sl.use_agg) exclusive_scan(sl.cnt, sl.off, ncap[l], scan_tmp, ss);
+            }
+            // a single-wave next tree level gets its counts from this fill
+            counted = l + 1 < L && level_waves(ncap[l + 1]) == 1;
+            if (counted) {
+                const TreeStep nx = tree_step(l + 1);
+                sl.nAch = nx.Ach;
+                sl.nBch = nx.Bch;
+                sl.nAn2 = nx.An2;
+                sl.nBn2 = nx.Bn2;
+                sl.ncnt = nx.cnt;
+                sl.ntot4 = nx.tot4;
+                sl.noff = nx.off;
+                sl.nwagg = nx.wagg;
+                sl.ngsum = nx.gsum;
+            }
+            if (prune && counted)
+                QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, true);
+            else if (prune)
+                QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, false);
+            else if (counted)
+                QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, true);
+            else
+                QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, false);
+        }
+
+        // leaf step
+        ls.fa = (const int32_t*)at(W, o_fa[L]);
+        ls.fb = (const int32_t*)at(W, o_fb[L]);
+        ls.cseg = (const int32_t*)at(W, o_cseg[L]);
+        ls.ckey = (const uint64_t*)at(W, u_key[L]);
+        ls.ncount = dcount + L;
+        ls.ncap = (int32_t)ncap[L];
+        ls.cnt = (int64_t*)at(W, o_cnt[L]);
+        ls.lane_cnt = (int32_t*)at(W, o_lcnt);
+        ls.off = (int64_t*)at(W, o_off[L]);
+        ls.wagg = (int64_t*)at(W, o_wagg[L]);
+        ls.gsum = (int64_t*)at(W, o_gsum) + gsum_at[L];
+        const int64_t leaf_wgs = level_wgs(ncap[L]);
+        ls.use_agg = leaf_wgs <= AGG_MAX;
+        ls.lbase = (int32_t*)at(W, u_lbase);
+        ls.lmo = (uint64_t*)at(W, u_lmo);
+        ls.lrm = (uint64_t*)at(W, u_lrm);
+        ls.lcm = (uint64_t*)at(W, u_lcm);
+        ls.nblocks_out = dcount + L + 1;
+        ls.check = dcount + 2 * L + 2;
+        ls.nil.L = L;
+        for (int l = 0; l <= L + 1; ++l) ls.nil.foff[l] = foff[l];
+        for (int l = 1; l <= L; ++l) ls.nil.uparent[l] = (const int32_t*)at(W, u_parent[l]);
+        ls.nil.flags = nflags;
+        ls.nil.tcnt = (int32_t*)at(W, o_ntcnt);
+        ls.nil.tiles = nil_tiles;
+        if (prune)
+            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, true);
+        else
+            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, false);
+        if (!ls.use_agg) exclusive_scan(ls.cnt, ls.off, ncap[L], scan_tmp, ss);
+        if (prune || ls.amap || ls.bmap)
+            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, false);
+        else
+            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, true);
+        {
+            // NIL normalisation: C keeps only the nodes with a block below them
+            NilTree nt{};
+            nt.L = L;
+            for (int l = 0; l <= L + 1; ++l) nt.foff[l] = foff[l];
+            for (int l = 0; l < L; ++l) {
+                nt.uchild[l] = (const int32_t*)at(W, u_child[l]);
+                nt.child[l] = (int32_t*)at(K, o_child[l]);
+            }
+            for (int l = 0; l <= L; ++l) {
+                nt.ukey[l] = (const uint64_t*)at(W, u_key[l]);
+                nt.key[l] = (uint64_t*)at(K, o_key[l]);
+            }
+            nt.ubase = ls.lbase;
+            nt.umo = ls.lmo;
+            nt.urm = ls.lrm;
+            nt.ucm = ls.lcm;
+            nt.flags = nflags;
+            nt.ex = (const int32_t*)at(W, o_nex);
+            nt.base = (int32_t*)at(K, o_lbase);
+            nt.mo = (uint64_t*)at(K, o_lmo);
+            nt.rm = (uint64_t*)at(K, o_lrm);
+            nt.cm = (uint64_t*)at(K, o_lcm);
+            nt.kept = dcount + 2 * L + 3;
+            k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nflags, ls.nil.tcnt, (int32_t*)at(W, o_nex));
+            QT_LAUNCH("k_nil_offsets");
+            k_nil_compact<<<(unsigned)((foff[L + 1] + 63) / 64), 64, 0, ss>>>(nt);
+            QT_LAUNCH("k_nil_compact");
+        }
+        counts.publish(dcount, ss);
+    }
+    const hipError_t traced = prof ? hipEventRecord(ev.e1, ss) : hipSuccess;
+
+    // the one synchronization: node and block counts of C
     // the caller's stream follows the traversal from here on (the numeric
     // kernel first), ordered while the counts are on their way; a launch order
     // built below adds a second wait
     const hipError_t ordered = stream_after(s, ss);
     const int32_t* hc = counts.wait(ss);
     QT_HIP(ordered);
+    QT_HIP(traced);
     for (int l = 0; l <= L; ++l) {
         if (hc[l] < 0 || hc[l] > ncap[l]) fail(QT_ERR_DEVICE, "symbolic phase: C node count out of range");
         if (hc[2 * L + 3 + l] < 0 || hc[2 * L + 3 + l] > hc[l])

@@ -47,6 +47,7 @@
 #include "qt_sort.h"
 
 #include <algorithm>
+#include <deque>
 #include <map>
 #include <string>
 
@@ -506,8 +507,14 @@ __device__ __forceinline__ bool level_wg_empty(const int32_t* ncount) {
     return (int64_t)blockIdx.x * W >= *ncount;
 }
 
+// The last workgroup of a level of ncap >= 1 node slots.
+template <int W>
+__device__ __forceinline__ bool level_wg_last(int32_t ncap) {
+    return (int32_t)blockIdx.x == (ncap - 1) / W;
+}
+
 template <int W, bool PRUNE>
-__global__ __launch_bounds__(64 * W) void k_tree_count(TreeStep st) {
+__device__ __forceinline__ void tree_count_level(const TreeStep& st) {
     __shared__ int64_t lds[W];
     if (st.use_agg && level_wg_empty<W>(st.ncount)) {
         if (threadIdx.x == 0) st.wagg[blockIdx.x] = 0;
@@ -519,21 +526,32 @@ __global__ __launch_bounds__(64 * W) void k_tree_count(TreeStep st) {
     if (st.use_agg) level_local_offsets<W>(v, c, st.ncap, st.off, st.wagg, st.gsum, lds);
 }
 
+template <int W, bool PRUNE>
+__global__ __launch_bounds__(64 * W) void k_tree_count(TreeStep st) {
+    tree_count_level<W, PRUNE>(st);
+}
+
 // COUNTS: the fill also makes the next level's counts (st.ncnt is set).
 template <int W, bool PRUNE, bool COUNTS>
-__global__ __launch_bounds__(64 * W) void k_tree_fill(TreeStep st) {
+__device__ __forceinline__ void tree_fill_level(const TreeStep& st) {
     __shared__ int64_t lds[W];
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     if (st.use_agg) {
-        if (level_wg_empty<W>(st.ncount) && blockIdx.x != gridDim.x - 1) return;
+        const bool last = level_wg_last<W>(st.ncap);
+        if (level_wg_empty<W>(st.ncount) && !last) return;
         const int64_t base = level_base<W>(st.wagg, st.gsum, lds);
-        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) tree_level_totals(st, base + st.wagg[blockIdx.x]);
+        if (last && threadIdx.x == 0) tree_level_totals(st, base + st.wagg[blockIdx.x]);
         if (c < st.ncap) tree_fill_node<PRUNE, COUNTS>(st, c, lane, base + st.off[c]);
     } else {
         if (c == 0 && lane == 0) tree_level_totals(st, st.off[st.ncap]);
         if (c < st.ncap) tree_fill_node<PRUNE, COUNTS>(st, c, lane, st.off[c]);
     }
+}
+
+template <int W, bool PRUNE, bool COUNTS>
+__global__ __launch_bounds__(64 * W) void k_tree_fill(TreeStep st) {
+    tree_fill_level<W, PRUNE, COUNTS>(st);
 }
 
 // Level-0 frontier: the pair of roots, one C node.
@@ -646,7 +664,6 @@ struct LeafStep {
     const double* Abn2;       // squared block norms (nullptr: no norm threshold): a block product
     const double* Bbn2;       // is dropped when Abn2 Bbn2 < tau2
     double tau2;
-    NilMark nil;              // the kept C leaves and their ancestors
 };
 
 // Lane t's value in every lane, for a t that is the same in every lane: a
@@ -736,7 +753,7 @@ __device__ __forceinline__ int leaf_lane_count_norms(const LeafStep& st, int32_t
 }
 
 template <bool PRUNE>
-__device__ __forceinline__ int64_t leaf_count_node(const LeafStep& st, int32_t c, int lane) {
+__device__ __forceinline__ int64_t leaf_count_node(const LeafStep& st, const NilMark& nil, int32_t c, int lane) {
     if (c >= *st.ncount) {
         if (lane == 0) st.cnt[c] = 0;
         return 0;
@@ -753,7 +770,7 @@ __device__ __forceinline__ int64_t leaf_count_node(const LeafStep& st, int32_t c
     const int64_t v = pack2(tot, __popcll(em));
     if (lane == 0) {
         st.cnt[c] = v;
-        if (em) nil_mark_up(st.nil, c);
+        if (em) nil_mark_up(nil, c);
     }
     return v;
 }
@@ -862,7 +879,7 @@ __device__ __forceinline__ void leaf_fill_node(const LeafStep& st, int32_t c, in
 }
 
 template <int W, bool PRUNE>
-__global__ __launch_bounds__(64 * W) void k_leaf_count(LeafStep st) {
+__device__ __forceinline__ void leaf_count_level(const LeafStep& st, const NilMark& nil) {
     __shared__ int64_t lds[W];
     if (st.use_agg && level_wg_empty<W>(st.ncount)) {
         if (threadIdx.x == 0) st.wagg[blockIdx.x] = 0;
@@ -870,25 +887,36 @@ __global__ __launch_bounds__(64 * W) void k_leaf_count(LeafStep st) {
     }
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
     int64_t v = 0;
-    if (c < st.ncap) v = leaf_count_node<PRUNE>(st, c, threadIdx.x & 63);
+    if (c < st.ncap) v = leaf_count_node<PRUNE>(st, nil, c, threadIdx.x & 63);
     if (st.use_agg) level_local_offsets<W>(v, c, st.ncap, st.off, st.wagg, st.gsum, lds);
 }
 
+template <int W, bool PRUNE>
+__global__ __launch_bounds__(64 * W) void k_leaf_count(LeafStep st, NilMark nil) {
+    leaf_count_level<W, PRUNE>(st, nil);
+}
+
 template <int W, bool PLAIN>
-__global__ __launch_bounds__(64 * W) void k_leaf_fill(LeafStep st) {
+__device__ __forceinline__ void leaf_fill_level(const LeafStep& st, const NilMark& nil) {
     __shared__ int64_t lds[W];
     const int32_t c = (int32_t)(blockIdx.x * W + (threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    nil_tile_counts(st.nil, c, (int64_t)gridDim.x * W);
+    nil_tile_counts(nil, c, (int64_t)((st.ncap - 1) / W + 1) * W);
     if (st.use_agg) {
-        if (level_wg_empty<W>(st.ncount) && blockIdx.x != gridDim.x - 1) return;
+        const bool last = level_wg_last<W>(st.ncap);
+        if (level_wg_empty<W>(st.ncount) && !last) return;
         const int64_t base = level_base<W>(st.wagg, st.gsum, lds);
-        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) leaf_level_totals(st, base + st.wagg[blockIdx.x]);
+        if (last && threadIdx.x == 0) leaf_level_totals(st, base + st.wagg[blockIdx.x]);
         if (c < st.ncap) leaf_fill_node<PLAIN>(st, c, lane, base + st.off[c]);
     } else {
         if (c == 0 && lane == 0) leaf_level_totals(st, st.off[st.ncap]);
         if (c < st.ncap) leaf_fill_node<PLAIN>(st, c, lane, st.off[c]);
     }
+}
+
+template <int W, bool PLAIN>
+__global__ __launch_bounds__(64 * W) void k_leaf_fill(LeafStep st, NilMark nil) {
+    leaf_fill_level<W, PLAIN>(st, nil);
 }
 
 // ---------------------------------------------- NIL normalisation of C
@@ -929,8 +957,10 @@ struct NilTree {
     const uint64_t* umo;
     const uint64_t* urm;
     const uint64_t* ucm;
-    const int32_t* flags;                    // foff[L+1] entries, set by the leaf fill
-    const int32_t* ex;                       // exclusive scan of flags (foff[L+1] + 1 entries)
+    const int32_t* flags;                    // foff[L+1] entries, set by the leaf count
+    const int32_t* tcnt;                     // flags set per tile
+    int64_t tiles;
+    int32_t* ex;                             // exclusive scan of flags (foff[L+1] + 1 entries)
     int32_t* child[NIL_MAX_LEVELS];          // the kept tree
     uint64_t* key[NIL_MAX_LEVELS + 1];
     int32_t* base;
@@ -944,8 +974,8 @@ struct NilTree {
 // them: the total); one wave per tile, which adds up the counts of the tiles
 // before its own. (With tiles of 64 and 4-byte loads the waves of an R-MAT
 // product with 1.4 M nodes read 1 GB of counts, 90 us; 6 us now.)
-__global__ __launch_bounds__(64) void k_nil_offsets(const int32_t* __restrict__ flags,
-                                                    const int32_t* __restrict__ tcnt, int32_t* __restrict__ ex) {
+__device__ __forceinline__ void nil_offsets_tile(const int32_t* __restrict__ flags, const int32_t* __restrict__ tcnt,
+                                                 int32_t* __restrict__ ex) {
     const int lane = threadIdx.x;
     const int64_t t = blockIdx.x;
     const int4 f = reinterpret_cast<const int4*>(flags)[t * 64 + lane];
@@ -961,11 +991,15 @@ __global__ __launch_bounds__(64) void k_nil_offsets(const int32_t* __restrict__ 
         make_int4(before, before + f.x, before + f.x + f.y, before + f.x + f.y + f.z);
 }
 
+__global__ __launch_bounds__(64) void k_nil_offsets(const int32_t* flags, const int32_t* tcnt, int32_t* ex) {
+    nil_offsets_tile(flags, tcnt, ex);
+}
+
 __device__ __forceinline__ int32_t nil_rank(const NilTree& t, int l, int64_t c) {
     return t.ex[t.foff[l] + c] - t.ex[t.foff[l]];
 }
 
-__global__ void k_nil_compact(NilTree t) {
+__device__ __forceinline__ void nil_compact(const NilTree& t) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int L = t.L;
     if (i == 0)
@@ -991,6 +1025,8 @@ __global__ void k_nil_compact(NilTree t) {
         t.cm[n] = t.ucm[c];
     }
 }
+
+__global__ __launch_bounds__(64) void k_nil_compact(NilTree t) { nil_compact(t); }
 
 // ------------------------------------------------ launch order of C's blocks
 //
@@ -1095,12 +1131,13 @@ struct SmallStep {
     uint64_t* mo;
     uint64_t* rm;
     uint64_t* cm;
-    HostSlot* slot;
+    HostSlot* slot;                            // the counts go there
     uint32_t seq;
+    int32_t* counts;                           // or (slot NULL) here, published with other problems'
 };
 
 template <bool PRUNE, bool PLAIN>
-__global__ __launch_bounds__(SMALL_THREADS) void k_small_symbolic(SmallStep a) {
+__device__ __forceinline__ void small_symbolic(const SmallStep& a) {
     __shared__ int32_t fa[2][SMALL_PAIRS], fb[2][SMALL_PAIRS];   // the frontier, this level's and the next
     __shared__ int32_t cseg[2][SMALL_NODES + 1];
     __shared__ uint64_t ukey[SMALL_NODES];                       // all levels' nodes, concatenated
@@ -1316,7 +1353,79 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_symbolic(SmallStep a) {
             a.cm[to] = rowmajor_to_colmajor(rm, lf.lb_log);
         }
     }
-    publish_words(counts, 3 * L + 4, a.slot, a.seq);
+    if (a.slot)
+        publish_words(counts, 3 * L + 4, a.slot, a.seq);
+    else if (tid < 3 * L + 4)   // written by this thread's wave or before the last barrier
+        a.counts[tid] = counts[tid];
+}
+
+template <bool PRUNE, bool PLAIN>
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_symbolic(SmallStep a) {
+    small_symbolic<PRUNE, PLAIN>(a);
+}
+
+// ------------------------------------------ the problems of a batch together
+//
+// A plan of many products ran their symbolic phases one after another, each a
+// dozen launches of few workgroups and a wait of the host for its counts: 16
+// products of up to 384 block rows took 1.2 ms so, on a GPU mostly idle.
+// Together they share the launches: the problem is the workgroup's y index
+// (x, for the small ones, a workgroup each) and its step record is read from
+// memory, in place of the kernel's arguments; trees of different depth are
+// aligned at their leaves. One kernel publishes all problems' counts. Those 16
+// products, their plan made and run and the results read out: 2299 us one by
+// one, 1413 together; what is left of the symbolic phase is its chain of a
+// dozen launches and the host's part, allocations and launch orders.
+struct ManyStep {
+    int first;        // the problem's first level among the launches: its root
+    RootInit root;
+    LeafStep leaf;
+    NilMark mark;
+    NilTree nil;
+};
+
+__global__ __launch_bounds__(64) void k_root_init_many(const ManyStep* __restrict__ many) {
+    root_init(many[blockIdx.y].root);
+}
+
+// steps: [level among the launches][problem]; no nodes where the problem has
+// no such level.
+__global__ __launch_bounds__(64) void k_tree_count_many(const ManyStep* __restrict__ many,
+                                                        const TreeStep* __restrict__ steps) {
+    const TreeStep st = steps[many[blockIdx.y].first * gridDim.y + blockIdx.y];
+    tree_count_level<1, false>(st);
+}
+
+template <bool COUNTS>
+__global__ __launch_bounds__(64) void k_tree_fill_many(const TreeStep* __restrict__ steps) {
+    const TreeStep st = steps[blockIdx.y];
+    if ((int32_t)blockIdx.x >= st.ncap) return;
+    tree_fill_level<1, false, COUNTS>(st);
+}
+
+__global__ __launch_bounds__(64) void k_leaf_count_many(const ManyStep* __restrict__ many) {
+    const LeafStep st = many[blockIdx.y].leaf;
+    if ((int32_t)blockIdx.x >= st.ncap) return;
+    leaf_count_level<1, false>(st, many[blockIdx.y].mark);
+}
+
+__global__ __launch_bounds__(64) void k_leaf_fill_many(const ManyStep* __restrict__ many) {
+    const LeafStep st = many[blockIdx.y].leaf;
+    if ((int32_t)blockIdx.x >= st.ncap) return;
+    leaf_fill_level<1, true>(st, many[blockIdx.y].mark);
+}
+
+__global__ __launch_bounds__(64) void k_nil_offsets_many(const ManyStep* __restrict__ many) {
+    const NilTree& t = many[blockIdx.y].nil;
+    if ((int64_t)blockIdx.x < t.tiles) nil_offsets_tile(t.flags, t.tcnt, t.ex);
+}
+
+__global__ __launch_bounds__(64) void k_nil_compact_many(const ManyStep* __restrict__ many) {
+    nil_compact(many[blockIdx.y].nil);
+}
+
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_symbolic_many(const SmallStep* __restrict__ steps) {
+    small_symbolic<false, true>(steps[blockIdx.x]);
 }
 
 // ----------------------------------------------------------- host side
@@ -1361,7 +1470,8 @@ static inline int64_t level_wgs(int64_t n) {
 }
 
 // Launch kernel template K (count or fill) with the level's workgroup width
-// and the template arguments that follow it.
+// and the template arguments that follow its own.
+#define QT_ARGS(...) __VA_ARGS__
 #define QT_LEVEL_LAUNCH(K, n, wgs, stream, arg, ...)                             \
     do {                                                                          \
         if (level_waves(n) == 1)                                                  \
@@ -1463,9 +1573,74 @@ static qt_matrix* empty_result(const qt_matrix* A, const qt_matrix* B, int L, qt
 
 // Symbolic phase of C = A*B: C's tree, block keys and (uninitialised) value
 // array, plus the product lists the numeric phase reads (kept in
-// out.scratch). Synchronizes once. out.na.nseg == 0 means C has no blocks.
-void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out, bool allow_profile,
-              const MulOp& op, bool launch_order) {
+// out.scratch). out.na.nseg == 0 means C has no blocks. In three steps, so that
+// the problems of a batch can share launches and one wait:
+//   plan:    checks, counts, operand forms, the two allocations;
+//   launch:  the kernels, on the traversal's stream, and the read-back;
+//   finish:  waits for the counts (the one synchronization), forms C.
+struct Symbolic {
+    qt_matrix* A;
+    qt_matrix* B;
+    qt_prec prec;
+    hipStream_t s;
+    SymbolicOut& out;
+    bool allow_profile;
+    MulOp op;
+    bool launch_order;
+
+    // plan
+    bool done = false;      // C is empty, known without a traversal
+    bool prune = false, bounds = false, small = false, may_strip = false, may_korder = false, prof = false;
+    int L = 0, liftA = 0, liftB = 0, lb_log = 0, strip_log = 0, strip_bits = 1, kbits = 1;
+    hipStream_t ss = nullptr;                 // the traversal's stream
+    std::vector<int64_t> pairs, ncap, foff, gsum_at;
+    int64_t P = 0, cap = 0, nil_tiles = 0, nclear = 0;
+    qt_matrix* Av = nullptr;
+    NumericArgs na{};
+    std::vector<size_t> o_child, o_key, u_child, u_key, u_parent, o_fa, o_fb, o_cseg, o_cnt, o_off, o_tot, o_wagg;
+    size_t o_lbase = 0, o_lmo = 0, o_lrm = 0, o_lcm = 0, o_bkey = 0, o_nex = 0, o_ntcnt = 0, u_lbase = 0, u_lmo = 0,
+           u_lrm = 0, u_lcm = 0, o_gsum = 0, o_scan = 0, o_lcnt = 0, o_sort = 0, o_order = 0;
+    char* K = nullptr;
+    char* W = nullptr;
+    const int32_t* lift = nullptr;
+    int32_t* dcount = nullptr;                // the counts (see plan)
+    int32_t* nflags = nullptr;
+    LeafStep ls{};
+
+    // launch
+    std::unique_ptr<ReadBack> counts;         // unless shared with other problems
+    hipError_t traced = hipSuccess;
+    bool running = false;                     // launched, not known to have ended
+
+    Symbolic(qt_matrix* a, qt_matrix* b, qt_prec p, hipStream_t stream, SymbolicOut& o, bool profile, const MulOp& which,
+             bool with_order)
+        : A(a), B(b), prec(p), s(stream), out(o), allow_profile(profile), op(which), launch_order(with_order) {}
+    Symbolic(const Symbolic&) = delete;
+    Symbolic& operator=(const Symbolic&) = delete;
+    // after an error between launch and finish: the kernels use the scratch
+    // and the slot
+    ~Symbolic() {
+        if (running) (void)hipStreamSynchronize(ss);
+    }
+
+    static void* at(char* base, size_t off) { return (void*)(base + off); }
+    int ncounts() const { return 3 * L + 4; }
+    void plan();
+    TreeStep tree_step(int l) const;
+    TreeStep fill_step(int l) const;          // with the next level's counts, where the fill makes them
+    bool fill_counts(int l) const;
+    bool together() const;                    // its launches may be shared with other problems
+    RootInit root_step() const;
+    LeafStep leaf_step() const;
+    NilMark nil_mark() const;
+    NilTree nil_tree() const;
+    SmallStep small_step() const;
+    void launch();
+    const int32_t* wait();                    // the counts, by the problem's own read-back
+    void finish(const int32_t* hc);
+};
+
+void Symbolic::plan() {
     if (prec != QT_F64 && prec != QT_F32 && prec != QT_BF16X3) fail(QT_ERR_ARG, "unknown precision");
     if (A->b != B->b || A->leaf != B->leaf) fail(QT_ERR_SHAPE, "operands differ in block or leaf size");
     const int64_t a_cols = op.ta ? A->n_rows : A->n_cols;   // op(A) = A or A^T
@@ -1474,22 +1649,24 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     if (op.upper && (op.ta ? A->n_cols : A->n_rows) != (op.tb ? B->n_rows : B->n_cols))
         fail(QT_ERR_SHAPE, "an upper-triangular product must be square");
     if (prec == QT_BF16X3 && A->b == 16) fail(QT_ERR_UNSUPPORTED, "split-bf16 path needs b = 32 or 64");
-    const bool prune = op.tau2 > 0;   // a norm threshold
+    prune = op.tau2 > 0;   // a norm threshold
     if (prune && (op.ta || op.tb || op.upper || A->vsrc || B->vsrc))
         fail(QT_ERR_UNSUPPORTED, "a norm threshold needs C = A * B of stored operands");
     // with a norm threshold (or only the upper triangle) the counts known
     // beforehand are bounds, not exact
-    const bool bounds = op.upper || prune;
-    const int L = std::max(A->L, B->L);
-    const int liftA = L - A->L, liftB = L - B->L;
+    bounds = op.upper || prune;
+    L = std::max(A->L, B->L);
+    liftA = L - A->L;
+    liftB = L - B->L;
     out.na = NumericArgs{};
     out.prof = false;
     if (A->nblocks == 0 || B->nblocks == 0) {
         out.C.reset(empty_result(A, B, L, prec, s, op));
+        done = true;
         return;
     }
 
-    const hipStream_t ss = side_stream();   // the traversal's stream
+    ss = side_stream();
     build_histograms(A, ss);
     build_histograms(B, ss);
     if (prune) {
@@ -1505,15 +1682,15 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // when A is used transposed, and likewise for B.
     const auto& a_col = op.ta ? A->hist.rowcnt : A->hist.colcnt;
     const auto& b_row = op.tb ? B->hist.colcnt : B->hist.rowcnt;
-    std::vector<int64_t> pairs(L + 1);
+    pairs.resize(L + 1);
     for (int l = 0; l <= L; ++l) {
         const auto& ca = (l < liftA) ? unit_hist() : a_col[l - liftA];
         const auto& rb = (l < liftB) ? unit_hist() : b_row[l - liftB];
         pairs[l] = dot_counts(ca, rb);
     }
-    const int64_t P = dot_counts(op.ta ? A->hist.blk_row : A->hist.blk_col,
-                                 op.tb ? B->hist.blk_col : B->hist.blk_row);
-    const int lb_log = A->lb_log;
+    P = dot_counts(op.ta ? A->hist.blk_row : A->hist.blk_col,
+                   op.tb ? B->hist.blk_col : B->hist.blk_row);
+    lb_log = A->lb_log;
     const int64_t lb2 = int64_t(1) << (2 * lb_log);
     for (int l = 0; l <= L; ++l)
         if (4 * pairs[l] > kMaxI32) fail(QT_ERR_UNSUPPORTED, "too many node pairs at one level");
@@ -1521,7 +1698,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // there are only so many node positions in C's shape at that level (the
     // per-node arrays and the level kernels' grids are sized by this; at the
     // deep levels of an unstructured product it is far below the pair count)
-    std::vector<int64_t> ncap(L + 1);
+    ncap.resize(L + 1);
     {
         const int64_t c_rows = op.ta ? A->n_cols : A->n_rows, c_cols = op.tb ? B->n_rows : B->n_cols;
         for (int l = 0; l <= L; ++l) {
@@ -1534,6 +1711,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     if (P == 0) {
         out.C.reset(empty_result(A, B, L, prec, s, op));
         out.C->pairs = pairs;
+        done = true;
         return;
     }
 
@@ -1541,9 +1719,8 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // (a structure-only operand reads its value source's blocks). A block read
     // transposed is marked in the product lists and transposed as it is
     // loaded: no transposed copy of any operand is made.
-    qt_matrix* Av = A->vsrc ? A->vsrc : A;
+    Av = A->vsrc ? A->vsrc : A;
     qt_matrix* Bv = B->vsrc ? B->vsrc : B;
-    NumericArgs na{};
     na.b = A->b;
     na.prec = prec;
     na.dyn = (op.ta || op.tb || A->vsrc || B->vsrc) ? 1 : 0;
@@ -1567,9 +1744,9 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     }
 
     // ---- plan the two allocations
-    const int64_t cap = std::min<int64_t>(P, lb2 * ncap[L]);   // bound on C blocks
+    cap = std::min<int64_t>(P, lb2 * ncap[L]);   // bound on C blocks
     // one launch for the whole phase when every level fits one workgroup
-    bool small = L <= SMALL_LEVELS && P <= SMALL_PRODUCTS;
+    small = L <= SMALL_LEVELS && P <= SMALL_PRODUCTS;
     int64_t all_nodes = 0;
     for (int l = 0; l <= L; ++l) {
         small = small && pairs[l] <= SMALL_PAIRS;
@@ -1579,28 +1756,26 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // the launch order in strips, of the block rows of C (see above)
     const int64_t c_rows_blk = (op.ta ? A->n_cols : A->n_rows) / A->b;
     const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);
-    int strip_log = 0;
     while (strip_log < STRIP_MAX_LOG && (row_bytes << (strip_log + 1)) <= STRIP_BYTES) ++strip_log;
-    int strip_bits = 1;
     while ((int64_t(1) << (strip_bits + strip_log)) < c_rows_blk) ++strip_bits;
-    const bool may_strip = launch_order && !small && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
+    may_strip = launch_order && !small && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
     // the order by inner index is built once C's block count is known, if
     // the products are then fewer than twice the C blocks (cap bounds those)
     const int64_t kdim = (op.ta ? A->n_rows : A->n_cols) / A->b;
-    int kbits = 1;
     while ((int64_t(1) << kbits) < kdim) ++kbits;
     const int64_t read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
-    const bool may_korder =
+    may_korder =
         launch_order && !small && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
     ArenaPlan keep, tmp;   // keep: C's tree; tmp: scratch freed after the call
-    std::vector<size_t> o_child(L), o_key(L + 1);
+    o_child.resize(L);
+    o_key.resize(L + 1);
     for (int l = 0; l < L; ++l) o_child[l] = keep.take(4 * ncap[l] * sizeof(int32_t));
     for (int l = 0; l <= L; ++l) o_key[l] = keep.take(ncap[l] * sizeof(uint64_t));
-    const size_t o_lbase = keep.take(ncap[L] * sizeof(int32_t));
-    const size_t o_lmo = keep.take(ncap[L] * sizeof(uint64_t));
-    const size_t o_lrm = keep.take(ncap[L] * sizeof(uint64_t));
-    const size_t o_lcm = keep.take(ncap[L] * sizeof(uint64_t));
-    const size_t o_bkey = keep.take(cap * sizeof(uint64_t));
+    o_lbase = keep.take(ncap[L] * sizeof(int32_t));
+    o_lmo = keep.take(ncap[L] * sizeof(uint64_t));
+    o_lrm = keep.take(ncap[L] * sizeof(uint64_t));
+    o_lcm = keep.take(ncap[L] * sizeof(uint64_t));
+    o_bkey = keep.take(cap * sizeof(uint64_t));
     if (L + 1 > NIL_MAX_LEVELS) fail(QT_ERR_UNSUPPORTED, "quadtree too deep");
     const size_t o_prodA = tmp.take(P * sizeof(int32_t));
     const size_t o_prodB = tmp.take(P * sizeof(int32_t));
@@ -1608,15 +1783,17 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // The scratch of the level by level traversal from here on (a small
     // product's stays in LDS): first the tree before NIL normalisation.
     const size_t small_bytes = tmp.bytes;
-    std::vector<size_t> u_child(L), u_key(L + 1), u_parent(L + 1);
+    u_child.resize(L);
+    u_key.resize(L + 1);
+    u_parent.resize(L + 1);
     for (int l = 0; l < L; ++l) u_child[l] = tmp.take(4 * ncap[l] * sizeof(int32_t));
     for (int l = 0; l <= L; ++l) u_key[l] = tmp.take(ncap[l] * sizeof(uint64_t));
     for (int l = 1; l <= L; ++l) u_parent[l] = tmp.take(ncap[l] * sizeof(int32_t));
-    const size_t u_lbase = tmp.take(ncap[L] * sizeof(int32_t));
-    const size_t u_lmo = tmp.take(ncap[L] * sizeof(uint64_t));
-    const size_t u_lrm = tmp.take(ncap[L] * sizeof(uint64_t));
-    const size_t u_lcm = tmp.take(ncap[L] * sizeof(uint64_t));
-    std::vector<int64_t> foff(L + 2, 0);
+    u_lbase = tmp.take(ncap[L] * sizeof(int32_t));
+    u_lmo = tmp.take(ncap[L] * sizeof(uint64_t));
+    u_lrm = tmp.take(ncap[L] * sizeof(uint64_t));
+    u_lcm = tmp.take(ncap[L] * sizeof(uint64_t));
+    foff.assign(L + 2, 0);
     for (int l = 0; l <= L; ++l) foff[l + 1] = foff[l] + ncap[l];
     if (foff[L + 1] > kMaxI32) fail(QT_ERR_UNSUPPORTED, "too many C nodes");
     // Cleared by the traversal's first kernel, in one run: the NIL flags of all
@@ -1624,21 +1801,20 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     // workgroup aggregates, and the aggregates themselves (the levels whose
     // counts the previous level's fill makes have no count kernel to write
     // the aggregates of workgroups without a node).
-    const int64_t nil_tiles = foff[L + 1] / NIL_TILE + 1;
-    const size_t o_ntcnt = tmp.take(nil_tiles * sizeof(int32_t));
+    nil_tiles = foff[L + 1] / NIL_TILE + 1;
+    o_ntcnt = tmp.take(nil_tiles * sizeof(int32_t));
     const size_t o_nflags = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
-    std::vector<int64_t> gsum_at(L + 1);
+    gsum_at.resize(L + 1);
     int64_t gsum_total = 0;
     for (int l = 0; l <= L; ++l) {
         gsum_at[l] = gsum_total;
         gsum_total += (level_wgs(ncap[l]) + (1 << AGG_GROUP_LOG) - 1) >> AGG_GROUP_LOG;
     }
-    const size_t o_gsum = tmp.take(std::max<int64_t>(gsum_total, 1) * sizeof(int64_t));
-    std::vector<size_t> o_fa(L + 1), o_fb(L + 1), o_cseg(L + 1), o_cnt(L + 1), o_off(L + 1), o_tot(L + 1),
-        o_wagg(L + 1);
+    o_gsum = tmp.take(std::max<int64_t>(gsum_total, 1) * sizeof(int64_t));
+    for (auto* v : {&o_fa, &o_fb, &o_cseg, &o_cnt, &o_off, &o_tot, &o_wagg}) v->resize(L + 1);
     for (int l = 0; l <= L; ++l) o_wagg[l] = tmp.take(level_wgs(ncap[l]) * sizeof(int64_t));
-    const int64_t nclear = (int64_t)(tmp.bytes - o_nflags) / (int64_t)sizeof(int32_t);
-    const size_t o_nex = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
+    nclear = (int64_t)(tmp.bytes - o_nflags) / (int64_t)sizeof(int32_t);
+    o_nex = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     size_t scan_elems = 0;
     for (int l = 0; l <= L; ++l) {
         o_fa[l] = tmp.take(pairs[l] * sizeof(int32_t));
@@ -1649,14 +1825,13 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
         o_tot[l] = tmp.take(ncap[l] * sizeof(int4));
         scan_elems = std::max(scan_elems, scan_tmp_elems(ncap[l]));
     }
-    const size_t o_scan = tmp.take((scan_elems + 1) * sizeof(int64_t));
-    const size_t o_lcnt = tmp.take(ncap[L] * 64 * sizeof(int32_t));   // leaf step: products per block position
-    size_t o_sort = 0, o_order = 0;
+    o_scan = tmp.take((scan_elems + 1) * sizeof(int64_t));
+    o_lcnt = tmp.take(ncap[L] * 64 * sizeof(int32_t));   // leaf step: products per block position
     if (may_strip || may_korder)   // one order is built at most
         o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
                                    may_korder ? sort_tmp_bound(cap, kbits) : 0) * sizeof(int32_t));
     if (may_strip || may_korder) o_order = tmp.take(cap * sizeof(int32_t));
-    const size_t o_count = tmp.take((3 * L + 4) * sizeof(int32_t));
+    const size_t o_count = tmp.take(ncounts() * sizeof(int32_t));
 
     out.C.reset(new_result(A, B, L, prec, s, op));
     qt_matrix* C = out.C.get();
@@ -1668,64 +1843,16 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     C->arena.s = s;
     out.scratch.alloc(small ? small_bytes : tmp.bytes, ss);
     out.scratch.s = s;
-    char* K = C->arena.p;
-    char* W = out.scratch.p;
-    auto at = [](char* base, size_t off) { return (void*)(base + off); };
+    K = C->arena.p;
+    W = out.scratch.p;
     // [0..L] C nodes per level as traversed, [L+1] C blocks, [L+2..2L+2] checks,
     // [2L+3..3L+3] C nodes per level after NIL normalisation
-    int32_t* dcount = (int32_t*)at(W, o_count);
-    int32_t* nflags = (int32_t*)at(W, o_nflags);
+    dcount = (int32_t*)at(W, o_count);
+    nflags = (int32_t*)at(W, o_nflags);
 
-    const bool prof = out.prof = allow_profile && profiling_on();
-    PhaseEvents& ev = out.ev;
-    if (prof) {
-        timing_event(&ev.e0);
-        timing_event(&ev.e1);
-        timing_event(&ev.e2);
-        timing_event(&ev.e3);
-        QT_HIP(hipEventRecord(ev.e0, ss));
-    }
-
-    const int32_t* lift = (liftA > 0 || liftB > 0) ? lift_table() : nullptr;
-    auto tree_step = [&](int l) {
-        TreeStep st{};
-        st.fa = (const int32_t*)at(W, o_fa[l]);
-        st.fb = (const int32_t*)at(W, o_fb[l]);
-        st.cseg = (const int32_t*)at(W, o_cseg[l]);
-        st.ckey = (const uint64_t*)at(W, u_key[l]);
-        st.ncount = dcount + l;
-        st.Ach = (l < liftA) ? lift : A->levels[l - liftA].child.p;
-        st.Bch = (l < liftB) ? lift : B->levels[l - liftB].child.p;
-        st.cnt = (int64_t*)at(W, o_cnt[l]);
-        st.tot4 = (int4*)at(W, o_tot[l]);
-        st.wagg = (int64_t*)at(W, o_wagg[l]);
-        st.gsum = (int64_t*)at(W, o_gsum) + gsum_at[l];
-        st.off = (int64_t*)at(W, o_off[l]);
-        st.ncap = (int32_t)ncap[l];
-        st.nfa = (int32_t*)at(W, o_fa[l + 1]);
-        st.nfb = (int32_t*)at(W, o_fb[l + 1]);
-        st.ncseg = (int32_t*)at(W, o_cseg[l + 1]);
-        st.nckey = (uint64_t*)at(W, u_key[l + 1]);
-        st.cchild = (int32_t*)at(W, u_child[l]);
-        st.nparent = (int32_t*)at(W, u_parent[l + 1]);
-        st.ncount_next = dcount + l + 1;
-        st.np_next = (int32_t)pairs[l + 1];
-        st.nc_next = (int32_t)ncap[l + 1];
-        st.check = dcount + L + 2 + l;
-        st.ta = op.ta;
-        st.tb = op.tb;
-        st.upper = op.upper;
-        if (prune) {
-            // norms of the next level's nodes; above a shallower operand's root
-            // (the lifted levels) every child is its root
-            st.An2 = (l + 1 <= liftA) ? A->nn2[0] : A->nn2[l + 1 - liftA];
-            st.Bn2 = (l + 1 <= liftB) ? B->nn2[0] : B->nn2[l + 1 - liftB];
-            st.tau2 = op.tau2;
-        }
-        return st;
-    };
+    prof = out.prof = allow_profile && profiling_on();
+    lift = (liftA > 0 || liftB > 0) ? lift_table() : nullptr;
     // the leaf step's operands and outputs
-    LeafStep ls{};
     ls.lb_log = lb_log;
     // rows of op(A) are columns of A when transposed; columns of op(B) rows of B
     ls.Arm = op.ta ? A->leaves.mask_cm.p : A->leaves.mask_rm.p;
@@ -1750,31 +1877,189 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     ls.cbkey = (uint64_t*)at(K, o_bkey);
     ls.cbseg = (int32_t*)at(W, o_cbseg);
     ls.cap = (int32_t)cap;
-    const int nhc = 3 * L + 4;
-    if (nhc > kSlotWords) fail(QT_ERR_UNSUPPORTED, "tree too deep for the count read-back");
-    ReadBack counts(nhc);
+    if (ncounts() > kSlotWords) fail(QT_ERR_UNSUPPORTED, "tree too deep for the count read-back");
+}
+
+TreeStep Symbolic::tree_step(int l) const {
+    TreeStep st{};
+    st.fa = (const int32_t*)at(W, o_fa[l]);
+    st.fb = (const int32_t*)at(W, o_fb[l]);
+    st.cseg = (const int32_t*)at(W, o_cseg[l]);
+    st.ckey = (const uint64_t*)at(W, u_key[l]);
+    st.ncount = dcount + l;
+    st.Ach = (l < liftA) ? lift : A->levels[l - liftA].child.p;
+    st.Bch = (l < liftB) ? lift : B->levels[l - liftB].child.p;
+    st.cnt = (int64_t*)at(W, o_cnt[l]);
+    st.tot4 = (int4*)at(W, o_tot[l]);
+    st.wagg = (int64_t*)at(W, o_wagg[l]);
+    st.gsum = (int64_t*)at(W, o_gsum) + gsum_at[l];
+    st.use_agg = level_wgs(ncap[l]) <= AGG_MAX;
+    st.off = (int64_t*)at(W, o_off[l]);
+    st.ncap = (int32_t)ncap[l];
+    st.nfa = (int32_t*)at(W, o_fa[l + 1]);
+    st.nfb = (int32_t*)at(W, o_fb[l + 1]);
+    st.ncseg = (int32_t*)at(W, o_cseg[l + 1]);
+    st.nckey = (uint64_t*)at(W, u_key[l + 1]);
+    st.cchild = (int32_t*)at(W, u_child[l]);
+    st.nparent = (int32_t*)at(W, u_parent[l + 1]);
+    st.ncount_next = dcount + l + 1;
+    st.np_next = (int32_t)pairs[l + 1];
+    st.nc_next = (int32_t)ncap[l + 1];
+    st.check = dcount + L + 2 + l;
+    st.ta = op.ta;
+    st.tb = op.tb;
+    st.upper = op.upper;
+    if (prune) {
+        // norms of the next level's nodes; above a shallower operand's root
+        // (the lifted levels) every child is its root
+        st.An2 = (l + 1 <= liftA) ? A->nn2[0] : A->nn2[l + 1 - liftA];
+        st.Bn2 = (l + 1 <= liftB) ? B->nn2[0] : B->nn2[l + 1 - liftB];
+        st.tau2 = op.tau2;
+    }
+    return st;
+}
+
+// a single-wave next tree level gets its counts from this level's fill
+bool Symbolic::fill_counts(int l) const { return l + 1 < L && level_waves(ncap[l + 1]) == 1; }
+
+TreeStep Symbolic::fill_step(int l) const {
+    TreeStep st = tree_step(l);
+    if (fill_counts(l)) {
+        const TreeStep nx = tree_step(l + 1);
+        st.nAch = nx.Ach;
+        st.nBch = nx.Bch;
+        st.nAn2 = nx.An2;
+        st.nBn2 = nx.Bn2;
+        st.ncnt = nx.cnt;
+        st.ntot4 = nx.tot4;
+        st.noff = nx.off;
+        st.nwagg = nx.wagg;
+        st.ngsum = nx.gsum;
+    }
+    return st;
+}
+
+// What the shared kernels are compiled for: no norms and no block maps, and
+// one node per workgroup (so every fill makes the next level's counts).
+bool Symbolic::together() const {
+    if (prof || prune || ls.amap || ls.bmap) return false;
+    if (small) return true;
+    if (L == 0) return false;
+    for (int l = 0; l <= L; ++l)
+        if (level_waves(ncap[l]) != 1) return false;
+    return true;
+}
+
+RootInit Symbolic::root_step() const {
+    return RootInit{(int32_t*)at(W, o_fa[0]), (int32_t*)at(W, o_fb[0]), (int32_t*)at(W, o_cseg[0]),
+                    (uint64_t*)at(W, u_key[0]), dcount, nflags, nclear};
+}
+
+LeafStep Symbolic::leaf_step() const {
+    LeafStep st = ls;
+    st.fa = (const int32_t*)at(W, o_fa[L]);
+    st.fb = (const int32_t*)at(W, o_fb[L]);
+    st.cseg = (const int32_t*)at(W, o_cseg[L]);
+    st.ckey = (const uint64_t*)at(W, u_key[L]);
+    st.ncount = dcount + L;
+    st.ncap = (int32_t)ncap[L];
+    st.cnt = (int64_t*)at(W, o_cnt[L]);
+    st.lane_cnt = (int32_t*)at(W, o_lcnt);
+    st.off = (int64_t*)at(W, o_off[L]);
+    st.wagg = (int64_t*)at(W, o_wagg[L]);
+    st.gsum = (int64_t*)at(W, o_gsum) + gsum_at[L];
+    st.use_agg = level_wgs(ncap[L]) <= AGG_MAX;
+    st.lbase = (int32_t*)at(W, u_lbase);
+    st.lmo = (uint64_t*)at(W, u_lmo);
+    st.lrm = (uint64_t*)at(W, u_lrm);
+    st.lcm = (uint64_t*)at(W, u_lcm);
+    st.nblocks_out = dcount + L + 1;
+    st.check = dcount + 2 * L + 2;
+    return st;
+}
+
+NilMark Symbolic::nil_mark() const {
+    NilMark m{};
+    m.L = L;
+    for (int l = 0; l <= L + 1; ++l) m.foff[l] = foff[l];
+    for (int l = 1; l <= L; ++l) m.uparent[l] = (const int32_t*)at(W, u_parent[l]);
+    m.flags = nflags;
+    m.tcnt = (int32_t*)at(W, o_ntcnt);
+    m.tiles = nil_tiles;
+    return m;
+}
+
+// NIL normalisation: C keeps only the nodes with a block below them
+NilTree Symbolic::nil_tree() const {
+    NilTree nt{};
+    nt.L = L;
+    for (int l = 0; l <= L + 1; ++l) nt.foff[l] = foff[l];
+    for (int l = 0; l < L; ++l) {
+        nt.uchild[l] = (const int32_t*)at(W, u_child[l]);
+        nt.child[l] = (int32_t*)at(K, o_child[l]);
+    }
+    for (int l = 0; l <= L; ++l) {
+        nt.ukey[l] = (const uint64_t*)at(W, u_key[l]);
+        nt.key[l] = (uint64_t*)at(K, o_key[l]);
+    }
+    nt.ubase = (const int32_t*)at(W, u_lbase);
+    nt.umo = (const uint64_t*)at(W, u_lmo);
+    nt.urm = (const uint64_t*)at(W, u_lrm);
+    nt.ucm = (const uint64_t*)at(W, u_lcm);
+    nt.flags = nflags;
+    nt.tcnt = (const int32_t*)at(W, o_ntcnt);
+    nt.tiles = nil_tiles;
+    nt.ex = (int32_t*)at(W, o_nex);
+    nt.base = (int32_t*)at(K, o_lbase);
+    nt.mo = (uint64_t*)at(K, o_lmo);
+    nt.rm = (uint64_t*)at(K, o_lrm);
+    nt.cm = (uint64_t*)at(K, o_lcm);
+    nt.kept = dcount + 2 * L + 3;
+    return nt;
+}
+
+SmallStep Symbolic::small_step() const {
+    SmallStep sm{};
+    sm.L = L;
+    for (int l = 0; l < L; ++l) {
+        sm.Ach[l] = (l < liftA) ? lift : A->levels[l - liftA].child.p;
+        sm.Bch[l] = (l < liftB) ? lift : B->levels[l - liftB].child.p;
+        sm.child[l] = (int32_t*)at(K, o_child[l]);
+    }
+    for (int l = 0; l <= L; ++l) {
+        if (prune) {
+            sm.An2[l] = A->nn2[std::max(l - liftA, 0)];
+            sm.Bn2[l] = B->nn2[std::max(l - liftB, 0)];
+        }
+        sm.key[l] = (uint64_t*)at(K, o_key[l]);
+    }
+    sm.leaf = ls;
+    sm.base = (int32_t*)at(K, o_lbase);
+    sm.mo = (uint64_t*)at(K, o_lmo);
+    sm.rm = (uint64_t*)at(K, o_lrm);
+    sm.cm = (uint64_t*)at(K, o_lcm);
+    if (counts) {
+        sm.slot = counts->device_slot();
+        sm.seq = counts->seq();
+    } else {
+        sm.counts = dcount;
+    }
+    return sm;
+}
+
+void Symbolic::launch() {
+    PhaseEvents& ev = out.ev;
+    if (prof) {
+        timing_event(&ev.e0);
+        timing_event(&ev.e1);
+        timing_event(&ev.e2);
+        timing_event(&ev.e3);
+        QT_HIP(hipEventRecord(ev.e0, ss));
+    }
+    counts.reset(new ReadBack(ncounts()));
+    running = true;
     if (small) {
-        SmallStep sm{};
-        sm.L = L;
-        for (int l = 0; l < L; ++l) {
-            sm.Ach[l] = (l < liftA) ? lift : A->levels[l - liftA].child.p;
-            sm.Bch[l] = (l < liftB) ? lift : B->levels[l - liftB].child.p;
-            sm.child[l] = (int32_t*)at(K, o_child[l]);
-        }
-        for (int l = 0; l <= L; ++l) {
-            if (prune) {
-                sm.An2[l] = A->nn2[std::max(l - liftA, 0)];
-                sm.Bn2[l] = B->nn2[std::max(l - liftB, 0)];
-            }
-            sm.key[l] = (uint64_t*)at(K, o_key[l]);
-        }
-        sm.leaf = ls;
-        sm.base = (int32_t*)at(K, o_lbase);
-        sm.mo = (uint64_t*)at(K, o_lmo);
-        sm.rm = (uint64_t*)at(K, o_lrm);
-        sm.cm = (uint64_t*)at(K, o_lcm);
-        sm.slot = counts.device_slot();
-        sm.seq = counts.seq();
+        const SmallStep sm = small_step();
         if (prune)
             k_small_symbolic<true, false><<<1, SMALL_THREADS, 0, ss>>>(sm);
         else if (ls.amap || ls.bmap)
@@ -1783,17 +2068,13 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
             k_small_symbolic<false, true><<<1, SMALL_THREADS, 0, ss>>>(sm);
         QT_LAUNCH("k_small_symbolic");
     } else {
-        RootInit root{(int32_t*)at(W, o_fa[0]), (int32_t*)at(W, o_fb[0]), (int32_t*)at(W, o_cseg[0]),
-                      (uint64_t*)at(W, u_key[0]), dcount, nflags, nclear};
-
-        k_root_init<<<(unsigned)((nclear + 63) / 64), 64, 0, ss>>>(root);
+        k_root_init<<<(unsigned)((nclear + 63) / 64), 64, 0, ss>>>(root_step());
         QT_LAUNCH("k_root_init");
         int64_t* scan_tmp = (int64_t*)at(W, o_scan);
         bool counted = false;   // this level's counts were made by the previous level's fill
         for (int l = 0; l < L; ++l) {
-            TreeStep sl = tree_step(l);
+            const TreeStep sl = fill_step(l);
             const int64_t wgs = level_wgs(ncap[l]);
-            sl.use_agg = wgs <= AGG_MAX;
             if (!counted) {
                 if (prune)
                     QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, true);
@@ -1801,20 +2082,7 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
                     QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, false);
                 if (!sl.use_agg) exclusive_scan(sl.cnt, sl.off, ncap[l], scan_tmp, ss);
             }
-            // a single-wave next tree level gets its counts from this fill
-            counted = l + 1 < L && level_waves(ncap[l + 1]) == 1;
-            if (counted) {
-                const TreeStep nx = tree_step(l + 1);
-                sl.nAch = nx.Ach;
-                sl.nBch = nx.Bch;
-                sl.nAn2 = nx.An2;
-                sl.nBn2 = nx.Bn2;
-                sl.ncnt = nx.cnt;
-                sl.ntot4 = nx.tot4;
-                sl.noff = nx.off;
-                sl.nwagg = nx.wagg;
-                sl.ngsum = nx.gsum;
-            }
+            counted = fill_counts(l);
             if (prune && counted)
                 QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, true, true);
             else if (prune)
@@ -1824,83 +2092,39 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
             else
                 QT_LEVEL_LAUNCH(k_tree_fill, ncap[l], wgs, ss, sl, false, false);
         }
-
-        // leaf step
-        ls.fa = (const int32_t*)at(W, o_fa[L]);
-        ls.fb = (const int32_t*)at(W, o_fb[L]);
-        ls.cseg = (const int32_t*)at(W, o_cseg[L]);
-        ls.ckey = (const uint64_t*)at(W, u_key[L]);
-        ls.ncount = dcount + L;
-        ls.ncap = (int32_t)ncap[L];
-        ls.cnt = (int64_t*)at(W, o_cnt[L]);
-        ls.lane_cnt = (int32_t*)at(W, o_lcnt);
-        ls.off = (int64_t*)at(W, o_off[L]);
-        ls.wagg = (int64_t*)at(W, o_wagg[L]);
-        ls.gsum = (int64_t*)at(W, o_gsum) + gsum_at[L];
+        const LeafStep st = leaf_step();
+        const NilMark mark = nil_mark();
         const int64_t leaf_wgs = level_wgs(ncap[L]);
-        ls.use_agg = leaf_wgs <= AGG_MAX;
-        ls.lbase = (int32_t*)at(W, u_lbase);
-        ls.lmo = (uint64_t*)at(W, u_lmo);
-        ls.lrm = (uint64_t*)at(W, u_lrm);
-        ls.lcm = (uint64_t*)at(W, u_lcm);
-        ls.nblocks_out = dcount + L + 1;
-        ls.check = dcount + 2 * L + 2;
-        ls.nil.L = L;
-        for (int l = 0; l <= L + 1; ++l) ls.nil.foff[l] = foff[l];
-        for (int l = 1; l <= L; ++l) ls.nil.uparent[l] = (const int32_t*)at(W, u_parent[l]);
-        ls.nil.flags = nflags;
-        ls.nil.tcnt = (int32_t*)at(W, o_ntcnt);
-        ls.nil.tiles = nil_tiles;
         if (prune)
-            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, true);
+            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), true);
         else
-            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, ls, false);
-        if (!ls.use_agg) exclusive_scan(ls.cnt, ls.off, ncap[L], scan_tmp, ss);
-        if (prune || ls.amap || ls.bmap)
-            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, false);
+            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), false);
+        if (!st.use_agg) exclusive_scan(st.cnt, st.off, ncap[L], scan_tmp, ss);
+        if (prune || st.amap || st.bmap)
+            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), false);
         else
-            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, ls, true);
-        {
-            // NIL normalisation: C keeps only the nodes with a block below them
-            NilTree nt{};
-            nt.L = L;
-            for (int l = 0; l <= L + 1; ++l) nt.foff[l] = foff[l];
-            for (int l = 0; l < L; ++l) {
-                nt.uchild[l] = (const int32_t*)at(W, u_child[l]);
-                nt.child[l] = (int32_t*)at(K, o_child[l]);
-            }
-            for (int l = 0; l <= L; ++l) {
-                nt.ukey[l] = (const uint64_t*)at(W, u_key[l]);
-                nt.key[l] = (uint64_t*)at(K, o_key[l]);
-            }
-            nt.ubase = ls.lbase;
-            nt.umo = ls.lmo;
-            nt.urm = ls.lrm;
-            nt.ucm = ls.lcm;
-            nt.flags = nflags;
-            nt.ex = (const int32_t*)at(W, o_nex);
-            nt.base = (int32_t*)at(K, o_lbase);
-            nt.mo = (uint64_t*)at(K, o_lmo);
-            nt.rm = (uint64_t*)at(K, o_lrm);
-            nt.cm = (uint64_t*)at(K, o_lcm);
-            nt.kept = dcount + 2 * L + 3;
-            k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nflags, ls.nil.tcnt, (int32_t*)at(W, o_nex));
-            QT_LAUNCH("k_nil_offsets");
-            k_nil_compact<<<(unsigned)((foff[L + 1] + 63) / 64), 64, 0, ss>>>(nt);
-            QT_LAUNCH("k_nil_compact");
-        }
-        counts.publish(dcount, ss);
+            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), true);
+        const NilTree nt = nil_tree();
+        k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nt.flags, nt.tcnt, nt.ex);
+        QT_LAUNCH("k_nil_offsets");
+        k_nil_compact<<<(unsigned)((foff[L + 1] + 63) / 64), 64, 0, ss>>>(nt);
+        QT_LAUNCH("k_nil_compact");
+        counts->publish(dcount, ss);
     }
-    const hipError_t traced = prof ? hipEventRecord(ev.e1, ss) : hipSuccess;
+    traced = prof ? hipEventRecord(ev.e1, ss) : hipSuccess;
+}
 
-    // the one synchronization: node and block counts of C
-    // the caller's stream follows the traversal from here on (the numeric
-    // kernel first), ordered while the counts are on their way; a launch order
-    // built below adds a second wait
-    const hipError_t ordered = stream_after(s, ss);
-    const int32_t* hc = counts.wait(ss);
-    QT_HIP(ordered);
+const int32_t* Symbolic::wait() {
+    const int32_t* hc = counts->wait(ss);
     QT_HIP(traced);
+    return hc;
+}
+
+// hc: the counts, published after all of the problem's kernels
+void Symbolic::finish(const int32_t* hc) {
+    running = false;
+    qt_matrix* C = out.C.get();
+    PhaseEvents& ev = out.ev;
     for (int l = 0; l <= L; ++l) {
         if (hc[l] < 0 || hc[l] > ncap[l]) fail(QT_ERR_DEVICE, "symbolic phase: C node count out of range");
         if (hc[2 * L + 3 + l] < 0 || hc[2 * L + 3 + l] > hc[l])
@@ -1960,6 +2184,161 @@ void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicO
     out.na = na;
     ev.products = C->products;
     ev.cblocks = nnzC;
+}
+
+void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out, bool allow_profile,
+              const MulOp& op, bool launch_order) {
+    Symbolic sym(A, B, prec, s, out, allow_profile, op, launch_order);
+    sym.plan();
+    if (sym.done) return;
+    sym.launch();
+    // the caller's stream follows the traversal from here on (the numeric
+    // kernel first), ordered while the counts are on their way; a launch order
+    // built by finish() adds a second wait
+    const hipError_t ordered = stream_after(s, sym.ss);
+    const int32_t* hc = sym.wait();
+    QT_HIP(ordered);
+    sym.finish(hc);
+}
+
+// The problems of `who` level by level, one launch per step for all of them;
+// their counts go to dcount. The step records are made in `host`, which lives
+// until the copy from it is known to have ended.
+static void launch_levels(const std::vector<Symbolic*>& who, std::vector<char>& host, DBuf<char>& dev, hipStream_t ss) {
+    const size_t np = who.size();
+    int depth = 0;
+    for (const Symbolic* p : who) depth = std::max(depth, p->L);
+    ArenaPlan ap;
+    const size_t o_many = ap.take(np * sizeof(ManyStep)), o_steps = ap.take(np * depth * sizeof(TreeStep));
+    host.assign(ap.bytes, 0);
+    ManyStep* many = (ManyStep*)(host.data() + o_many);
+    TreeStep* steps = (TreeStep*)(host.data() + o_steps);
+    int64_t clear = 1, leaves = 1, tiles = 1, nodes = 1;
+    std::vector<int64_t> widest(depth, 1);
+    for (size_t i = 0; i < np; ++i) {
+        Symbolic& p = *who[i];
+        many[i].first = depth - p.L;
+        many[i].root = p.root_step();
+        many[i].leaf = p.leaf_step();
+        many[i].mark = p.nil_mark();
+        many[i].nil = p.nil_tree();
+        for (int l = 0; l < p.L; ++l) {
+            steps[(many[i].first + l) * np + i] = p.fill_step(l);
+            widest[many[i].first + l] = std::max(widest[many[i].first + l], p.ncap[l]);
+        }
+        clear = std::max(clear, p.nclear);
+        leaves = std::max(leaves, p.ncap[p.L]);
+        tiles = std::max(tiles, p.nil_tiles);
+        nodes = std::max(nodes, p.foff[p.L + 1]);
+        p.running = true;
+    }
+    dev.alloc(ap.bytes, ss);
+    QT_HIP(hipMemcpyAsync(dev.p, host.data(), ap.bytes, hipMemcpyHostToDevice, ss));
+    const ManyStep* dm = (const ManyStep*)(dev.p + o_many);
+    const TreeStep* ds = (const TreeStep*)(dev.p + o_steps);
+    const unsigned y = (unsigned)np;
+    k_root_init_many<<<dim3((unsigned)((clear + 63) / 64), y), 64, 0, ss>>>(dm);
+    QT_LAUNCH("k_root_init_many");
+    k_tree_count_many<<<dim3(1, y), 64, 0, ss>>>(dm, ds);
+    QT_LAUNCH("k_tree_count_many");
+    for (int r = 0; r < depth; ++r) {
+        const dim3 grid((unsigned)widest[r], y);
+        if (r + 1 < depth)
+            k_tree_fill_many<true><<<grid, 64, 0, ss>>>(ds + r * np);
+        else
+            k_tree_fill_many<false><<<grid, 64, 0, ss>>>(ds + r * np);
+        QT_LAUNCH("k_tree_fill_many");
+    }
+    k_leaf_count_many<<<dim3((unsigned)leaves, y), 64, 0, ss>>>(dm);
+    QT_LAUNCH("k_leaf_count_many");
+    k_leaf_fill_many<<<dim3((unsigned)leaves, y), 64, 0, ss>>>(dm);
+    QT_LAUNCH("k_leaf_fill_many");
+    k_nil_offsets_many<<<dim3((unsigned)tiles, y), 64, 0, ss>>>(dm);
+    QT_LAUNCH("k_nil_offsets_many");
+    k_nil_compact_many<<<dim3((unsigned)((nodes + 63) / 64), y), 64, 0, ss>>>(dm);
+    QT_LAUNCH("k_nil_compact_many");
+}
+
+// The small problems of `who`, one workgroup each.
+static void launch_small(const std::vector<Symbolic*>& who, std::vector<char>& host, DBuf<char>& dev, hipStream_t ss) {
+    if (who.empty()) return;
+    host.assign(who.size() * sizeof(SmallStep), 0);
+    SmallStep* steps = (SmallStep*)host.data();
+    for (size_t i = 0; i < who.size(); ++i) {
+        steps[i] = who[i]->small_step();
+        who[i]->running = true;
+    }
+    dev.alloc(host.size(), ss);
+    QT_HIP(hipMemcpyAsync(dev.p, host.data(), host.size(), hipMemcpyHostToDevice, ss));
+    k_small_symbolic_many<<<(unsigned)who.size(), SMALL_THREADS, 0, ss>>>((const SmallStep*)dev.p);
+    QT_LAUNCH("k_small_symbolic_many");
+}
+
+// Problems whose launches are shared: at most MANY_MAX (their records, counts
+// and read-back slots are bounded by it), and level by level only while the
+// workgroups of a launch that find no node of their problem stay few: the grid
+// is the widest problem's times the number of problems, at most MANY_GRID or
+// MANY_WASTE times what the problems need (an idle workgroup costs about a
+// nanosecond: below MANY_GRID less than the twelve launches that a group of
+// its own takes).
+constexpr int32_t MANY_MAX = 256;
+constexpr int64_t MANY_GRID = 65536, MANY_WASTE = 4;
+
+void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
+                    SymbolicOut* out) {
+    for (int32_t at = 0; at < count; at += MANY_MAX) {
+        const int32_t n = std::min(MANY_MAX, count - at);
+        // declared before the problems, whose destructors wait for the kernels
+        std::deque<std::vector<char>> host;
+        std::deque<DBuf<char>> dev;
+        DBuf<int32_t> words;
+        std::unique_ptr<ReadBack> shared;
+        std::vector<std::unique_ptr<Symbolic>> all;
+        std::vector<Symbolic*> alone, small, levels, order;   // order: as their counts lie in words
+        for (int32_t i = at; i < at + n; ++i) {
+            all.emplace_back(new Symbolic(A[i], B[i], prec, s, out[i], false, MulOp{}, true));
+            Symbolic* p = all.back().get();
+            p->plan();
+            if (p->done) continue;
+            if (!p->together())
+                alone.push_back(p);
+            else
+                (p->small ? small : levels).push_back(p);
+        }
+        order = small;
+        order.insert(order.end(), levels.begin(), levels.end());
+        if (order.empty() && alone.empty()) continue;
+        const hipStream_t ss = (order.empty() ? alone[0] : order[0])->ss;
+        for (Symbolic* p : alone) p->launch();
+        int stride = 0;
+        for (Symbolic* p : order) stride = std::max(stride, p->ncounts());
+        if (!order.empty()) {
+            words.alloc(stride * order.size(), ss);
+            for (size_t i = 0; i < order.size(); ++i) order[i]->dcount = words.p + i * stride;
+            launch_small(small, host.emplace_back(), dev.emplace_back(), ss);
+            // widest first, so that problems of about one size share launches
+            std::stable_sort(levels.begin(), levels.end(),
+                             [](const Symbolic* x, const Symbolic* y) { return x->foff[x->L + 1] > y->foff[y->L + 1]; });
+            for (size_t i = 0; i < levels.size();) {
+                std::vector<Symbolic*> group;
+                int64_t need = 0;
+                const int64_t widest = levels[i]->foff[levels[i]->L + 1];
+                for (; i < levels.size(); ++i) {
+                    need += levels[i]->foff[levels[i]->L + 1];
+                    if (widest * (int64_t)(group.size() + 1) > std::max(MANY_GRID, MANY_WASTE * need)) break;
+                    group.push_back(levels[i]);
+                }
+                launch_levels(group, host.emplace_back(), dev.emplace_back(), ss);
+            }
+            shared.reset(new ReadBack(stride * order.size()));
+            shared->publish(words.p, ss);
+        }
+        const hipError_t ordered = stream_after(s, ss);
+        const int32_t* hc = order.empty() ? nullptr : shared->wait(ss);
+        QT_HIP(ordered);
+        for (size_t i = 0; i < order.size(); ++i) order[i]->finish(hc + i * stride);
+        for (Symbolic* p : alone) p->finish(p->wait());
+    }
 }
 
 qt_matrix* multiply(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, const MulOp& op) {

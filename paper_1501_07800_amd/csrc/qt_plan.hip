@@ -1,7 +1,7 @@
 // Batched multiplies: many independent C_i = A_i * B_i in one launch.
 //
-// qt_plan_create runs the symbolic phase of every problem (it synchronizes
-// and allocates every C_i), then lays the numeric work of all problems out as
+// qt_plan_create runs the symbolic phases of all problems, their launches
+// shared (it synchronizes and allocates every C_i), then lays the numeric work of all problems out as
 // one list of work items: problems ordered by decreasing block products (the
 // longest first, so the tail of the launch is made of small ones), the C
 // blocks of a problem in the launch order a single multiply would use
@@ -105,16 +105,17 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     plan->scratch.resize(count);
     std::vector<NumericArgs> na(count);
     std::vector<int64_t> prods(count, 0);
-    for (int32_t i = 0; i < count; ++i) {
-        SymbolicOut sym;
-        // with the launch order the single multiply would use (by inner index
-        // where C blocks average under two block products)
-        symbolic(const_cast<qt_matrix*>(A[i]), const_cast<qt_matrix*>(B[i]), prec, s, sym, false, MulOp{}, true);
-        na[i] = sym.na;
-        prods[i] = sym.C->products;
-        plan->results[i] = std::move(sym.C);
-        plan->results[i]->plan_owned = true;
-        plan->scratch[i] = std::move(sym.scratch);
+    {
+        // with the launch orders the single multiplies would use
+        std::vector<SymbolicOut> sym(count);
+        symbolic_batch(count, const_cast<qt_matrix* const*>(A), const_cast<qt_matrix* const*>(B), prec, s, sym.data());
+        for (int32_t i = 0; i < count; ++i) {
+            na[i] = sym[i].na;
+            prods[i] = sym[i].C->products;
+            plan->results[i] = std::move(sym[i].C);
+            plan->results[i]->plan_owned = true;
+            plan->scratch[i] = std::move(sym[i].scratch);
+        }
     }
     // problems with work, largest first
     std::vector<int32_t> order;
@@ -163,13 +164,20 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     const size_t o_probs = ap.take(hp.size() * sizeof(BatchProblem));
     const size_t o_base_t = ap.take(base_t.size() * sizeof(int64_t));
     const size_t o_base_b = ap.take(base_b.size() * sizeof(int64_t));
+    const size_t copied = ap.bytes;
     const size_t o_counter = ap.take(64 * sizeof(unsigned long long));
     plan->dev.alloc(ap.bytes, s);
     char* D = plan->dev.p;
-    QT_HIP(hipMemcpyAsync(D + o_probs, hp.data(), hp.size() * sizeof(BatchProblem), hipMemcpyHostToDevice, s));
-    QT_HIP(hipMemcpyAsync(D + o_base_t, base_t.data(), base_t.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
-    QT_HIP(hipMemcpyAsync(D + o_base_b, base_b.data(), base_b.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
-    QT_HIP(hipStreamSynchronize(s));
+    std::vector<char> host(copied);
+    std::memcpy(host.data() + o_probs, hp.data(), hp.size() * sizeof(BatchProblem));
+    std::memcpy(host.data() + o_base_t, base_t.data(), base_t.size() * sizeof(int64_t));
+    std::memcpy(host.data() + o_base_b, base_b.data(), base_b.size() * sizeof(int64_t));
+    // `host` stays until the copy has ended: also when a later step throws
+    struct Drain {
+        hipStream_t s;
+        ~Drain() { (void)hipStreamSynchronize(s); }
+    } drain{s};
+    QT_HIP(hipMemcpyAsync(D, host.data(), copied, hipMemcpyHostToDevice, s));
 
     plan->probs_own = (const BatchProblem*)(D + o_probs);
     plan->probs_morton = plan->probs_own + np;
@@ -186,17 +194,25 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
 
     // the balanced schedules' work prefix sums, one per layout of the work
     // list (own launch orders or Morton; per-wave tiles or C blocks at b = 64)
+    // that differs from those before it: without launch orders of their own
+    // the problems lie in Morton order in both, and below b = 64 the items are
+    // the C blocks in both
     {
+        const int norders = plan->has_order ? 2 : 1, nforms = b == 64 ? 2 : 1;
         ArenaPlan cp;
         size_t o_cum[2][2];
         const int64_t nmax = std::max(plan->items_tiles, plan->items_blocks);
-        for (int o = 0; o < 2; ++o)
-            for (int t = 0; t < 2; ++t)
+        for (int o = 0; o < norders; ++o)
+            for (int t = 0; t < nforms; ++t)
                 o_cum[o][t] = cp.take(((t ? plan->items_blocks : plan->items_tiles) + 1) * sizeof(int64_t));
         DBuf<int64_t> cost(std::max<int64_t>(nmax, 1), s), stmp(scan_tmp_elems(nmax) + 1, s);
         plan->cum.alloc(cp.bytes, s);
         for (int o = 0; o < 2; ++o)
             for (int t = 0; t < 2; ++t) {
+                if (o >= norders || t >= nforms) {
+                    plan->cum_of[o][t] = plan->cum_of[o < norders ? o : 0][t < nforms ? t : 0];
+                    continue;
+                }
                 plan->configure((o ? QT_PLAN_ORDER_MORTON : 0) | (t ? 0 : QT_PLAN_TILE_WAVE));
                 int64_t* cum = (int64_t*)(plan->cum.p + o_cum[o][t]);
                 plan->cum_of[o][t] = cum;

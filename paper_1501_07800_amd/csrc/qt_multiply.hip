@@ -484,9 +484,10 @@ __device__ __forceinline__ void level_local_offsets(int64_t v, int32_t c, int32_
 // Aggregate path, fill side: the sum of the aggregates of all earlier
 // workgroups (every thread gets it).
 template <int W>
-__device__ __forceinline__ int64_t level_base(const int64_t* wagg, const int64_t* gsum, int64_t* lds) {
+__device__ __forceinline__ int64_t level_base(const int64_t* wagg, const int64_t* gsum, int64_t* lds,
+                                              int32_t b = (int32_t)blockIdx.x) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int32_t b = (int32_t)blockIdx.x, g = b >> AGG_GROUP_LOG, first = g << AGG_GROUP_LOG;
+    const int32_t g = b >> AGG_GROUP_LOG, first = g << AGG_GROUP_LOG;
     int64_t part = 0;
     for (int32_t i = threadIdx.x; i < g; i += 64 * W) part += gsum[i];
     for (int32_t i = first + threadIdx.x; i < b; i += 64 * W) part += wagg[i];
@@ -635,6 +636,10 @@ struct LeafStep {
     int lb_log;
     const uint64_t* Arm;      // A leaves: row-major masks
     const uint64_t* Bcm;      // B leaves: column-major masks
+    const uint64_t* Brm;      // B leaves: row-major masks (leaves of few products)
+    int32_t group;            // leaves of few products: C leaves per wave
+    int32_t* heavy;           // and the leaves among them of many: their number (zeroed first), then the leaves
+    int32_t heavy_max;
     const uint64_t* Amo;      // Morton-order masks (rank of a block in its leaf)
     const uint64_t* Bmo;
     const int32_t* Abase;
@@ -917,6 +922,276 @@ __device__ __forceinline__ void leaf_fill_level(const LeafStep& st, const NilMar
 template <int W, bool PLAIN>
 __global__ __launch_bounds__(64 * W) void k_leaf_fill(LeafStep st, NilMark nil) {
     leaf_fill_level<W, PLAIN>(st, nil);
+}
+
+// ------------------------------------------- C leaves of few block products
+//
+// The kernels above give a C leaf to a wave and a block position to a lane, and
+// walk its leaf pairs one by one: right where a leaf has hundreds of products.
+// In an unstructured product it has a few (an R-MAT product of 39634 blocks of
+// 16: 475 k leaves, 4.6 leaf pairs and 2.4 products each; random48000 at b =
+// 32: 55 pairs, 14 products), and each then costs a wave's fixed part and, per
+// leaf pair, instructions for 64 lanes of which one or two have a product. Here
+// a lane takes a leaf pair instead, and a wave the pairs of `group` leaves, 64
+// at a time:
+//   count: a lane forms its pair's boolean product, eight outer products of
+//          bytes, and adds the number of block products and the C blocks to
+//          its leaf's in LDS;
+//   fill:  leaves are taken together while their products are at most 64.
+//          Every lane lists the products of its pairs in LDS, one per step; each
+//          gets a key (leaf, block position, pair, k), the order of the product
+//          list, and its place is the number of smaller keys. The list goes out
+//          with one product per lane.
+// A leaf of more than 64 products goes through the walk above, in a wave of its
+// own: the count lists these leaves, and the fill's first workgroups take them
+// (sixteen of them in one wave, next to R-MAT's hubs, took as long as all other
+// waves together). Products, their order and C's tree are the same either way.
+// Count and fill alone: that R-MAT product 253 + 373 -> 51 + 97 us, random48000
+// 47 + 76 -> 46 + 44. What is left of them are the gathers of the leaves' masks
+// and bases and the LDS round trips of one wave.
+constexpr int SPARSE_MAX = 64;                 // products listed together
+constexpr int SPARSE_GROUP_MAX = 64;           // C leaves per wave
+// Chosen up to 40 products per C leaf position that the host's bounds allow. The
+// symbolic phase, wave per leaf and lane per pair, in us: random of 1500 block
+// rows with 1.5 products per leaf 175 and 134, 14: 269 and 230, 38: 374 and 288,
+// 55: 431 and 344, 86 (most leaves above SPARSE_MAX): 599 and 867; R-MAT of
+// 8192 with 1.1: 1163 and 646; of 1024 with 0.9 (4517 leaves): 113 and 121, with
+// 34 (hubs): 158 and 149.
+constexpr int SPARSE_LEAF = 40;
+
+// x: a flag in the lowest bit of each byte; y: a byte. y in every flagged byte.
+__device__ __forceinline__ uint64_t bytes_where(uint64_t x, uint32_t y) {
+    return (uint64_t)((uint32_t)x * y) | ((uint64_t)((uint32_t)(x >> 32) * y) << 32);
+}
+
+// Column k of a row-major 8 x 8 mask, as flags of the rows.
+__device__ __forceinline__ uint64_t mask_column(uint64_t m, int k) { return (m >> k) & 0x0101010101010101ull; }
+
+__device__ __forceinline__ uint64_t rowmajor_to_morton8(uint64_t m) {
+    m = swap_index_bits(m, 3, 2, 0x00F000F000F000F0ull);
+    m = swap_index_bits(m, 2, 1, 0x0C0C0C0C0C0C0C0Cull);
+    return swap_index_bits(m, 4, 3, 0x0000FF000000FF00ull);
+}
+
+// Of the pairs base .. base + 63, the C leaf (lane of the wave) that this
+// lane's pair belongs to; seg: the first pair of the leaf of each lane
+// (INT32_MAX past the last). Every C leaf has a pair. mark: 64 words of LDS.
+__device__ __forceinline__ int pair_leaf(int32_t seg, int32_t base, int lane, int32_t* mark) {
+    mark[lane] = 0;
+    __syncthreads();
+    const bool here = seg >= base && seg - base < 64;
+    if (here) mark[seg - base] = 1;
+    __syncthreads();
+    const uint64_t heads = __ballot(mark[lane] != 0);
+    const int before = __popcll(__ballot(seg < base));
+    __syncthreads();
+    return before + __popcll(heads & (lanes_below(lane) | (1ull << lane))) - 1;
+}
+
+__global__ __launch_bounds__(64) void k_leaf_count_sparse(LeafStep st, NilMark nil) {
+    __shared__ int32_t mark[64];
+    __shared__ int32_t lcnt[64];
+    __shared__ unsigned long long lem[64];
+    const int lane = threadIdx.x;
+    const int32_t n = *st.ncount, c0 = (int32_t)blockIdx.x * st.group;
+    if (c0 >= n) {
+        if (lane == 0) st.wagg[blockIdx.x] = 0;
+        return;
+    }
+    const int32_t nl = min(st.group, n - c0), c = c0 + lane;
+    const int32_t seg = lane < nl ? st.cseg[c] : INT32_MAX;
+    const int32_t end = st.cseg[c0 + nl];
+    lcnt[lane] = 0;
+    lem[lane] = 0;
+    for (int32_t base = __builtin_amdgcn_readfirstlane(seg); base < end; base += 64) {
+        uint64_t ra = 0, rb = 0;
+        if (base + lane < end) {
+            const int32_t a = st.fa[base + lane], b = st.fb[base + lane];
+            ra = st.Arm[a];
+            rb = st.Brm[b];
+        }
+        const int q = pair_leaf(seg, base, lane, mark);
+        uint64_t e = 0;
+        int cnt = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint64_t x = mask_column(ra, k);
+            const uint32_t y = (uint32_t)(rb >> (8 * k)) & 255u;
+            e |= bytes_where(x, y);
+            cnt += __popcll(x) * __popc(y);
+        }
+        if (cnt) {
+            atomicAdd(&lcnt[q], cnt);
+            atomicOr(&lem[q], (unsigned long long)e);
+        }
+    }
+    __syncthreads();
+    const int cnt = lcnt[lane];
+    const uint64_t em = lem[lane];
+    const int nb = __popcll(em);
+    const int s_cnt = wave_incl_scan(cnt), s_nb = wave_incl_scan(nb);
+    if (lane < nl) {
+        st.off[c] = pack2(s_cnt - cnt, s_nb - nb);
+        st.lrm[c] = em;
+        st.lcm[c] = rowmajor_to_colmajor(em, 3);
+        st.lmo[c] = rowmajor_to_morton8(em);
+        if (em) nil_mark_up(nil, c);
+        if (cnt > SPARSE_MAX) {
+            const int32_t h = atomicAdd(st.heavy, 1);
+            if (h < st.heavy_max) st.heavy[1 + h] = c;
+        }
+    }
+    if (lane == 63) {
+        const int64_t tot = pack2(s_cnt, s_nb);
+        st.wagg[blockIdx.x] = tot;
+        if (tot) atomicAdd((unsigned long long*)(st.gsum + (blockIdx.x >> AGG_GROUP_LOG)), (unsigned long long)tot);
+    }
+}
+
+// The block products of C leaf c, one of more than SPARSE_MAX.
+__device__ __forceinline__ void leaf_fill_heavy(const LeafStep& st, int32_t c, int64_t* lds) {
+    const int lane = threadIdx.x;
+    const int64_t o = level_base<1>(st.wagg, st.gsum, lds, c / st.group) + st.off[c];
+    const int i = (int)morton_row((uint64_t)lane), j = (int)morton_col((uint64_t)lane);
+    const int32_t s0 = st.cseg[c], len = st.cseg[c + 1] - s0;
+    const int cnt = leaf_lane_count(st, s0, len, lane, i, j, 8, true);
+    const uint64_t em = __ballot(cnt > 0);
+    const int32_t bidx = hi32(o) + __popcll(em & lanes_below(lane));
+    const int32_t out = lo32(o) + wave_excl_scan(cnt);
+    if (cnt > 0 && bidx < st.cap) {
+        st.cbkey[bidx] = (st.ckey[c] << 6) | (uint64_t)lane;
+        st.cbseg[bidx] = out;
+    }
+    leaf_fill_products<true>(st, s0, len, lane, i, j, 8, true, out);
+}
+
+// The first heavy_max workgroups take the leaves of many products.
+__global__ __launch_bounds__(64) void k_leaf_fill_sparse(LeafStep st, NilMark nil) {
+    __shared__ int64_t lds[1];
+    __shared__ int32_t mark[64];
+    __shared__ uint32_t skey[64];                  // leaf << 26 | block position << 20 | pair << 3 | k
+    __shared__ int32_t sa[64], sb[64];
+    __shared__ uint64_t lkey[64];
+    const int lane = threadIdx.x;
+    if ((int32_t)blockIdx.x < st.heavy_max) {
+        if ((int32_t)blockIdx.x < *st.heavy) leaf_fill_heavy(st, st.heavy[1 + blockIdx.x], lds);
+        return;
+    }
+    const int32_t wg = (int32_t)blockIdx.x - st.heavy_max;
+    nil_tile_counts(nil, wg, (int64_t)(st.ncap - 1) / st.group + 1);
+    const int32_t n = *st.ncount, c0 = wg * st.group;
+    const bool last = wg == (st.ncap - 1) / st.group;
+    if (c0 >= n && !last) return;
+    const int64_t base0 = level_base<1>(st.wagg, st.gsum, lds, wg);
+    const int64_t agg = st.wagg[wg];
+    if (last && lane == 0) leaf_level_totals(st, base0 + agg);
+    if (c0 >= n) return;
+    const int32_t nl = min(st.group, n - c0), c = c0 + lane;
+    int32_t seg = INT32_MAX, lo = 0, hi = 0, lo_end = 0;   // the leaf's first pair, product and C block; the products' end
+    if (lane < nl) {
+        seg = st.cseg[c];
+        const int64_t o = st.off[c], oe = lane + 1 < nl ? st.off[c + 1] : agg;
+        lo = lo32(o);
+        hi = hi32(o);
+        lo_end = lo32(oe);
+        st.lbase[c] = hi32(base0) + hi;
+        lkey[lane] = st.ckey[c];
+    }
+    const int32_t end = st.cseg[c0 + nl];
+    __syncthreads();
+    const uint32_t tra = st.ta ? PROD_TRANS : 0u, trb = st.tb ? PROD_TRANS : 0u;
+    for (int q = 0; q < nl;) {
+        const int32_t plo = (int32_t)lane_value((uint32_t)lo, q), s0 = (int32_t)lane_value((uint32_t)seg, q);
+        // the leaves from q on whose products are together at most 64
+        const int take = __popcll(__ballot(lane >= q && lane < nl && lo_end - plo <= SPARSE_MAX));
+        if (take == 0) {   // taken by a workgroup of its own
+            ++q;
+            continue;
+        }
+        const int qe = q + take;
+        const int32_t np = (int32_t)lane_value((uint32_t)lo_end, qe - 1) - plo;
+        const int32_t hi_q = (int32_t)lane_value((uint32_t)hi, q);
+        const int32_t s1 = qe < nl ? (int32_t)lane_value((uint32_t)seg, qe) : end;
+        q = qe;
+        if (np == 0) continue;
+        // the list, in any order
+        int listed = 0;
+        for (int32_t base = s0; base < s1; base += 64) {
+            uint64_t ra = 0, rb = 0, amo = 0, bmo = 0;
+            int32_t ab = 0, bb = 0;
+            if (base + lane < s1) {
+                const int32_t a = st.fa[base + lane], b = st.fb[base + lane];
+                ra = st.Arm[a];
+                rb = st.Brm[b];
+                amo = st.Amo[a];
+                bmo = st.Bmo[b];
+                ab = st.Abase[a];
+                bb = st.Bbase[b];
+            }
+            const int leaf = pair_leaf(seg, base, lane, mark);
+            // inner indices with a block on either side
+            uint32_t km = mask_fold(ra, 8);
+            {
+                uint64_t y = rb | (rb >> 4);       // bit 8 k: row k is occupied
+                y |= y >> 2;
+                y |= y >> 1;
+                y &= 0x0101010101010101ull;
+                km &= (uint32_t)((y * 0x0102040810204080ull) >> 56);
+            }
+            uint64_t e = 0;
+            int k = 0;
+            while (true) {
+                if (e == 0 && km != 0) {
+                    k = __ffs(km) - 1;
+                    km &= km - 1;
+                    e = bytes_where(mask_column(ra, k), (uint32_t)(rb >> (8 * k)) & 255u);
+                }
+                const uint64_t live = __ballot(e != 0);
+                if (live == 0) break;
+                const int slot = listed + __popcll(live & lanes_below(lane));
+                if (e != 0 && slot < 64) {
+                    const int pos = __ffsll((unsigned long long)e) - 1, i = pos >> 3, j = pos & 7;
+                    uint32_t qa, qb;
+                    leaf_positions(st, i, k, j, qa, qb);
+                    skey[slot] = ((uint32_t)leaf << 26) | ((uint32_t)morton_key((uint32_t)i, (uint32_t)j) << 20) |
+                                 ((uint32_t)(base + lane - s0) << 3) | (uint32_t)k;
+                    sa[slot] = (int32_t)((uint32_t)(ab + __popcll(amo & ((1ull << qa) - 1))) | tra);
+                    sb[slot] = (int32_t)((uint32_t)(bb + __popcll(bmo & ((1ull << qb) - 1))) | trb);
+                }
+                e &= e - 1;
+                listed += __popcll(live);
+            }
+        }
+        // its order: the place of a product is the number of smaller keys
+        __syncthreads();
+        const int m = min(np, 64);
+        const bool on = lane < m;
+        const uint32_t key = on ? skey[lane] : 0xffffffffu;
+        const int32_t ia = on ? sa[lane] : 0, ib = on ? sb[lane] : 0;
+        int rank = 0;
+        for (int t = 0; t < m; ++t) rank += lane_value(key, t) < key;
+        __syncthreads();
+        if (on && rank < 64) {
+            skey[rank] = key;
+            sa[rank] = ia;
+            sb[rank] = ib;
+        }
+        __syncthreads();
+        const uint32_t sk = skey[lane] >> 20, prev = lane ? skey[lane - 1] >> 20 : 0xffffffffu;
+        const bool head = on && sk != prev;
+        const uint64_t heads = __ballot(head);
+        const int32_t out = lo32(base0) + plo + lane;
+        if (on && out < st.P) {
+            st.prodA[out] = sa[lane];
+            st.prodB[out] = sb[lane];
+        }
+        const int32_t bidx = hi32(base0) + hi_q + __popcll(heads & lanes_below(lane));
+        if (head && bidx < st.cap) {
+            st.cbkey[bidx] = (lkey[sk >> 6] << 6) | (uint64_t)(sk & 63u);
+            st.cbseg[bidx] = out;
+        }
+        __syncthreads();
+    }
 }
 
 // ---------------------------------------------- NIL normalisation of C
@@ -1587,10 +1862,12 @@ struct Symbolic {
     bool allow_profile;
     MulOp op;
     bool launch_order;
+    bool batched = false;   // launches may be shared with other problems
 
     // plan
     bool done = false;      // C is empty, known without a traversal
-    bool prune = false, bounds = false, small = false, may_strip = false, may_korder = false, prof = false;
+    bool prune = false, bounds = false, small = false, sparse = false, may_strip = false, may_korder = false, prof = false;
+    int32_t group = 1;      // sparse: C leaves per wave
     int L = 0, liftA = 0, liftB = 0, lb_log = 0, strip_log = 0, strip_bits = 1, kbits = 1;
     hipStream_t ss = nullptr;                 // the traversal's stream
     std::vector<int64_t> pairs, ncap, foff, gsum_at;
@@ -1599,7 +1876,7 @@ struct Symbolic {
     NumericArgs na{};
     std::vector<size_t> o_child, o_key, u_child, u_key, u_parent, o_fa, o_fb, o_cseg, o_cnt, o_off, o_tot, o_wagg;
     size_t o_lbase = 0, o_lmo = 0, o_lrm = 0, o_lcm = 0, o_bkey = 0, o_nex = 0, o_ntcnt = 0, u_lbase = 0, u_lmo = 0,
-           u_lrm = 0, u_lcm = 0, o_gsum = 0, o_scan = 0, o_lcnt = 0, o_sort = 0, o_order = 0;
+           u_lrm = 0, u_lcm = 0, o_gsum = 0, o_scan = 0, o_lcnt = 0, o_heavy = 0, o_sort = 0, o_order = 0;
     char* K = nullptr;
     char* W = nullptr;
     const int32_t* lift = nullptr;
@@ -1625,6 +1902,9 @@ struct Symbolic {
 
     static void* at(char* base, size_t off) { return (void*)(base + off); }
     int ncounts() const { return 3 * L + 4; }
+    int64_t leaf_wgs() const { return sparse ? (ncap[L] + group - 1) / group : level_wgs(ncap[L]); }
+    int32_t heavy_max() const { return (int32_t)(P / (SPARSE_MAX + 1)); }   // leaves of more than SPARSE_MAX products
+    bool single_waves() const;                // every level in single-wave workgroups
     void plan();
     TreeStep tree_step(int l) const;
     TreeStep fill_step(int l) const;          // with the next level's counts, where the fill makes them
@@ -1753,6 +2033,18 @@ void Symbolic::plan() {
         all_nodes += ncap[l];
     }
     small = small && all_nodes <= SMALL_NODES;
+    // leaves of few products: as many per wave as fill it with pairs, while
+    // the waves still fill the GPU
+    sparse = !small && !bounds && !A->vsrc && !B->vsrc && lb_log == 3 && P <= SPARSE_LEAF * ncap[L] &&
+             !(batched && single_waves());
+    if (sparse) {
+        while (group < 16 && 2 * group * pairs[L] <= 64 * ncap[L] && ncap[L] / (2 * group) >= 4096) group *= 2;
+        while (group < SPARSE_GROUP_MAX && leaf_wgs() > AGG_MAX) group *= 2;
+        // the keys number the pairs of the leaves listed together with 17 bits: a
+        // leaf has at most as many as there are inner leaf positions
+        const int64_t inner = ((op.ta ? A->n_rows : A->n_cols) + A->leaf - 1) / A->leaf;
+        sparse = leaf_wgs() <= AGG_MAX && inner * group <= (1 << 17);
+    }
     // the launch order in strips, of the block rows of C (see above)
     const int64_t c_rows_blk = (op.ta ? A->n_cols : A->n_rows) / A->b;
     const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);
@@ -1806,14 +2098,17 @@ void Symbolic::plan() {
     const size_t o_nflags = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     gsum_at.resize(L + 1);
     int64_t gsum_total = 0;
+    auto level_aggs = [&](int l) { return l == L ? leaf_wgs() : level_wgs(ncap[l]); };
     for (int l = 0; l <= L; ++l) {
         gsum_at[l] = gsum_total;
-        gsum_total += (level_wgs(ncap[l]) + (1 << AGG_GROUP_LOG) - 1) >> AGG_GROUP_LOG;
+        gsum_total += (level_aggs(l) + (1 << AGG_GROUP_LOG) - 1) >> AGG_GROUP_LOG;
     }
     o_gsum = tmp.take(std::max<int64_t>(gsum_total, 1) * sizeof(int64_t));
     for (auto* v : {&o_fa, &o_fb, &o_cseg, &o_cnt, &o_off, &o_tot, &o_wagg}) v->resize(L + 1);
-    for (int l = 0; l <= L; ++l) o_wagg[l] = tmp.take(level_wgs(ncap[l]) * sizeof(int64_t));
+    for (int l = 0; l <= L; ++l) o_wagg[l] = tmp.take(level_aggs(l) * sizeof(int64_t));
+    if (sparse) o_heavy = tmp.take(sizeof(int32_t));   // its number is cleared, too; the list lies behind
     nclear = (int64_t)(tmp.bytes - o_nflags) / (int64_t)sizeof(int32_t);
+    if (sparse) (void)tmp.take(heavy_max() * sizeof(int32_t));
     o_nex = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     size_t scan_elems = 0;
     for (int l = 0; l <= L; ++l) {
@@ -1826,7 +2121,7 @@ void Symbolic::plan() {
         scan_elems = std::max(scan_elems, scan_tmp_elems(ncap[l]));
     }
     o_scan = tmp.take((scan_elems + 1) * sizeof(int64_t));
-    o_lcnt = tmp.take(ncap[L] * 64 * sizeof(int32_t));   // leaf step: products per block position
+    o_lcnt = sparse ? 0 : tmp.take(ncap[L] * 64 * sizeof(int32_t));   // leaf step: products per block position
     if (may_strip || may_korder)   // one order is built at most
         o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
                                    may_korder ? sort_tmp_bound(cap, kbits) : 0) * sizeof(int32_t));
@@ -1857,6 +2152,8 @@ void Symbolic::plan() {
     // rows of op(A) are columns of A when transposed; columns of op(B) rows of B
     ls.Arm = op.ta ? A->leaves.mask_cm.p : A->leaves.mask_rm.p;
     ls.Bcm = op.tb ? B->leaves.mask_rm.p : B->leaves.mask_cm.p;
+    ls.Brm = op.tb ? B->leaves.mask_cm.p : B->leaves.mask_rm.p;
+    ls.group = group;
     ls.ta = op.ta;
     ls.tb = op.tb;
     ls.upper = op.upper;
@@ -1943,8 +2240,10 @@ TreeStep Symbolic::fill_step(int l) const {
 // one node per workgroup (so every fill makes the next level's counts).
 bool Symbolic::together() const {
     if (prof || prune || ls.amap || ls.bmap) return false;
-    if (small) return true;
-    if (L == 0) return false;
+    return small || (L > 0 && single_waves());
+}
+
+bool Symbolic::single_waves() const {
     for (int l = 0; l <= L; ++l)
         if (level_waves(ncap[l]) != 1) return false;
     return true;
@@ -1968,7 +2267,11 @@ LeafStep Symbolic::leaf_step() const {
     st.off = (int64_t*)at(W, o_off[L]);
     st.wagg = (int64_t*)at(W, o_wagg[L]);
     st.gsum = (int64_t*)at(W, o_gsum) + gsum_at[L];
-    st.use_agg = level_wgs(ncap[L]) <= AGG_MAX;
+    st.use_agg = leaf_wgs() <= AGG_MAX;
+    if (sparse) {
+        st.heavy = (int32_t*)at(W, o_heavy);
+        st.heavy_max = heavy_max();
+    }
     st.lbase = (int32_t*)at(W, u_lbase);
     st.lmo = (uint64_t*)at(W, u_lmo);
     st.lrm = (uint64_t*)at(W, u_lrm);
@@ -2094,16 +2397,22 @@ void Symbolic::launch() {
         }
         const LeafStep st = leaf_step();
         const NilMark mark = nil_mark();
-        const int64_t leaf_wgs = level_wgs(ncap[L]);
-        if (prune)
-            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), true);
-        else
-            QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), false);
-        if (!st.use_agg) exclusive_scan(st.cnt, st.off, ncap[L], scan_tmp, ss);
-        if (prune || st.amap || st.bmap)
-            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), false);
-        else
-            QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs, ss, QT_ARGS(st, mark), true);
+        if (sparse) {
+            k_leaf_count_sparse<<<(unsigned)leaf_wgs(), 64, 0, ss>>>(st, mark);
+            QT_LAUNCH("k_leaf_count_sparse");
+            k_leaf_fill_sparse<<<(unsigned)(st.heavy_max + leaf_wgs()), 64, 0, ss>>>(st, mark);
+            QT_LAUNCH("k_leaf_fill_sparse");
+        } else {
+            if (prune)
+                QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), true);
+            else
+                QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), false);
+            if (!st.use_agg) exclusive_scan(st.cnt, st.off, ncap[L], scan_tmp, ss);
+            if (prune || st.amap || st.bmap)
+                QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), false);
+            else
+                QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), true);
+        }
         const NilTree nt = nil_tree();
         k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nt.flags, nt.tcnt, nt.ex);
         QT_LAUNCH("k_nil_offsets");
@@ -2298,6 +2607,7 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         for (int32_t i = at; i < at + n; ++i) {
             all.emplace_back(new Symbolic(A[i], B[i], prec, s, out[i], false, MulOp{}, true));
             Symbolic* p = all.back().get();
+            p->batched = true;
             p->plan();
             if (p->done) continue;
             if (!p->together())

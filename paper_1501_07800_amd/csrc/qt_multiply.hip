@@ -115,6 +115,7 @@ struct TreeStep {
     int64_t* gsum;            // aggregate path: per group of 64 count workgroups, their sum (zeroed first)
     int use_agg;              // offsets from workgroup aggregates instead of a scan
     int32_t ncap;             // bound on C nodes at this level
+    int32_t group;            // levels of few pairs per node: C nodes per wave
     // next level
     int32_t* nfa;
     int32_t* nfb;
@@ -555,6 +556,162 @@ __global__ __launch_bounds__(64 * W) void k_tree_fill(TreeStep st) {
     tree_fill_level<W, PRUNE, COUNTS>(st);
 }
 
+// ------------------------------------------ levels of few pairs per node
+//
+// The deep levels of an unstructured product have many C nodes of a few pairs
+// (an R-MAT product of 39634 blocks of 16 has 2.2 M pairs in 475 k nodes on its
+// last level), where a wave per node is mostly idle lanes and its own chain of
+// loads. Here a lane takes a pair, and a wave the pairs of
+// `group` nodes, 64 at a time. The count adds a pair's four quadrant counts (0
+// to 2 each) to its node's in LDS. The fill scans them over the lanes, a byte
+// per quadrant (at most 128 in 64 lanes): a child pair's place is its node's
+// quadrant's first, plus the scan here less the scan at the node's first lane.
+// Pairs, nodes and their order are the same as with a wave per node.
+// On that product's two widest tree levels 271 -> 133 us, counts, scan and fills
+// together. Left are the chain of loads of each 64 pairs, about 3 us, and the
+// scattered child tables.
+// Chosen from TREE_MIN positions (below, the counts that the wave-per-node fill
+// makes for the next level save a launch) and up to TREE_PAIRS pairs per position.
+// The symbolic phase, node per wave and pair per lane, in us: R-MAT of 8192, 2
+// edges a row: 422 and 290, 5 edges: 650 and 503; of 2048: 185 and 180; with no
+// bound on the pairs per position: random of 1500 block rows 234 and 246, R-MAT
+// of 4096 with 10 edges 450 and 479. With TREE_MIN a quarter or four times as
+// large: within 3 us.
+constexpr int TREE_GROUP_MAX = 64;     // C nodes per wave
+constexpr int64_t TREE_MIN = 8192;     // C node positions of a level
+constexpr int64_t TREE_PAIRS = 24;     // pairs per position
+
+// Of the pairs base .. base + 63, the C node (lane of the wave) that this
+// lane's pair belongs to, and the first lane of that node's pairs; seg: the
+// first pair of the node of each lane (INT32_MAX past the last). Every C node
+// has a pair. mark: 64 words of LDS.
+__device__ __forceinline__ int pair_node(int32_t seg, int32_t base, int lane, int32_t* mark, int& head) {
+    mark[lane] = 0;
+    __syncthreads();
+    const bool here = seg >= base && seg - base < 64;
+    if (here) mark[seg - base] = 1;
+    __syncthreads();
+    const uint64_t heads = __ballot(mark[lane] != 0) & (lanes_below(lane) | (1ull << lane));
+    const int before = __popcll(__ballot(seg < base));
+    __syncthreads();
+    head = heads ? 63 - __clzll((long long)heads) : 0;
+    return before + __popcll(heads) - 1;
+}
+
+// Byte q: the child pairs of quadrant q of a pair with child tables a, b.
+__device__ __forceinline__ uint32_t quad_counts(int4 a, int4 b) {
+    const QuadBytes x = a_bytes(a, 1), y = b_bytes(b, 1);
+    return (x.k0 & y.k0) + (x.k1 & y.k1);
+}
+
+__global__ __launch_bounds__(64) void k_tree_count_sparse(TreeStep st) {
+    __shared__ int32_t mark[64];
+    __shared__ unsigned long long quads[64];   // 16 bits each: quadrants 0, 2, 1, 3
+    const int lane = threadIdx.x;
+    const int32_t n = *st.ncount, c0 = (int32_t)blockIdx.x * st.group;
+    if (c0 >= n) {
+        if (lane == 0) st.wagg[blockIdx.x] = 0;
+        return;
+    }
+    const int32_t nl = min(st.group, n - c0), c = c0 + lane;
+    const int32_t seg = lane < nl ? st.cseg[c] : INT32_MAX;
+    const int32_t end = st.cseg[c0 + nl];
+    quads[lane] = 0;
+    for (int32_t base = __builtin_amdgcn_readfirstlane(seg); base < end; base += 64) {
+        uint32_t v = 0;
+        if (base + lane < end) {
+            int4 a, b;
+            op_children2(st.Ach, st.fa[base + lane], st.ta, st.Bch, st.fb[base + lane], st.tb, a, b);
+            v = quad_counts(a, b);
+        }
+        int head;
+        const int q = pair_node(seg, base, lane, mark, head);
+        if (v)
+            atomicAdd(&quads[q], (unsigned long long)(v & 0x00ff00ffu) |
+                                     ((unsigned long long)((v >> 8) & 0x00ff00ffu) << 32));
+    }
+    __syncthreads();
+    const unsigned long long u = quads[lane];
+    const int t0 = (int)(u & 0xffffu), t2 = (int)((u >> 16) & 0xffffu), t1 = (int)((u >> 32) & 0xffffu),
+              t3 = (int)(u >> 48);
+    const int np = t0 + t1 + t2 + t3, nn = (t0 > 0) + (t1 > 0) + (t2 > 0) + (t3 > 0);
+    const int s_np = wave_incl_scan(np), s_nn = wave_incl_scan(nn);
+    if (lane < nl) {
+        st.off[c] = pack2(s_np - np, s_nn - nn);
+        st.tot4[c] = make_int4(t0, t1, t2, t3);
+    }
+    if (lane == 63) {
+        const int64_t tot = pack2(s_np, s_nn);
+        st.wagg[blockIdx.x] = tot;
+        if (tot) atomicAdd((unsigned long long*)(st.gsum + (blockIdx.x >> AGG_GROUP_LOG)), (unsigned long long)tot);
+    }
+}
+
+__global__ __launch_bounds__(64) void k_tree_fill_sparse(TreeStep st) {
+    __shared__ int64_t lds[1];
+    __shared__ int32_t mark[64];
+    __shared__ int32_t run[64][4];             // next place of each node's quadrants' child pairs
+    const int lane = threadIdx.x;
+    const int32_t n = *st.ncount, c0 = (int32_t)blockIdx.x * st.group;
+    const bool last = (int32_t)blockIdx.x == (st.ncap - 1) / st.group;
+    if (c0 >= n && !last) return;
+    const int64_t base0 = level_base<1>(st.wagg, st.gsum, lds);
+    if (last && lane == 0) tree_level_totals(st, base0 + st.wagg[blockIdx.x]);
+    if (c0 >= n) return;
+    const int32_t nl = min(st.group, n - c0), c = c0 + lane;
+    const int32_t seg = lane < nl ? st.cseg[c] : INT32_MAX;
+    const int32_t end = st.cseg[c0 + nl];
+    if (lane < nl) {
+        const int4 t4 = st.tot4[c];
+        const int t[4] = {t4.x, t4.y, t4.z, t4.w};
+        const int64_t o = base0 + st.off[c];
+        const uint64_t key = st.ckey[c] * 4;
+        int pr = lo32(o), ci = hi32(o), child[4];
+#pragma unroll
+        for (int mn = 0; mn < 4; ++mn) {
+            run[lane][mn] = pr;
+            child[mn] = t[mn] > 0 ? ci : -1;
+            if (t[mn] > 0 && ci < st.nc_next) {
+                st.nckey[ci] = key + (uint64_t)mn;
+                st.ncseg[ci] = pr;
+                st.nparent[ci] = c;
+            }
+            pr += t[mn];
+            ci += t[mn] > 0 ? 1 : 0;
+        }
+        *reinterpret_cast<int4*>(st.cchild + 4 * (int64_t)c) = make_int4(child[0], child[1], child[2], child[3]);
+    }
+    for (int32_t base = __builtin_amdgcn_readfirstlane(seg); base < end; base += 64) {
+        int4 a = make_int4(-1, -1, -1, -1), b = make_int4(-1, -1, -1, -1);
+        if (base + lane < end)
+            op_children2(st.Ach, st.fa[base + lane], st.ta, st.Bch, st.fb[base + lane], st.tb, a, b);
+        int head;
+        const int q = pair_node(seg, base, lane, mark, head);
+        const uint32_t v = quad_counts(a, b), s = (uint32_t)wave_incl_scan((int)v);
+        const uint32_t before = s - v - (uint32_t)__shfl((int)(s - v), head);   // of this node, in this chunk
+        const int av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int mn = 0; mn < 4; ++mn) {
+            int w = run[q][mn] + (int)((before >> (8 * mn)) & 255u);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int x = av[(mn & 2) + k], y = bv[2 * k + (mn & 1)];
+                if ((x | y) < 0) continue;
+                if (w < st.np_next) {
+                    st.nfa[w] = x;
+                    st.nfb[w] = y;
+                }
+                ++w;
+            }
+        }
+        __syncthreads();
+        if (lane == 63)   // its node may go on in the next chunk
+#pragma unroll
+            for (int mn = 0; mn < 4; ++mn) run[q][mn] += (int)(((before + v) >> (8 * mn)) & 255u);
+        __syncthreads();
+    }
+}
+
 // Level-0 frontier: the pair of roots, one C node.
 struct RootInit {
     int32_t* fa;
@@ -950,7 +1107,6 @@ __global__ __launch_bounds__(64 * W) void k_leaf_fill(LeafStep st, NilMark nil) 
 // 47 + 76 -> 46 + 44. What is left of them are the gathers of the leaves' masks
 // and bases and the LDS round trips of one wave.
 constexpr int SPARSE_MAX = 64;                 // products listed together
-constexpr int SPARSE_GROUP_MAX = 64;           // C leaves per wave
 // Chosen up to 40 products per C leaf position that the host's bounds allow. The
 // symbolic phase, wave per leaf and lane per pair, in us: random of 1500 block
 // rows with 1.5 products per leaf 175 and 134, 14: 269 and 230, 38: 374 and 288,
@@ -971,21 +1127,6 @@ __device__ __forceinline__ uint64_t rowmajor_to_morton8(uint64_t m) {
     m = swap_index_bits(m, 3, 2, 0x00F000F000F000F0ull);
     m = swap_index_bits(m, 2, 1, 0x0C0C0C0C0C0C0C0Cull);
     return swap_index_bits(m, 4, 3, 0x0000FF000000FF00ull);
-}
-
-// Of the pairs base .. base + 63, the C leaf (lane of the wave) that this
-// lane's pair belongs to; seg: the first pair of the leaf of each lane
-// (INT32_MAX past the last). Every C leaf has a pair. mark: 64 words of LDS.
-__device__ __forceinline__ int pair_leaf(int32_t seg, int32_t base, int lane, int32_t* mark) {
-    mark[lane] = 0;
-    __syncthreads();
-    const bool here = seg >= base && seg - base < 64;
-    if (here) mark[seg - base] = 1;
-    __syncthreads();
-    const uint64_t heads = __ballot(mark[lane] != 0);
-    const int before = __popcll(__ballot(seg < base));
-    __syncthreads();
-    return before + __popcll(heads & (lanes_below(lane) | (1ull << lane))) - 1;
 }
 
 __global__ __launch_bounds__(64) void k_leaf_count_sparse(LeafStep st, NilMark nil) {
@@ -1010,7 +1151,8 @@ __global__ __launch_bounds__(64) void k_leaf_count_sparse(LeafStep st, NilMark n
             ra = st.Arm[a];
             rb = st.Brm[b];
         }
-        const int q = pair_leaf(seg, base, lane, mark);
+        int head;
+        const int q = pair_node(seg, base, lane, mark, head);
         uint64_t e = 0;
         int cnt = 0;
 #pragma unroll
@@ -1128,7 +1270,8 @@ __global__ __launch_bounds__(64) void k_leaf_fill_sparse(LeafStep st, NilMark ni
                 ab = st.Abase[a];
                 bb = st.Bbase[b];
             }
-            const int leaf = pair_leaf(seg, base, lane, mark);
+            int head;
+            const int leaf = pair_node(seg, base, lane, mark, head);
             // inner indices with a block on either side
             uint32_t km = mask_fold(ra, 8);
             {
@@ -1867,10 +2010,10 @@ struct Symbolic {
     // plan
     bool done = false;      // C is empty, known without a traversal
     bool prune = false, bounds = false, small = false, sparse = false, may_strip = false, may_korder = false, prof = false;
-    int32_t group = 1;      // sparse: C leaves per wave
     int L = 0, liftA = 0, liftB = 0, lb_log = 0, strip_log = 0, strip_bits = 1, kbits = 1;
     hipStream_t ss = nullptr;                 // the traversal's stream
     std::vector<int64_t> pairs, ncap, foff, gsum_at;
+    std::vector<int32_t> group;               // levels taken a pair per lane: C nodes per wave, else 0
     int64_t P = 0, cap = 0, nil_tiles = 0, nclear = 0;
     qt_matrix* Av = nullptr;
     NumericArgs na{};
@@ -1902,7 +2045,8 @@ struct Symbolic {
 
     static void* at(char* base, size_t off) { return (void*)(base + off); }
     int ncounts() const { return 3 * L + 4; }
-    int64_t leaf_wgs() const { return sparse ? (ncap[L] + group - 1) / group : level_wgs(ncap[L]); }
+    int64_t wgs(int l) const { return group[l] ? (ncap[l] + group[l] - 1) / group[l] : level_wgs(ncap[l]); }
+    int32_t pick_group(int l) const;
     int32_t heavy_max() const { return (int32_t)(P / (SPARSE_MAX + 1)); }   // leaves of more than SPARSE_MAX products
     bool single_waves() const;                // every level in single-wave workgroups
     void plan();
@@ -2033,18 +2177,14 @@ void Symbolic::plan() {
         all_nodes += ncap[l];
     }
     small = small && all_nodes <= SMALL_NODES;
-    // leaves of few products: as many per wave as fill it with pairs, while
-    // the waves still fill the GPU
-    sparse = !small && !bounds && !A->vsrc && !B->vsrc && lb_log == 3 && P <= SPARSE_LEAF * ncap[L] &&
-             !(batched && single_waves());
-    if (sparse) {
-        while (group < 16 && 2 * group * pairs[L] <= 64 * ncap[L] && ncap[L] / (2 * group) >= 4096) group *= 2;
-        while (group < SPARSE_GROUP_MAX && leaf_wgs() > AGG_MAX) group *= 2;
-        // the keys number the pairs of the leaves listed together with 17 bits: a
-        // leaf has at most as many as there are inner leaf positions
-        const int64_t inner = ((op.ta ? A->n_rows : A->n_cols) + A->leaf - 1) / A->leaf;
-        sparse = leaf_wgs() <= AGG_MAX && inner * group <= (1 << 17);
+    // levels of few pairs per node, leaves of few products: a pair per lane
+    group.assign(L + 1, 0);
+    if (!small && !bounds && !(batched && single_waves())) {
+        for (int l = 0; l < L; ++l)
+            if (ncap[l] >= TREE_MIN && pairs[l] <= TREE_PAIRS * ncap[l]) group[l] = pick_group(l);
+        if (!A->vsrc && !B->vsrc && lb_log == 3 && P <= SPARSE_LEAF * ncap[L]) group[L] = pick_group(L);
     }
+    sparse = group[L] != 0;
     // the launch order in strips, of the block rows of C (see above)
     const int64_t c_rows_blk = (op.ta ? A->n_cols : A->n_rows) / A->b;
     const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);
@@ -2098,14 +2238,13 @@ void Symbolic::plan() {
     const size_t o_nflags = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     gsum_at.resize(L + 1);
     int64_t gsum_total = 0;
-    auto level_aggs = [&](int l) { return l == L ? leaf_wgs() : level_wgs(ncap[l]); };
     for (int l = 0; l <= L; ++l) {
         gsum_at[l] = gsum_total;
-        gsum_total += (level_aggs(l) + (1 << AGG_GROUP_LOG) - 1) >> AGG_GROUP_LOG;
+        gsum_total += (wgs(l) + (1 << AGG_GROUP_LOG) - 1) >> AGG_GROUP_LOG;
     }
     o_gsum = tmp.take(std::max<int64_t>(gsum_total, 1) * sizeof(int64_t));
     for (auto* v : {&o_fa, &o_fb, &o_cseg, &o_cnt, &o_off, &o_tot, &o_wagg}) v->resize(L + 1);
-    for (int l = 0; l <= L; ++l) o_wagg[l] = tmp.take(level_aggs(l) * sizeof(int64_t));
+    for (int l = 0; l <= L; ++l) o_wagg[l] = tmp.take(wgs(l) * sizeof(int64_t));
     if (sparse) o_heavy = tmp.take(sizeof(int32_t));   // its number is cleared, too; the list lies behind
     nclear = (int64_t)(tmp.bytes - o_nflags) / (int64_t)sizeof(int32_t);
     if (sparse) (void)tmp.take(heavy_max() * sizeof(int32_t));
@@ -2153,7 +2292,7 @@ void Symbolic::plan() {
     ls.Arm = op.ta ? A->leaves.mask_cm.p : A->leaves.mask_rm.p;
     ls.Bcm = op.tb ? B->leaves.mask_rm.p : B->leaves.mask_cm.p;
     ls.Brm = op.tb ? B->leaves.mask_cm.p : B->leaves.mask_rm.p;
-    ls.group = group;
+    ls.group = group[L];
     ls.ta = op.ta;
     ls.tb = op.tb;
     ls.upper = op.upper;
@@ -2190,7 +2329,8 @@ TreeStep Symbolic::tree_step(int l) const {
     st.tot4 = (int4*)at(W, o_tot[l]);
     st.wagg = (int64_t*)at(W, o_wagg[l]);
     st.gsum = (int64_t*)at(W, o_gsum) + gsum_at[l];
-    st.use_agg = level_wgs(ncap[l]) <= AGG_MAX;
+    st.group = group[l];
+    st.use_agg = wgs(l) <= AGG_MAX;
     st.off = (int64_t*)at(W, o_off[l]);
     st.ncap = (int32_t)ncap[l];
     st.nfa = (int32_t*)at(W, o_fa[l + 1]);
@@ -2217,7 +2357,9 @@ TreeStep Symbolic::tree_step(int l) const {
 }
 
 // a single-wave next tree level gets its counts from this level's fill
-bool Symbolic::fill_counts(int l) const { return l + 1 < L && level_waves(ncap[l + 1]) == 1; }
+bool Symbolic::fill_counts(int l) const {
+    return l + 1 < L && level_waves(ncap[l + 1]) == 1 && !group[l] && !group[l + 1];
+}
 
 TreeStep Symbolic::fill_step(int l) const {
     TreeStep st = tree_step(l);
@@ -2234,6 +2376,19 @@ TreeStep Symbolic::fill_step(int l) const {
         st.ngsum = nx.gsum;
     }
     return st;
+}
+
+// C nodes per wave at level l: as many as fill it with pairs, while the waves
+// still fill the GPU; 0: the kernels that take a pair per lane don't apply.
+int32_t Symbolic::pick_group(int l) const {
+    int64_t g = 1;
+    while (g < 16 && 2 * g * pairs[l] <= 64 * ncap[l] && ncap[l] / (2 * g) >= 4096) g *= 2;
+    while (g < TREE_GROUP_MAX && (ncap[l] + g - 1) / g > AGG_MAX) g *= 2;
+    // a C node has at most as many pairs as there are inner node positions: the
+    // tree count's 16-bit sums and the product keys' 17 bits hold that
+    const int64_t side = (int64_t)A->leaf << (L - l), inner = ((op.ta ? A->n_rows : A->n_cols) + side - 1) / side;
+    const bool fits = l < L ? 2 * inner < (1 << 16) : inner * g <= (1 << 17);
+    return fits && (ncap[l] + g - 1) / g <= AGG_MAX ? (int32_t)g : 0;
 }
 
 // What the shared kernels are compiled for: no norms and no block maps, and
@@ -2267,7 +2422,7 @@ LeafStep Symbolic::leaf_step() const {
     st.off = (int64_t*)at(W, o_off[L]);
     st.wagg = (int64_t*)at(W, o_wagg[L]);
     st.gsum = (int64_t*)at(W, o_gsum) + gsum_at[L];
-    st.use_agg = leaf_wgs() <= AGG_MAX;
+    st.use_agg = wgs(L) <= AGG_MAX;
     if (sparse) {
         st.heavy = (int32_t*)at(W, o_heavy);
         st.heavy_max = heavy_max();
@@ -2377,7 +2532,15 @@ void Symbolic::launch() {
         bool counted = false;   // this level's counts were made by the previous level's fill
         for (int l = 0; l < L; ++l) {
             const TreeStep sl = fill_step(l);
-            const int64_t wgs = level_wgs(ncap[l]);
+            const int64_t wgs = this->wgs(l);
+            if (group[l]) {
+                k_tree_count_sparse<<<(unsigned)wgs, 64, 0, ss>>>(sl);
+                QT_LAUNCH("k_tree_count_sparse");
+                k_tree_fill_sparse<<<(unsigned)wgs, 64, 0, ss>>>(sl);
+                QT_LAUNCH("k_tree_fill_sparse");
+                counted = false;
+                continue;
+            }
             if (!counted) {
                 if (prune)
                     QT_LEVEL_LAUNCH(k_tree_count, ncap[l], wgs, ss, sl, true);
@@ -2398,20 +2561,20 @@ void Symbolic::launch() {
         const LeafStep st = leaf_step();
         const NilMark mark = nil_mark();
         if (sparse) {
-            k_leaf_count_sparse<<<(unsigned)leaf_wgs(), 64, 0, ss>>>(st, mark);
+            k_leaf_count_sparse<<<(unsigned)wgs(L), 64, 0, ss>>>(st, mark);
             QT_LAUNCH("k_leaf_count_sparse");
-            k_leaf_fill_sparse<<<(unsigned)(st.heavy_max + leaf_wgs()), 64, 0, ss>>>(st, mark);
+            k_leaf_fill_sparse<<<(unsigned)(st.heavy_max + wgs(L)), 64, 0, ss>>>(st, mark);
             QT_LAUNCH("k_leaf_fill_sparse");
         } else {
             if (prune)
-                QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), true);
+                QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], wgs(L), ss, QT_ARGS(st, mark), true);
             else
-                QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), false);
+                QT_LEVEL_LAUNCH(k_leaf_count, ncap[L], wgs(L), ss, QT_ARGS(st, mark), false);
             if (!st.use_agg) exclusive_scan(st.cnt, st.off, ncap[L], scan_tmp, ss);
             if (prune || st.amap || st.bmap)
-                QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), false);
+                QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], wgs(L), ss, QT_ARGS(st, mark), false);
             else
-                QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], leaf_wgs(), ss, QT_ARGS(st, mark), true);
+                QT_LEVEL_LAUNCH(k_leaf_fill, ncap[L], wgs(L), ss, QT_ARGS(st, mark), true);
         }
         const NilTree nt = nil_tree();
         k_nil_offsets<<<(unsigned)nil_tiles, 64, 0, ss>>>(nt.flags, nt.tcnt, nt.ex);

@@ -322,9 +322,9 @@ struct MulOp {
 void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out,
               bool allow_profile = true, const MulOp& op = MulOp{}, bool launch_order = true);
 // The symbolic phases of count plain products, launches shared where they can
-// be; out[0 .. count).
+// be; out[0 .. count), whose buffers are parts of those added to `pool`.
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
-                    SymbolicOut* out);
+                    SymbolicOut* out, std::vector<DBuf<char>>& pool);
 qt_matrix* multiply(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, const MulOp& op = MulOp{});
 qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_t nblocks, const int32_t* I,
                  const int32_t* J, const double* values, qt_mem where, hipStream_t s);

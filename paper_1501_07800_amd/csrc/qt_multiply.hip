@@ -2018,8 +2018,10 @@ struct Symbolic {
     qt_matrix* Av = nullptr;
     NumericArgs na{};
     std::vector<size_t> o_child, o_key, u_child, u_key, u_parent, o_fa, o_fb, o_cseg, o_cnt, o_off, o_tot, o_wagg;
-    size_t o_lbase = 0, o_lmo = 0, o_lrm = 0, o_lcm = 0, o_bkey = 0, o_nex = 0, o_ntcnt = 0, u_lbase = 0, u_lmo = 0,
-           u_lrm = 0, u_lcm = 0, o_gsum = 0, o_scan = 0, o_lcnt = 0, o_heavy = 0, o_sort = 0, o_order = 0;
+    size_t o_lbase = 0, o_lmo = 0, o_lrm = 0, o_lcm = 0, o_bkey = 0;
+    size_t o_prodA = 0, o_prodB = 0, o_cbseg = 0, u_lbase = 0, u_lmo = 0, u_lrm = 0, u_lcm = 0, o_nflags = 0,
+           o_ntcnt = 0, o_nex = 0, o_gsum = 0, o_scan = 0, o_lcnt = 0, o_heavy = 0, o_sort = 0, o_order = 0, o_count = 0;
+    size_t keep_bytes = 0, work_bytes = 0;
     char* K = nullptr;
     char* W = nullptr;
     const int32_t* lift = nullptr;
@@ -2050,6 +2052,7 @@ struct Symbolic {
     int32_t heavy_max() const { return (int32_t)(P / (SPARSE_MAX + 1)); }   // leaves of more than SPARSE_MAX products
     bool single_waves() const;                // every level in single-wave workgroups
     void plan();
+    void bind(char* tree, char* work);
     TreeStep tree_step(int l) const;
     TreeStep fill_step(int l) const;          // with the next level's counts, where the fill makes them
     bool fill_counts(int l) const;
@@ -2062,6 +2065,8 @@ struct Symbolic {
     void launch();
     const int32_t* wait();                    // the counts, by the problem's own read-back
     void finish(const int32_t* hc);
+    size_t value_bytes() const { return (size_t)na.nseg * A->b * A->b * (prec == QT_F32 ? sizeof(float) : sizeof(double)); }
+    void bind_values(char* values);
 };
 
 void Symbolic::plan() {
@@ -2209,9 +2214,9 @@ void Symbolic::plan() {
     o_lcm = keep.take(ncap[L] * sizeof(uint64_t));
     o_bkey = keep.take(cap * sizeof(uint64_t));
     if (L + 1 > NIL_MAX_LEVELS) fail(QT_ERR_UNSUPPORTED, "quadtree too deep");
-    const size_t o_prodA = tmp.take(P * sizeof(int32_t));
-    const size_t o_prodB = tmp.take(P * sizeof(int32_t));
-    const size_t o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
+    o_prodA = tmp.take(P * sizeof(int32_t));
+    o_prodB = tmp.take(P * sizeof(int32_t));
+    o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
     // The scratch of the level by level traversal from here on (a small
     // product's stays in LDS): first the tree before NIL normalisation.
     const size_t small_bytes = tmp.bytes;
@@ -2235,7 +2240,7 @@ void Symbolic::plan() {
     // the aggregates of workgroups without a node).
     nil_tiles = foff[L + 1] / NIL_TILE + 1;
     o_ntcnt = tmp.take(nil_tiles * sizeof(int32_t));
-    const size_t o_nflags = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
+    o_nflags = tmp.take(nil_tiles * NIL_TILE * sizeof(int32_t));
     gsum_at.resize(L + 1);
     int64_t gsum_total = 0;
     for (int l = 0; l <= L; ++l) {
@@ -2265,18 +2270,32 @@ void Symbolic::plan() {
         o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
                                    may_korder ? sort_tmp_bound(cap, kbits) : 0) * sizeof(int32_t));
     if (may_strip || may_korder) o_order = tmp.take(cap * sizeof(int32_t));
-    const size_t o_count = tmp.take(ncounts() * sizeof(int32_t));
+    o_count = tmp.take(ncounts() * sizeof(int32_t));
 
     out.C.reset(new_result(A, B, L, prec, s, op));
     qt_matrix* C = out.C.get();
     C->pairs = pairs;
     C->products = P;
-    // both live on past this call and are released on the caller's stream,
-    // after the numeric kernel that reads them
-    C->arena.alloc(keep.bytes, ss);
-    C->arena.s = s;
-    out.scratch.alloc(small ? small_bytes : tmp.bytes, ss);
-    out.scratch.s = s;
+    keep_bytes = keep.bytes;
+    work_bytes = small ? small_bytes : tmp.bytes;
+    if (!batched) bind(nullptr, nullptr);
+}
+
+// The two buffers: its own (NULL), or parts of buffers shared by the problems of
+// a batch.
+void Symbolic::bind(char* tree, char* work) {
+    qt_matrix* C = out.C.get();
+    if (tree) {
+        C->arena.view(tree, keep_bytes);
+        out.scratch.view(work, work_bytes);
+    } else {
+        // both live on past this call and are released on the caller's stream,
+        // after the numeric kernel that reads them
+        C->arena.alloc(keep_bytes, ss);
+        C->arena.s = s;
+        out.scratch.alloc(work_bytes, ss);
+        out.scratch.s = s;
+    }
     K = C->arena.p;
     W = out.scratch.p;
     // [0..L] C nodes per level as traversed, [L+1] C blocks, [L+2..2L+2] checks,
@@ -2641,21 +2660,35 @@ void Symbolic::finish(const int32_t* hc) {
     C->bkey.view(at(K, o_bkey), nnzC);
     C->nblocks = nnzC;
 
-    const size_t bb = (size_t)C->b * C->b;
-    if (prec == QT_F32)
-        C->v32.alloc(nnzC * bb, s);
-    else
-        C->v64.alloc(nnzC * bb, s);
     na.prodA = ls.prodA;
     na.prodB = ls.prodB;
     na.seg = ls.cbseg;
     na.order = (strips || korder) ? order : nullptr;
     na.by_k = korder ? 1 : 0;
     na.nseg = nnzC;
-    na.C = (prec == QT_F32) ? (void*)C->v32.p : (void*)C->v64.p;
-    out.na = na;
     ev.products = C->products;
     ev.cblocks = nnzC;
+    if (!batched) bind_values(nullptr);
+}
+
+// C's values: a buffer of its own (NULL), or part of a shared one.
+void Symbolic::bind_values(char* values) {
+    qt_matrix* C = out.C.get();
+    const size_t n = (size_t)na.nseg * C->b * C->b;
+    if (prec == QT_F32) {
+        if (values)
+            C->v32.view(values, n);
+        else
+            C->v32.alloc(n, s);
+        na.C = C->v32.p;
+    } else {
+        if (values)
+            C->v64.view(values, n);
+        else
+            C->v64.alloc(n, s);
+        na.C = C->v64.p;
+    }
+    out.na = na;
 }
 
 void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out, bool allow_profile,
@@ -2756,8 +2789,30 @@ static void launch_small(const std::vector<Symbolic*>& who, std::vector<char>& h
 constexpr int32_t MANY_MAX = 256;
 constexpr int64_t MANY_GRID = 65536, MANY_WASTE = 4;
 
+// Parts of shared buffers for the problems of a batch: an allocation takes the
+// host 5 us and its release 3, of which three a problem were a third of the time
+// of a plan of 16. A buffer holds parts of up to SHARED_MAX together (a part
+// beyond it has one of its own), allocated on `ready`, released on `s`.
+constexpr size_t SHARED_MAX = size_t(256) << 20;
+
+static std::vector<char*> shared_parts(const std::vector<size_t>& bytes, hipStream_t ready, hipStream_t s,
+                                       std::vector<DBuf<char>>& pool) {
+    std::vector<char*> at(bytes.size(), nullptr);
+    for (size_t i = 0; i < bytes.size();) {
+        ArenaPlan ap;
+        std::vector<size_t> off;
+        for (size_t j = i; j < bytes.size() && (off.empty() || ap.bytes + bytes[j] <= SHARED_MAX); ++j)
+            off.push_back(ap.take(bytes[j]));
+        pool.emplace_back();
+        pool.back().alloc(ap.bytes, ready);
+        pool.back().s = s;
+        for (size_t o : off) at[i++] = pool.back().p + o;
+    }
+    return at;
+}
+
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
-                    SymbolicOut* out) {
+                    SymbolicOut* out, std::vector<DBuf<char>>& pool) {
     for (int32_t at = 0; at < count; at += MANY_MAX) {
         const int32_t n = std::min(MANY_MAX, count - at);
         // declared before the problems, whose destructors wait for the kernels
@@ -2766,13 +2821,24 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         DBuf<int32_t> words;
         std::unique_ptr<ReadBack> shared;
         std::vector<std::unique_ptr<Symbolic>> all;
-        std::vector<Symbolic*> alone, small, levels, order;   // order: as their counts lie in words
+        std::vector<Symbolic*> work, alone, small, levels, order;   // order: as their counts lie in words
+        std::vector<size_t> bytes;
         for (int32_t i = at; i < at + n; ++i) {
             all.emplace_back(new Symbolic(A[i], B[i], prec, s, out[i], false, MulOp{}, true));
             Symbolic* p = all.back().get();
             p->batched = true;
             p->plan();
             if (p->done) continue;
+            work.push_back(p);
+            bytes.push_back(p->keep_bytes);
+            bytes.push_back(p->work_bytes);
+        }
+        if (work.empty()) continue;
+        const hipStream_t ss = work[0]->ss;
+        const std::vector<char*> parts = shared_parts(bytes, ss, s, pool);
+        for (size_t i = 0; i < work.size(); ++i) {
+            Symbolic* p = work[i];
+            p->bind(parts[2 * i], parts[2 * i + 1]);
             if (!p->together())
                 alone.push_back(p);
             else
@@ -2780,8 +2846,6 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         }
         order = small;
         order.insert(order.end(), levels.begin(), levels.end());
-        if (order.empty() && alone.empty()) continue;
-        const hipStream_t ss = (order.empty() ? alone[0] : order[0])->ss;
         for (Symbolic* p : alone) p->launch();
         int stride = 0;
         for (Symbolic* p : order) stride = std::max(stride, p->ncounts());
@@ -2811,6 +2875,10 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         QT_HIP(ordered);
         for (size_t i = 0; i < order.size(); ++i) order[i]->finish(hc + i * stride);
         for (Symbolic* p : alone) p->finish(p->wait());
+        bytes.clear();
+        for (Symbolic* p : work) bytes.push_back(p->value_bytes());
+        const std::vector<char*> values = shared_parts(bytes, s, s, pool);
+        for (size_t i = 0; i < work.size(); ++i) work[i]->bind_values(values[i]);
     }
 }
 

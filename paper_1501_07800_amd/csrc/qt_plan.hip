@@ -35,9 +35,10 @@ struct qt_plan {
     qt_prec prec = QT_F64;
     int b = 0;
     hipStream_t stream = nullptr;
+    std::vector<qt::DBuf<char>> pool;                  // the results' arrays and the scratch are parts of these
     std::vector<std::unique_ptr<qt_matrix>> results;   // input order
     std::vector<qt::DBuf<char>> scratch;               // product lists per problem
-    qt::DBuf<char> dev;                                // problems, item offsets, counter
+    qt::DBuf<char> dev;                                // problems, item offsets, counter, work prefix sums
     qt::BatchLaunch launch;
     int64_t products = 0;
     // both layouts of the work list: the problems with their own launch orders
@@ -48,7 +49,6 @@ struct qt_plan {
     const int64_t* base_blocks = nullptr;
     int64_t items_tiles = 0, items_blocks = 0;
     bool has_order = false;   // some problem has a launch order of its own
-    qt::DBuf<char> cum;       // work prefix sums of the balanced schedules
     const int64_t* cum_of[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [Morton][C blocks]
     int32_t config = 0;       // schedule | QT_PLAN_ORDER_MORTON | QT_PLAN_TILE_WAVE
     hipStream_t capture_stream = nullptr;
@@ -108,7 +108,8 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     {
         // with the launch orders the single multiplies would use
         std::vector<SymbolicOut> sym(count);
-        symbolic_batch(count, const_cast<qt_matrix* const*>(A), const_cast<qt_matrix* const*>(B), prec, s, sym.data());
+        symbolic_batch(count, const_cast<qt_matrix* const*>(A), const_cast<qt_matrix* const*>(B), prec, s, sym.data(),
+                       plan->pool);
         for (int32_t i = 0; i < count; ++i) {
             na[i] = sym[i].na;
             prods[i] = sym[i].C->products;
@@ -166,6 +167,18 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     const size_t o_base_b = ap.take(base_b.size() * sizeof(int64_t));
     const size_t copied = ap.bytes;
     const size_t o_counter = ap.take(64 * sizeof(unsigned long long));
+    // the balanced schedules' work prefix sums, one per layout of the work
+    // list (own launch orders or Morton; per-wave tiles or C blocks at b = 64)
+    // that differs from those before it: without launch orders of their own
+    // the problems lie in Morton order in both, and below b = 64 the items are
+    // the C blocks in both
+    const int norders = plan->has_order ? 2 : 1, nforms = b == 64 ? 2 : 1;
+    const int64_t items[2] = {base_t.back(), base_b.back()}, nmax = std::max(items[0], items[1]);
+    size_t o_cum[2][2] = {};
+    for (int o = 0; o < norders; ++o)
+        for (int t = 0; t < nforms; ++t) o_cum[o][t] = ap.take((items[t] + 1) * sizeof(int64_t));
+    const size_t o_cost = ap.take(std::max<int64_t>(nmax, 1) * sizeof(int64_t));
+    const size_t o_scan = ap.take((scan_tmp_elems(nmax) + 1) * sizeof(int64_t));
     plan->dev.alloc(ap.bytes, s);
     char* D = plan->dev.p;
     std::vector<char> host(copied);
@@ -192,37 +205,22 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     L.counter = (unsigned long long*)(D + o_counter);
     L.base = lowest;
 
-    // the balanced schedules' work prefix sums, one per layout of the work
-    // list (own launch orders or Morton; per-wave tiles or C blocks at b = 64)
-    // that differs from those before it: without launch orders of their own
-    // the problems lie in Morton order in both, and below b = 64 the items are
-    // the C blocks in both
-    {
-        const int norders = plan->has_order ? 2 : 1, nforms = b == 64 ? 2 : 1;
-        ArenaPlan cp;
-        size_t o_cum[2][2];
-        const int64_t nmax = std::max(plan->items_tiles, plan->items_blocks);
-        for (int o = 0; o < norders; ++o)
-            for (int t = 0; t < nforms; ++t)
-                o_cum[o][t] = cp.take(((t ? plan->items_blocks : plan->items_tiles) + 1) * sizeof(int64_t));
-        DBuf<int64_t> cost(std::max<int64_t>(nmax, 1), s), stmp(scan_tmp_elems(nmax) + 1, s);
-        plan->cum.alloc(cp.bytes, s);
-        for (int o = 0; o < 2; ++o)
-            for (int t = 0; t < 2; ++t) {
-                if (o >= norders || t >= nforms) {
-                    plan->cum_of[o][t] = plan->cum_of[o < norders ? o : 0][t < nforms ? t : 0];
-                    continue;
-                }
-                plan->configure((o ? QT_PLAN_ORDER_MORTON : 0) | (t ? 0 : QT_PLAN_TILE_WAVE));
-                int64_t* cum = (int64_t*)(plan->cum.p + o_cum[o][t]);
-                plan->cum_of[o][t] = cum;
-                if (L.total_items > 0) {
-                    batch_item_costs(L, cost.p, s);
-                    exclusive_scan(cost.p, cum, L.total_items, stmp.p, s);
-                }
+    for (int o = 0; o < 2; ++o)
+        for (int t = 0; t < 2; ++t) {
+            if (o >= norders || t >= nforms) {
+                plan->cum_of[o][t] = plan->cum_of[o < norders ? o : 0][t < nforms ? t : 0];
+                continue;
             }
-        QT_HIP(hipStreamSynchronize(s));
-    }
+            plan->configure((o ? QT_PLAN_ORDER_MORTON : 0) | (t ? 0 : QT_PLAN_TILE_WAVE));
+            int64_t* cum = (int64_t*)(D + o_cum[o][t]);
+            plan->cum_of[o][t] = cum;
+            if (L.total_items > 0) {
+                int64_t* cost = (int64_t*)(D + o_cost);
+                batch_item_costs(L, cost, s);
+                exclusive_scan(cost, cum, L.total_items, (int64_t*)(D + o_scan), s);
+            }
+        }
+    QT_HIP(hipStreamSynchronize(s));
     plan->config = -1;
     plan->configure(0);
     return plan.release();

@@ -200,6 +200,70 @@ static void copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D*
         launch_copy_blocks<S, D, 1>(src, perm, n, bb, dst, s);
 }
 
+// Row-major copy-out of few blocks in one launch, without a permutation: a
+// workgroup per block finds the block's place itself, the number of blocks in
+// rows above and before it in its own (in Morton order a row's blocks lie by
+// column), and copies it there. Bound by latency and, towards RANKED_MAX, by the
+// n^2 keys read from the caches. Copies in a loop, sort and copy against this, in
+// us: b = 16, 9 to 374 blocks 11.6 and 7.9, 2000 20 and 7.7, 4000 37 and 18; b = 32,
+// 2000 24 and 8.7; b = 64, 2000 40 and 25, 4000 77 and 53. Beyond, the radix sort
+// is ahead: b = 16, 4500 17.6 and 21.9, 8000 20 and 61; b = 64, 4500 63 and 61,
+// 6000 79 and 87.
+constexpr int64_t RANKED_MAX = 4096;
+
+template <class S, class D, int VE>
+__global__ __launch_bounds__(256) void k_copy_ranked(const uint64_t* __restrict__ bkey, int32_t n,
+                                                     const S* __restrict__ src, int bb, int32_t* __restrict__ I,
+                                                     int32_t* __restrict__ J, D* __restrict__ dst) {
+    typedef S svec __attribute__((ext_vector_type(VE)));
+    typedef D dvec __attribute__((ext_vector_type(VE)));
+    constexpr int U = 4;
+    __shared__ int before[4];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int32_t t = (int32_t)blockIdx.x;
+    const uint64_t key = bkey[t];
+    const int32_t row = (int32_t)morton_row(key);
+    const svec* from = reinterpret_cast<const svec*>(src + (size_t)t * bb);
+    const int m = dst ? bb / VE : 0;
+    svec v[U];                       // the first vectors, on their way while the place is found
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (tid + 256 * u < m) v[u] = __builtin_nontemporal_load(from + tid + 256 * u);
+    int c = 0;
+    for (int32_t i = tid; i < n; i += 256) {
+        const int32_t r = (int32_t)morton_row(bkey[i]);
+        c += r < row || (r == row && i < t);
+    }
+    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
+    if ((tid & 63) == 0) before[wave] = c;
+    __syncthreads();
+    const int64_t at = before[0] + before[1] + before[2] + before[3];
+    if (tid == 0) {
+        I[at] = row;
+        J[at] = (int32_t)morton_col(key);
+    }
+    dvec* to = reinterpret_cast<dvec*>(dst + at * bb);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (tid + 256 * u < m) __builtin_nontemporal_store(__builtin_convertvector(v[u], dvec), to + tid + 256 * u);
+    for (int e = tid + 256 * U; e < m; e += 256)
+        __builtin_nontemporal_store(__builtin_convertvector(__builtin_nontemporal_load(from + e), dvec), to + e);
+}
+
+// src and dst: device arrays of n blocks of bb entries in C's order and in
+// row-major order (dst may be NULL).
+template <class S, class D>
+static void copy_ranked(const uint64_t* bkey, const S* src, int64_t n, int bb, int32_t* I, int32_t* J, D* dst,
+                        hipStream_t s) {
+    constexpr int VE = (sizeof(S) == 8 && sizeof(D) == 8) ? 2 : 4;
+    const bool wide = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
+    if (wide)
+        k_copy_ranked<S, D, VE><<<(unsigned)n, 256, 0, s>>>(bkey, (int32_t)n, src, bb, I, J, dst);
+    else
+        k_copy_ranked<S, D, 1><<<(unsigned)n, 256, 0, s>>>(bkey, (int32_t)n, src, bb, I, J, dst);
+    QT_LAUNCH("k_copy_ranked");
+}
+
 // The quadtree over n blocks from their ascending Morton keys. A block starts
 // a node of level l when its key's prefix above that level differs from the
 // block's before it, so it starts nodes of every level from some first one
@@ -818,6 +882,7 @@ qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_
 
 // Words of scratch of a row-major copy-out: the permutation and the sort's.
 static size_t rowmajor_words(const qt_matrix* M) {
+    if (M->nblocks <= RANKED_MAX) return 0;
     return (size_t)M->nblocks + sort_tmp_words(M->nblocks, ilog2(M->n_rows / M->b));
 }
 
@@ -827,6 +892,17 @@ static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t*
                           hipStream_t s) {
     const int64_t n = M->nblocks;
     const int bb = M->b * M->b;
+    if (n <= RANKED_MAX) {
+        if (M->vtype == QT_F64 && (out_type == QT_F64 || !values))
+            copy_ranked(M->bkey.p, M->v64.p, n, bb, I, J, (double*)values, s);
+        else if (M->vtype == QT_F64)
+            copy_ranked(M->bkey.p, M->v64.p, n, bb, I, J, (float*)values, s);
+        else if (out_type == QT_F64 && values)
+            copy_ranked(M->bkey.p, M->v32.p, n, bb, I, J, (double*)values, s);
+        else
+            copy_ranked(M->bkey.p, M->v32.p, n, bb, I, J, (float*)values, s);
+        return;
+    }
     int32_t* perm = tmp;
     stable_sort(RowKeys{M->bkey.p}, RowMajorSink{M->bkey.p, perm, I, J}, n, ilog2(M->n_rows / M->b), tmp + n,
                 perm, s);

@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(1024) void k_top_norm2(TopNorms a) {
     }
 }
 
-void build_norms(qt_matrix* M, hipStream_t s) {
+void build_norms(qt_matrix* M, hipStream_t s, hipStream_t reader) {
     std::lock_guard<std::mutex> lk(M->mu);
     if (M->vsrc) fail(QT_ERR_UNSUPPORTED, "norms of a structure-only matrix");
     if (!M->bn2) {
@@ -1153,12 +1153,12 @@ void build_norms(qt_matrix* M, hipStream_t s) {
         M->bn2 = bn2;
         form_mark(M->ev_norms, s);
     }
-    form_ready(M->ev_norms, s);
+    form_ready(M->ev_norms, reader);
 }
 
 // The squared norms of M's blocks in (I, J) row-major order, and of M.
 void norms_out(qt_matrix* M, double* block_norm2, double* total_norm2, qt_mem where, hipStream_t s) {
-    build_norms(M, s);
+    build_norms(M, s, s);
     const int64_t n = M->nblocks;
     if (block_norm2 && n > 0) {
         const int row_bits = ilog2(M->n_rows / M->b);

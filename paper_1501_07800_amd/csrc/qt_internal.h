@@ -229,8 +229,8 @@ const double* operand_f64(qt_matrix* M, hipStream_t s);
 const float* operand_f32(qt_matrix* M, hipStream_t s);
 void operand_bf16(qt_matrix* M, hipStream_t s);
 // the squared Frobenius norms of M's blocks and nodes (M->bn2, M->nn2), made
-// on s the first time and waited for on s afterwards
-void build_norms(qt_matrix* M, hipStream_t s);
+// on s the first time; work queued on `reader` from here on sees them
+void build_norms(qt_matrix* M, hipStream_t s, hipStream_t reader);
 uint64_t morton2(uint32_t r, uint32_t c);
 
 // numeric.hip --------------------------------------------------------------

@@ -12,6 +12,8 @@
 #include "qt_sort.h"
 
 #include <algorithm>
+#include <map>
+#include <mutex>
 #include <atomic>
 #include <set>
 
@@ -110,17 +112,10 @@ struct RowKeys {
     __device__ uint64_t operator()(int32_t t) const { return morton_row(bkey[t]); }
 };
 
-// Row-major copy-out: coordinates and source block of every output position.
-struct RowMajorSink {
-    const uint64_t* bkey;
+// Row-major copy-out: source block of every output position.
+struct PermSink {
     int32_t* perm;
-    int32_t* I;
-    int32_t* J;
-    __device__ void operator()(int32_t at, int32_t t, uint64_t row) const {
-        perm[at] = t;
-        I[at] = (int32_t)row;
-        J[at] = (int32_t)morton_col(bkey[t]);
-    }
+    __device__ void operator()(int32_t at, int32_t t, uint64_t) const { perm[at] = t; }
 };
 
 struct GatherF64Sink {
@@ -155,10 +150,23 @@ struct NormSink {
 // is not aligned to 16 bytes.
 constexpr int COPY_PIECES = 4, COPY_WAVES = 4;
 
+// Where a copy-out writes its blocks' coordinates (I NULL: nowhere), and the
+// blocks' keys.
+struct Coords {
+    const uint64_t* bkey;
+    int32_t* I;
+    int32_t* J;
+    __device__ void operator()(int64_t at, int32_t t) const {
+        const uint64_t key = bkey[t];
+        I[at] = (int32_t)morton_row(key);
+        J[at] = (int32_t)morton_col(key);
+    }
+};
+
 template <class S, class D, int VE>
 __global__ __launch_bounds__(64 * COPY_WAVES) void k_copy_blocks(const S* __restrict__ src,
                                                                  const int32_t* __restrict__ perm, int64_t pieces,
-                                                                 int ppb_log, D* __restrict__ dst) {
+                                                                 int ppb_log, D* __restrict__ dst, Coords coords) {
     typedef S svec __attribute__((ext_vector_type(VE)));
     typedef D dvec __attribute__((ext_vector_type(VE)));
     const int lane = threadIdx.x & 63;
@@ -177,27 +185,38 @@ __global__ __launch_bounds__(64 * COPY_WAVES) void k_copy_blocks(const S* __rest
         if (p >= pieces) break;
         __builtin_nontemporal_store(__builtin_convertvector(v[r], dvec), reinterpret_cast<dvec*>(dst) + p * 64 + lane);
     }
+    if (coords.I && lane < COPY_PIECES) {
+        const int64_t p = p0 + lane;
+        if (p < pieces && (p & ((int64_t(1) << ppb_log) - 1)) == 0) coords(p >> ppb_log, perm[p >> ppb_log]);
+    }
+}
+
+__global__ void k_coords(const int32_t* __restrict__ perm, int64_t n, Coords coords) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) coords(t, perm[t]);
 }
 
 template <class S, class D, int VE>
-static void launch_copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D* dst, hipStream_t s) {
+static void launch_copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D* dst, hipStream_t s,
+                               const Coords& coords) {
     int ppb_log = 0;   // b is 16, 32 or 64: a power of two of pieces per block
     while (((64 * VE) << ppb_log) < bb) ++ppb_log;
     const int64_t pieces = n << ppb_log, per = COPY_WAVES * COPY_PIECES;
     k_copy_blocks<S, D, VE><<<(unsigned)((pieces + per - 1) / per), 64 * COPY_WAVES, 0, s>>>(src, perm, pieces, ppb_log,
-                                                                                           dst);
+                                                                                           dst, coords);
     QT_LAUNCH("k_copy_blocks");
 }
 
 // src and dst: device arrays of n blocks of bb entries; perm: n entries.
 template <class S, class D>
-static void copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D* dst, hipStream_t s) {
+static void copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D* dst, hipStream_t s,
+                        const Coords& coords = Coords{}) {
     constexpr int VE = (sizeof(S) == 8 && sizeof(D) == 8) ? 2 : 4;
     const bool wide = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
     if (wide)
-        launch_copy_blocks<S, D, VE>(src, perm, n, bb, dst, s);
+        launch_copy_blocks<S, D, VE>(src, perm, n, bb, dst, s, coords);
     else
-        launch_copy_blocks<S, D, 1>(src, perm, n, bb, dst, s);
+        launch_copy_blocks<S, D, 1>(src, perm, n, bb, dst, s, coords);
 }
 
 // Row-major copy-out of few blocks in one launch, without a permutation: a
@@ -886,10 +905,48 @@ static size_t rowmajor_words(const qt_matrix* M) {
     return (size_t)M->nblocks + sort_tmp_words(M->nblocks, ilog2(M->n_rows / M->b));
 }
 
-// Copy-out into device arrays I, J, values (values may be NULL); tmp holds
-// rowmajor_words(M).
+// A stream of the library's own for the sort of a copy-out, which needs only the
+// blocks' keys, there since the call that made the matrix returned: beside
+// whatever is queued on the caller's stream, usually the kernel that computes
+// the values. The caller's arrays are written on the caller's stream alone. One
+// per device, of default priority. For copies of ASIDE_BYTES and more: the event
+// between the streams costs host and GPU some 15 us, which a product of 27 MB
+// lost (13 k blocks of 16, 140 and 156 us a pass with its copy-out), while the
+// sort's 25 to 70 us show from some 200 MB on: build and copy-out of 240 MB 282 and
+// 274 us, sysq with 360 MB 734 and 722, an R-MAT product with 1.7 GB 1546 and 1493.
+constexpr size_t ASIDE_BYTES = size_t(128) << 20;
+static std::mutex g_sort_mu;
+static std::map<int, hipStream_t> g_sort_stream;
+
+static hipStream_t sort_stream() {
+    int dev = 0;
+    QT_HIP(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(g_sort_mu);
+    auto it = g_sort_stream.find(dev);
+    if (it != g_sort_stream.end()) return it->second;
+    hipStream_t st = nullptr;
+    QT_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+    g_sort_stream[dev] = st;
+    return st;
+}
+
+// Whether work is queued on s that the sort need not wait for; not while s is
+// captured, where all of a call's work belongs to s.
+static bool stream_behind(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const bool behind = hipStreamQuery(s) == hipErrorNotReady;
+    (void)hipGetLastError();
+    return behind;
+}
+
+// Copy-out into device arrays I, J, values (values may be NULL) on s, its sort
+// on `sorts`; tmp holds rowmajor_words(M), allocated on `sorts`.
 static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t* J, void* values, qt_prec out_type,
-                          hipStream_t s) {
+                          hipStream_t s, hipStream_t sorts) {
     const int64_t n = M->nblocks;
     const int bb = M->b * M->b;
     if (n <= RANKED_MAX) {
@@ -904,17 +961,20 @@ static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t*
         return;
     }
     int32_t* perm = tmp;
-    stable_sort(RowKeys{M->bkey.p}, RowMajorSink{M->bkey.p, perm, I, J}, n, ilog2(M->n_rows / M->b), tmp + n,
-                perm, s);
-    if (!values) return;   // pattern only
-    if (M->vtype == QT_F64 && out_type == QT_F64)
-        copy_blocks(M->v64.p, perm, n, bb, (double*)values, s);
+    stable_sort(RowKeys{M->bkey.p}, PermSink{perm}, n, ilog2(M->n_rows / M->b), tmp + n, perm, sorts);
+    if (sorts != s) QT_HIP(stream_after(s, sorts));
+    const Coords coords{M->bkey.p, I, J};
+    if (!values) {   // pattern only
+        k_coords<<<grid_for(n), 256, 0, s>>>(perm, n, coords);
+        QT_LAUNCH("k_coords");
+    } else if (M->vtype == QT_F64 && out_type == QT_F64)
+        copy_blocks(M->v64.p, perm, n, bb, (double*)values, s, coords);
     else if (M->vtype == QT_F64)
-        copy_blocks(M->v64.p, perm, n, bb, (float*)values, s);
+        copy_blocks(M->v64.p, perm, n, bb, (float*)values, s, coords);
     else if (out_type == QT_F64)
-        copy_blocks(M->v32.p, perm, n, bb, (double*)values, s);
+        copy_blocks(M->v32.p, perm, n, bb, (double*)values, s, coords);
     else
-        copy_blocks(M->v32.p, perm, n, bb, (float*)values, s);
+        copy_blocks(M->v32.p, perm, n, bb, (float*)values, s, coords);
 }
 
 void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec out_type, qt_mem where,
@@ -925,8 +985,11 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
     if (n == 0) return;
     if (!I || !J) fail(QT_ERR_ARG, "NULL output array");
     const int bb = M->b * M->b;
-    DBuf<int32_t> tmp(rowmajor_words(M), s);
+    const size_t words = rowmajor_words(M);
     const size_t vbytes = values ? (size_t)n * bb * (out_type == QT_F64 ? sizeof(double) : sizeof(float)) : 0;
+    const hipStream_t sorts = words > 0 && vbytes >= ASIDE_BYTES && stream_behind(s) ? sort_stream() : s;
+    DBuf<int32_t> tmp(words, sorts);
+    tmp.s = s;   // released after the copy
     DBuf<int32_t> tI, tJ;
     DBuf<char> tV;
     int32_t* oI = I;
@@ -940,7 +1003,7 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
         oJ = tJ.p;
         oV = values ? (void*)tV.p : nullptr;
     }
-    rowmajor_copy(M, tmp.p, oI, oJ, oV, out_type, s);
+    rowmajor_copy(M, tmp.p, oI, oJ, oV, out_type, s, sorts);
     if (where == QT_MEM_HOST) {
         QT_HIP(hipMemcpyAsync(I, oI, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         QT_HIP(hipMemcpyAsync(J, oJ, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -996,7 +1059,7 @@ void to_blocks_noalloc(const qt_matrix* M, int32_t* I, int32_t* J, void* values,
     // every word is written before it is read, so nothing left by an earlier
     // call is seen and nothing needs clearing
     if (rowmajor_words(M) > (size_t)kNoAllocWords) fail(QT_ERR_DEVICE, "copy-out scratch exceeded");
-    rowmajor_copy(M, tmp, I, J, values, out_type, s);
+    rowmajor_copy(M, tmp, I, J, values, out_type, s, s);
 }
 
 // ------------------------------------------------------------ norms

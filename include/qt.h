@@ -346,8 +346,10 @@ void qt_free(qt_matrix* M);
  *               of neighbouring items per XCD;
  *   schedule 3  persistent, dynamic: 16 items at a time from a counter;
  *   QT_PLAN_ORDER_MORTON  every problem's C blocks in Morton order (without
- *               it a problem whose C blocks average under two block products
- *               is launched grouped by inner index, as qt_multiply does);
+ *               it a problem is launched in the order qt_multiply would use:
+ *               by inner index where C blocks average under two block
+ *               products and these read 700 MB of operand blocks or more, in
+ *               strips of block rows at b = 64, else in Morton order);
  *   QT_PLAN_TILE_WAVE     at b = 64, one wave per 32 x 32 tile instead of one
  *               four-wave workgroup per C block sharing its operands through
  *               LDS (no effect at other block sizes).

@@ -89,9 +89,15 @@ constexpr int XCD_RUN_LOG = 10, XCD_RUN_LOG_B64 = 8;
 
 // Logical tile of physical workgroup w, in runs of 2^log tiles; a bijection
 // on [0, grid) when the grid is a multiple of 8 << log (XcdGrid pads it so).
+// The tile is the same in all lanes and is handed on in a scalar register, so
+// that what is loaded by it (product range, block indices) is scalar as well:
+// with the run length an argument the compiler did not see that through, and the
+// FP32 kernel of a decay32768 product took 0.93 instead of 0.85 ms, of a
+// decay16384 one 0.455 instead of 0.407; FP64 and BF16X3 unchanged.
 __device__ __forceinline__ int64_t xcd_logical(int64_t w, int log) {
     const int64_t x = w & 7, i = w >> 3;
-    return ((((i >> log) << 3) + x) << log) | (i & ((int64_t(1) << log) - 1));
+    const int64_t tile = ((((i >> log) << 3) + x) << log) | (i & ((int64_t(1) << log) - 1));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)tile);   // a grid has at most 2^31 - 1 workgroups
 }
 
 // The grid over `tiles` tiles and its run length: the longest that still gives

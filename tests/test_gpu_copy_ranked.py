@@ -42,3 +42,26 @@ def test_row_major(qt, b, nb, n, offset):
     oI, oJ = (torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
     M.to_blocks_noalloc(oI, oJ, None)
     assert torch.equal(oI, I[o]) and torch.equal(oJ, J[o])
+
+
+@pytest.mark.parametrize("b,nb", [(16, 4096), (16, 4097), (32, 4100), (64, 4097)])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_fp32_values(qt, b, nb, offset):
+    """A product stored in fp32 (a block diagonal matrix times the identity), both
+    output types, on both sides of the size."""
+    import torch
+    print("ranked fp32", b, nb, offset, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nb)
+    V = torch.randn((nb, b, b), generator=g, dtype=torch.float64, device="cuda")
+    I = torch.arange(nb, dtype=torch.int32, device="cuda")
+    J = torch.randperm(nb, generator=g, device="cuda").int()
+    E = torch.eye(b, dtype=torch.float64, device="cuda").repeat(nb, 1, 1)
+    C = qt.multiply(qt.build(nb * b, nb * b, b, 8 * b, I, J, V), qt.build(nb * b, nb * b, b, 8 * b, I, I, E), "f32")
+    for dtype, name in ((torch.float64, "f64"), (torch.float32, "f32")):
+        out = torch.full((nb * b * b + 8,), 7.0, dtype=dtype, device="cuda")
+        W = out[offset:offset + nb * b * b].view(nb, b, b)
+        oI, oJ = (torch.full((nb,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        C.to_blocks_device(oI, oJ, W, name)
+        assert torch.equal(oI, I) and torch.equal(oJ, J) and torch.equal(W, V.float().to(dtype))
+        assert bool((out[:offset] == 7).all()) and bool((out[offset + nb * b * b:] == 7).all())

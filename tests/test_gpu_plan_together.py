@@ -77,3 +77,23 @@ def test_plan_equals_single_products(qt, name):
             out.append((I, J, V))
         for x, y in zip(*out):
             assert torch.equal(x, y), (name, i, s)
+
+
+def test_leaf_sizes_side_by_side(qt):
+    """Problems of different leaf sizes (4 x 4 and 8 x 8 blocks, one block) in one plan."""
+    import torch
+    mats = [_matrix(qt, 200, 200, 2000, 40 + lb, lb=lb) for lb in (8, 4, 1, 2, 8)]
+    plan = qt.Plan(mats, mats, "f64")
+    plan.execute(graph=False)
+    for i, A in enumerate(mats):
+        one, got = qt.multiply(A, A), plan.result(i)
+        assert got.nblocks == one.nblocks and got.levels().tolist() == one.levels().tolist()
+        out = []
+        for M in (got, one):
+            V = torch.empty((M.nblocks, 16, 16), dtype=torch.float64, device="cuda")
+            I = torch.empty(M.nblocks, dtype=torch.int32, device="cuda")
+            J = torch.empty_like(I)
+            M.to_blocks_device(I, J, V)
+            out.append((I, J, V))
+        for x, y in zip(*out):
+            assert torch.equal(x, y)

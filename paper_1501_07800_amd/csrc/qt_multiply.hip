@@ -19,7 +19,12 @@
 //          k' = 0 before k' = 1 (child k = 2k + k'), so the new frontier is
 //          again grouped by C node with k ascending; quadrants without pairs
 //          are NIL children and get no node.
-// Each level takes two launches (count, fill), plus a scan on large levels.
+// A level takes one launch (its counts are made by the fill before it) or two
+// (count, fill), plus a scan on the largest. Three kinds of product go other
+// ways to the same lists: levels of few pairs per node and leaves of few
+// products give a lane, not a wave, to a pair; a small product runs in one
+// launch; the problems of a batch share launches (each below, where it says
+// why).
 //
 // The leaf step gives a C leaf one wavefront whose lanes are the lb x lb
 // blocks of the leaf: lane (i, j) counts popcount(rowmask_A(i) & colmask_B(j))

@@ -90,7 +90,7 @@ struct ListKeys {
         const int32_t i = I[t], j = J[t];
         if (i < 0 || j < 0 || i >= nbr || j >= nbc) {
             atomicOr(err, 1);
-            return 0;   // some position of the grid: the tree is formed before the flag is read
+            return 0;   // a position of any grid build() accepts: the tree is formed before the flag is read
         }
         return morton_key((uint32_t)i, (uint32_t)j);
     }
@@ -729,7 +729,8 @@ static void tree_begin(TreeJob& j, qt_matrix* M, int64_t bound, int64_t n, hipSt
     std::vector<int64_t> cap(L + 1);
     for (int l = 0; l <= L; ++l) {   // node positions of M's shape at level l
         const int64_t side = (int64_t)M->leaf << (L - l);
-        cap[l] = std::min(bound, ((M->n_rows + side - 1) / side) * ((M->n_cols + side - 1) / side));
+        const int64_t positions = ((M->n_rows + side - 1) / side) * ((M->n_cols + side - 1) / side);
+        cap[l] = std::max<int64_t>(std::min(bound, positions), 1);   // a list's first entry starts a node whatever it is
         j.child_at.push_back(0);
         j.key_at.push_back(0);
     }
@@ -843,6 +844,9 @@ qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_
     const int64_t nbr = n_rows / b, nbc = n_cols / b;
     if (nbr > (int64_t(1) << 30) || nbc > (int64_t(1) << 30)) fail(QT_ERR_UNSUPPORTED, "too many blocks per side");
     if (nblocks > (int64_t(1) << 31) - 2) fail(QT_ERR_UNSUPPORTED, "too many blocks");
+    // a grid without positions: no index is in range, and the tree, formed before
+    // the device's error flag is read, would have no place for a node
+    if (nblocks > 0 && (nbr == 0 || nbc == 0)) fail(QT_ERR_ARG, "block index out of range");
 
     std::unique_ptr<qt_matrix> M(new qt_matrix);
     M->n_rows = n_rows;

@@ -160,7 +160,9 @@ qt_status qt_multiply_ex(const qt_matrix* A, const qt_matrix* B, int32_t op_flag
  * ||C - A B||_F is at most the sum of ||A(I,K)|| ||B(K,J)|| over the dropped
  * products. tau = 0 gives the exact product (as qt_multiply). Comparisons are
  * made on squares in fp64; a product whose norm lies within rounding of tau
- * may go either way. The norms are made on `stream` from the operands'
+ * may go either way, and with tau > 0 a pair or product whose norm product is
+ * not a number (a submatrix with a NaN, an infinite one times a zero one) is
+ * dropped, at any level. The norms are made on `stream` from the operands'
  * values, and the traversal waits for them there; otherwise as qt_multiply
  * (qt_stats counts the pairs and products actually formed).
  * Errors: ARG (NULL argument, tau negative, NaN or above 1e150), SHAPE, OOM,

@@ -152,6 +152,12 @@ struct TreeStep {
     int64_t* ngsum;
 };
 
+// The norm threshold's one comparison, of squared norms: nodes and blocks, counts
+// and lists alike. A product that is not a number (a NaN block, an infinite one
+// times a zero one) is not kept; a count and a list that judged it differently
+// would write over each other's places.
+__device__ __forceinline__ bool norms_kept(double a2, double b2, double tau2) { return a2 * b2 >= tau2; }
+
 // Child a of op(A) and child b of op(B) form a pair: both present and, with
 // a norm threshold (PRUNE), the product of their norms not below it. PRUNE is
 // a template argument of every traversal kernel: tested at run time, the
@@ -160,7 +166,7 @@ struct TreeStep {
 template <bool PRUNE>
 __device__ __forceinline__ bool pair_kept(const double* An2, const double* Bn2, double tau2, int32_t a, int32_t b) {
     if constexpr (PRUNE)
-        return a >= 0 && b >= 0 && An2[a] * Bn2[b] >= tau2;
+        return a >= 0 && b >= 0 && norms_kept(An2[a], Bn2[b], tau2);
     else
         return (a | b) >= 0;
 }
@@ -912,7 +918,7 @@ __device__ __forceinline__ int leaf_lane_count_norms(const LeafStep& st, int32_t
                 leaf_positions(st, i, k, j, qa, qb);
                 const int32_t ia = abt + __popcll(amot & ((1ull << qa) - 1));
                 const int32_t ib = bbt + __popcll(bmot & ((1ull << qb) - 1));
-                cnt += st.Abn2[ia] * st.Bbn2[ib] >= st.tau2;
+                cnt += norms_kept(st.Abn2[ia], st.Bbn2[ib], st.tau2);
             }
         }
     }
@@ -1006,7 +1012,7 @@ __device__ __forceinline__ void leaf_fill_products(const LeafStep& st, int32_t s
                 leaf_positions(st, i, k, j, qa, qb);
                 const int32_t ia = abt + __popcll(amot & ((1ull << qa) - 1));
                 const int32_t ib = bbt + __popcll(bmot & ((1ull << qb) - 1));
-                if (st.Abn2 && st.Abn2[ia] * st.Bbn2[ib] < st.tau2) continue;   // dropped by its norm
+                if (st.Abn2 && !norms_kept(st.Abn2[ia], st.Bbn2[ib], st.tau2)) continue;
                 if (out < st.P) {
                     // the block of the value source, with the transposition bit
                     st.prodA[out] = st.amap ? st.amap[ia] : (int32_t)((uint32_t)ia | (st.ta ? PROD_TRANS : 0u));

@@ -950,10 +950,18 @@ static bool stream_behind(hipStream_t s) {
     return behind;
 }
 
-// Copy-out into device arrays I, J, values (values may be NULL) on s, its sort
-// on `sorts`; tmp holds rowmajor_words(M), allocated on `sorts`.
-static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t* J, void* values, qt_prec out_type,
-                          hipStream_t s, hipStream_t sorts) {
+// Row-major order of more than RANKED_MAX blocks, on `sorts`: tmp, of
+// rowmajor_words(M), begins with the source block of every output position.
+static void rowmajor_sort(const qt_matrix* M, int32_t* tmp, hipStream_t sorts) {
+    const int64_t n = M->nblocks;
+    if (n > RANKED_MAX)
+        stable_sort(RowKeys{M->bkey.p}, PermSink{tmp}, n, ilog2(M->n_rows / M->b), tmp + n, tmp, sorts);
+}
+
+// Copy-out into device arrays I, J, values (values may be NULL) on s, in the
+// order that rowmajor_sort left in perm.
+static void rowmajor_copy(const qt_matrix* M, const int32_t* perm, int32_t* I, int32_t* J, void* values,
+                          qt_prec out_type, hipStream_t s) {
     const int64_t n = M->nblocks;
     const int bb = M->b * M->b;
     if (n <= RANKED_MAX) {
@@ -967,9 +975,6 @@ static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t*
             copy_ranked(M->bkey.p, M->v32.p, n, bb, I, J, (float*)values, s);
         return;
     }
-    int32_t* perm = tmp;
-    stable_sort(RowKeys{M->bkey.p}, PermSink{perm}, n, ilog2(M->n_rows / M->b), tmp + n, perm, sorts);
-    if (sorts != s) QT_HIP(stream_after(s, sorts));
     const Coords coords{M->bkey.p, I, J};
     if (!values) {   // pattern only
         k_coords<<<grid_for(n), 256, 0, s>>>(perm, n, coords);
@@ -984,6 +989,22 @@ static void rowmajor_copy(const qt_matrix* M, int32_t* tmp, int32_t* I, int32_t*
         copy_blocks(M->v32.p, perm, n, bb, (float*)values, s, coords);
 }
 
+// The sort on a stream other than the caller's s: s runs after it, and takes
+// its scratch over, once that order is known to stand; after an error the sort
+// has ended before the scratch and M's keys can go.
+static void rowmajor_sort_aside(const qt_matrix* M, DBuf<int32_t>& tmp, hipStream_t sorts, hipStream_t s) {
+    struct Drain {
+        hipStream_t st;
+        ~Drain() {
+            if (st) (void)hipStreamSynchronize(st);
+        }
+    } drain{sorts};
+    rowmajor_sort(M, tmp.p, sorts);
+    QT_HIP(stream_after(s, sorts));
+    tmp.s = s;
+    drain.st = nullptr;
+}
+
 void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec out_type, qt_mem where,
                hipStream_t s) {
     if (out_type != QT_F64 && out_type != QT_F32) fail(QT_ERR_UNSUPPORTED, "output type must be F64 or F32");
@@ -996,7 +1017,6 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
     const size_t vbytes = values ? (size_t)n * bb * (out_type == QT_F64 ? sizeof(double) : sizeof(float)) : 0;
     const hipStream_t sorts = words > 0 && vbytes >= ASIDE_BYTES && stream_behind(s) ? sort_stream() : s;
     DBuf<int32_t> tmp(words, sorts);
-    tmp.s = s;   // released after the copy
     DBuf<int32_t> tI, tJ;
     DBuf<char> tV;
     int32_t* oI = I;
@@ -1010,7 +1030,11 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
         oJ = tJ.p;
         oV = values ? (void*)tV.p : nullptr;
     }
-    rowmajor_copy(M, tmp.p, oI, oJ, oV, out_type, s, sorts);
+    if (sorts != s)
+        rowmajor_sort_aside(M, tmp, sorts, s);
+    else
+        rowmajor_sort(M, tmp.p, s);
+    rowmajor_copy(M, tmp.p, oI, oJ, oV, out_type, s);
     if (where == QT_MEM_HOST) {
         QT_HIP(hipMemcpyAsync(I, oI, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         QT_HIP(hipMemcpyAsync(J, oJ, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -1066,7 +1090,8 @@ void to_blocks_noalloc(const qt_matrix* M, int32_t* I, int32_t* J, void* values,
     // every word is written before it is read, so nothing left by an earlier
     // call is seen and nothing needs clearing
     if (rowmajor_words(M) > (size_t)kNoAllocWords) fail(QT_ERR_DEVICE, "copy-out scratch exceeded");
-    rowmajor_copy(M, tmp, I, J, values, out_type, s, s);
+    rowmajor_sort(M, tmp, s);
+    rowmajor_copy(M, tmp, I, J, values, out_type, s);
 }
 
 // ------------------------------------------------------------ norms

@@ -2647,12 +2647,14 @@ void Symbolic::finish(const int32_t* hc) {
     const bool korder = may_korder && nnzC > 0 && C->products < 2 * (int64_t)nnzC;
     if (strips || korder) {
         int32_t* sort_tmp = (int32_t*)at(W, o_sort);
+        running = true;   // until s runs after the sort, which uses the scratch
         if (strips)
             stable_sort(StripKeys{ls.cbkey, strip_log}, OrderSink{order}, nnzC, strip_bits, sort_tmp, order, ss);
         else
             stable_sort(FirstKeys{Av->bkey.p, ls.prodA, ls.cbseg}, OrderSink{order}, nnzC, kbits, sort_tmp, order, ss);
         if (prof) QT_HIP(hipEventRecord(ev.e1, ss));   // the symbolic phase ends here then
         QT_HIP(stream_after(s, ss));
+        running = false;
     }
 
     // C's tree (NIL-normalised): views into its arena

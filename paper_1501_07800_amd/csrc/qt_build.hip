@@ -922,19 +922,39 @@ static size_t rowmajor_words(const qt_matrix* M) {
 // sort's 25 to 70 us show from some 200 MB on: build and copy-out of 240 MB 282 and
 // 274 us, sysq with 360 MB 734 and 722, an R-MAT product with 1.7 GB 1546 and 1493.
 constexpr size_t ASIDE_BYTES = size_t(128) << 20;
-static std::mutex g_sort_mu;
-static std::map<int, hipStream_t> g_sort_stream;
 
-static hipStream_t sort_stream() {
+// The stream is lent to one call at a time, and not while another caller's sort
+// may still run on it: nobody waits for the sort of a stream that is not its own.
+// Such a call, rare as a sort takes tens of us, sorts on its own stream.
+struct SortStream {
+    std::mutex mu;                // held from the loan until the sort is queued
+    hipStream_t st = nullptr;
+    hipEvent_t done = nullptr;    // recorded behind the latest sort
+    hipStream_t user = nullptr;   // the stream it was for
+    bool used = false;
+};
+static std::mutex g_sort_mu;
+static std::map<int, SortStream> g_sort_stream;   // per device; entries stay where they are
+
+// nullptr: none to be had (the lock says for how long it is).
+static SortStream* borrow_sort_stream(hipStream_t s, std::unique_lock<std::mutex>& lock) {
     int dev = 0;
     QT_HIP(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lk(g_sort_mu);
-    auto it = g_sort_stream.find(dev);
-    if (it != g_sort_stream.end()) return it->second;
-    hipStream_t st = nullptr;
-    QT_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-    g_sort_stream[dev] = st;
-    return st;
+    SortStream* b;
+    {
+        std::lock_guard<std::mutex> lk(g_sort_mu);
+        b = &g_sort_stream[dev];
+    }
+    std::unique_lock<std::mutex> mine(b->mu, std::try_to_lock);
+    if (!mine.owns_lock()) return nullptr;
+    if (!b->st) QT_HIP(hipStreamCreateWithFlags(&b->st, hipStreamNonBlocking));
+    if (!b->done) QT_HIP(hipEventCreateWithFlags(&b->done, hipEventDisableTiming));
+    if (b->used && b->user != s && hipEventQuery(b->done) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    lock = std::move(mine);
+    return b;
 }
 
 // Whether work is queued on s that the sort need not wait for; not while s is
@@ -989,18 +1009,21 @@ static void rowmajor_copy(const qt_matrix* M, const int32_t* perm, int32_t* I, i
         copy_blocks(M->v32.p, perm, n, bb, (float*)values, s, coords);
 }
 
-// The sort on a stream other than the caller's s: s runs after it, and takes
-// its scratch over, once that order is known to stand; after an error the sort
-// has ended before the scratch and M's keys can go.
-static void rowmajor_sort_aside(const qt_matrix* M, DBuf<int32_t>& tmp, hipStream_t sorts, hipStream_t s) {
+// The sort on the borrowed stream: the caller's s runs after it, and takes its
+// scratch over, once that order is known to stand; after an error the sort has
+// ended before the scratch and M's keys can go.
+static void rowmajor_sort_aside(const qt_matrix* M, DBuf<int32_t>& tmp, SortStream& aside, hipStream_t s) {
     struct Drain {
         hipStream_t st;
         ~Drain() {
             if (st) (void)hipStreamSynchronize(st);
         }
-    } drain{sorts};
-    rowmajor_sort(M, tmp.p, sorts);
-    QT_HIP(stream_after(s, sorts));
+    } drain{aside.st};
+    rowmajor_sort(M, tmp.p, aside.st);
+    QT_HIP(hipEventRecord(aside.done, aside.st));
+    QT_HIP(hipStreamWaitEvent(s, aside.done, 0));
+    aside.user = s;
+    aside.used = true;
     tmp.s = s;
     drain.st = nullptr;
 }
@@ -1015,8 +1038,10 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
     const int bb = M->b * M->b;
     const size_t words = rowmajor_words(M);
     const size_t vbytes = values ? (size_t)n * bb * (out_type == QT_F64 ? sizeof(double) : sizeof(float)) : 0;
-    const hipStream_t sorts = words > 0 && vbytes >= ASIDE_BYTES && stream_behind(s) ? sort_stream() : s;
-    DBuf<int32_t> tmp(words, sorts);
+    std::unique_lock<std::mutex> loan;
+    SortStream* aside = nullptr;
+    if (words > 0 && vbytes >= ASIDE_BYTES && stream_behind(s)) aside = borrow_sort_stream(s, loan);
+    DBuf<int32_t> tmp(words, aside ? aside->st : s);
     DBuf<int32_t> tI, tJ;
     DBuf<char> tV;
     int32_t* oI = I;
@@ -1030,10 +1055,12 @@ void to_blocks(const qt_matrix* M, int32_t* I, int32_t* J, void* values, qt_prec
         oJ = tJ.p;
         oV = values ? (void*)tV.p : nullptr;
     }
-    if (sorts != s)
-        rowmajor_sort_aside(M, tmp, sorts, s);
-    else
+    if (aside) {
+        rowmajor_sort_aside(M, tmp, *aside, s);
+        loan.unlock();
+    } else {
         rowmajor_sort(M, tmp.p, s);
+    }
     rowmajor_copy(M, tmp.p, oI, oJ, oV, out_type, s);
     if (where == QT_MEM_HOST) {
         QT_HIP(hipMemcpyAsync(I, oI, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));

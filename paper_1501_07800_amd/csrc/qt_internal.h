@@ -304,8 +304,6 @@ struct PhaseEvents { hipEvent_t e0, e1, e2, e3; int64_t products, cblocks; };
 void profile_push(const PhaseEvents& ev);
 
 // multiply.hip -------------------------------------------------------------
-// Work queued on `waiter` from here on runs after what is queued on `first`.
-hipError_t stream_after(hipStream_t waiter, hipStream_t first);
 struct SymbolicOut {
     std::unique_ptr<qt_matrix> C;
     DBuf<char> scratch;       // product lists and other symbolic buffers

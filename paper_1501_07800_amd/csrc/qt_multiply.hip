@@ -1866,7 +1866,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_symbolic_many(const Sma
 static std::mutex g_order_ev_mu;
 static std::map<int, std::vector<hipEvent_t>> g_order_ev;
 
-hipError_t stream_after(hipStream_t waiter, hipStream_t first) {
+// Work queued on `waiter` from here on runs after what is queued on `first`.
+static hipError_t stream_after(hipStream_t waiter, hipStream_t first) {
     int dev = 0;
     hipError_t r = hipGetDevice(&dev);
     if (r != hipSuccess) return r;

@@ -1,5 +1,7 @@
 """A large copy-out whose sort has a stream of its own: where its scratch is
-obtained and given back."""
+obtained and given back, and callers on other streams."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -78,3 +80,73 @@ def test_scratch_goes_back_where_it_is_safe(qt, fail_at):
     if fail_at is None:
         assert np.array_equal(I, wI.cpu().numpy()) and np.array_equal(J, wJ.cpu().numpy())
         assert np.array_equal(V, wV.cpu().numpy())
+
+
+def test_no_caller_waits_for_another_streams_sorts(qt):
+    """While sorts for one stream are still to run, a copy-out on another
+    stream sorts on its own: its scratch is made there."""
+    import torch
+    n = 20000
+    M, wI, wJ, wV = _matrix(qt, n)
+    rec = Recording(qt.TorchAllocator())
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    big = torch.randn(6144, 6144, device="cuda")
+    outs = [(torch.zeros_like(wI), torch.zeros_like(wJ), torch.zeros_like(wV)) for _ in range(2)]
+    torch.cuda.synchronize()
+    seen = 0
+    try:
+        qt.set_allocator(rec.alloc, rec.free)
+        for _ in range(30):
+            for s in (s1, s2):
+                with torch.cuda.stream(s):
+                    for _ in range(4):
+                        big @ big
+            first = len(rec.made)
+            for _ in range(6):
+                M.to_blocks_device(*outs[0], stream=s1)
+            aside = rec.made[first][1]
+            assert aside not in (s1.cuda_stream, s2.cuda_stream)
+            behind = torch.cuda.Event()
+            behind.record(torch.cuda.ExternalStream(aside))
+            last = len(rec.made)
+            M.to_blocks_device(*outs[1], stream=s2)
+            if not behind.query():                  # so the other stream's sorts were not done at that call
+                seen += 1
+                assert rec.made[last][1] == s2.cuda_stream
+            torch.cuda.synchronize()
+            for o in outs:
+                assert torch.equal(o[0], wI) and torch.equal(o[1], wJ) and torch.equal(o[2], wV)
+                for x in o:
+                    x.zero_()
+            torch.cuda.synchronize()
+    finally:
+        _restore(qt)
+        torch.cuda.synchronize()
+    print("calls beside another stream's sorts:", seen, flush=True)
+    assert seen > 0
+
+
+def test_threads_on_their_own_streams(qt):
+    import torch
+    M, wI, wJ, wV = _matrix(qt, 17000, seed=3)
+    bad = []
+
+    def work():
+        s = torch.cuda.Stream()
+        big = torch.randn(4096, 4096, device="cuda")
+        out = (torch.zeros_like(wI), torch.zeros_like(wJ), torch.zeros_like(wV))
+        torch.cuda.synchronize()
+        for _ in range(8):
+            with torch.cuda.stream(s):
+                big @ big
+            M.to_blocks_device(*out, stream=s)
+            s.synchronize()
+            if not (torch.equal(out[0], wI) and torch.equal(out[1], wJ) and torch.equal(out[2], wV)):
+                bad.append(1)
+
+    ts = [threading.Thread(target=work) for _ in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad

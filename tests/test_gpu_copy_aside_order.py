@@ -1,5 +1,6 @@
 """A large copy-out whose sort has a stream of its own: where its scratch is
-obtained and given back, and callers on other streams."""
+obtained and given back, callers on other streams, a product whose values are
+still being computed, and a caller that captures the copy-out."""
 import threading
 
 import numpy as np
@@ -150,3 +151,62 @@ def test_threads_on_their_own_streams(qt):
     for t in ts:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_product_still_running(qt, prec):
+    """C's keys are sorted while C's values are computed, behind other work."""
+    import torch
+    b, nb = 32, 190
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    pos = torch.randperm(nb * nb, generator=g, device="cuda")[:nb * nb // 4]
+    A = qt.build(nb * b, nb * b, b, 8 * b, (pos // nb).int(), (pos % nb).int(),
+                 torch.randn((len(pos), b, b), generator=g, dtype=torch.float64, device="cuda"))
+    dtype = torch.float64 if prec == "f64" else torch.float32
+    big = torch.randn(6144, 6144, device="cuda")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            for _ in range(6):
+                big @ big
+        C = qt.multiply(A, A, prec, stream=s)
+        n = C.nblocks
+        assert n > 4096 and n * b * b * dtype.itemsize >= 128 << 20
+        I = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        J = torch.full_like(I, -1)
+        V = torch.zeros((n, b, b), dtype=dtype, device="cuda")
+        torch.cuda.current_stream().synchronize()       # the fills; s is still busy
+        C.to_blocks_device(I, J, V, prec, stream=s)
+        torch.cuda.synchronize()
+        again = [torch.empty_like(x) for x in (I, J, V)]
+        C.to_blocks_device(*again, prec, stream=s)      # from an idle stream
+        torch.cuda.synchronize()
+        at = I.long() * nb + J
+        assert bool((at[1:] > at[:-1]).all()) and bool(V.any())
+        assert all(torch.equal(x, y) for x, y in zip((I, J, V), again))
+
+
+def test_captured_with_its_allocations(qt):
+    """to_blocks itself, which allocates, on a stream that is being captured:
+    all of it belongs to that stream."""
+    import torch
+    if qt.ALLOCATOR is None:
+        pytest.skip("needs torch's allocator, whose memory a capture may use")
+    M, wI, wJ, wV = _matrix(qt, 20000, seed=7)
+    out = (torch.zeros_like(wI), torch.zeros_like(wJ), torch.zeros_like(wV))
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        M.to_blocks_device(*out, stream=s)
+    big = torch.randn(2048, 2048, device="cuda")
+    for _ in range(4):
+        for x in out:
+            x.zero_()
+        big = big @ big
+        big /= big.norm()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], wI) and torch.equal(out[1], wJ) and torch.equal(out[2], wV)

@@ -177,9 +177,20 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     size_t o_cum[2][2] = {};
     for (int o = 0; o < norders; ++o)
         for (int t = 0; t < nforms; ++t) o_cum[o][t] = ap.take((items[t] + 1) * sizeof(int64_t));
-    const size_t o_cost = ap.take(std::max<int64_t>(nmax, 1) * sizeof(int64_t));
-    const size_t o_scan = ap.take((scan_tmp_elems(nmax) + 1) * sizeof(int64_t));
+    // what the prefix sums are made in: part of the same buffer while it is small
+    // (an allocation takes the host some 8 us), else given back when they are done
+    ArenaPlan work;
+    const size_t o_cost = work.take(std::max<int64_t>(nmax, 1) * sizeof(int64_t));
+    const size_t o_scan = work.take((scan_tmp_elems(nmax) + 1) * sizeof(int64_t));
+    constexpr size_t WORK_KEPT = size_t(2) << 20;
+    DBuf<char> apart;
+    size_t o_work = 0;
+    if (work.bytes <= WORK_KEPT)
+        o_work = ap.take(work.bytes);
+    else
+        apart.alloc(work.bytes, s);
     plan->dev.alloc(ap.bytes, s);
+    char* const W = apart.p ? apart.p : plan->dev.p + o_work;
     char* D = plan->dev.p;
     std::vector<char> host(copied);
     std::memcpy(host.data() + o_probs, hp.data(), hp.size() * sizeof(BatchProblem));
@@ -215,9 +226,9 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
             int64_t* cum = (int64_t*)(D + o_cum[o][t]);
             plan->cum_of[o][t] = cum;
             if (L.total_items > 0) {
-                int64_t* cost = (int64_t*)(D + o_cost);
+                int64_t* cost = (int64_t*)(W + o_cost);
                 batch_item_costs(L, cost, s);
-                exclusive_scan(cost, cum, L.total_items, (int64_t*)(D + o_scan), s);
+                exclusive_scan(cost, cum, L.total_items, (int64_t*)(W + o_scan), s);
             }
         }
     QT_HIP(hipStreamSynchronize(s));

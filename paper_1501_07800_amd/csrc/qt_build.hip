@@ -788,6 +788,74 @@ static void tree_fill(TreeJob& j, const uint64_t* keys, hipStream_t s) {
     QT_LAUNCH("k_tree_tables");
 }
 
+// Parts of a buffer moved to another one.
+constexpr int MAX_PARTS = 2 * MAX_TREE_LEVELS + 6;
+struct Parts {
+    int n;
+    const int32_t* from[MAX_PARTS];
+    int32_t* to[MAX_PARTS];
+    int64_t words[MAX_PARTS];
+};
+
+__global__ void k_copy_parts(Parts a) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int p = 0; p < a.n; ++p)
+        for (int64_t i = i0; i < a.words[p]; i += step) a.to[p][i] = a.from[p][i];
+}
+
+// The tree and keys of M in buffers of their size, where those made by bounds
+// hold much more: over 1 MiB and a 64th of what the values take (a truncation to
+// few blocks, many blocks in few leaves). Waits for the move: products on any
+// stream read a handle's structure without waiting for the stream that made it.
+static void tree_shrink(TreeJob& j, const int32_t* cnt, hipStream_t s) {
+    qt_matrix* M = j.M;
+    const int L = M->L;
+    const int64_t n = M->nblocks;
+    ArenaPlan plan;
+    std::vector<size_t> child_at, key_at;
+    for (int l = 0; l < L; ++l) child_at.push_back(plan.take(4 * (size_t)cnt[l] * sizeof(int32_t)));
+    for (int l = 0; l < L; ++l) key_at.push_back(plan.take((size_t)cnt[l] * sizeof(uint64_t)));
+    const size_t nl = cnt[L];
+    const size_t base_at = plan.take(nl * sizeof(int32_t)), lkey_at = plan.take(nl * sizeof(uint64_t));
+    const size_t mo_at = plan.take(nl * sizeof(uint64_t)), rm_at = plan.take(nl * sizeof(uint64_t));
+    const size_t cm_at = plan.take(nl * sizeof(uint64_t)), bkey_at = plan.take(n * sizeof(uint64_t));
+    const int64_t held = (int64_t)(M->arena.n + M->bkey.n * sizeof(uint64_t));
+    const int64_t values = M->vsrc ? 0 : n * M->b * M->b * (int64_t)sizeof(double);
+    if (held - (int64_t)plan.bytes <= std::max(int64_t(1) << 20, values / 64)) return;
+    DBuf<char> arena(plan.bytes, s);
+    Parts parts{};
+    auto move = [&](size_t& at, size_t to, size_t bytes) {
+        if (bytes) {
+            parts.from[parts.n] = (const int32_t*)(M->arena.p + at);
+            parts.to[parts.n] = (int32_t*)(arena.p + to);
+            parts.words[parts.n++] = (int64_t)(bytes / sizeof(int32_t));
+        }
+        at = to;
+    };
+    for (int l = 0; l < L; ++l) {
+        move(j.child_at[l], child_at[l], 4 * (size_t)cnt[l] * sizeof(int32_t));
+        move(j.key_at[l], key_at[l], (size_t)cnt[l] * sizeof(uint64_t));
+    }
+    move(j.base_at, base_at, nl * sizeof(int32_t));
+    move(j.lkey_at, lkey_at, nl * sizeof(uint64_t));
+    move(j.mo_at, mo_at, nl * sizeof(uint64_t));
+    move(j.rm_at, rm_at, nl * sizeof(uint64_t));
+    move(j.cm_at, cm_at, nl * sizeof(uint64_t));
+    if (n > 0) {
+        parts.from[parts.n] = (const int32_t*)M->bkey.p;
+        parts.to[parts.n] = (int32_t*)(arena.p + bkey_at);
+        parts.words[parts.n++] = 2 * n;
+    }
+    k_copy_parts<<<(unsigned)std::min<int64_t>(grid_for((int64_t)plan.bytes / 16), 1024), 256, 0, s>>>(parts);
+    QT_LAUNCH("k_copy_parts");
+    QT_HIP(hipStreamSynchronize(s));
+    M->arena = std::move(arena);
+    if (n > 0)
+        M->bkey.view(M->arena.p + bkey_at, n);
+    else
+        M->bkey.release();
+}
+
 // Reads the words back and sets M's tree, block count and histograms; throws
 // what the error flags say. out (may be nullptr): the caller's double.
 static void tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
@@ -800,6 +868,7 @@ static void tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
     const int L = M->L;
     const int32_t* cnt = w + TreeJob::kLevels;
     M->nblocks = w[TreeJob::kCount];
+    tree_shrink(j, cnt, s);
     char* at = M->arena.p;
     for (int l = 0; l < L; ++l) {
         M->levels[l].n = cnt[l];

@@ -150,6 +150,20 @@ struct NormSink {
 // is not aligned to 16 bytes.
 constexpr int COPY_PIECES = 4, COPY_WAVES = 4;
 
+// VE entries as a copy reads and writes them: 16 bytes at an address that is
+// aligned to that, also where the vector itself is longer (four doubles).
+constexpr size_t COPY_ALIGN = 16;
+template <class T, int VE>
+struct CopyVec {
+    static constexpr size_t align = sizeof(T) * VE < COPY_ALIGN ? sizeof(T) * VE : COPY_ALIGN;
+    typedef T type __attribute__((ext_vector_type(VE), aligned(align)));
+    static_assert(alignof(type) == align, "the alignment that copy_aligned checks");
+};
+
+static bool copy_aligned(const void* src, const void* dst) {
+    return ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & (COPY_ALIGN - 1)) == 0;
+}
+
 // Where a copy-out writes its blocks' coordinates (I NULL: nowhere), and the
 // blocks' keys.
 struct Coords {
@@ -167,8 +181,8 @@ template <class S, class D, int VE>
 __global__ __launch_bounds__(64 * COPY_WAVES) void k_copy_blocks(const S* __restrict__ src,
                                                                  const int32_t* __restrict__ perm, int64_t pieces,
                                                                  int ppb_log, D* __restrict__ dst, Coords coords) {
-    typedef S svec __attribute__((ext_vector_type(VE)));
-    typedef D dvec __attribute__((ext_vector_type(VE)));
+    typedef typename CopyVec<S, VE>::type svec;
+    typedef typename CopyVec<D, VE>::type dvec;
     const int lane = threadIdx.x & 63;
     const int64_t p0 = ((int64_t)blockIdx.x * COPY_WAVES + (threadIdx.x >> 6)) * COPY_PIECES;
     svec v[COPY_PIECES];
@@ -212,8 +226,7 @@ template <class S, class D>
 static void copy_blocks(const S* src, const int32_t* perm, int64_t n, int bb, D* dst, hipStream_t s,
                         const Coords& coords = Coords{}) {
     constexpr int VE = (sizeof(S) == 8 && sizeof(D) == 8) ? 2 : 4;
-    const bool wide = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
-    if (wide)
+    if (copy_aligned(src, dst))
         launch_copy_blocks<S, D, VE>(src, perm, n, bb, dst, s, coords);
     else
         launch_copy_blocks<S, D, 1>(src, perm, n, bb, dst, s, coords);
@@ -234,8 +247,8 @@ template <class S, class D, int VE>
 __global__ __launch_bounds__(256) void k_copy_ranked(const uint64_t* __restrict__ bkey, int32_t n,
                                                      const S* __restrict__ src, int bb, int32_t* __restrict__ I,
                                                      int32_t* __restrict__ J, D* __restrict__ dst) {
-    typedef S svec __attribute__((ext_vector_type(VE)));
-    typedef D dvec __attribute__((ext_vector_type(VE)));
+    typedef typename CopyVec<S, VE>::type svec;
+    typedef typename CopyVec<D, VE>::type dvec;
     constexpr int U = 4;
     __shared__ int before[4];
     const int tid = threadIdx.x, wave = tid >> 6;
@@ -275,8 +288,7 @@ template <class S, class D>
 static void copy_ranked(const uint64_t* bkey, const S* src, int64_t n, int bb, int32_t* I, int32_t* J, D* dst,
                         hipStream_t s) {
     constexpr int VE = (sizeof(S) == 8 && sizeof(D) == 8) ? 2 : 4;
-    const bool wide = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
-    if (wide)
+    if (copy_aligned(src, dst))
         k_copy_ranked<S, D, VE><<<(unsigned)n, 256, 0, s>>>(bkey, (int32_t)n, src, bb, I, J, dst);
     else
         k_copy_ranked<S, D, 1><<<(unsigned)n, 256, 0, s>>>(bkey, (int32_t)n, src, bb, I, J, dst);

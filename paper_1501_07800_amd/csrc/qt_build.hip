@@ -215,10 +215,16 @@ static void launch_copy_blocks(const S* src, const int32_t* perm, int64_t n, int
                                const Coords& coords) {
     int ppb_log = 0;   // b is 16, 32 or 64: a power of two of pieces per block
     while (((64 * VE) << ppb_log) < bb) ++ppb_log;
-    const int64_t pieces = n << ppb_log, per = COPY_WAVES * COPY_PIECES;
-    k_copy_blocks<S, D, VE><<<(unsigned)((pieces + per - 1) / per), 64 * COPY_WAVES, 0, s>>>(src, perm, pieces, ppb_log,
-                                                                                           dst, coords);
-    QT_LAUNCH("k_copy_blocks");
+    // A grid has fewer than 2^32 threads, 16 of them per piece; one of more runs
+    // in part, without an error (69 GB of fp32, an entry per lane).
+    constexpr int64_t per = COPY_WAVES * COPY_PIECES, LAUNCH_PIECES = int64_t(1) << 27;
+    for (int64_t at = 0; at < n; at += LAUNCH_PIECES >> ppb_log) {
+        const int64_t pieces = std::min(n - at, LAUNCH_PIECES >> ppb_log) << ppb_log;
+        const Coords here{coords.bkey, coords.I ? coords.I + at : nullptr, coords.J ? coords.J + at : nullptr};
+        k_copy_blocks<S, D, VE><<<(unsigned)((pieces + per - 1) / per), 64 * COPY_WAVES, 0, s>>>(
+            src, perm + at, pieces, ppb_log, dst + at * bb, here);
+        QT_LAUNCH("k_copy_blocks");
+    }
 }
 
 // src and dst: device arrays of n blocks of bb entries; perm: n entries.

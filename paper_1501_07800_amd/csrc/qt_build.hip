@@ -75,8 +75,16 @@ void dev_free(void* p, hipStream_t s, const Allocator* who) {
 // --------------------------------------------------------------- kernels
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) p[i] = v;
+}
+
+// fn(first, count) over 0 .. n-1 in runs of at most 2^30 threads, `each` an item
+// (a grid of 2^32 threads or more is launched in part, without an error).
+template <class F>
+static void in_launches(int64_t n, int64_t each, const F& fn) {
+    const int64_t most = (int64_t(1) << 30) / each;
+    for (int64_t at = 0; at < n; at += most) fn(at, std::min(n - at, most));
 }
 
 // Sort sources and sinks (see qt_sort.h). A block list's entry t sorts by the
@@ -215,16 +223,15 @@ static void launch_copy_blocks(const S* src, const int32_t* perm, int64_t n, int
                                const Coords& coords) {
     int ppb_log = 0;   // b is 16, 32 or 64: a power of two of pieces per block
     while (((64 * VE) << ppb_log) < bb) ++ppb_log;
-    // A grid has fewer than 2^32 threads, 16 of them per piece; one of more runs
-    // in part, without an error (69 GB of fp32, an entry per lane).
-    constexpr int64_t per = COPY_WAVES * COPY_PIECES, LAUNCH_PIECES = int64_t(1) << 27;
-    for (int64_t at = 0; at < n; at += LAUNCH_PIECES >> ppb_log) {
-        const int64_t pieces = std::min(n - at, LAUNCH_PIECES >> ppb_log) << ppb_log;
+    // 16 threads per piece: 69 GB of fp32, an entry per lane, are 2^32
+    constexpr int64_t per = COPY_WAVES * COPY_PIECES;
+    in_launches(n, (64 * COPY_WAVES / per) << ppb_log, [&](int64_t at, int64_t m) {
         const Coords here{coords.bkey, coords.I ? coords.I + at : nullptr, coords.J ? coords.J + at : nullptr};
+        const int64_t pieces = m << ppb_log;
         k_copy_blocks<S, D, VE><<<(unsigned)((pieces + per - 1) / per), 64 * COPY_WAVES, 0, s>>>(
             src, perm + at, pieces, ppb_log, dst + at * bb, here);
         QT_LAUNCH("k_copy_blocks");
-    }
+    });
 }
 
 // src and dst: device arrays of n blocks of bb entries; perm: n entries.
@@ -627,7 +634,7 @@ void build_histograms(qt_matrix* M, hipStream_t s) {
     const int64_t nb_pad = (int64_t)M->lb << M->L;
     const int64_t total = histogram_words(M);
     DBuf<int32_t> d(total, s);
-    k_fill_i32<<<grid_for(total), 256, 0, s>>>(d.p, total, 0);
+    k_fill_i32<<<std::min(grid_for(total), 4096u), 256, 0, s>>>(d.p, total, 0);
     QT_LAUNCH("k_fill_i32");
     int64_t off = 0;
     for (int l = 0; l <= M->L; ++l) {
@@ -678,8 +685,10 @@ const double* operand_f64(qt_matrix* M, hipStream_t s) {
     if (!M->v64_cache.p && M->nblocks > 0) {
         const int64_t n = M->nblocks * (int64_t)M->b * M->b;
         M->v64_cache.alloc(n, s);
-        k_f32_to_f64<<<grid_for(n), 256, 0, s>>>(M->v32.p, n, M->v64_cache.p);
-        QT_LAUNCH("k_f32_to_f64");
+        in_launches(n, 1, [&](int64_t at, int64_t m) {
+            k_f32_to_f64<<<grid_for(m), 256, 0, s>>>(M->v32.p + at, m, M->v64_cache.p + at);
+            QT_LAUNCH("k_f32_to_f64");
+        });
         form_mark(M->ev_v64, s);
     }
     form_ready(M->ev_v64, s);
@@ -691,8 +700,10 @@ const float* operand_f32(qt_matrix* M, hipStream_t s) {
     if (!M->v32.p && M->nblocks > 0) {
         const int64_t n = M->nblocks * (int64_t)M->b * M->b;
         M->v32.alloc(n, s);
-        k_f64_to_f32<<<grid_for(n), 256, 0, s>>>(M->v64.p, n, M->v32.p);
-        QT_LAUNCH("k_f64_to_f32");
+        in_launches(n, 1, [&](int64_t at, int64_t m) {
+            k_f64_to_f32<<<grid_for(m), 256, 0, s>>>(M->v64.p + at, m, M->v32.p + at);
+            QT_LAUNCH("k_f64_to_f32");
+        });
         form_mark(M->ev_v32, s);
     }
     form_ready(M->ev_v32, s);
@@ -706,11 +717,16 @@ void operand_bf16(qt_matrix* M, hipStream_t s) {
         // so a failed allocation leaves no partial form behind
         const int64_t n = M->nblocks * (int64_t)M->b * M->b;
         DBuf<uint16_t> hi(n, s), lo(n, s), hi_t(n, s), lo_t(n, s);
-        if (M->vtype == QT_F64)
-            k_bf16_split<double><<<grid_for(n), 256, 0, s>>>(M->v64.p, M->nblocks, M->b, hi.p, lo.p, hi_t.p, lo_t.p);
-        else
-            k_bf16_split<float><<<grid_for(n), 256, 0, s>>>(M->v32.p, M->nblocks, M->b, hi.p, lo.p, hi_t.p, lo_t.p);
-        QT_LAUNCH("k_bf16_split");
+        const int64_t bb = (int64_t)M->b * M->b;
+        in_launches(M->nblocks, bb, [&](int64_t at, int64_t m) {
+            const unsigned g = grid_for(m * bb);
+            const int64_t e = at * bb;
+            if (M->vtype == QT_F64)
+                k_bf16_split<double><<<g, 256, 0, s>>>(M->v64.p + e, m, M->b, hi.p + e, lo.p + e, hi_t.p + e, lo_t.p + e);
+            else
+                k_bf16_split<float><<<g, 256, 0, s>>>(M->v32.p + e, m, M->b, hi.p + e, lo.p + e, hi_t.p + e, lo_t.p + e);
+            QT_LAUNCH("k_bf16_split");
+        });
         form_mark(M->ev_bf16, s);
         M->bf_hi = std::move(hi);
         M->bf_lo = std::move(lo);
@@ -1253,13 +1269,15 @@ __global__ __launch_bounds__(256) void k_block_norm2(const T* __restrict__ v, in
 }
 
 static void launch_block_norm2(const qt_matrix* M, double* out, hipStream_t s) {
-    const unsigned g = (unsigned)((M->nblocks + 3) / 4);
     const int bb = M->b * M->b;
-    if (M->vtype == QT_F64)
-        k_block_norm2<double><<<g, 256, 0, s>>>(M->v64.p, M->nblocks, bb, out);
-    else
-        k_block_norm2<float><<<g, 256, 0, s>>>(M->v32.p, M->nblocks, bb, out);
-    QT_LAUNCH("k_block_norm2");
+    in_launches(M->nblocks, 64, [&](int64_t at, int64_t n) {
+        const unsigned g = (unsigned)((n + 3) / 4);
+        if (M->vtype == QT_F64)
+            k_block_norm2<double><<<g, 256, 0, s>>>(M->v64.p + at * bb, n, bb, out + at);
+        else
+            k_block_norm2<float><<<g, 256, 0, s>>>(M->v32.p + at * bb, n, bb, out + at);
+        QT_LAUNCH("k_block_norm2");
+    });
 }
 
 // The leaf's norms are added in block order, eight loads at a time.

@@ -1141,8 +1141,7 @@ static void launch_bf_op(const NumericArgs& a, hipStream_t s) {
     }
 }
 
-void launch_numeric(const NumericArgs& a, hipStream_t s) {
-    if (a.nseg <= 0) return;
+static void launch_blocks(const NumericArgs& a, hipStream_t s) {
     if (a.dyn) {
         if (a.prec == QT_F64) {
             switch (a.b) {
@@ -1183,6 +1182,25 @@ void launch_numeric(const NumericArgs& a, hipStream_t s) {
         }
     }
     fail(QT_ERR_UNSUPPORTED, "no numeric kernel for this block size and precision");
+}
+
+// The C blocks in launches of at most 2^30 threads (64 a block, 256 at b = 64):
+// a grid of 2^32 or more is launched in part, without an error, which a product
+// of 67 M blocks of 16 would need.
+void launch_numeric(const NumericArgs& a, hipStream_t s) {
+    const int32_t most = a.b == 64 ? 1 << 22 : 1 << 24;
+    const size_t block = (size_t)a.b * a.b * (a.prec == QT_F32 ? sizeof(float) : sizeof(double));
+    for (int64_t at = 0; at < a.nseg; at += most) {
+        NumericArgs part = a;
+        part.nseg = (int32_t)std::min<int64_t>(a.nseg - at, most);
+        if (a.order) {   // slots name their blocks
+            part.order = a.order + at;
+        } else {
+            part.seg = a.seg + at;
+            part.C = (char*)a.C + at * block;
+        }
+        launch_blocks(part, s);
+    }
 }
 
 // ------------------------------------------------- a batch of multiplies
@@ -1458,7 +1476,8 @@ template <int KIND, int BS, bool LDS>
 static void launch_batch_k(const BatchLaunch& L, hipStream_t s) {
     constexpr int T = Item<KIND, BS, LDS>::THREADS;
     const int64_t items = L.total_items;
-    if (L.schedule == 0) {
+    // (items beyond the threads of one grid go to the last schedule)
+    if (L.schedule == 0 && items < (int64_t(1) << 31) / T) {
         const XcdGrid x(items, LDS ? XCD_RUN_LOG_B64 : XCD_RUN_LOG);
         k_batch_flat<KIND, BS, LDS><<<x.grid, T, 0, s>>>(L.probs, L.base, L.item_base, L.nprob, x.log);
         QT_LAUNCH("k_batch_flat");

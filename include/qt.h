@@ -124,7 +124,8 @@ qt_status qt_build(int64_t n_rows, int64_t n_cols, int32_t block_size, int32_t l
  * but does not wait for work already queued on `stream`. The numeric kernel
  * is queued on `stream` behind an event of that phase, and the call returns
  * without waiting for it: C is ready in stream order on `stream`.
- * Errors: ARG, SHAPE, OOM, DEVICE, UNSUPPORTED (more than 2^31 - 1 products).
+ * Errors: ARG, SHAPE, OOM, DEVICE, UNSUPPORTED (more than 2^31 - 1 products,
+ * or node positions of C at one level beyond 2^26 where a wave takes a node).
  */
 qt_status qt_multiply(const qt_matrix* A, const qt_matrix* B, qt_prec prec,
                       void* stream, qt_matrix** C);

@@ -2204,6 +2204,10 @@ void Symbolic::plan() {
         if (!A->vsrc && !B->vsrc && lb_log == 3 && P <= SPARSE_LEAF * ncap[L]) group[L] = pick_group(L);
     }
     sparse = group[L] != 0;
+    // a wave per node is 64 threads, of which a grid has fewer than 2^32 (a larger
+    // one is launched in part, without an error)
+    for (int l = 0; l <= L; ++l)
+        if (!group[l] && ncap[l] >= (int64_t(1) << 26) - 4) fail(QT_ERR_UNSUPPORTED, "too many C nodes at one level");
     // the launch order in strips, of the block rows of C (see above)
     const int64_t c_rows_blk = (op.ta ? A->n_cols : A->n_rows) / A->b;
     const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);

@@ -95,3 +95,13 @@ def test_operands_of_many_entries(qt, prec):
     A.free()
     del V
     torch.cuda.empty_cache()
+
+
+def test_more_nodes_than_waves_are_refused(qt):
+    """67.2 M C leaves, of one block each: a wave per leaf is more than a grid
+    holds, and the call says so before it launches anything."""
+    A, B, _, _ = _outer(qt, 8200, 8200, 16, 16)
+    for call in (lambda: qt.multiply(A, B, "f32"), lambda: qt.Plan([A], [B], "f32")):
+        with pytest.raises(qt.QtError) as e:
+            call()
+        assert e.value.status == qt.QT_ERR_UNSUPPORTED

@@ -592,8 +592,6 @@ static inline unsigned block_grid(int64_t n) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, 1 << 20));
 }
 
-uint64_t morton2(uint32_t r, uint32_t c) { return morton_key(r, c); }
-
 static int ilog2(int64_t x) {
     int l = 0;
     while ((int64_t(1) << l) < x) ++l;

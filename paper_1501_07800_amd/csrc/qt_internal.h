@@ -161,9 +161,11 @@ struct qt_matrix {
 
     std::vector<qt::TreeLevel> levels;   // levels 0 .. L-1
     qt::LeafLevel leaves;                // level L
-    qt::DBuf<char> arena;                // owns the tree arrays (of a multiply result, and of
-                                         // a built matrix unless it is very large); the DBufs
-                                         // below then view into it
+    qt::DBuf<char> arena;                // owns the tree arrays, which view into it: placed by
+                                         // bounds on the levels' sizes (node positions, pairs, or the
+                                         // blocks listed; na + nb for a sum), except where those held
+                                         // much more than the tree of a build, sum or truncation takes
+                                         // (then also the keys); parts of a plan's buffers for its results
 
     // derived operand forms (built on demand, guarded by mu). Each is queued
     // on the stream of the call that first needs it; the matching event is
@@ -231,7 +233,6 @@ void operand_bf16(qt_matrix* M, hipStream_t s);
 // the squared Frobenius norms of M's blocks and nodes (M->bn2, M->nn2), made
 // on s the first time; work queued on `reader` from here on sees them
 void build_norms(qt_matrix* M, hipStream_t s, hipStream_t reader);
-uint64_t morton2(uint32_t r, uint32_t c);
 
 // numeric.hip --------------------------------------------------------------
 struct NumericArgs {
@@ -269,7 +270,7 @@ struct BatchProblem {
     int64_t C;
 };
 // schedules of the batch kernel: 0 flat grid, 1 persistent with work-balanced
-// contiguous runs, 2 persistent taking 4 items per grab from a counter per
+// contiguous runs, 2 persistent taking 2 items per grab from a counter per
 // XCD, 3 persistent taking 16 items per grab from one counter
 constexpr int kBatchSchedules = 4;
 struct BatchLaunch {
@@ -317,12 +318,9 @@ struct MulOp {
     int ta = 0, tb = 0, upper = 0;
     double tau2 = 0;          // > 0: drop pairs and block products with ||A||^2 ||B||^2 < tau2
 };
-// launch_order: also build the launch order of C's blocks that suits the
-// product, for a numeric kernel launched from out.na (a batch plan does not)
-void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out,
-              bool allow_profile = true, const MulOp& op = MulOp{}, bool launch_order = true);
 // The symbolic phases of count plain products, launches shared where they can
-// be; out[0 .. count), whose buffers are parts of those added to `pool`.
+// be; out[0 .. count), whose buffers are parts of those added to `pool`, each with
+// the launch order a single multiply would use.
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
                     SymbolicOut* out, std::vector<DBuf<char>>& pool);
 qt_matrix* multiply(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, const MulOp& op = MulOp{});

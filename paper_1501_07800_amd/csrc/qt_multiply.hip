@@ -85,10 +85,6 @@ __device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlan
 
 __device__ __forceinline__ int wave_excl_scan(int x) { return wave_incl_scan(x) - x; }
 
-__device__ __forceinline__ int4 load_children(const int32_t* tab, int32_t node) {
-    return *reinterpret_cast<const int4*>(tab + 4 * (int64_t)node);
-}
-
 // bits k of row r of an lb x lb occupancy mask stored row-major
 __device__ __forceinline__ uint32_t mask_row(uint64_t m, int r, int lb) {
     return (uint32_t)((m >> (r * lb)) & ((1ull << lb) - 1));
@@ -180,10 +176,6 @@ __device__ __forceinline__ int4 op_swap(int4 c, int transposed) {
         c.z = t;
     }
     return c;
-}
-
-__device__ __forceinline__ int4 op_children(const int32_t* tab, int32_t node, int transposed) {
-    return op_swap(*reinterpret_cast<const int4*>(tab + 4 * (int64_t)node), transposed);
 }
 
 // The child tables of A node a and B node b, both loads issued before either
@@ -2014,10 +2006,8 @@ struct Symbolic {
     qt_prec prec;
     hipStream_t s;
     SymbolicOut& out;
-    bool allow_profile;
     MulOp op;
-    bool launch_order;
-    bool batched = false;   // launches may be shared with other problems
+    bool batched = false;   // one of many: its launches may be shared, and are not timed
 
     // plan
     bool done = false;      // C is empty, known without a traversal
@@ -2046,9 +2036,8 @@ struct Symbolic {
     hipError_t traced = hipSuccess;
     bool running = false;                     // launched, not known to have ended
 
-    Symbolic(qt_matrix* a, qt_matrix* b, qt_prec p, hipStream_t stream, SymbolicOut& o, bool profile, const MulOp& which,
-             bool with_order)
-        : A(a), B(b), prec(p), s(stream), out(o), allow_profile(profile), op(which), launch_order(with_order) {}
+    Symbolic(qt_matrix* a, qt_matrix* b, qt_prec p, hipStream_t stream, SymbolicOut& o, const MulOp& which)
+        : A(a), B(b), prec(p), s(stream), out(o), op(which) {}
     Symbolic(const Symbolic&) = delete;
     Symbolic& operator=(const Symbolic&) = delete;
     // after an error between launch and finish: the kernels use the scratch
@@ -2213,14 +2202,13 @@ void Symbolic::plan() {
     const int64_t row_bytes = A->nblocks * (int64_t)A->b * A->b * (prec == QT_F64 ? 8 : 4) / std::max<int64_t>(c_rows_blk, 1);
     while (strip_log < STRIP_MAX_LOG && (row_bytes << (strip_log + 1)) <= STRIP_BYTES) ++strip_log;
     while ((int64_t(1) << (strip_bits + strip_log)) < c_rows_blk) ++strip_bits;
-    may_strip = launch_order && !small && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
+    may_strip = !small && A->b == 64 && cap >= STRIP_MIN_BLOCKS && P >= 2 * STRIP_MIN_BLOCKS;
     // the order by inner index is built once C's block count is known, if
     // the products are then fewer than twice the C blocks (cap bounds those)
     const int64_t kdim = (op.ta ? A->n_rows : A->n_cols) / A->b;
     while ((int64_t(1) << kbits) < kdim) ++kbits;
     const int64_t read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
-    may_korder =
-        launch_order && !small && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
+    may_korder = !small && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
     ArenaPlan keep, tmp;   // keep: C's tree; tmp: scratch freed after the call
     o_child.resize(L);
     o_key.resize(L + 1);
@@ -2321,7 +2309,7 @@ void Symbolic::bind(char* tree, char* work) {
     dcount = (int32_t*)at(W, o_count);
     nflags = (int32_t*)at(W, o_nflags);
 
-    prof = out.prof = allow_profile && profiling_on();
+    prof = out.prof = !batched && profiling_on();
     lift = (liftA > 0 || liftB > 0) ? lift_table() : nullptr;
     // the leaf step's operands and outputs
     ls.lb_log = lb_log;
@@ -2711,9 +2699,8 @@ void Symbolic::bind_values(char* values) {
     out.na = na;
 }
 
-void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out, bool allow_profile,
-              const MulOp& op, bool launch_order) {
-    Symbolic sym(A, B, prec, s, out, allow_profile, op, launch_order);
+static void symbolic(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, SymbolicOut& out, const MulOp& op) {
+    Symbolic sym(A, B, prec, s, out, op);
     sym.plan();
     if (sym.done) return;
     sym.launch();
@@ -2844,7 +2831,7 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         std::vector<Symbolic*> work, alone, small, levels, order;   // order: as their counts lie in words
         std::vector<size_t> bytes;
         for (int32_t i = at; i < at + n; ++i) {
-            all.emplace_back(new Symbolic(A[i], B[i], prec, s, out[i], false, MulOp{}, true));
+            all.emplace_back(new Symbolic(A[i], B[i], prec, s, out[i], MulOp{}));
             Symbolic* p = all.back().get();
             p->batched = true;
             p->plan();
@@ -2904,7 +2891,7 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
 
 qt_matrix* multiply(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, const MulOp& op) {
     SymbolicOut sym;
-    symbolic(A, B, prec, s, sym, true, op);
+    symbolic(A, B, prec, s, sym, op);
     if (sym.prof) QT_HIP(hipEventRecord(sym.ev.e3, s));
     if (sym.na.nseg > 0) launch_numeric(sym.na, s);
     if (sym.prof) {

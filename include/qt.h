@@ -349,10 +349,11 @@ void qt_free(qt_matrix* M);
  *               of neighbouring items per XCD;
  *   schedule 3  persistent, dynamic: 16 items at a time from a counter;
  *   QT_PLAN_ORDER_MORTON  every problem's C blocks in Morton order (without
- *               it a problem is launched in the order qt_multiply would use:
- *               by inner index where C blocks average under two block
- *               products and these read 700 MB of operand blocks or more, in
- *               strips of block rows at b = 64, else in Morton order);
+ *               it a problem is launched by inner index where its C blocks
+ *               average under two block products (qt_multiply sorts C blocks
+ *               so only where the products read 700 MB of operand blocks or
+ *               more), in strips of block rows at b = 64 as in qt_multiply,
+ *               else in Morton order);
  *   QT_PLAN_TILE_WAVE     at b = 64, one wave per 32 x 32 tile instead of one
  *               four-wave workgroup per C block sharing its operands through
  *               LDS (no effect at other block sizes).

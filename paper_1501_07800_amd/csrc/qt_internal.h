@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstring>
+#include <deque>
 #include <memory>
 #include <mutex>
 #include <stdexcept>
@@ -320,9 +321,10 @@ struct MulOp {
 };
 // The symbolic phases of count plain products, launches shared where they can
 // be; out[0 .. count), whose buffers are parts of those added to `pool`, each with
-// the launch order a single multiply would use.
+// the launch order of its C blocks. `copied`: host memory that work queued on s
+// or before it may still read; it is kept until s has been waited for.
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
-                    SymbolicOut* out, std::vector<DBuf<char>>& pool);
+                    SymbolicOut* out, std::vector<DBuf<char>>& pool, std::deque<std::vector<char>>& copied);
 qt_matrix* multiply(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, const MulOp& op = MulOp{});
 qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_t nblocks, const int32_t* I,
                  const int32_t* J, const double* values, qt_mem where, hipStream_t s);

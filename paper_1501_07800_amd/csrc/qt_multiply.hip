@@ -1501,6 +1501,12 @@ struct OrderSink {
 // FP32 b = 32, 0.42 GB 225 and 248 us, 0.82 GB 311 and 312, 4.0 GB 944 and 818;
 // FP64 b = 32, 0.35 GB 203 and 209, 0.84 GB 302 and 272, 8.0 GB 1663 and 1070;
 // FP64 b = 16, 0.41 GB 240 and 247, 2.0 GB 565 and 492.
+// A plan's problems are sorted at any size: it pays once, 30 to 60 us when it is
+// made, and gains at every run. Replays, Morton and by k: b = 16 FP64, one problem
+// of 64 k blocks 54.8 and 36.5 us, 16 of 4 k 53.5 and 44.0, 64 of 1 k 50.2 and 42.7; b =
+// 32, 8 of 4.5 k FP64 113.8 and 86.2, one of 61 k BF16X3 130 and 103; b = 64, 4 of 2.6 k
+// FP32 74.9 and 68.9. Slower, by 2 to 6 %: b = 32 FP32, 64 of 2.1 k 199 and 211, 8 of 25 k
+// 323 and 335 (qt_plan_tune tries both).
 constexpr int64_t KORDER_MIN_BYTES = int64_t(700) << 20;
 constexpr int KORDER_MAX_BITS = 22;   // inner blocks: two sort passes
 
@@ -2035,6 +2041,7 @@ struct Symbolic {
     std::unique_ptr<ReadBack> counts;         // unless shared with other problems
     hipError_t traced = hipSuccess;
     bool running = false;                     // launched, not known to have ended
+    bool strips = false, korder = false;      // the launch order, known once C's blocks are counted
 
     Symbolic(qt_matrix* a, qt_matrix* b, qt_prec p, hipStream_t stream, SymbolicOut& o, const MulOp& which)
         : A(a), B(b), prec(p), s(stream), out(o), op(which) {}
@@ -2065,7 +2072,9 @@ struct Symbolic {
     SmallStep small_step() const;
     void launch();
     const int32_t* wait();                    // the counts, by the problem's own read-back
-    void finish(const int32_t* hc);
+    void finish(const int32_t* hc);           // of a batch, the launch orders are sorted after it
+    int32_t* order() const { return (int32_t*)at(W, o_order); }
+    void sort_order(int32_t nnzC);
     size_t value_bytes() const { return (size_t)na.nseg * A->b * A->b * (prec == QT_F32 ? sizeof(float) : sizeof(double)); }
     void bind_values(char* values);
 };
@@ -2208,7 +2217,7 @@ void Symbolic::plan() {
     const int64_t kdim = (op.ta ? A->n_rows : A->n_cols) / A->b;
     while ((int64_t(1) << kbits) < kdim) ++kbits;
     const int64_t read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
-    may_korder = !small && P < 2 * cap && read_bytes >= KORDER_MIN_BYTES && kbits <= KORDER_MAX_BITS;
+    may_korder = P < 2 * cap && kbits <= KORDER_MAX_BITS && (batched || (!small && read_bytes >= KORDER_MIN_BYTES));
     ArenaPlan keep, tmp;   // keep: C's tree; tmp: scratch freed after the call
     o_child.resize(L);
     o_key.resize(L + 1);
@@ -2223,6 +2232,11 @@ void Symbolic::plan() {
     o_prodA = tmp.take(P * sizeof(int32_t));
     o_prodB = tmp.take(P * sizeof(int32_t));
     o_cbseg = tmp.take((cap + 1) * sizeof(int32_t));
+    if (may_strip || may_korder) {   // one order is built at most
+        o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
+                                   may_korder ? sort_tmp_bound(cap, kbits) : 0) * sizeof(int32_t));
+        o_order = tmp.take(cap * sizeof(int32_t));
+    }
     // The scratch of the level by level traversal from here on (a small
     // product's stays in LDS): first the tree before NIL normalisation.
     const size_t small_bytes = tmp.bytes;
@@ -2272,10 +2286,6 @@ void Symbolic::plan() {
     }
     o_scan = tmp.take((scan_elems + 1) * sizeof(int64_t));
     o_lcnt = sparse ? 0 : tmp.take(ncap[L] * 64 * sizeof(int32_t));   // leaf step: products per block position
-    if (may_strip || may_korder)   // one order is built at most
-        o_sort = tmp.take(std::max(may_strip ? sort_tmp_bound(cap, strip_bits) : 0,
-                                   may_korder ? sort_tmp_bound(cap, kbits) : 0) * sizeof(int32_t));
-    if (may_strip || may_korder) o_order = tmp.take(cap * sizeof(int32_t));
     o_count = tmp.take(ncounts() * sizeof(int32_t));
 
     out.C.reset(new_result(A, B, L, prec, s, op));
@@ -2635,16 +2645,11 @@ void Symbolic::finish(const int32_t* hc) {
     const int32_t nnzC = hc[L + 1];
     if (nnzC < 0 || nnzC > cap || (nnzC == 0 && !bounds)) fail(QT_ERR_DEVICE, "symbolic phase: C block count out of range");
 
-    int32_t* order = (may_strip || may_korder) ? (int32_t*)at(W, o_order) : nullptr;
-    const bool strips = may_strip && nnzC >= STRIP_MIN_BLOCKS && C->products >= 2 * (int64_t)nnzC;
-    const bool korder = may_korder && nnzC > 0 && C->products < 2 * (int64_t)nnzC;
-    if (strips || korder) {
-        int32_t* sort_tmp = (int32_t*)at(W, o_sort);
+    strips = may_strip && nnzC >= STRIP_MIN_BLOCKS && C->products >= 2 * (int64_t)nnzC;
+    korder = may_korder && nnzC > 0 && C->products < 2 * (int64_t)nnzC;
+    if ((strips || korder) && !batched) {
         running = true;   // until s runs after the sort, which uses the scratch
-        if (strips)
-            stable_sort(StripKeys{ls.cbkey, strip_log}, OrderSink{order}, nnzC, strip_bits, sort_tmp, order, ss);
-        else
-            stable_sort(FirstKeys{Av->bkey.p, ls.prodA, ls.cbseg}, OrderSink{order}, nnzC, kbits, sort_tmp, order, ss);
+        sort_order(nnzC);
         if (prof) QT_HIP(hipEventRecord(ev.e1, ss));   // the symbolic phase ends here then
         QT_HIP(stream_after(s, ss));
         running = false;
@@ -2671,12 +2676,21 @@ void Symbolic::finish(const int32_t* hc) {
     na.prodA = ls.prodA;
     na.prodB = ls.prodB;
     na.seg = ls.cbseg;
-    na.order = (strips || korder) ? order : nullptr;
+    na.order = (strips || korder) ? order() : nullptr;
     na.by_k = korder ? 1 : 0;
     na.nseg = nnzC;
     ev.products = C->products;
     ev.cblocks = nnzC;
     if (!batched) bind_values(nullptr);
+}
+
+// The launch order that finish() chose, sorted on ss.
+void Symbolic::sort_order(int32_t nnzC) {
+    int32_t* tmp = (int32_t*)at(W, o_sort);
+    if (strips)
+        stable_sort(StripKeys{ls.cbkey, strip_log}, OrderSink{order()}, nnzC, strip_bits, tmp, order(), ss);
+    else
+        stable_sort(FirstKeys{Av->bkey.p, ls.prodA, ls.cbseg}, OrderSink{order()}, nnzC, kbits, tmp, order(), ss);
 }
 
 // C's values: a buffer of its own (NULL), or part of a shared one.
@@ -2818,8 +2832,49 @@ static std::vector<char*> shared_parts(const std::vector<size_t>& bytes, hipStre
     return at;
 }
 
+// The launch orders of the problems of `who`; s runs after them. Orders by inner
+// index of up to RANK_SORT_MAX blocks share one launch: a launch, an event and a
+// wait for each took 17 us a problem (plans of 64 small problems 268 and 1387 us).
+static void sort_orders(const std::vector<Symbolic*>& who, std::vector<char>& host, DBuf<char>& dev, hipStream_t s,
+                        hipStream_t ss) {
+    typedef RankJob<FirstKeys, OrderSink> Job;
+    struct Drain {   // the sorts use the problems' scratch: after an error they have ended before it goes
+        hipStream_t st;
+        bool on;
+        ~Drain() {
+            if (on) (void)hipStreamSynchronize(st);
+        }
+    } drain{ss, false};
+    std::vector<Job> jobs;
+    int32_t most = 0;
+    for (Symbolic* p : who) {
+        if (!p->strips && !p->korder) continue;
+        const int32_t n = p->na.nseg;
+        if (p->korder && n <= RANK_SORT_MAX) {
+            jobs.push_back(Job{FirstKeys{p->Av->bkey.p, p->ls.prodA, p->ls.cbseg}, OrderSink{p->order()}, n});
+            most = std::max(most, n);
+            continue;
+        }
+        drain.on = true;
+        p->sort_order(n);
+    }
+    if (!jobs.empty()) {
+        host.assign((const char*)jobs.data(), (const char*)(jobs.data() + jobs.size()));
+        dev.alloc(host.size(), ss);
+        drain.on = true;
+        QT_HIP(hipMemcpyAsync(dev.p, host.data(), host.size(), hipMemcpyHostToDevice, ss));
+        k_rank_sort_many<FirstKeys, OrderSink>
+            <<<dim3((unsigned)((most + 63) / 64), (unsigned)jobs.size()), 256, most * sizeof(uint64_t), ss>>>(
+                (const Job*)dev.p);
+        QT_LAUNCH("k_rank_sort_many");
+    }
+    if (!drain.on) return;
+    QT_HIP(stream_after(s, ss));
+    drain.on = false;
+}
+
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
-                    SymbolicOut* out, std::vector<DBuf<char>>& pool) {
+                    SymbolicOut* out, std::vector<DBuf<char>>& pool, std::deque<std::vector<char>>& copied) {
     for (int32_t at = 0; at < count; at += MANY_MAX) {
         const int32_t n = std::min(MANY_MAX, count - at);
         // declared before the problems, whose destructors wait for the kernels
@@ -2882,6 +2937,7 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         QT_HIP(ordered);
         for (size_t i = 0; i < order.size(); ++i) order[i]->finish(hc + i * stride);
         for (Symbolic* p : alone) p->finish(p->wait());
+        sort_orders(work, copied.emplace_back(), dev.emplace_back(), s, ss);
         bytes.clear();
         for (Symbolic* p : work) bytes.push_back(p->value_bytes());
         const std::vector<char*> values = shared_parts(bytes, s, s, pool);

@@ -1,12 +1,13 @@
 // Batched multiplies: many independent C_i = A_i * B_i in one launch.
 //
 // qt_plan_create runs the symbolic phases of all problems, their launches
-// shared (it synchronizes and allocates every C_i), then lays the numeric work of all problems out as
-// one list of work items: problems ordered by decreasing block products (the
+// shared (it synchronizes and allocates every C_i), then lays the numeric work
+// of all problems out as one list of work items: problems ordered by decreasing block products (the
 // longest first, so the tail of the launch is made of small ones), the C
-// blocks of a problem in the launch order a single multiply would use
-// (Morton order, whose neighbouring blocks share operand blocks in cache, or
-// grouped by inner index where C blocks average under two block products).
+// blocks of a problem in its launch order (Morton order, whose neighbouring
+// blocks share operand blocks in cache; strips of block rows at b = 64; grouped
+// by inner index where C blocks average under two block products, at any size,
+// since a plan pays for the order once and runs it many times).
 // qt_plan_execute runs the numeric phase of the whole batch as one kernel
 // launch that allocates nothing and never synchronizes (a caller may capture
 // it); the first qt_plan_replay captures it (counter reset kernel + batch
@@ -105,11 +106,18 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     plan->scratch.resize(count);
     std::vector<NumericArgs> na(count);
     std::vector<int64_t> prods(count, 0);
+    // host memory that queued copies read: it stays until they have ended, also
+    // when a later step throws
+    std::deque<std::vector<char>> sources;
+    struct Drain {
+        hipStream_t s;
+        ~Drain() { (void)hipStreamSynchronize(s); }
+    } drain{s};
     {
-        // with the launch orders the single multiplies would use
+        // with their launch orders
         std::vector<SymbolicOut> sym(count);
         symbolic_batch(count, const_cast<qt_matrix* const*>(A), const_cast<qt_matrix* const*>(B), prec, s, sym.data(),
-                       plan->pool);
+                       plan->pool, sources);
         for (int32_t i = 0; i < count; ++i) {
             na[i] = sym[i].na;
             prods[i] = sym[i].C->products;
@@ -192,15 +200,10 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     plan->dev.alloc(ap.bytes, s);
     char* const W = apart.p ? apart.p : plan->dev.p + o_work;
     char* D = plan->dev.p;
-    std::vector<char> host(copied);
+    std::vector<char>& host = sources.emplace_back(copied);
     std::memcpy(host.data() + o_probs, hp.data(), hp.size() * sizeof(BatchProblem));
     std::memcpy(host.data() + o_base_t, base_t.data(), base_t.size() * sizeof(int64_t));
     std::memcpy(host.data() + o_base_b, base_b.data(), base_b.size() * sizeof(int64_t));
-    // `host` stays until the copy has ended: also when a later step throws
-    struct Drain {
-        hipStream_t s;
-        ~Drain() { (void)hipStreamSynchronize(s); }
-    } drain{s};
     QT_HIP(hipMemcpyAsync(D, host.data(), copied, hipMemcpyHostToDevice, s));
 
     plan->probs_own = (const BatchProblem*)(D + o_probs);

@@ -54,15 +54,18 @@ inline size_t sort_tmp_words(int64_t n, int key_bits) {
     return (size_t)p.bins() * (p.tiles + 1) + (p.passes > 1 ? (size_t)n : 0);
 }
 
-// The same for any number of entries up to n (fewer can mean more tiles).
+// The same for any number of entries up to n (beyond the smallest tiles, fewer
+// entries can mean more tiles).
 inline size_t sort_tmp_bound(int64_t n, int key_bits) {
+    if (n <= RANK_SORT_MAX) return 0;
     const RadixPlan p = radix_plan(n, key_bits);
-    return (size_t)p.bins() * (RADIX_TILES_MAX + 1) + (p.passes > 1 ? (size_t)n : 0);
+    const int64_t tiles = p.tile == RADIX_TILE_MIN ? p.tiles : RADIX_TILES_MAX;
+    return (size_t)p.bins() * (tiles + 1) + (p.passes > 1 ? (size_t)n : 0);
 }
 
+// Entries 64 blockIdx.x .. + 63 to their places (256 threads; sort_keys: n words of LDS).
 template <class Src, class Sink>
-__global__ __launch_bounds__(256) void k_rank_sort(Src src, Sink sink, int n) {
-    extern __shared__ uint64_t sort_keys[];
+__device__ __forceinline__ void rank_sort(const Src& src, const Sink& sink, int n, uint64_t* sort_keys) {
     __shared__ int part[4][64];
     for (int t = threadIdx.x; t < n; t += 256) sort_keys[t] = src(t);
     __syncthreads();
@@ -79,6 +82,28 @@ __global__ __launch_bounds__(256) void k_rank_sort(Src src, Sink sink, int n) {
     part[wave][lane] = before;
     __syncthreads();
     if (wave == 0 && item < n) sink(part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane], item, k);
+}
+
+template <class Src, class Sink>
+__global__ __launch_bounds__(256) void k_rank_sort(Src src, Sink sink, int n) {
+    extern __shared__ uint64_t sort_keys[];
+    rank_sort(src, sink, n, sort_keys);
+}
+
+// Several sorts of up to RANK_SORT_MAX entries in one launch: the job is the
+// workgroup's y index.
+template <class Src, class Sink>
+struct RankJob {
+    Src src;
+    Sink sink;
+    int32_t n;
+};
+
+template <class Src, class Sink>
+__global__ __launch_bounds__(256) void k_rank_sort_many(const RankJob<Src, Sink>* __restrict__ jobs) {
+    extern __shared__ uint64_t sort_keys[];
+    const RankJob<Src, Sink> j = jobs[blockIdx.y];
+    if ((int)blockIdx.x * 64 < j.n) rank_sort(j.src, j.sink, j.n, sort_keys);
 }
 
 // counts[tile * bins + d]: entries of the tile whose digit is d

@@ -328,7 +328,8 @@ void qt_free(qt_matrix* M);
  * Errors: ARG, SHAPE, OOM, DEVICE, UNSUPPORTED.
  *
  * qt_plan_execute computes every C_i: one kernel launch (plus a one-thread
- * counter reset for the dynamic schedules, a kernel, not a memset) on
+ * counter reset for the dynamic schedules, a kernel, not a memset, and once the
+ * kernels that make launch orders, see QT_PLAN_ORDER_MORTON) on
  * `stream`, which allocates nothing and does not synchronize, so a caller may
  * capture it into a HIP graph of its own. qt_plan_replay computes the same:
  * its first call captures that launch sequence into a HIP graph the plan
@@ -350,10 +351,13 @@ void qt_free(qt_matrix* M);
  *   schedule 3  persistent, dynamic: 16 items at a time from a counter;
  *   QT_PLAN_ORDER_MORTON  every problem's C blocks in Morton order (without
  *               it a problem is launched by inner index where its C blocks
- *               average under two block products (qt_multiply sorts C blocks
- *               so only where the products read 700 MB of operand blocks or
- *               more), in strips of block rows at b = 64 as in qt_multiply,
- *               else in Morton order);
+ *               average under two block products, in strips of block rows at
+ *               b = 64 as in qt_multiply, else in Morton order. By inner
+ *               index below 700 MB of operand blocks, where qt_multiply keeps
+ *               Morton order, only a plan that runs again gains: these orders
+ *               are made by the first qt_plan_replay or qt_plan_tune, or by the
+ *               second qt_plan_execute, on its stream, before the plan runs,
+ *               unless that stream is being captured);
  *   QT_PLAN_TILE_WAVE     at b = 64, one wave per 32 x 32 tile instead of one
  *               four-wave workgroup per C block sharing its operands through
  *               LDS (no effect at other block sizes).

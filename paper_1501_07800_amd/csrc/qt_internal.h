@@ -5,7 +5,6 @@
 
 #include <cstdint>
 #include <cstring>
-#include <deque>
 #include <memory>
 #include <mutex>
 #include <stdexcept>
@@ -306,8 +305,20 @@ struct PhaseEvents { hipEvent_t e0, e1, e2, e3; int64_t products, cblocks; };
 void profile_push(const PhaseEvents& ev);
 
 // multiply.hip -------------------------------------------------------------
+// A launch order by inner index that is not sorted yet (device arrays; akey: the
+// keys of A's blocks, there as long as A is).
+struct LaterOrder {
+    const uint64_t* akey = nullptr;
+    const int32_t* prodA = nullptr;
+    const int32_t* seg = nullptr;
+    int32_t* order = nullptr;   // nullptr: there is none
+    int32_t* tmp = nullptr;
+    int32_t n = 0;
+    int kbits = 1;
+};
 struct SymbolicOut {
     std::unique_ptr<qt_matrix> C;
+    LaterOrder later;         // of a batch's problem
     DBuf<char> scratch;       // product lists and other symbolic buffers
     NumericArgs na{};         // ready for launch_numeric (na.nseg C blocks)
     PhaseEvents ev{};
@@ -321,10 +332,15 @@ struct MulOp {
 };
 // The symbolic phases of count plain products, launches shared where they can
 // be; out[0 .. count), whose buffers are parts of those added to `pool`, each with
-// the launch order of its C blocks. `copied`: host memory that work queued on s
-// or before it may still read; it is kept until s has been waited for.
+// its launch order, or what a later one is sorted from.
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
-                    SymbolicOut* out, std::vector<DBuf<char>>& pool, std::deque<std::vector<char>>& copied);
+                    SymbolicOut* out, std::vector<DBuf<char>>& pool);
+// The later orders of `who`, queued on s; jobs (device): a record of
+// later_job_bytes() for each that later_shares(), in turn, as later_job() writes it.
+size_t later_job_bytes();
+bool later_shares(const LaterOrder& o);
+void later_job(const LaterOrder& o, void* job);
+void sort_later(const std::vector<LaterOrder>& who, const void* jobs, hipStream_t s);
 qt_matrix* multiply(qt_matrix* A, qt_matrix* B, qt_prec prec, hipStream_t s, const MulOp& op = MulOp{});
 qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_t nblocks, const int32_t* I,
                  const int32_t* J, const double* values, qt_mem where, hipStream_t s);

@@ -1501,12 +1501,13 @@ struct OrderSink {
 // FP32 b = 32, 0.42 GB 225 and 248 us, 0.82 GB 311 and 312, 4.0 GB 944 and 818;
 // FP64 b = 32, 0.35 GB 203 and 209, 0.84 GB 302 and 272, 8.0 GB 1663 and 1070;
 // FP64 b = 16, 0.41 GB 240 and 247, 2.0 GB 565 and 492.
-// A plan's problems are sorted at any size: it pays once, 30 to 60 us when it is
-// made, and gains at every run. Replays, Morton and by k: b = 16 FP64, one problem
-// of 64 k blocks 54.8 and 36.5 us, 16 of 4 k 53.5 and 44.0, 64 of 1 k 50.2 and 42.7; b =
-// 32, 8 of 4.5 k FP64 113.8 and 86.2, one of 61 k BF16X3 130 and 103; b = 64, 4 of 2.6 k
-// FP32 74.9 and 68.9. Slower, by 2 to 6 %: b = 32 FP32, 64 of 2.1 k 199 and 211, 8 of 25 k
-// 323 and 335 (qt_plan_tune tries both).
+// A plan sorts once and runs many times: its problems are sorted at any size, the
+// smaller ones when it first runs again (a plan that runs once would lose what the
+// sorts take, 16 problems made, run and read out 1156 and 1228 us). Replays, Morton
+// and by k, in us: b = 16 FP64, one problem of 64 k blocks 54.8 and 36.5, 16 of 4 k 53.5
+// and 44.0, 64 of 1 k 50.2 and 42.7; b = 32, 8 of 4.5 k FP64 113.8 and 86.2, one of 61 k
+// BF16X3 130 and 103; b = 64, 4 of 2.6 k FP32 74.9 and 68.9. Slower, by 2 to 6 %: b = 32 FP32,
+// 64 of 2.1 k 199 and 211, 8 of 25 k 323 and 335 (qt_plan_tune tries both).
 constexpr int64_t KORDER_MIN_BYTES = int64_t(700) << 20;
 constexpr int KORDER_MAX_BITS = 22;   // inner blocks: two sort passes
 
@@ -2022,7 +2023,7 @@ struct Symbolic {
     hipStream_t ss = nullptr;                 // the traversal's stream
     std::vector<int64_t> pairs, ncap, foff, gsum_at;
     std::vector<int32_t> group;               // levels taken a pair per lane: C nodes per wave, else 0
-    int64_t P = 0, cap = 0, nil_tiles = 0, nclear = 0;
+    int64_t P = 0, cap = 0, nil_tiles = 0, nclear = 0, read_bytes = 0;
     qt_matrix* Av = nullptr;
     NumericArgs na{};
     std::vector<size_t> o_child, o_key, u_child, u_key, u_parent, o_fa, o_fb, o_cseg, o_cnt, o_off, o_tot, o_wagg;
@@ -2042,6 +2043,7 @@ struct Symbolic {
     hipError_t traced = hipSuccess;
     bool running = false;                     // launched, not known to have ended
     bool strips = false, korder = false;      // the launch order, known once C's blocks are counted
+    bool later = false;                       // by inner index, left to the plan
 
     Symbolic(qt_matrix* a, qt_matrix* b, qt_prec p, hipStream_t stream, SymbolicOut& o, const MulOp& which)
         : A(a), B(b), prec(p), s(stream), out(o), op(which) {}
@@ -2216,7 +2218,7 @@ void Symbolic::plan() {
     // the products are then fewer than twice the C blocks (cap bounds those)
     const int64_t kdim = (op.ta ? A->n_rows : A->n_cols) / A->b;
     while ((int64_t(1) << kbits) < kdim) ++kbits;
-    const int64_t read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
+    read_bytes = 2 * P * A->b * A->b * (prec == QT_F64 ? 8 : 4);
     may_korder = P < 2 * cap && kbits <= KORDER_MAX_BITS && (batched || (!small && read_bytes >= KORDER_MIN_BYTES));
     ArenaPlan keep, tmp;   // keep: C's tree; tmp: scratch freed after the call
     o_child.resize(L);
@@ -2647,6 +2649,9 @@ void Symbolic::finish(const int32_t* hc) {
 
     strips = may_strip && nnzC >= STRIP_MIN_BLOCKS && C->products >= 2 * (int64_t)nnzC;
     korder = may_korder && nnzC > 0 && C->products < 2 * (int64_t)nnzC;
+    later = korder && batched && read_bytes < KORDER_MIN_BYTES;
+    if (later)
+        out.later = LaterOrder{Av->bkey.p, ls.prodA, ls.cbseg, order(), (int32_t*)at(W, o_sort), nnzC, kbits};
     if ((strips || korder) && !batched) {
         running = true;   // until s runs after the sort, which uses the scratch
         sort_order(nnzC);
@@ -2676,8 +2681,8 @@ void Symbolic::finish(const int32_t* hc) {
     na.prodA = ls.prodA;
     na.prodB = ls.prodB;
     na.seg = ls.cbseg;
-    na.order = (strips || korder) ? order() : nullptr;
-    na.by_k = korder ? 1 : 0;
+    na.order = (strips || (korder && !later)) ? order() : nullptr;
+    na.by_k = korder && !later ? 1 : 0;
     na.nseg = nnzC;
     ev.products = C->products;
     ev.cblocks = nnzC;
@@ -2832,12 +2837,9 @@ static std::vector<char*> shared_parts(const std::vector<size_t>& bytes, hipStre
     return at;
 }
 
-// The launch orders of the problems of `who`; s runs after them. Orders by inner
-// index of up to RANK_SORT_MAX blocks share one launch: a launch, an event and a
-// wait for each took 17 us a problem (plans of 64 small problems 268 and 1387 us).
-static void sort_orders(const std::vector<Symbolic*>& who, std::vector<char>& host, DBuf<char>& dev, hipStream_t s,
-                        hipStream_t ss) {
-    typedef RankJob<FirstKeys, OrderSink> Job;
+// The launch orders of the problems of `who`, but those left to the plan; s runs
+// after them.
+static void sort_orders(const std::vector<Symbolic*>& who, hipStream_t s, hipStream_t ss) {
     struct Drain {   // the sorts use the problems' scratch: after an error they have ended before it goes
         hipStream_t st;
         bool on;
@@ -2845,36 +2847,49 @@ static void sort_orders(const std::vector<Symbolic*>& who, std::vector<char>& ho
             if (on) (void)hipStreamSynchronize(st);
         }
     } drain{ss, false};
-    std::vector<Job> jobs;
-    int32_t most = 0;
     for (Symbolic* p : who) {
-        if (!p->strips && !p->korder) continue;
-        const int32_t n = p->na.nseg;
-        if (p->korder && n <= RANK_SORT_MAX) {
-            jobs.push_back(Job{FirstKeys{p->Av->bkey.p, p->ls.prodA, p->ls.cbseg}, OrderSink{p->order()}, n});
-            most = std::max(most, n);
-            continue;
-        }
+        if (!p->strips && (!p->korder || p->later)) continue;
         drain.on = true;
-        p->sort_order(n);
-    }
-    if (!jobs.empty()) {
-        host.assign((const char*)jobs.data(), (const char*)(jobs.data() + jobs.size()));
-        dev.alloc(host.size(), ss);
-        drain.on = true;
-        QT_HIP(hipMemcpyAsync(dev.p, host.data(), host.size(), hipMemcpyHostToDevice, ss));
-        k_rank_sort_many<FirstKeys, OrderSink>
-            <<<dim3((unsigned)((most + 63) / 64), (unsigned)jobs.size()), 256, most * sizeof(uint64_t), ss>>>(
-                (const Job*)dev.p);
-        QT_LAUNCH("k_rank_sort_many");
+        p->sort_order(p->na.nseg);
     }
     if (!drain.on) return;
     QT_HIP(stream_after(s, ss));
     drain.on = false;
 }
 
+// A plan's orders by inner index, sorted when it first runs again. Those of up to
+// RANK_SORT_MAX blocks share a launch: one, with an event and a wait, for each took 17 us
+// a problem (64 small ones 1.1 ms).
+typedef RankJob<FirstKeys, OrderSink> LaterJob;
+
+size_t later_job_bytes() { return sizeof(LaterJob); }
+bool later_shares(const LaterOrder& o) { return o.n <= RANK_SORT_MAX; }
+void later_job(const LaterOrder& o, void* job) {
+    const LaterJob j{FirstKeys{o.akey, o.prodA, o.seg}, OrderSink{o.order}, o.n};
+    std::memcpy(job, &j, sizeof(j));
+}
+
+void sort_later(const std::vector<LaterOrder>& who, const void* jobs, hipStream_t s) {
+    int32_t most = 0;
+    unsigned shared = 0;
+    for (const LaterOrder& o : who) {
+        if (later_shares(o)) {
+            most = std::max(most, o.n);
+            ++shared;
+        } else {
+            stable_sort(FirstKeys{o.akey, o.prodA, o.seg}, OrderSink{o.order}, o.n, o.kbits, o.tmp, o.order, s);
+        }
+    }
+    for (unsigned at = 0; at < shared; at += 32768) {   // of the 65535 a grid may have in y
+        const dim3 grid((unsigned)((most + 63) / 64), std::min(shared - at, 32768u));
+        k_rank_sort_many<FirstKeys, OrderSink>
+            <<<grid, 256, most * sizeof(uint64_t), s>>>((const LaterJob*)jobs + at);
+        QT_LAUNCH("k_rank_sort_many");
+    }
+}
+
 void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_prec prec, hipStream_t s,
-                    SymbolicOut* out, std::vector<DBuf<char>>& pool, std::deque<std::vector<char>>& copied) {
+                    SymbolicOut* out, std::vector<DBuf<char>>& pool) {
     for (int32_t at = 0; at < count; at += MANY_MAX) {
         const int32_t n = std::min(MANY_MAX, count - at);
         // declared before the problems, whose destructors wait for the kernels
@@ -2937,7 +2952,7 @@ void symbolic_batch(int32_t count, qt_matrix* const* A, qt_matrix* const* B, qt_
         QT_HIP(ordered);
         for (size_t i = 0; i < order.size(); ++i) order[i]->finish(hc + i * stride);
         for (Symbolic* p : alone) p->finish(p->wait());
-        sort_orders(work, copied.emplace_back(), dev.emplace_back(), s, ss);
+        sort_orders(work, s, ss);
         bytes.clear();
         for (Symbolic* p : work) bytes.push_back(p->value_bytes());
         const std::vector<char*> values = shared_parts(bytes, s, s, pool);

@@ -7,7 +7,8 @@
 // blocks of a problem in its launch order (Morton order, whose neighbouring
 // blocks share operand blocks in cache; strips of block rows at b = 64; grouped
 // by inner index where C blocks average under two block products, at any size,
-// since a plan pays for the order once and runs it many times).
+// since a plan that runs again pays for the order once: the smaller problems'
+// are sorted when it does, or is replayed or tuned).
 // qt_plan_execute runs the numeric phase of the whole batch as one kernel
 // launch that allocates nothing and never synchronizes (a caller may capture
 // it); the first qt_plan_replay captures it (counter reset kernel + batch
@@ -51,6 +52,15 @@ struct qt_plan {
     int64_t items_tiles = 0, items_blocks = 0;
     bool has_order = false;   // some problem has a launch order of its own
     const int64_t* cum_of[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [Morton][C blocks]
+    // orders that are sorted when the plan first runs again (see order_later): the
+    // problems with these too, and where their work prefix sums go
+    std::vector<qt::LaterOrder> later;
+    const qt::BatchProblem* probs_later = nullptr;
+    const char* later_jobs = nullptr;
+    int64_t* cum_later[2] = {nullptr, nullptr};
+    int64_t* cost = nullptr;
+    int64_t* scan = nullptr;
+    bool ran = false;
     int32_t config = 0;       // schedule | QT_PLAN_ORDER_MORTON | QT_PLAN_TILE_WAVE
     hipStream_t capture_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -106,21 +116,16 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     plan->scratch.resize(count);
     std::vector<NumericArgs> na(count);
     std::vector<int64_t> prods(count, 0);
-    // host memory that queued copies read: it stays until they have ended, also
-    // when a later step throws
-    std::deque<std::vector<char>> sources;
-    struct Drain {
-        hipStream_t s;
-        ~Drain() { (void)hipStreamSynchronize(s); }
-    } drain{s};
+    std::vector<LaterOrder> later(count);
     {
         // with their launch orders
         std::vector<SymbolicOut> sym(count);
         symbolic_batch(count, const_cast<qt_matrix* const*>(A), const_cast<qt_matrix* const*>(B), prec, s, sym.data(),
-                       plan->pool, sources);
+                       plan->pool);
         for (int32_t i = 0; i < count; ++i) {
             na[i] = sym[i].na;
             prods[i] = sym[i].C->products;
+            later[i] = sym[i].later;
             plan->results[i] = std::move(sym[i].C);
             plan->results[i]->plan_owned = true;
             plan->scratch[i] = std::move(sym[i].scratch);
@@ -133,7 +138,8 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return prods[x] > prods[y]; });
     const int wpb = (b == 64) ? 4 : 1;   // per-wave tiles of a C block
     const size_t np = order.size();
-    std::vector<BatchProblem> hp(2 * std::max<size_t>(np, 1));   // [0, np): own launch orders; [np, 2 np): Morton
+    // [0, np): own launch orders; [np, 2 np): Morton; [2 np, 3 np): with the later orders
+    std::vector<BatchProblem> hp(3 * std::max<size_t>(np, 1));
     std::vector<int64_t> base_t(np + 1, 0), base_b(np + 1, 0);    // items: per-wave tiles, C blocks
     // the problems' arrays as offsets from the lowest address among them
     const char* lowest = nullptr;
@@ -144,7 +150,7 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
         const NumericArgs& a = na[order[j]];
         for (const void* p : {a.A, a.B, (const void*)a.Ahi, (const void*)a.Alo, (const void*)a.Bhi_t,
                               (const void*)a.Blo_t, (const void*)a.prodA, (const void*)a.prodB, (const void*)a.seg,
-                              (const void*)a.order, (const void*)a.C})
+                              (const void*)a.order, (const void*)later[order[j]].order, (const void*)a.C})
             note(p);
     }
     auto off = [&](const void* p) -> int64_t { return p ? (int64_t)((const char*)p - lowest) : -1; };
@@ -165,6 +171,12 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
         hp[np + j] = P;
         hp[np + j].order = -1;
         if (a.order) plan->has_order = true;
+        const LaterOrder& lo = later[order[j]];
+        hp[2 * np + j] = P;
+        if (lo.order) {
+            hp[2 * np + j].order = off(lo.order);
+            plan->later.push_back(lo);
+        }
         base_t[j + 1] = base_t[j] + (int64_t)a.nseg * wpb;
         base_b[j + 1] = base_b[j] + (int64_t)a.nseg;
         plan->products += prods[order[j]];
@@ -173,6 +185,8 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     const size_t o_probs = ap.take(hp.size() * sizeof(BatchProblem));
     const size_t o_base_t = ap.take(base_t.size() * sizeof(int64_t));
     const size_t o_base_b = ap.take(base_b.size() * sizeof(int64_t));
+    const size_t shared = std::count_if(plan->later.begin(), plan->later.end(), later_shares);
+    const size_t o_jobs = ap.take(shared * later_job_bytes());
     const size_t copied = ap.bytes;
     const size_t o_counter = ap.take(64 * sizeof(unsigned long long));
     // the balanced schedules' work prefix sums, one per layout of the work
@@ -185,29 +199,50 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     size_t o_cum[2][2] = {};
     for (int o = 0; o < norders; ++o)
         for (int t = 0; t < nforms; ++t) o_cum[o][t] = ap.take((items[t] + 1) * sizeof(int64_t));
+    size_t o_cum_later[2] = {};
+    if (!plan->later.empty())
+        for (int t = 0; t < nforms; ++t) o_cum_later[t] = ap.take((items[t] + 1) * sizeof(int64_t));
     // what the prefix sums are made in: part of the same buffer while it is small
-    // (an allocation takes the host some 8 us), else given back when they are done
+    // (an allocation takes the host some 8 us) or needed again, else given back
+    // when they are done
     ArenaPlan work;
     const size_t o_cost = work.take(std::max<int64_t>(nmax, 1) * sizeof(int64_t));
     const size_t o_scan = work.take((scan_tmp_elems(nmax) + 1) * sizeof(int64_t));
     constexpr size_t WORK_KEPT = size_t(2) << 20;
     DBuf<char> apart;
     size_t o_work = 0;
-    if (work.bytes <= WORK_KEPT)
+    if (work.bytes <= WORK_KEPT || !plan->later.empty())
         o_work = ap.take(work.bytes);
     else
         apart.alloc(work.bytes, s);
     plan->dev.alloc(ap.bytes, s);
     char* const W = apart.p ? apart.p : plan->dev.p + o_work;
     char* D = plan->dev.p;
-    std::vector<char>& host = sources.emplace_back(copied);
+    std::vector<char> host(copied);
     std::memcpy(host.data() + o_probs, hp.data(), hp.size() * sizeof(BatchProblem));
     std::memcpy(host.data() + o_base_t, base_t.data(), base_t.size() * sizeof(int64_t));
     std::memcpy(host.data() + o_base_b, base_b.data(), base_b.size() * sizeof(int64_t));
+    size_t o_job = o_jobs;
+    for (const LaterOrder& lo : plan->later)
+        if (later_shares(lo)) {
+            later_job(lo, host.data() + o_job);
+            o_job += later_job_bytes();
+        }
+    // `host` stays until the copy has ended: also when a later step throws
+    struct Drain {
+        hipStream_t s;
+        ~Drain() { (void)hipStreamSynchronize(s); }
+    } drain{s};
     QT_HIP(hipMemcpyAsync(D, host.data(), copied, hipMemcpyHostToDevice, s));
 
     plan->probs_own = (const BatchProblem*)(D + o_probs);
     plan->probs_morton = plan->probs_own + np;
+    plan->probs_later = plan->probs_own + 2 * np;
+    plan->later_jobs = D + o_jobs;
+    for (int t = 0; t < 2; ++t)
+        if (!plan->later.empty()) plan->cum_later[t] = (int64_t*)(D + o_cum_later[t < nforms ? t : 0]);
+    plan->cost = (int64_t*)(W + o_cost);
+    plan->scan = (int64_t*)(W + o_scan);
     plan->base_tiles = (const int64_t*)(D + o_base_t);
     plan->base_blocks = (const int64_t*)(D + o_base_b);
     plan->items_tiles = base_t.back();
@@ -229,9 +264,8 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
             int64_t* cum = (int64_t*)(D + o_cum[o][t]);
             plan->cum_of[o][t] = cum;
             if (L.total_items > 0) {
-                int64_t* cost = (int64_t*)(W + o_cost);
-                batch_item_costs(L, cost, s);
-                exclusive_scan(cost, cum, L.total_items, (int64_t*)(W + o_scan), s);
+                batch_item_costs(L, plan->cost, s);
+                exclusive_scan(plan->cost, cum, L.total_items, plan->scan, s);
             }
         }
     QT_HIP(hipStreamSynchronize(s));
@@ -240,9 +274,39 @@ qt_plan* plan_create(int32_t count, const qt_matrix* const* A, const qt_matrix* 
     return plan.release();
 }
 
+// Sorts the later orders and puts them to use: queued on s, no allocation and no
+// wait. Not while s is captured (the sorts would run at every replay of it).
+static void order_later(qt_plan* plan, hipStream_t s) {
+    if (plan->later.empty()) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    sort_later(plan->later, plan->later_jobs, s);
+    BatchLaunch L = plan->launch;
+    L.probs = plan->probs_later;
+    for (int t = 0; t < (plan->b == 64 ? 2 : 1); ++t) {
+        L.lds = t == 1;
+        L.item_base = L.lds ? plan->base_blocks : plan->base_tiles;
+        L.total_items = L.lds ? plan->items_blocks : plan->items_tiles;
+        batch_item_costs(L, plan->cost, s);
+        exclusive_scan(plan->cost, plan->cum_later[t], L.total_items, plan->scan, s);
+    }
+    plan->probs_own = plan->probs_later;
+    plan->has_order = true;
+    for (int t = 0; t < 2; ++t) plan->cum_of[0][t] = plan->cum_later[t];
+    plan->later.clear();
+    const int32_t config = plan->config;
+    plan->config = -1;
+    plan->configure(config);
+}
+
 void plan_execute(qt_plan* plan, hipStream_t s, int use_graph) {
     plan->last_stream = s;
     if (plan->launch.total_items <= 0) return;
+    if ((use_graph || plan->ran) && !(plan->config & QT_PLAN_ORDER_MORTON)) order_later(plan, s);
+    plan->ran = true;
     if (!use_graph) {
         launch_batch(plan->launch, s);
         return;
@@ -272,6 +336,8 @@ int plan_tune(qt_plan* plan, hipStream_t s, int reps, float* ms_out) {
     hipEvent_t e0, e1;
     timing_event(&e0);
     timing_event(&e1);
+    plan->last_stream = s;
+    if (plan->launch.total_items > 0) order_later(plan, s);
     const int32_t start = plan->config;
     int32_t best = start;
     float best_ms = -1.f;

@@ -47,10 +47,11 @@ def test_mixed_sizes(qt, b, prec):
         print("plan", b, prec, sizes, name, flush=True)
         plan = qt.Plan(As, Bs, prec)
         plan.set_schedule(name)
-        plan.execute(graph=c % 2 == 0)
-        for i, want in enumerate(ref):
-            for x, y in zip(want, _out(plan.result(i), b, prec)):
-                assert torch.equal(x, y), (name, i)
+        for run in range(3):                 # the orders come with the first replay, the second other run
+            plan.execute(graph=c % 2 == 0)
+            for i, want in enumerate(ref):
+                for x, y in zip(want, _out(plan.result(i), b, prec)):
+                    assert torch.equal(x, y), (name, run, i)
         plan.destroy()
     plan = qt.Plan(As, Bs, prec)
     _, times = plan.tune(reps=1)
@@ -68,4 +69,53 @@ def test_many_problems(qt):
     for i, h in enumerate(hs):
         for x, y in zip(_out(qt.multiply(h, h), b, "f64"), _out(plan.result(i), b, "f64")):
             assert torch.equal(x, y), i
+    plan.destroy()
+
+
+@pytest.mark.parametrize("first", [None, "flat+morton", "balanced", "dynamic-16"])
+def test_captured_runs_and_changes_between(qt, first):
+    """Runs captured by the caller before and after the orders are made, and
+    configurations changed between replays."""
+    import torch
+    b = 32
+    As = [_build(qt, m, k, na, b, 2 * t) for t, (m, k, n, na, nb) in enumerate(MIXED)]
+    Bs = [_build(qt, k, n, nb, b, 2 * t + 1) for t, (m, k, n, na, nb) in enumerate(MIXED)]
+    ref = [_out(qt.multiply(x, y), b, "f64") for x, y in zip(As, Bs)]
+    plan = qt.Plan(As, Bs, "f64")
+    big = torch.randn(1024, 1024, device="cuda")
+
+    def check():
+        for i, want in enumerate(ref):
+            for x, y in zip(want, _out(plan.result(i), b, "f64")):
+                assert torch.equal(x, y), i
+
+    def captured():
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            plan.execute(stream=s, graph=False)
+        return g
+
+    if first:
+        plan.set_schedule(first)
+    graphs = [captured()]
+    plan.execute(graph=False)
+    check()
+    graphs.append(captured())                # the third run, but on a captured stream
+    plan.execute(graph=False)
+    check()
+    graphs.append(captured())
+    for name in ("flat", "balanced", "flat+morton", "xcd-dynamic", "flat"):
+        plan.set_schedule(name)
+        for _ in range(2):
+            plan.execute()
+            big = big @ big
+            big /= big.norm()
+            check()
+    for _ in range(3):
+        for g in graphs:
+            g.replay()
+            torch.cuda.synchronize()
+            check()
     plan.destroy()

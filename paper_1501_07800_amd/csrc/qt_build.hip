@@ -628,7 +628,7 @@ static void adopt_histograms(qt_matrix* M, const int32_t* w) {
 
 void build_histograms(qt_matrix* M, hipStream_t s) {
     std::lock_guard<std::mutex> lk(M->mu);
-    if (M->hist.ready) return;
+    if (M->hist.ready || M->nblocks == 0) return;   // (nothing counts an empty matrix's pairs)
     const int64_t nb_pad = (int64_t)M->lb << M->L;
     const int64_t total = histogram_words(M);
     DBuf<int32_t> d(total, s);
@@ -645,10 +645,8 @@ void build_histograms(qt_matrix* M, hipStream_t s) {
         }
         off += 2 * side;
     }
-    if (M->nblocks > 0) {
-        k_hist<<<grid_for(M->nblocks), 256, 0, s>>>(M->bkey.p, M->nblocks, d.p + off, d.p + off + nb_pad);
-        QT_LAUNCH("k_hist");
-    }
+    k_hist<<<grid_for(M->nblocks), 256, 0, s>>>(M->bkey.p, M->nblocks, d.p + off, d.p + off + nb_pad);
+    QT_LAUNCH("k_hist");
     ReadBack words(total);
     words.publish(d.p, s);
     adopt_histograms(M, words.wait(s));
@@ -973,10 +971,7 @@ qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_
     M->levels.resize(L);
     const int bb = b * b;
 
-    if (nblocks == 0) {
-        build_histograms(M.get(), s);
-        return M.release();
-    }
+    if (nblocks == 0) return M.release();
 
     // operands on the device
     DBuf<int32_t> dI, dJ;
@@ -1497,8 +1492,6 @@ qt_matrix* symmetric_full(qt_matrix* A, hipStream_t s) {
         k_gather_i32<<<grid_for(total), 256, 0, s>>>(src.p, perm.p, total, S->bmap.p);
         QT_LAUNCH("k_gather_i32");
         tree_finish(job, s);
-    } else {
-        build_histograms(S.get(), s);
     }
     A->sym_full = std::move(S);
     return A->sym_full.get();

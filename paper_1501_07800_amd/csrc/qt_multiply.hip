@@ -1988,15 +1988,6 @@ static qt_matrix* empty_result(const qt_matrix* A, const qt_matrix* B, int L, qt
                                const MulOp& op) {
     qt_matrix* C = new_result(A, B, L, prec, s, op);
     C->pairs.assign(L + 1, 0);
-    C->hist.ready = true;
-    C->hist.rowcnt.resize(L + 1);
-    C->hist.colcnt.resize(L + 1);
-    for (int l = 0; l <= L; ++l) {
-        C->hist.rowcnt[l].assign(size_t(1) << l, 0);
-        C->hist.colcnt[l].assign(size_t(1) << l, 0);
-    }
-    C->hist.blk_row.assign((size_t)C->lb << L, 0);
-    C->hist.blk_col.assign((size_t)C->lb << L, 0);
     return C;
 }
 

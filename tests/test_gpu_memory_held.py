@@ -138,3 +138,22 @@ def test_band_of_full_leaves(qt, counting):
     C = qt.sysq(A)
     for x, y in zip(B.to_blocks(), C.to_blocks()):
         assert (x == (4 * y if y.ndim == 3 else y)).all()
+
+
+def test_empty_matrices_of_many_block_rows(qt, counting):
+    """2^30 block rows and columns, no block: nothing is counted, held or summed
+    over the positions, whatever is done with the matrix."""
+    import numpy as np
+    b, n = 16, 1 << 34
+    none = (np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros((0, b, b)))
+    before = counting.held()
+    A = qt.build(n, n, b, 8 * b, *none)
+    for C in (qt.multiply(A, A), qt.multiply_ex(A, A, trans_a=True, prec="f32"), qt.sysq(A), qt.add(A, A),
+              qt.truncate(A, 1.0)[0]):
+        assert C.nblocks == 0 and C.info()["n_rows"] == n
+        assert qt.multiply(C, A).nblocks == 0
+    plan = qt.Plan([A, A], [A, A], "f64")
+    plan.execute()
+    assert plan.result(1).nblocks == 0
+    plan.destroy()
+    assert counting.held() - before <= 1 << 20

@@ -105,11 +105,16 @@ __device__ __forceinline__ int64_t xcd_logical(int64_t w, int log) {
 // blocks on one XCD (its numeric kernel 22.7 instead of 11.3 us) and one of
 // 70 k blocks with nine runs on some XCDs and eight on others (sysq of a
 // 24576 decay matrix 818 instead of 746 us with the copy-out).
+// BF16X3 at b = 64 is fed from L2 more than any other path and takes longer runs, 5
+// to an XCD (decay products, runs of 256 whatever the size, 16 to an XCD, 5: 1460 C
+// blocks 56.5, 55.4, 48.9 us, 6852 206, 228, 197, 13188 301, 315, 301; A^T A of 6790
+// 190, 195, 175; symmetric squares of 6588 178, 188, 161, of 15756 321, 353, 321).
+constexpr int XCD_RUNS = 16, XCD_RUNS_BF16_B64 = 5;
 struct XcdGrid {
     unsigned grid;
     int log;
-    XcdGrid(int64_t tiles, int max_log) : log(max_log) {
-        while (log > 0 && tiles < (int64_t(128) << log)) --log;
+    XcdGrid(int64_t tiles, int max_log, int runs = XCD_RUNS) : log(max_log) {
+        while (log > 0 && tiles < (int64_t(8 * runs) << log)) --log;
         const int64_t q = int64_t(8) << log;
         const int64_t g = (tiles + q - 1) / q * q;
         if (g > 0x7fffffffLL) fail(QT_ERR_UNSUPPORTED, "numeric launch too large");
@@ -1097,7 +1102,7 @@ __global__ __launch_bounds__(256, 2) void k_numeric_bf16x3_op_b64(SplitOps ops, 
 template <int BS>
 static void launch_bf(const NumericArgs& a, hipStream_t s) {
     if (BS == 64) {
-        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64, XCD_RUNS_BF16_B64);
         k_numeric_bf16x3_b64<<<x.grid, 256, 0, s>>>(a.Ahi, a.Alo, a.Bhi_t, a.Blo_t, a.prodA, a.prodB, a.seg,
                                                   a.nseg, a.order, (double*)a.C, x.log);
         QT_LAUNCH("k_numeric_bf16x3_b64");
@@ -1129,7 +1134,7 @@ template <int BS>
 static void launch_bf_op(const NumericArgs& a, hipStream_t s) {
     const SplitOps ops{a.Ahi, a.Alo, a.Ahi_t, a.Alo_t, a.Bhi, a.Blo, a.Bhi_t, a.Blo_t};
     if constexpr (BS == 64) {
-        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64);
+        const XcdGrid x(a.nseg, XCD_RUN_LOG_B64, XCD_RUNS_BF16_B64);
         k_numeric_bf16x3_op_b64<<<x.grid, 256, 0, s>>>(ops, a.prodA, a.prodB, a.seg, a.nseg, a.order, (double*)a.C,
                                                        x.log);
         QT_LAUNCH("k_numeric_bf16x3_op_b64");
@@ -1478,7 +1483,7 @@ static void launch_batch_k(const BatchLaunch& L, hipStream_t s) {
     const int64_t items = L.total_items;
     // (items beyond the threads of one grid go to the last schedule)
     if (L.schedule == 0 && items < (int64_t(1) << 31) / T) {
-        const XcdGrid x(items, LDS ? XCD_RUN_LOG_B64 : XCD_RUN_LOG);
+        const XcdGrid x(items, LDS ? XCD_RUN_LOG_B64 : XCD_RUN_LOG, LDS && KIND == 2 ? XCD_RUNS_BF16_B64 : XCD_RUNS);
         k_batch_flat<KIND, BS, LDS><<<x.grid, T, 0, s>>>(L.probs, L.base, L.item_base, L.nprob, x.log);
         QT_LAUNCH("k_batch_flat");
         return;

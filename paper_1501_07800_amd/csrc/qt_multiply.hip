@@ -1509,7 +1509,12 @@ struct OrderSink {
 // BF16X3 130 and 103; b = 64, 4 of 2.6 k FP32 74.9 and 68.9. Slower, by 2 to 6 %: b = 32 FP32,
 // 64 of 2.1 k 199 and 211, 8 of 25 k 323 and 335 (qt_plan_tune tries both).
 constexpr int64_t KORDER_MIN_BYTES = int64_t(700) << 20;
-constexpr int KORDER_MAX_BITS = 22;   // inner blocks: two sort passes
+// Up to 16384 inner blocks: beyond, the two passes take 45 to 130 us and what they
+// give depends on the pattern. Lone calls, Morton and by k: bands of two or three
+// blocks b = 16 FP64, 20000 block rows 285 and 331 us, 40000 464 and 515, b = 32 589
+// and 640; random within 4 % of 20000 block rows 544 and 598; random b = 16 17000
+// 2765 and 2806; random b = 32 FP64 17000 1394 and 1336.
+constexpr int KORDER_MAX_BITS = 14;
 
 struct FirstKeys {
     const uint64_t* akey;      // keys of the blocks the products name

@@ -834,10 +834,12 @@ __global__ void k_copy_parts(Parts a) {
 }
 
 // The tree and keys of M in buffers of their size, where those made by bounds
-// hold much more: over 1 MiB and a 64th of what the values take (a truncation to
-// few blocks, many blocks in few leaves). Waits for the move: products on any
-// stream read a handle's structure without waiting for the stream that made it.
-static void tree_shrink(TreeJob& j, const int32_t* cnt, hipStream_t s) {
+// hold much more: over 1 MiB and a 16th of what the values take (a truncation to
+// few blocks, many blocks in few leaves: 100 k blocks over 2048 block rows
+// truncated to three held 3.7 MB). A move takes a call some 15 us. True: it is
+// queued on s and has to be waited for before the handle is given out, as products
+// on any stream read a handle's structure without waiting for its own.
+static bool tree_shrink(TreeJob& j, const int32_t* cnt, hipStream_t s) {
     qt_matrix* M = j.M;
     const int L = M->L;
     const int64_t n = M->nblocks;
@@ -851,7 +853,12 @@ static void tree_shrink(TreeJob& j, const int32_t* cnt, hipStream_t s) {
     const size_t cm_at = plan.take(nl * sizeof(uint64_t)), bkey_at = plan.take(n * sizeof(uint64_t));
     const int64_t held = (int64_t)(M->arena.n + M->bkey.n * sizeof(uint64_t));
     const int64_t values = M->vsrc ? 0 : n * M->b * M->b * (int64_t)sizeof(double);
-    if (held - (int64_t)plan.bytes <= std::max(int64_t(1) << 20, values / 64)) return;
+    if (held - (int64_t)plan.bytes <= std::max(int64_t(1) << 20, values / 16)) return false;
+    if (n == 0) {
+        M->arena.release();
+        M->bkey.release();
+        return false;
+    }
     DBuf<char> arena(plan.bytes, s);
     Parts parts{};
     auto move = [&](size_t& at, size_t to, size_t bytes) {
@@ -871,24 +878,20 @@ static void tree_shrink(TreeJob& j, const int32_t* cnt, hipStream_t s) {
     move(j.mo_at, mo_at, nl * sizeof(uint64_t));
     move(j.rm_at, rm_at, nl * sizeof(uint64_t));
     move(j.cm_at, cm_at, nl * sizeof(uint64_t));
-    if (n > 0) {
-        parts.from[parts.n] = (const int32_t*)M->bkey.p;
-        parts.to[parts.n] = (int32_t*)(arena.p + bkey_at);
-        parts.words[parts.n++] = 2 * n;
-    }
+    parts.from[parts.n] = (const int32_t*)M->bkey.p;
+    parts.to[parts.n] = (int32_t*)(arena.p + bkey_at);
+    parts.words[parts.n++] = 2 * n;
     k_copy_parts<<<(unsigned)std::min<int64_t>(grid_for((int64_t)plan.bytes / 16), 1024), 256, 0, s>>>(parts);
     QT_LAUNCH("k_copy_parts");
-    QT_HIP(hipStreamSynchronize(s));
-    M->arena = std::move(arena);
-    if (n > 0)
-        M->bkey.view(M->arena.p + bkey_at, n);
-    else
-        M->bkey.release();
+    M->arena = std::move(arena);   // the old buffers go in order, after the move
+    M->bkey.view(M->arena.p + bkey_at, n);
+    return true;
 }
 
 // Reads the words back and sets M's tree, block count and histograms; throws
-// what the error flags say. out (may be nullptr): the caller's double.
-static void tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
+// what the error flags say. out (may be nullptr): the caller's double. True: s is
+// to be waited for (see tree_shrink).
+static bool tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
     ReadBack back(j.nwords);
     back.publish(j.words.p, s);
     const int32_t* w = back.wait(s);
@@ -898,7 +901,7 @@ static void tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
     const int L = M->L;
     const int32_t* cnt = w + TreeJob::kLevels;
     M->nblocks = w[TreeJob::kCount];
-    tree_shrink(j, cnt, s);
+    const bool moved = tree_shrink(j, cnt, s);
     char* at = M->arena.p;
     for (int l = 0; l < L; ++l) {
         M->levels[l].n = cnt[l];
@@ -914,6 +917,7 @@ static void tree_finish(TreeJob& j, hipStream_t s, double* out = nullptr) {
     lv.mask_cm.view(at + j.cm_at, cnt[L]);
     if (out) std::memcpy(out, w + TreeJob::kSum, sizeof(double));
     adopt_histograms(M, cnt + (L + 1));
+    return moved;
 }
 
 // Block keys in Morton order and the quadtree of M (shape fields set) from a
@@ -996,7 +1000,8 @@ qt_matrix* build(int64_t n_rows, int64_t n_cols, int32_t b, int32_t leaf, int64_
     M->v64.alloc((size_t)nblocks * bb, s);
     begin_structure(job, M.get(), pI, pJ, nblocks, nbr, nbc, perm, s);
     copy_blocks(pV, perm.p, nblocks, bb, M->v64.p, s);
-    tree_finish(job, s);   // the last thing queued: the caller's arrays have been read
+    // the last thing queued, but for a moved tree: the caller's arrays have been read
+    if (tree_finish(job, s)) QT_HIP(hipStreamSynchronize(s));
     return M.release();
 }
 
@@ -1491,7 +1496,7 @@ qt_matrix* symmetric_full(qt_matrix* A, hipStream_t s) {
         begin_structure(job, S.get(), I.p, J.p, total, A->n_rows / A->b, A->n_cols / A->b, perm, s);
         k_gather_i32<<<grid_for(total), 256, 0, s>>>(src.p, perm.p, total, S->bmap.p);
         QT_LAUNCH("k_gather_i32");
-        tree_finish(job, s);
+        if (tree_finish(job, s)) QT_HIP(hipStreamSynchronize(s));
     }
     A->sym_full = std::move(S);
     return A->sym_full.get();

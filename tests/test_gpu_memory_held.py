@@ -69,7 +69,7 @@ def _structure_bytes(M):
 
 def _allowed(M, b, values=True):
     v = 8 * M.nblocks * b * b if values else 0
-    return v + _structure_bytes(M) + max(1 << 20, v // 64)
+    return v + _structure_bytes(M) + max(1 << 20, v // 16)
 
 
 def _check(M, b, ref):

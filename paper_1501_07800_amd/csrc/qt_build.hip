@@ -33,6 +33,10 @@ static void ensure_pool() {
     QT_HIP(hipDeviceGetDefaultMemPool(&pool, dev));
     uint64_t thr = ~0ull;
     QT_HIP(hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr));
+    // The pool takes any wait of stream X for an event of stream A, however old the
+    // event, as leave to hand X what was freed on A since, work on A or not.
+    int no = 0;
+    QT_HIP(hipMemPoolSetAttribute(pool, hipMemPoolReuseFollowEventDependencies, &no));
     g_pool_ready.insert(dev);
 }
 
@@ -41,6 +45,60 @@ static std::atomic<const Allocator*> g_allocator{nullptr};
 const Allocator* current_allocator() { return g_allocator.load(std::memory_order_acquire); }
 
 void set_allocator(const Allocator* a) { g_allocator.store(a, std::memory_order_release); }
+
+// Memory made on one stream and released on another. The pool hands memory freed
+// on a stream to the stream it was made on at once, whatever still runs on the
+// first: the next traversal would write its lists where the numeric kernel reads
+// them. So it goes back to the pool, on its own stream, once an event recorded
+// at its release has been passed; looked at with every allocation.
+struct Parked {
+    void* p;
+    hipStream_t made;
+    hipEvent_t passed;
+};
+static std::mutex g_park_mu;
+static std::map<int, std::vector<Parked>> g_parked;       // per device
+static std::map<int, std::vector<hipEvent_t>> g_park_ev;  // for reuse
+
+// wait: until all of it is passed
+static void unpark(int dev, bool wait) {
+    std::lock_guard<std::mutex> lk(g_park_mu);
+    auto& list = g_parked[dev];
+    size_t kept = 0;
+    for (const Parked& k : list) {
+        if ((wait ? hipEventSynchronize(k.passed) : hipEventQuery(k.passed)) == hipSuccess) {
+            (void)hipFreeAsync(k.p, k.made);
+            g_park_ev[dev].push_back(k.passed);
+        } else {
+            (void)hipGetLastError();
+            list[kept++] = k;
+        }
+    }
+    list.resize(kept);
+}
+
+static void park(void* p, hipStream_t s, hipStream_t made) {
+    int dev = 0;
+    hipEvent_t e = nullptr;
+    if (hipGetDevice(&dev) == hipSuccess) {
+        std::lock_guard<std::mutex> lk(g_park_mu);
+        auto& events = g_park_ev[dev];
+        if (!events.empty()) {
+            e = events.back();
+            events.pop_back();
+        }
+    }
+    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) e = nullptr;
+    if (!e || hipEventRecord(e, s) != hipSuccess) {   // no event to be had: wait here
+        (void)hipGetLastError();
+        (void)hipDeviceSynchronize();
+        (void)hipFreeAsync(p, made);
+        if (e) (void)hipEventDestroy(e);
+        return;
+    }
+    std::lock_guard<std::mutex> lk(g_park_mu);
+    g_parked[dev].push_back(Parked{p, made, e});
+}
 
 void* dev_alloc(size_t bytes, hipStream_t s, const Allocator** who) {
     const Allocator* a = current_allocator();
@@ -56,7 +114,15 @@ void* dev_alloc(size_t bytes, hipStream_t s, const Allocator** who) {
         return p;
     }
     ensure_pool();
+    int dev = 0;
+    QT_HIP(hipGetDevice(&dev));
+    unpark(dev, false);
     hipError_t e = hipMallocAsync(&p, bytes, s);
+    if (e == hipErrorOutOfMemory) {   // what is parked may be what is missing
+        (void)hipGetLastError();
+        unpark(dev, true);
+        e = hipMallocAsync(&p, bytes, s);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         hip_check(e, "hipMallocAsync");
@@ -64,12 +130,14 @@ void* dev_alloc(size_t bytes, hipStream_t s, const Allocator** who) {
     return p;
 }
 
-void dev_free(void* p, hipStream_t s, const Allocator* who) {
+void dev_free(void* p, hipStream_t s, hipStream_t made, const Allocator* who) {
     if (!p) return;
     if (who)
         who->free_(p, (void*)s, who->ctx);
-    else
+    else if (s == made)
         (void)hipFreeAsync(p, s);
+    else
+        park(p, s, made);
 }
 
 // --------------------------------------------------------------- kernels

@@ -51,9 +51,10 @@ void set_allocator(const Allocator* a);   // nullptr: back to HIP's pool
 // Stream-ordered device allocation: from the installed allocator, else
 // hipMallocAsync from the device's default pool (whose release threshold is
 // raised so freed memory is reused). *who receives the allocator used.
-// Throws QT_ERR_OOM when the allocation fails.
+// Throws QT_ERR_OOM when the allocation fails. dev_free gives p back in order on
+// s, which need not be the stream `made` that it was obtained on.
 void* dev_alloc(size_t bytes, hipStream_t s, const Allocator** who);
-void dev_free(void* p, hipStream_t s, const Allocator* who);
+void dev_free(void* p, hipStream_t s, hipStream_t made, const Allocator* who);
 
 // Owning device buffer; released stream-ordered on the stream it was made on
 // (or on the stream assigned to `s` later), through the allocator that made
@@ -63,14 +64,15 @@ template <class T>
 struct DBuf {
     T* p = nullptr;
     size_t n = 0;
-    hipStream_t s = nullptr;
+    hipStream_t s = nullptr;      // released on
+    hipStream_t made = nullptr;   // obtained on
     bool own = true;
     const Allocator* al = nullptr;
     DBuf() = default;
     DBuf(size_t count, hipStream_t st) { alloc(count, st); }
     void alloc(size_t count, hipStream_t st) {
         release();
-        s = st;
+        s = made = st;
         n = count;
         p = count ? static_cast<T*>(dev_alloc(count * sizeof(T), st, &al)) : nullptr;
     }
@@ -81,7 +83,7 @@ struct DBuf {
         own = false;
     }
     void release() {
-        if (p && own) dev_free(p, s, al);
+        if (p && own) dev_free(p, s, made, al);
         p = nullptr;
         n = 0;
         own = true;
@@ -90,13 +92,13 @@ struct DBuf {
     ~DBuf() { release(); }
     DBuf(const DBuf&) = delete;
     DBuf& operator=(const DBuf&) = delete;
-    DBuf(DBuf&& o) noexcept : p(o.p), n(o.n), s(o.s), own(o.own), al(o.al) {
+    DBuf(DBuf&& o) noexcept : p(o.p), n(o.n), s(o.s), made(o.made), own(o.own), al(o.al) {
         o.p = nullptr; o.n = 0; o.own = true; o.al = nullptr;
     }
     DBuf& operator=(DBuf&& o) noexcept {
         if (this != &o) {
             release();
-            p = o.p; n = o.n; s = o.s; own = o.own; al = o.al;
+            p = o.p; n = o.n; s = o.s; made = o.made; own = o.own; al = o.al;
             o.p = nullptr; o.n = 0; o.own = true; o.al = nullptr;
         }
         return *this;

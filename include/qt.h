@@ -312,7 +312,9 @@ qt_status qt_prepare(const qt_matrix* M, qt_prec prec, void* stream);
 
 /* Release a handle (NULL is ignored): a matrix, like a registered chunk
  * (Sec. 2), belongs to the library from its creation until it is released.
- * Its device memory is released in order on the stream that created it. */
+ * Its device memory, the operand forms and norms made with it included, is
+ * released in order on the stream that created it: work on other streams that
+ * uses M has to be done by then, or that stream to wait for it. */
 void qt_free(qt_matrix* M);
 
 /*

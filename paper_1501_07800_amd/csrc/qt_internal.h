@@ -201,6 +201,10 @@ struct qt_matrix {
     qt_matrix(const qt_matrix&) = delete;
     qt_matrix& operator=(const qt_matrix&) = delete;
     ~qt_matrix() {
+        // the forms were made on the streams of the calls that first needed them
+        // and read on others; all work on M precedes its release on its own stream
+        bf_hi.s = bf_lo.s = bf_hi_t.s = bf_lo_t.s = stream;
+        v32.s = v64_cache.s = norms.s = stream;
         for (hipEvent_t e : {ev_v32, ev_v64, ev_bf16, ev_norms})
             if (e) (void)hipEventDestroy(e);
     }

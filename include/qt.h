@@ -79,9 +79,11 @@ typedef enum { QT_MEM_HOST = 0, QT_MEM_DEVICE = 1 } qt_mem;
  * from several at once. Buffers made before a change are still returned to
  * the allocator that made them, so ctx must stay valid while any of them
  * lives. alloc == free_ == NULL restores the default: HIP's stream-ordered
- * pool (hipMallocAsync / hipFreeAsync on the device's default pool). A few
- * bytes per device that the library keeps until the process ends (a lift
- * table, pinned read-back slots) never go through the allocator.
+ * pool (hipMallocAsync / hipFreeAsync on the device's default pool, which then
+ * keeps what is freed and reuses it across streams only once its last work is
+ * done). What the library keeps until the process ends (a lift table per
+ * device, up to 2 MiB of pinned read-back slots, the 12 MiB of
+ * qt_to_blocks_noalloc) never goes through the allocator.
  * Errors: ARG (exactly one of alloc, free_ is NULL).
  */
 qt_status qt_set_allocator(void* (*alloc)(size_t bytes, void* stream, void* ctx),

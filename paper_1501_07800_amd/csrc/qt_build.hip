@@ -77,27 +77,30 @@ static void unpark(int dev, bool wait) {
     list.resize(kept);
 }
 
-static void park(void* p, hipStream_t s, hipStream_t made) {
-    int dev = 0;
+// Called by destructors: whatever cannot be had, the memory is waited for here.
+static void park(void* p, hipStream_t s, hipStream_t made) noexcept {
     hipEvent_t e = nullptr;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        std::lock_guard<std::mutex> lk(g_park_mu);
-        auto& events = g_park_ev[dev];
-        if (!events.empty()) {
-            e = events.back();
-            events.pop_back();
+    try {
+        int dev = 0;
+        QT_HIP(hipGetDevice(&dev));
+        {
+            std::lock_guard<std::mutex> lk(g_park_mu);
+            auto& events = g_park_ev[dev];
+            if (!events.empty()) {
+                e = events.back();
+                events.pop_back();
+            }
         }
-    }
-    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) e = nullptr;
-    if (!e || hipEventRecord(e, s) != hipSuccess) {   // no event to be had: wait here
+        if (!e) QT_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        QT_HIP(hipEventRecord(e, s));
+        std::lock_guard<std::mutex> lk(g_park_mu);
+        g_parked[dev].push_back(Parked{p, made, e});
+    } catch (...) {
         (void)hipGetLastError();
         (void)hipDeviceSynchronize();
         (void)hipFreeAsync(p, made);
         if (e) (void)hipEventDestroy(e);
-        return;
     }
-    std::lock_guard<std::mutex> lk(g_park_mu);
-    g_parked[dev].push_back(Parked{p, made, e});
 }
 
 void* dev_alloc(size_t bytes, hipStream_t s, const Allocator** who) {

@@ -49,25 +49,34 @@ void set_allocator(const Allocator* a) { g_allocator.store(a, std::memory_order_
 // Memory made on one stream and released on another. The pool hands memory freed
 // on a stream to the stream it was made on at once, whatever still runs on the
 // first: the next traversal would write its lists where the numeric kernel reads
-// them. So it goes back to the pool, on its own stream, once an event recorded
-// at its release has been passed; looked at with every allocation.
+// them. So it goes back to the pool once an event recorded at its release has
+// been passed: looked at with every allocation, and on that allocation's stream,
+// as the one that it was made on may be a caller's that is gone by then.
 struct Parked {
     void* p;
-    hipStream_t made;
     hipEvent_t passed;
 };
 static std::mutex g_park_mu;
 static std::map<int, std::vector<Parked>> g_parked;       // per device
 static std::map<int, std::vector<hipEvent_t>> g_park_ev;  // for reuse
 
-// wait: until all of it is passed
-static void unpark(int dev, bool wait) {
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// wait: until all of it is passed. Not while s is captured: it would go back at
+// every replay.
+static void unpark(int dev, hipStream_t s, bool wait) {
     std::lock_guard<std::mutex> lk(g_park_mu);
     auto& list = g_parked[dev];
+    if (list.empty() || capturing(s)) return;
     size_t kept = 0;
     for (const Parked& k : list) {
         if ((wait ? hipEventSynchronize(k.passed) : hipEventQuery(k.passed)) == hipSuccess) {
-            (void)hipFreeAsync(k.p, k.made);
+            (void)hipFreeAsync(k.p, s);
             g_park_ev[dev].push_back(k.passed);
         } else {
             (void)hipGetLastError();
@@ -78,8 +87,14 @@ static void unpark(int dev, bool wait) {
 }
 
 // Called by destructors: whatever cannot be had, the memory is waited for here.
-static void park(void* p, hipStream_t s, hipStream_t made) noexcept {
+// An event of a stream that is captured never reads as passed: a release in the
+// capture is the graph's.
+static void park(void* p, hipStream_t s) noexcept {
     hipEvent_t e = nullptr;
+    if (capturing(s)) {
+        (void)hipFreeAsync(p, s);
+        return;
+    }
     try {
         int dev = 0;
         QT_HIP(hipGetDevice(&dev));
@@ -94,11 +109,11 @@ static void park(void* p, hipStream_t s, hipStream_t made) noexcept {
         if (!e) QT_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         QT_HIP(hipEventRecord(e, s));
         std::lock_guard<std::mutex> lk(g_park_mu);
-        g_parked[dev].push_back(Parked{p, made, e});
+        g_parked[dev].push_back(Parked{p, e});
     } catch (...) {
         (void)hipGetLastError();
         (void)hipDeviceSynchronize();
-        (void)hipFreeAsync(p, made);
+        (void)hipFreeAsync(p, s);
         if (e) (void)hipEventDestroy(e);
     }
 }
@@ -119,11 +134,11 @@ void* dev_alloc(size_t bytes, hipStream_t s, const Allocator** who) {
     ensure_pool();
     int dev = 0;
     QT_HIP(hipGetDevice(&dev));
-    unpark(dev, false);
+    unpark(dev, s, false);
     hipError_t e = hipMallocAsync(&p, bytes, s);
     if (e == hipErrorOutOfMemory) {   // what is parked may be what is missing
         (void)hipGetLastError();
-        unpark(dev, true);
+        unpark(dev, s, true);
         e = hipMallocAsync(&p, bytes, s);
     }
     if (e != hipSuccess) {
@@ -140,7 +155,7 @@ void dev_free(void* p, hipStream_t s, hipStream_t made, const Allocator* who) {
     else if (s == made)
         (void)hipFreeAsync(p, s);
     else
-        park(p, s, made);
+        park(p, s);
 }
 
 // --------------------------------------------------------------- kernels

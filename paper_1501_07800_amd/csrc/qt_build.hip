@@ -945,7 +945,13 @@ static bool tree_shrink(TreeJob& j, const int32_t* cnt, hipStream_t s) {
         M->bkey.release();
         return false;
     }
-    DBuf<char> arena(plan.bytes, s);
+    DBuf<char> arena;
+    try {
+        arena.alloc(plan.bytes, s);
+    } catch (const Error& e) {
+        if (e.status != QT_ERR_OOM) throw;
+        return false;   // the call has all that it needs
+    }
     Parts parts{};
     auto move = [&](size_t& at, size_t to, size_t bytes) {
         if (bytes) {
